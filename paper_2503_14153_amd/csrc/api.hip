@@ -1,5 +1,6 @@
 // Host side of libspecdec: handle management, argument validation, and the sequencing of the
 // kernels of one speculative step (paper Section III-B) on a caller-supplied HIP stream.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -70,6 +71,7 @@ struct sd_model {
     void* xh;                                // draft-head rows of every tree row, in 256-row operand chunks
     int draft_schedule = SD_DRAFT_AFTER_ACCEPT;
     RowTable rt;
+    RowMap* rm_dev;                          // the row map of a prompt pass, in device memory
     int32_t *am, *g_parent, *g_depth, *g_rank;
     float4* row_stats;                     // [Mp]: per tree row, statistics for typical acceptance
     uint32_t* zero_stop;
@@ -102,7 +104,8 @@ struct sd_model {
     unsigned long long sync_timeout_ticks = 5000000ull;     // 50 ms of the 100 MHz counter
     unsigned long long* timeline = nullptr;  // caller's buffer for the layer kernel's time stamps, or NULL
     size_t timeline_launches = 0;
-    int scratch_B = 0, scratch_Tp = 0;       // geometry of the tree K/V scratch as the last pass left it
+    int scratch_B = 0, scratch_Tp = 0;       // the tree K/V scratch as the last pass left it: its cache's batch, rows per
+    int scratch_n = 0, scratch_seq[SD_MAX_BATCH] = {};   // sequence, and the sequences that it holds, in order
     bool plan_missing = false;               // set by run_gemm if it ever had to skip a launch
     bool greedy_drafts = true;               // sd_greedy_step also runs the draft heads
     // float32 path (dtype SD_DTYPE_F32; f32.hip): weights [out][in] as float, natural activation layouts
@@ -221,6 +224,7 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     const size_t w_z = wtake((size_t)SD_MAX_BATCH * H * d * 4), w_xh = wtake((size_t)HBp * d * 4);
     const size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
     const size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_am = wtake((size_t)Mp * 4), w_g = wtake(3 * 4);
+    const size_t w_rm = wtake(sizeof(RowMap));
     const size_t w_rs = wtake((size_t)Mp * 16), w_zs = wtake((size_t)ceil_div(V, 32) * 4);
     if (e == hipSuccess) e = hipMalloc((void**)&m->work, wz);
     if (e == hipSuccess) e = hipMemsetAsync(m->work, 0, wz, s);
@@ -240,6 +244,7 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
     m->am = (int32_t*)(Wk + w_am);
+    m->rm_dev = (RowMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
     m->zero_stop = (uint32_t*)(Wk + w_zs);
@@ -390,7 +395,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     size_t w_kt = wtake((size_t)L * Mp * d * 2), w_vt = wtake((size_t)L * Mp * d * 2);
     size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
     size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_am = wtake((size_t)Mp * 4), w_g = wtake(3 * 4);
-    size_t w_rs = wtake((size_t)Mp * 16);
+    size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(RowMap));
     size_t w_xh = wtake(align_up((size_t)H * Mp, 256) * d * 4);
     size_t w_zs = wtake((size_t)ceil_div(V, 32) * 4), w_zf = wtake(1024);
     size_t w_ssqa = wtake((size_t)align_up(d / 16, 4) * Mp * 4), w_ssqf = wtake((size_t)align_up(d / 16, 4) * Mp * 4);
@@ -439,6 +444,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
     m->am = (int32_t*)(Wk + w_am);
+    m->rm_dev = (RowMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
     m->zero_stop = (uint32_t*)(Wk + w_zs);
@@ -794,7 +800,7 @@ static SkRowScale row_scale(const sd_model* m, const float* ssq) {
 }
 static const SkRowScale NO_SCALE = {nullptr, 0, 0.f, 0.f};
 
-static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out, int MB, int KB, int NB, int n_real,
+static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out, int rows, int MB, int KB, int NB, int n_real,
                          hipStream_t s) {
     const GemmPlan* p = m->find_plan(MB, KB, NB);
     if (!p) {                                          // unreachable after have_plans(); never launch with another shape's plan
@@ -802,7 +808,7 @@ static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out
         return PartView{out, 0, NB * 32, nullptr, 0};  // no slots: the consumer adds nothing
     }
     const int pi = prof_claim(m, PROF_GEMM, (double)n_real * KB * 16 * 2);
-    return launch_gemm(*p, Xp, Wp, m->zfrag, out, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
+    return launch_gemm(*p, Xp, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
 }
 
 // Every GEMM shape a pass over M rows issues (and, with heads = true, the draft heads after it, in the
@@ -863,16 +869,16 @@ static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool s
     return g;
 }
 
-static PartView run_layers(sd_model* m, sd_kv* kv, int B, int Tp, int n_hi, hipStream_t s) {
+static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, hipStream_t s) {
     const sd_config& c = m->cfg;
-    const int M = B * Tp, MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
+    const int MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
     const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, /*split_ok=*/Tp == 64);   // (one query group of two blocks)
     PartView prev = {nullptr, 0, d, nullptr, 0};
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW& lw = m->layers[l];
         launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
-        PartView pq = run_gemm(m, m->xn, lw.wqkv, m->part, MB, m->KBd, m->NBqkv, 3 * d, s);
+        PartView pq = run_gemm(m, m->xn, lw.wqkv, m->part, M, MB, m->KBd, m->NBqkv, 3 * d, s);
         uint16_t* kt = (uint16_t*)m->kt + l * t_stride;
         uint16_t* vt = (uint16_t*)m->vt + l * t_stride;
         // With one query group per head (trees of up to 64 nodes, plain decoding, short prompt chunks) the attention
@@ -885,18 +891,18 @@ static PartView run_layers(sd_model* m, sd_kv* kv, int B, int Tp, int n_hi, hipS
         // the launch saved is worth more than it costs (batch of eight 32-node trees: attention 65.4 -> 72.8 us, the
         // 11.8 us launch gone, step -0.8 %).
         const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1);
-        if (!fr) launch_rope_kv(pq, m->rt, m->q, kt, vt, B, Tp, nh, hd, s);
+        if (!fr) launch_rope_kv(pq, m->rt, rr, m->q, kt, vt, B, Tp, nh, hd, s);
         // algorithmic bytes: one read of K and V of the committed rows (upper bound n_hi) + tree rows
         const int pa = prof_claim(m, PROF_ATTN, (double)B * (n_hi + Tp) * 2.0 * d * 2.0);
         launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kt, vt, kv->kv_len,
-                         m->rt.anc, m->opart, m->mlpart, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
+                         m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
                          prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
-        launch_attn_merge(m->opart, m->mlpart, m->attn_x, B, nh, hd, Tp, ag.nparts, MB, s);
-        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, MB, m->KBd, m->NBo, d, s);
+        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, *std::max_element(rm.len, rm.len + B), B, nh, hd, Tp, ag.nparts, MB, s);
+        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
-        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
+        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
         launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
-        prev = run_gemm(m, m->act, lw.wdown, m->part, MB, m->KBf, m->NBo, d, s);
+        prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
     }
     return prev;
 }
@@ -922,7 +928,8 @@ static bool fused_eligible(const sd_model* m, int M) {
 }
 // Layers 0..L-1 and, with want_lm, the final norm and the LM-head GEMM, whose partial sums the returned view
 // describes (without want_lm: the last down projection's, still to be added to m->x).
-static PartView run_forward_fused(sd_model* m, sd_kv* kv, int B, int Tp, int n_hi, bool want_lm, hipStream_t s) {
+// (Its phases take the rows as [sequence][Tp]: the row map says off[i] = i * Tp.)
+static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int Tp, int n_hi, bool want_lm, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int M = B * Tp, MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32, L = c.n_layers;
     const AttnGeom ag = attn_geometry(m, B, Tp, n_hi);
@@ -979,7 +986,7 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, int B, int Tp, int n_h
         if (l < L) {
             const int pa = prof_claim(m, PROF_ATTN, (double)B * (n_hi + Tp) * 2.0 * d * 2.0);
             launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, a.kt, a.vt, kv->kv_len,
-                             m->rt.anc, m->opart, m->mlpart, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
+                             m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
                              prof_ev(m, pa, 0), prof_ev(m, pa, 1));
         }
     }
@@ -988,14 +995,19 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, int B, int Tp, int n_h
 
 // final norm + LM head on all rows + arg-max of the first T rows of every sequence
 // ------------------------------------------------------------------------------------------ float32 pass
-static void commit_rows(sd_model* m, sd_kv* kv, const int32_t* slots, const int32_t* n_acc, int Tp, int W, hipStream_t s) {
+// by_seq: slots, counts and old lengths are listed by sequence of the cache (else by sequence of the pass)
+static void commit_rows(sd_model* m, sd_kv* kv, bool by_seq, const int32_t* slots, const int32_t* n_acc, int Tp, int W,
+                        hipStream_t s) {
     const sd_config& c = m->cfg;
+    RowMap rm;
+    memset(&rm, 0, sizeof(rm));
+    for (int i = 0; i < m->scratch_n; ++i) { rm.seq[i] = m->scratch_seq[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
     if (m->f32)
         launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, c.n_layers, kv->B, c.d_model, Tp,
                              kv->cap, W, s);
     else
-        launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, c.n_layers, kv->B, c.n_heads, c.head_dim,
-                         Tp / 32, kv->cap_blocks, W, W, s);
+        launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, m->scratch_n, c.n_heads,
+                         c.head_dim, Tp / 32, kv->cap_blocks, W, s);
 }
 
 static void run_forward_f32(sd_model* m, sd_kv* kv, int B, int T, int Tp, bool want_lm, hipStream_t s) {
@@ -1038,30 +1050,35 @@ static void run_draft_heads_f32(sd_model* m, sd_kv* kv, int B, uint32_t seq_mask
 
 // (keep_h: also leaves the normalised rows in m->hf as fp32, for draft heads on every row)
 // need_logits: somebody reads m->logits afterwards (the caller's copy, sampling decoding); else only the arg-max
-static void run_lm_head(sd_model* m, PartView prev, int B, int T, int Tp, hipStream_t s, bool keep_h, bool need_logits) {
+static void run_lm_head(sd_model* m, PartView prev, int B, int T, int R, int M, hipStream_t s, bool keep_h, bool need_logits) {
     const sd_config& c = m->cfg;
-    const int M = B * Tp, MB = pow2_blocks(M);
+    const int MB = pow2_blocks(M);
     launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, keep_h ? m->hf : nullptr, M, c.d_model, MB, nullptr, s);
-    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, MB, m->KBd, m->NBv, c.vocab, s);
-    launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, c.vocab, m->am, B, T, Tp, s);
+    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
+    launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, c.vocab, m->am, B, T, R, s);
 }
 
 // The whole verifying pass: layers, and with want_lm the final norm, the LM head and the arg-max of the first T rows
-// of every sequence (logits in m->logits, arg-max in m->am).
-static void run_forward(sd_model* m, sd_kv* kv, int B, int T, int Tp, int n_hi, bool want_lm, bool keep_h, bool need_logits,
-                        hipStream_t s) {
-    m->scratch_B = B;
+// of every sequence (logits in m->logits, arg-max in m->am). Sequence i's rows start at row i * R (R = 0: at rm.off[i],
+// prompt chunks, where the arg-max is taken of every row).
+static void run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int T, int R, int Tp, int n_hi, bool want_lm,
+                        bool keep_h, bool need_logits, hipStream_t s) {
+    m->scratch_B = kv->B;
+    m->scratch_n = B;
+    for (int i = 0; i < B; ++i) m->scratch_seq[i] = rm.seq[i];
     m->scratch_Tp = Tp;
     if (m->f32) { run_forward_f32(m, kv, B, T, Tp, want_lm, s); return; }
+    const RowRef rr = {R ? nullptr : m->rm_dev, R};
+    const int am_B = R ? B : 1, am_T = R ? T : M, am_R = R ? R : M;
     if (fused_eligible(m, B * Tp)) {
         // (when the final norm's rows themselves are wanted, the last stage runs as kernels of its own)
-        PartView pl = run_forward_fused(m, kv, B, Tp, n_hi, want_lm && !keep_h, s);
-        if (want_lm && keep_h) run_lm_head(m, pl, B, T, Tp, s, true, need_logits);
-        else if (want_lm) launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, m->cfg.vocab, m->am, B, T, Tp, s);
+        PartView pl = run_forward_fused(m, kv, rr, B, Tp, n_hi, want_lm && !keep_h, s);
+        if (want_lm && keep_h) run_lm_head(m, pl, am_B, am_T, am_R, M, s, true, need_logits);
+        else if (want_lm) launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, m->cfg.vocab, m->am, am_B, am_T, am_R, s);
         return;
     }
-    PartView prev = run_layers(m, kv, B, Tp, n_hi, s);
-    if (want_lm) run_lm_head(m, prev, B, T, Tp, s, keep_h, need_logits);
+    PartView prev = run_layers(m, kv, rr, rm, B, M, Tp, n_hi, s);
+    if (want_lm) run_lm_head(m, prev, am_B, am_T, am_R, M, s, keep_h, need_logits);
 }
 
 // draft heads at row last_row[b] of every sequence -> cand (sequences in seq_mask only)
@@ -1071,10 +1088,10 @@ static void run_draft_heads(sd_model* m, sd_kv* kv, int B, uint32_t seq_mask, fl
     const int d = c.d_model, H = c.n_medusa;
     const PartView none = {nullptr, 0, d, nullptr, 0};
     launch_norm_pack(m->x, none, m->final_norm, c.rms_eps, m->xn, m->h_rows, B, d, 1, kv->last_row, s);
-    PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, 1, m->KBd, m->NBmed, H * d, s);
+    PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, B, 1, m->KBd, m->NBmed, H * d, s);
     const int MBh = pow2_blocks(H * B);
     launch_medusa_act(pm, m->h_rows, m->medusa_b, B, H, d, m->xn, MBh * 32, MBh, MBh, s);
-    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, MBh, m->KBd, m->NBv, c.vocab, s);
+    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, H * B, MBh, m->KBd, m->NBv, c.vocab, s);
     // (a top-k that sums the slots itself was measured: 54 us against 5 + 22 us for these two, its few workgroups
     // pull the partial sums too slowly)
     launch_reduce_slots(pl, m->hlogits, H * B, s);
@@ -1082,20 +1099,20 @@ static void run_draft_heads(sd_model* m, sd_kv* kv, int B, uint32_t seq_mask, fl
     if (head_logits_out) launch_copy_head_logits(m->hlogits, m->Vpad, head_logits_out, c.vocab, B, H, s);
 }
 
-// The other schedule: the draft heads run on all B*Tp rows of the verifying pass (m->xn and m->hf
-// still hold the final norm's output), the shared LM head on all H*B*Tp head rows in chunks of 256
+// The other schedule: the draft heads run on all M rows of the verifying pass (m->xn and m->hf
+// still hold the final norm's output), the shared LM head on all H*M head rows in chunks of 256
 // rows, and only the H rows of every sequence's last kept row (kv->last_row, set by the acceptance kernel) are
 // summed out of the partial tiles and ranked.
-static void run_draft_heads_all_rows(sd_model* m, sd_kv* kv, int B, int Tp, float* head_logits_out, hipStream_t s) {
+static void run_draft_heads_all_rows(sd_model* m, sd_kv* kv, int B, int M, float* head_logits_out, hipStream_t s) {
     const sd_config& c = m->cfg;
-    const int d = c.d_model, H = c.n_medusa, M = B * Tp, MB = pow2_blocks(M), R = H * M, CH = 256;
-    PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, MB, m->KBd, m->NBmed, H * d, s);
+    const int d = c.d_model, H = c.n_medusa, MB = pow2_blocks(M), R = H * M, CH = 256;
+    PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, M, MB, m->KBd, m->NBmed, H * d, s);
     const int n_chunks = ceil_div(R, CH), MBlast = pow2_blocks(R - (n_chunks - 1) * CH);
     launch_medusa_act(pm, m->hf, m->medusa_b, M, H, d, m->xh, CH, CH / 32, MBlast, s);
     for (int ch = 0; ch < n_chunks; ++ch) {
         const int rows = std::min(CH, R - ch * CH);
         const char* xc = (const char*)m->xh + (size_t)ch * CH * d * 4;
-        PartView pl = run_gemm(m, xc, m->lm_head, m->part, ch == n_chunks - 1 ? MBlast : CH / 32, m->KBd, m->NBv,
+        PartView pl = run_gemm(m, xc, m->lm_head, m->part, rows, ch == n_chunks - 1 ? MBlast : CH / 32, m->KBd, m->NBv,
                                c.vocab, s);
         launch_reduce_selected(pl, m->hlogits, kv->last_row, B, H, M, ch * CH, rows, s);
     }
@@ -1113,34 +1130,50 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
     int Tp = (m->max_rows / B) / 32 * 32;
     if (Tp > 256) Tp = 256;                            // prompt chunks of up to 256 rows (the widest GEMM)
     if (Tp < 32) return fail(SD_ERR_SHAPE, "sd_prefill: max_rows %d too small for batch %d", m->max_rows, B);
-    int maxlen = 0;
     for (int b = 0; b < B; ++b) {
         if (lens[b] < 1) return fail(SD_ERR_SHAPE, "sd_prefill: every prompt needs at least one token");
         if (kv->len_hi[b] + lens[b] > kv->cap) return fail(SD_ERR_KV_FULL, "sd_prefill: sequence %d does not fit", b);
-        maxlen = std::max(maxlen, lens[b]);
     }
-    if (!have_plans(m, B * Tp, B, true, false))
-        return fail(SD_ERR_STATE, "sd_prefill: no launch plan for %d rows (internal inconsistency)", B * Tp);
-    std::vector<int> start(B), done(B, 0);
-    for (int b = 0, o = 0; b < B; ++b) { start[b] = o; o += lens[b]; }
-    for (int pos = 0; pos < maxlen; pos += Tp) {
+    for (int rows = 32; rows <= 256; rows *= 2)            // every row count a pass can come down to
+        if (pow2_blocks(rows) <= m->MBmax && !have_plans(m, rows, B, true, false))
+            return fail(SD_ERR_STATE, "sd_prefill: no launch plan for %d rows (internal inconsistency)", rows);
+    std::vector<int> next(B), left(lens, lens + B);        // first prompt token not yet enqueued, how many are left
+    for (int b = 0, o = 0; b < B; ++b) { next[b] = o; o += lens[b]; }
+    for (;;) {
+        // The sequences that still have tokens share the pass's rows: a prompt that has ended takes none of them.
+        // (float32: all sequences, every pass.)
         ChainArgs ca;
+        RowMap rm;
         memset(&ca, 0, sizeof(ca));
+        memset(&rm, 0, sizeof(rm));
+        int A = 0, M = 0, n_hi = 0;
         uint32_t fin = 0;
-        int n_hi = 0;
-        for (int b = 0; b < B; ++b) {
-            int left = lens[b] - pos;
-            ca.len[b] = left <= 0 ? 0 : std::min(left, Tp);
-            ca.off[b] = start[b] + pos;
-            if (left > 0 && left <= Tp) fin |= 1u << b;
+        for (int b = 0; b < B; ++b)
+            if (left[b] > 0 || m->f32) rm.seq[A++] = b;
+        if (*std::max_element(left.begin(), left.end()) <= 0) break;
+        if (!m->f32) Tp = std::min(m->max_rows / A / 32 * 32, 256);
+        const bool padded = m->f32 || fused_eligible(m, A * Tp);        // these passes take the rows as [sequence][Tp]
+        for (int i = 0; i < A; ++i) {
+            const int b = rm.seq[i];
+            ca.len[i] = std::min(left[b], Tp);
+            ca.off[i] = next[b];
+            rm.off[i] = M;
+            rm.len[i] = padded ? Tp : ca.len[i];
+            M += rm.len[i];
+            if (left[b] > 0 && left[b] <= Tp) fin |= 1u << b;
             n_hi = std::max(n_hi, kv->len_hi[b]);
         }
-        launch_build_rows_chain(m->rt, tokens, ca, kv->kv_len, B, Tp, c.head_dim, c.rope_theta, m->embed, m->f32 ? 1 : 0,
+        launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, c.rope_theta, m->embed, m->f32 ? 1 : 0,
                                 c.d_model, c.vocab, m->x, s);
-        run_forward(m, kv, B, Tp, Tp, n_hi, fin != 0, false, false, s);
-        launch_prefill_commit_setup(ca, B, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, kv->last_row, s);
-        commit_rows(m, kv, kv->i_slots, kv->i_nacc, Tp, Tp, s);
-        for (int b = 0; b < B; ++b) kv->len_hi[b] += ca.len[b];
+        run_forward(m, kv, rm, A, M, Tp, 0, Tp, n_hi, fin != 0, false, false, s);
+        launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, kv->last_row, s);
+        commit_rows(m, kv, false, kv->i_slots, kv->i_nacc, Tp, Tp, s);
+        for (int i = 0; i < A; ++i) {
+            const int b = rm.seq[i];
+            kv->len_hi[b] += ca.len[i];
+            next[b] += ca.len[i];
+            left[b] -= ca.len[i];
+        }
         if (fin) {
             launch_pick_root(m->am, kv->last_row, kv->root_tok, B, fin, s);
             run_draft_heads(m, kv, B, fin, nullptr, s);
@@ -1171,8 +1204,14 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     }
     const bool all_rows = m->draft_schedule == SD_DRAFT_ALL_NODES && T > 1 && !m->f32;   // (float32: one schedule only)
     const bool heads = T > 1 || m->greedy_drafts;      // plain greedy decoding may leave the draft heads out
-    if (!have_plans(m, B * Tp, B, heads, all_rows))
-        return fail(SD_ERR_STATE, "%s: no launch plan for %d rows (internal inconsistency)", who, B * Tp);
+    // rows of a sequence lie R apart: the tree's own nodes, no padding (see RowMap), except where the pass takes them
+    // as [sequence][Tp]
+    const int R = m->f32 || fused_eligible(m, B * Tp) ? Tp : T, M = B * R;
+    RowMap rm;
+    memset(&rm, 0, sizeof(rm));
+    for (int b = 0; b < B; ++b) { rm.off[b] = b * R; rm.len[b] = R; rm.seq[b] = b; }
+    if (!have_plans(m, M, B, heads, all_rows))
+        return fail(SD_ERR_STATE, "%s: no launch plan for %d rows (internal inconsistency)", who, M);
     int32_t* n_accept = io->n_accept ? io->n_accept : kv->i_nacc;
     int32_t* tokens = io->tokens ? io->tokens : kv->i_tokens;
     int32_t* slots = io->src_slots ? io->src_slots : kv->i_slots;
@@ -1180,31 +1219,31 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
 
     // everything the launch sequence depends on besides device-resident state
     auto enqueue = [&](hipStream_t s) {
-    launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, H, c.topk, c.head_dim,
+    launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
                            c.rope_theta, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);
-    run_forward(m, kv, B, T, Tp, n_hi, true, all_rows, io->logits != nullptr || ty != nullptr, s);
-    if (io->logits) launch_copy_logits(m->logits, m->Vpad, io->logits, c.vocab, B, T, Tp, s);
-    if (io->argmax) launch_copy_rows_i32(m->am, io->argmax, B, T, Tp, s);
+    run_forward(m, kv, rm, B, M, T, R, Tp, n_hi, true, all_rows, io->logits != nullptr || ty != nullptr, s);
+    if (io->logits) launch_copy_logits(m->logits, m->Vpad, io->logits, c.vocab, B, T, R, s);
+    if (io->argmax) launch_copy_rows_i32(m->am, io->argmax, B, T, R, s);
     VerifyArgs va;
     va.parent = parent; va.depth = depth; va.T = T; va.H = H; va.fallback = c.trunc_fallback;
-    va.src_stride = Tp; va.Tp = Tp; va.V = c.vocab;
+    va.src_stride = R; va.Tp = R; va.V = c.vocab;
     va.tok = m->rt.tok; va.am = m->am; va.stop_mask = stop_mask;
     va.n_accept = n_accept; va.n_accept_raw = io->n_accept_raw; va.tokens = tokens; va.src_slots = slots;
     va.kv_len = kv->kv_len; va.n_old = kv->n_old; va.root_tok = kv->root_tok; va.last_row = kv->last_row;
     va.logits = nullptr; va.ld = 0; va.row_stats = nullptr; va.inv_temperature = 1.f;
     if (ty) {
         va.inv_temperature = 1.f / ty->temperature;
-        launch_row_stats(m->logits, m->Vpad, c.vocab, m->row_stats, B, T, Tp, va.inv_temperature, ty->epsilon,
+        launch_row_stats(m->logits, m->Vpad, c.vocab, m->row_stats, B, T, R, va.inv_temperature, ty->epsilon,
                          ty->delta, s);
-        if (ty->row_stats) launch_copy_row_stats(m->row_stats, (float4*)ty->row_stats, B, T, Tp, s);
+        if (ty->row_stats) launch_copy_row_stats(m->row_stats, (float4*)ty->row_stats, B, T, R, s);
         va.logits = m->logits; va.ld = m->Vpad; va.row_stats = m->row_stats;
     }
     launch_verify(va, B, s);
     if (ty)      // the next root is drawn from the base distribution at the last kept node
         launch_sample_root(m->logits, m->Vpad, c.vocab, kv->last_row, ty->u, va.inv_temperature, kv->root_tok, B,
-                           B * Tp, s);
-    commit_rows(m, kv, slots, n_accept, Tp, H + 1, s);
-    if (all_rows) run_draft_heads_all_rows(m, kv, B, Tp, io->head_logits, s);
+                           M, s);
+    commit_rows(m, kv, false, slots, n_accept, Tp, H + 1, s);
+    if (all_rows) run_draft_heads_all_rows(m, kv, B, M, io->head_logits, s);
     else if (heads) run_draft_heads(m, kv, B, 0xffffffffu, io->head_logits, s);
     };
 
@@ -1272,7 +1311,7 @@ extern "C" int sd_kv_commit_rows(sd_model* m, sd_kv* kv, const int32_t* src_slot
                         kv->len_hi[b], kv->cap);
     hipStream_t s = (hipStream_t)stream;
     launch_commit_setup(n_rows, width, kv->B, kv->i_nacc, kv->n_old, kv->kv_len, s);
-    commit_rows(m, kv, src_slots, kv->i_nacc, m->scratch_Tp, width, s);
+    commit_rows(m, kv, true, src_slots, kv->i_nacc, m->scratch_Tp, width, s);
     HIP_TRY(hipGetLastError());
     for (int b = 0; b < kv->B; ++b) kv->len_hi[b] += width;
     return SD_OK;

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
                                                    const uint32_t* __restrict__ anc, float* __restrict__ opart,
                                                    float2* __restrict__ mlpart, int nh, int Tp, int cap_blocks,
                                                    int ncparts, int per, int tree_sep, float scale_log2,
-                                                   int xcd_stride, int nseq, PartView pv, RowTable rt) {
+                                                   int xcd_stride, int nseq, PartView pv, RowTable rt, RowRef rr) {
     constexpr int KK = HD / 16;        // contraction steps of QK^T = K fragments per block
     constexpr int EB = HD / 32;        // 32-wide output blocks of PV
     constexpr int NV = 2 * EB;         // V fragments per block
@@ -144,8 +144,9 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     const int total = ntree + (has_cache ? per : 0);
     const int share = (total + 3) >> 2;
     const int jw = __builtin_amdgcn_readfirstlane(wave * share);
-    const bf16x8* kcb = Kc + ((size_t)b * nh + h) * cap_blocks * BLK + lane;
-    const bf16x8* vcb = Vc + ((size_t)b * nh + h) * cap_blocks * BLK + lane;
+    const int sq = rr.seq(b);                         // sequence of the cache
+    const bf16x8* kcb = Kc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
+    const bf16x8* vcb = Vc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* ktb = Kt + ((size_t)b * nh + h) * TB * BLK + lane;
     const bf16x8* vtb = Vt + ((size_t)b * nh + h) * TB * BLK + lane;
     // item -> block address, always inside the tree scratch or the cache allocation
@@ -162,6 +163,8 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // there: no wait for the stores to the scratch, no round trip to read them back.
     bf16x8* const tkv = lds + QF * 64;                 // K blocks of the tree, then its V blocks
     const bool tree_only = FR && ntree && !has_cache;  // (workgroup-uniform)
+    const int row0 = FR ? rr.off(b) : 0, row_last = FR ? rr.len(b) - 1 : 0;       // this sequence's rows of the partial sums
+    auto row_of = [&](int t) { return row0 + min(t, row_last); };
     if constexpr (FR) {
         static_assert(2 * TBW * BLK <= 4 * WAVE_UNITS, "the tree blocks fit the merge area");
         if (ntree) {                                   // (workgroup-uniform) the tree's keys and values of this head
@@ -177,14 +180,16 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
                 for (int u = 0; u < 2 * 32 * NA / 256; ++u) {
                     const int it = u * 256 + tid;
                     const int which = 1 + it / (32 * NA), rem_ = it % (32 * NA);
-                    rope_kv_item<true, NS>(pv, rt, nullptr, ktw, vtw, TPC, nh, HD, which, h, rem_ % NA, tb0 * 32 + rem_ / NA, b, 0, kcp, vcp);
+                    const int t = tb0 * 32 + rem_ / NA;
+                    rope_kv_item<true, NS>(pv, rt, nullptr, ktw, vtw, TPC, nh, HD, which, h, rem_ % NA, t, b, row_of(t), 0, kcp, vcp);
                 }
             } else {
 #pragma unroll
                 for (int u = 0; u < 2 * TPC * NA / 256; ++u) {
                     const int it = u * 256 + tid;
                     const int which = 1 + it / (TPC * NA), rem_ = it % (TPC * NA);
-                    rope_kv_item<true, NS>(pv, rt, nullptr, ktw, vtw, TPC, nh, HD, which, h, rem_ % NA, rem_ / NA, b, 0, kcp, vcp);
+                    const int t = rem_ / NA;
+                    rope_kv_item<true, NS>(pv, rt, nullptr, ktw, vtw, TPC, nh, HD, which, h, rem_ % NA, t, b, row_of(t), 0, kcp, vcp);
                 }
             }
             if (!tree_only) {
@@ -224,7 +229,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
         for (int u = 0; u < (TPC * NA + 255) / 256; ++u) {
             const int it = u * 256 + tid;
             if (TPC * NA >= 256 || it < TPC * NA)
-                rope_kv_item<true, NS>(pv, rt, (bf16x8*)lds, nullptr, nullptr, TPC, nh, HD, 0, h, it % NA, it / NA, b, q_unit0);
+                rope_kv_item<true, NS>(pv, rt, (bf16x8*)lds, nullptr, nullptr, TPC, nh, HD, 0, h, it % NA, it / NA, b, row_of(it / NA), q_unit0);
         }
     } else {   // queries of this (sequence, head, query group) -> LDS, a quarter per wave
         const bf16x8* qsrc = Qp + (((size_t)b * nh + h) * TB + tg * TBW) * (KK * 2 * 64) + lane;
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
         for (int i = 0; i < QW; ++i) lds_dma16(qsrc + (wave * QW + i) * 64, myq_addr + i * 1024);
     }
 
-    const int n = kv_len[b];
+    const int n = kv_len[sq];
     const int nblk = (n + 31) >> 5;
     const int ncache = has_cache ? max(0, min(per, nblk - c0)) : 0;
     const int nit = __builtin_amdgcn_readfirstlane(max(0, min(share, ntree + ncache - jw)));       // this wave's items [jw, jw + nit)
@@ -436,7 +441,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
 // qkv: NULL (the queries and the tree's keys / values were made by launch_rope_kv), or the QKV projection's partial
 // sums: then this launch makes them itself (one query group only: Tp <= 64), and `rt` gives the rotation table
 void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, const void* kt, const void* vt,
-                      const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart, int B, int nh,
+                      const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart, RowRef rr, int B, int nh,
                       int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep, hipStream_t s, hipEvent_t ev0,
                       hipEvent_t ev1, const PartView* qkv, const RowTable* rt) {
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
@@ -453,7 +458,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
         grid = dim3(nh, nparts, B);
     }
 #define ATT_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (const bf16x8*)kt, (const bf16x8*)vt, \
-                 kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg
+                 kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg, rr
 #define ATT(HD_, TBW_, AW_, ...)                                                                                     \
     do {                                                                                                        \
         if (ev0 || ev1)                                                                                         \
@@ -484,16 +489,17 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 // Merge the split-KV partials and emit the packed bf16 operand of the O-projection (body: row_ops.h).
 // one thread per (seq, head, query t, 8 consecutive output dims), grid (chunks of t x dims, head, seq)
 __global__ void k_attn_merge(const float* __restrict__ opart, const float2* __restrict__ mlpart,
-                             bf16x8* __restrict__ xp, int nh, int hd, int e8_shift, int Tp, int nparts, int MB) {
+                             bf16x8* __restrict__ xp, RowRef rr, int nh, int hd, int e8_shift, int Tp, int nparts, int MB) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;      // hd / 8 = 1 << e8_shift pieces per query row
     const int e8 = idx & ((1 << e8_shift) - 1), t = idx >> e8_shift;
-    if (t >= Tp) return;
-    attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, MB, /*b=*/blockIdx.z, /*h=*/blockIdx.y, t, e8);
+    const int b = blockIdx.z;
+    if (t >= rr.len(b)) return;
+    attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, MB, b, /*h=*/blockIdx.y, t, rr.off(b) + t, e8);
 }
 
-void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, int B, int nh, int hd, int Tp,
-                       int nparts, int MB, hipStream_t s) {
+void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
+                       int Tp, int nparts, int MB, hipStream_t s) {
     const int e8_shift = hd == 128 ? 4 : 3;            // head_dim is 128 or 64
-    hipLaunchKernelGGL(k_attn_merge, dim3((Tp * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
-                       (bf16x8*)x_packed, nh, hd, e8_shift, Tp, nparts, MB);
+    hipLaunchKernelGGL(k_attn_merge, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
+                       (bf16x8*)x_packed, rr, nh, hd, e8_shift, Tp, nparts, MB);
 }

@@ -431,7 +431,8 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 // Commit the kept nodes' K/V rows: tree-scratch row src_slots[j] -> cache row n_old + j, for
 // every layer and head. A kept node at chain index j was rotated for position n_old + j
 // already (depth = chain index), so this is a pure copy.
-// grid: x = head, y = sequence, z = layer; eight waves that share a list of wave-sized tasks, every task a run of
+// grid: x = head, y = sequence b of the pass that filled the scratch (sequence rm.seq[b] of the cache, entry rm.off[b] of
+// src_slots, n_accept and n_old), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
 // whole 16-byte pieces that lie side by side in the cache:
 //   values: a 16-byte piece of the value layout holds one dim of EIGHT rows (a "group": of a 16-row half of a block,
 //     the four rows of one quad and of the quad two further on), so a row cannot move as a piece, and a piece
@@ -452,7 +453,7 @@ static __device__ inline int vgroup_of(int c) { return (c >> 5) * 4 + ((c >> 4) 
 __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const uint16_t* __restrict__ kt, const uint16_t* __restrict__ vt, uint16_t* __restrict__ kc,
     uint16_t* __restrict__ vc, const int32_t* __restrict__ src_slots, const int32_t* __restrict__ n_accept,
-    const int32_t* __restrict__ n_old, int nh, int hd, int TB, int cap_blocks, int W, int mirror_groups,
+    const int32_t* __restrict__ n_old, RowMap rm, int nh, int hd, int TB, int cap_blocks, int W, int mirror_groups,
     int L, int lpw, size_t layer_stride_t, size_t layer_stride_c) {
     extern __shared__ __align__(16) uint16_t kvc_mirror[];          // [kept group][hd / 32][32 dims][8 rows]
     __shared__ int s_slots[SD_MAX_TREE];
@@ -460,10 +461,11 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int l0 = blockIdx.z * lpw, l1 = min(l0 + lpw, L);
     const int wave = tid >> 6, lane = tid & 63;
-    const int a = min(n_accept[b], W);                              // <= SD_MAX_TREE < KVC_THREADS
+    const int lst = rm.off[b];                                      // whose list, count and old length these are
+    const int a = min(n_accept[lst], W);                            // <= SD_MAX_TREE < KVC_THREADS
     if (a <= 0) return;
-    const int n = n_old[b];
-    const int slot = tid < a ? min(max(src_slots[(size_t)b * W + tid], 0), TB * 32 - 1) : 0;
+    const int n = n_old[lst];
+    const int slot = tid < a ? min(max(src_slots[(size_t)lst * W + tid], 0), TB * 32 - 1) : 0;
     if (tid == 0) s_need = 0;
     __syncthreads();
     if (tid < a) {
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     }
     __syncthreads();
     const size_t toff0 = ((size_t)b * nh + h) * TB * (32 * hd);
-    const size_t coff0 = ((size_t)b * nh + h) * cap_blocks * (32 * hd);
+    const size_t coff0 = ((size_t)rm.seq[b] * nh + h) * cap_blocks * (32 * hd);
     const int EB = hd / 32, KP = hd / 64;                  // wave tasks per 16-row half (values), per 8 rows (keys)
     typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -534,10 +536,9 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
 }
 
 void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void* vc_all, const int32_t* src_slots,
-                      const int32_t* n_accept, const int32_t* n_old, int L, int B, int nh, int hd, int TB,
-                      int cap_blocks, int rows, int W, hipStream_t s) {
-    (void)rows;
-    size_t lst = (size_t)B * nh * TB * 32 * hd, lsc = (size_t)B * nh * cap_blocks * 32 * hd;
+                      const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B, int L, int B, int nh, int hd,
+                      int TB, int cap_blocks, int W, hipStream_t s) {
+    size_t lst = (size_t)B * nh * TB * 32 * hd, lsc = (size_t)kv_B * nh * cap_blocks * 32 * hd;
     // LDS copy of the scratch groups (8 rows x hd) with a kept row: at most one per row, at most all of them
     int groups = W < TB * 4 ? W : TB * 4;
     size_t mirror = (size_t)groups * 8 * hd * 2;
@@ -546,7 +547,7 @@ void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void
     lpw = lpw < 1 ? 1 : lpw > L ? L : lpw;
     hipLaunchKernelGGL(k_kv_commit, dim3(nh, B, (L + lpw - 1) / lpw), dim3(KVC_THREADS), mirror, s,
                        (const uint16_t*)kt_all, (const uint16_t*)vt_all, (uint16_t*)kc_all, (uint16_t*)vc_all, src_slots,
-                       n_accept, n_old, nh, hd, TB, cap_blocks, W, groups, L, lpw, lst, lsc);
+                       n_accept, n_old, rm, nh, hd, TB, cap_blocks, W, groups, L, lpw, lst, lsc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -627,23 +628,24 @@ void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_copy_i32, dim3((n + 255) / 256), dim3(256), 0, s, src, dst, n);
 }
 
-// Prompt chunks commit every row: slots are the identity, the count is the chunk length.
-__global__ void k_prefill_commit_setup(ChainArgs ca, int B, int Tp, int32_t* __restrict__ src_slots,
+// Prompt chunks commit every row: slots are the identity, the count is the chunk length. (src_slots, n_accept and n_old
+// by sequence of the pass, kv_len and last_row by sequence of the cache.)
+__global__ void k_prefill_commit_setup(ChainArgs ca, RowMap rm, int B, int Tp, int32_t* __restrict__ src_slots,
                                        int32_t* __restrict__ n_accept, int32_t* __restrict__ n_old,
                                        int32_t* __restrict__ kv_len, int32_t* __restrict__ last_row) {
     const int b = blockIdx.x, j = threadIdx.x;
     if (j < Tp) src_slots[(size_t)b * Tp + j] = j;
     if (j == 0) {
-        int n = kv_len[b];
+        const int sq = rm.seq[b], n = kv_len[sq];
         n_old[b] = n;
         n_accept[b] = ca.len[b];
-        kv_len[b] = n + ca.len[b];
-        if (ca.len[b] > 0) last_row[b] = b * Tp + ca.len[b] - 1;
+        kv_len[sq] = n + ca.len[b];
+        if (ca.len[b] > 0) last_row[sq] = rm.off[b] + ca.len[b] - 1;
     }
 }
-void launch_prefill_commit_setup(const ChainArgs& ca, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
+void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
                                  int32_t* n_old, int32_t* kv_len, int32_t* last_row, hipStream_t s) {
-    hipLaunchKernelGGL(k_prefill_commit_setup, dim3(B), dim3(SD_MAX_TREE), 0, s, ca, B, Tp, src_slots, n_accept, n_old,
+    hipLaunchKernelGGL(k_prefill_commit_setup, dim3(B), dim3(SD_MAX_TREE), 0, s, ca, rm, B, Tp, src_slots, n_accept, n_old,
                        kv_len, last_row);
 }
 

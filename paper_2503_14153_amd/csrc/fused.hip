@@ -111,7 +111,7 @@ __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_layer(const FusedArgs 
         rows();
         drain();
         mark();                                            // [4p+2] ... and its results have left this workgroup
-        gm.setup(fg.X, fg.W, a.zfrag, fg.out, fg.KB, fg.NB, fg.ldo, fg.slot_stride, fg.upw, fg.rem, fg.kb_magic, fg.slot0,
+        gm.setup(fg.X, fg.W, a.zfrag, fg.out, fg.KB, fg.NB, fg.ldo, fg.slot_stride, Mp, fg.upw, fg.rem, fg.kb_magic, fg.slot0,
                  (int)g, fg.G);
         gm.issue_ring();                                   // the first ring sets out while the grid gathers
         barrier();
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_layer(const FusedArgs 
                 const unsigned kbh = item % nk, r1 = item / nk, tblk = r1 % TB, r2 = r1 / TB;
                 const unsigned h = r2 % (unsigned)a.nh, b = r2 / (unsigned)a.nh;
                 attn_merge_item<true>(a.opart, a.mlpart, a.att, a.nh, a.hd, a.Tp, a.nparts, MB, b, h,
-                                      tblk * 32 + (lane & 31), kbh * 2 + (lane >> 5));
+                                      tblk * 32 + (lane & 31), b * a.Tp + tblk * 32 + (lane & 31), kbh * 2 + (lane >> 5));
             }
         });
     }
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_layer(const FusedArgs 
         for (unsigned item = g * 512u + tid; item < total; item += G * 512u) {
             const unsigned ha = item % han, r1 = item / han, m = r1 % (unsigned)M, which = r1 / (unsigned)M;
             const unsigned b = m / (unsigned)a.Tp, t = m % (unsigned)a.Tp;
-            rope_kv_item<true>(pv, a.rt, a.q, a.kt, a.vt, a.Tp, a.nh, a.hd, which, ha / na, ha % na, t, b);
+            rope_kv_item<true>(pv, a.rt, a.q, a.kt, a.vt, a.Tp, a.nh, a.hd, which, ha / na, ha % na, t, b, m);
         }
     }
     mark();

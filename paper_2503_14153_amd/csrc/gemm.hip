@@ -71,11 +71,11 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int nb_offset,
 template <int MT>
 __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_gemm_sk(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                     const bf16x8* __restrict__ zfrag, float* __restrict__ out,
-                                                    int KB, int NB, int ldo, size_t slot_stride, int upw, int rem,
+                                                    int KB, int NB, int ldo, size_t slot_stride, int rows, int upw, int rem,
                                                     uint32_t kb_magic, const int32_t* __restrict__ slot0_tab) {
     __shared__ bf16x8 xs[SK_LDS_UNITS];
     SkGemm<MT> gm;
-    gm.setup(Xp, Wp, zfrag, out, KB, NB, ldo, slot_stride, upw, rem, kb_magic, slot0_tab, blockIdx.x, gridDim.x);
+    gm.setup(Xp, Wp, zfrag, out, KB, NB, ldo, slot_stride, rows, upw, rem, kb_magic, slot0_tab, blockIdx.x, gridDim.x);
     gm.issue_x();                                      // the short L2 loads first: a wave's loads return in order
     gm.issue_ring();
     gm.template run<false>(xs, SkRowScale{nullptr, 0, 0.f, 0.f}, nullptr);
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_gemm_sk(const bf16x8* 
 template <int MT, int CG>
 __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                       const bf16x8* __restrict__ zfrag, float* __restrict__ out,
-                                                      int KB, int NB, int ldo, size_t slot_stride, int S) {
+                                                      int KB, int NB, int ldo, size_t slot_stride, int rows, int S) {
     static_assert((MT == 4 || MT == 8) && (CG * MT) % 16 == 0 && CG <= 8, "row blocks / column group");
     constexpr int R = 4;                                // ring depth in steps; even (the LDS buffer of step i is i & 1)
     constexpr int CPW = CG * MT / 8;                    // column blocks per wave: 8 waves cover MT rows x CG columns
@@ -186,15 +186,16 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
     }
     int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
     asm volatile("" : "+v"(gq), "+s"(ldo_here));
+    const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(r) * 32, rows, ldo_here);
 #pragma unroll
     for (int j = 0; j < CPW; ++j) {
         const int nb = ng * CG + ch * CPW + j;
         if (nb < NB) {
-            float* o = out + (size_t)seg * slot_stride + (size_t)nb * 32 + (lane & 31);
+            const int col = nb * 32 + (lane & 31);
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int m = r * 32 + 8 * (v >> 2) + 4 * gq + (v & 3);
-                __hip_atomic_store(&o[(size_t)m * ldo_here], acc[j][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int m = 8 * (v >> 2) + 4 * gq + (v & 3);
+                ts.put(acc[j][v], (m * ldo_here + col) * 4);
             }
         }
     }
@@ -329,7 +330,7 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     if (MB >= 4) gemm_plan_rows(p);
 }
 
-PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, hipStream_t s,
+PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
                      hipEvent_t ev0, hipEvent_t ev1) {
     PartView pv;
     pv.base = out;
@@ -338,7 +339,7 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
     pv.cnt = p.uniform ? nullptr : p.cnt_dev;         // NULL: nmax slots everywhere, the consumer need not look it up
     pv.nmax = p.slots;
     const uint32_t kb_magic = (uint32_t)((0x100000000ull + (uint64_t)p.KB - 1) / (uint64_t)p.KB);
-#define SK_ARGS (const bf16x8*)Xp, (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, p.upw, p.rem, kb_magic, p.slot0_dev
+#define SK_ARGS (const bf16x8*)Xp, (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.upw, p.rem, kb_magic, p.slot0_dev
 #define SK_LAUNCH(KERNEL_, THREADS_, ...)                                                                  \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
@@ -354,10 +355,10 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
             hipExtLaunchKernelGGL((k_gemm_rows<MT_, CG_>), dim3(G), dim3(512), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
-                                  (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, p.S); \
+                                  (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S); \
         else                                                                                               \
             hipLaunchKernelGGL((k_gemm_rows<MT_, CG_>), dim3(G), dim3(512), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, p.S);         \
+                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S);   \
     } while (0)
         const int key = p.MB * 10 + p.CG;
         if (key == 88) ROWS_LAUNCH(8, 8);

@@ -172,6 +172,8 @@ static __device__ __forceinline__ void norm_tile(float* __restrict__ x, const Pa
 // expansion), k and v (tree scratch, block layouts, bf16). One item = (row t of sequence b, head h, piece a,
 // which): dims [8a, 8a+8) and their rotary partners [hd/2 + 8a, +8) of q (which = 0), k (1) or v (2).
 // Nothing written here is read again within the launch (the attention kernel is the consumer).
+// m = the packed row that is read; a padding row (t past the sequence's rows) is given the last real one, so that what is
+// written for it is finite: attention multiplies padding values by probabilities that are exactly 0.
 // NS > 0: every column group of the QKV projection has NS slots (its plan says so): all loads in a straight line.
 // q_unit0: subtracted from the 16-byte unit index of the query fragments (a caller that keeps one head's queries in a
 // buffer of its own, e.g. in LDS, passes that head's offset). k_copy / v_copy: if not NULL, this head's key / value
@@ -179,9 +181,8 @@ static __device__ __forceinline__ void norm_tile(float* __restrict__ x, const Pa
 template <bool BATCH, int NS = 0>
 static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const RowTable& rt, bf16x8* __restrict__ qp,
                                                     uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp, int nh,
-                                                    int hd, int which, int h, int a, int t, int b, size_t q_unit0 = 0,
+                                                    int hd, int which, int h, int a, int t, int b, int m, size_t q_unit0 = 0,
                                                     uint16_t* k_copy = nullptr, uint16_t* v_copy = nullptr) {
-    const int m = b * Tp + t;
     const int d = nh * hd, half = hd / 2;
     const int col0 = which * d + h * hd + a * 8;
     const float* p0 = pv.base + (size_t)m * pv.ld + col0;
@@ -282,13 +283,13 @@ static __device__ __forceinline__ void swiglu_item(const PartView& pv, int F, in
 
 // ------------------------------------------------------------------------------------------
 // Merge the split-KV partials of one (sequence b, head h, query t, 8 consecutive output dims e8) and emit
-// the packed bf16 operand of the O-projection. The parts are read in batches of eight whose loads are all
+// the packed bf16 operand of the O-projection (row m). The parts are read in batches of eight whose loads are all
 // issued before any is used (a part index past the end re-reads the last part with weight zero, so no load
 // sits behind a branch).
 template <bool WT>
 static __device__ __forceinline__ void attn_merge_item(const float* __restrict__ opart, const float2* __restrict__ mlpart,
                                                        bf16x8* __restrict__ xp, int nh, int hd, int Tp, int nparts, int MB,
-                                                       int b, int h, int t, int e8) {
+                                                       int b, int h, int t, int m, int e8) {
     constexpr int PB = 8;
     size_t base = ((size_t)b * nh + h) * nparts;
     float M = NEG_INF_F, den = 0.f, o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -326,7 +327,7 @@ static __device__ __forceinline__ void attn_merge_item(const float* __restrict__
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] *= inv;
     split_hilo(o, hi, lo);
-    int m = b * Tp + t, k = h * hd + e8 * 8;
+    const int k = h * hd + e8 * 8;
     const size_t u = xpack_index(m, k, MB) >> 3;
     store_frag16<WT>(xp + u, hi);
     store_frag16<WT>(xp + u + XPART / 8, lo);

@@ -28,13 +28,14 @@ static __device__ inline void embed_row(const void* __restrict__ embed, int embe
 
 // Tree assembly (paper Section III-B): node 0 = the base model's token, node j >= 1 = the
 // candidate number rank[j] of head depth[j]-1; position = committed length + depth; a node
-// attends its ancestors and itself.  One workgroup per row.
+// attends its ancestors and itself.  One workgroup per row of the padded tree: a padding row only gets its ancestor words
+// (itself), unless the rows of a sequence lie R > T apart (then rows T .. R - 1 are rows of zeros).
 __global__ void k_build_rows_tree(RowTable rt, const int32_t* __restrict__ parent, const int32_t* __restrict__ depth,
                                   const int32_t* __restrict__ rank, const int32_t* __restrict__ root_tok,
-                                  const int32_t* __restrict__ cand, const int32_t* __restrict__ kv_len, int T, int Tp,
+                                  const int32_t* __restrict__ cand, const int32_t* __restrict__ kv_len, int T, int Tp, int R,
                                   int H, int topk, int hd, float theta, const void* __restrict__ embed, int embed_f32,
                                   int d, int V, float* __restrict__ x) {
-    const int m = blockIdx.x, b = m / Tp, j = m % Tp;
+    const int b = blockIdx.x / Tp, j = blockIdx.x % Tp, m = b * R + j;
     const bool valid = j < T;
     int tok = 0, pos = kv_len[b];
     uint32_t a[SD_ANC_WORDS] = {};
@@ -47,33 +48,40 @@ __global__ void k_build_rows_tree(RowTable rt, const int32_t* __restrict__ paren
     } else {
         a[j >> 5] |= 1u << (j & 31);
     }
+    if (threadIdx.x == 0)
+        for (int w = 0; w < SD_ANC_WORDS; ++w) rt.anc[(size_t)blockIdx.x * SD_ANC_WORDS + w] = a[w];
+    if (j >= R) return;
     if (threadIdx.x == 0) {
         rt.tok[m] = tok;
         rt.pos[m] = pos;
-        for (int w = 0; w < SD_ANC_WORDS; ++w) rt.anc[(size_t)m * SD_ANC_WORDS + w] = a[w];
     }
     for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, i, hd, theta);
     embed_row(embed, embed_f32, tok, d, x + (size_t)m * d, valid);
 }
 
 void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* depth, const int32_t* rank,
-                            const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len, int B, int T, int Tp,
+                            const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len, int B, int T, int Tp, int R,
                             int H, int topk, int hd, float theta, const void* embed, int embed_f32, int d, int V, float* x,
                             hipStream_t s) {
     hipLaunchKernelGGL(k_build_rows_tree, dim3(B * Tp), dim3(256), 0, s, rt, parent, depth, rank, root_tok, cand,
-                       kv_len, T, Tp, H, topk, hd, theta, embed, embed_f32, d, V, x);
+                       kv_len, T, Tp, R, H, topk, hd, theta, embed, embed_f32, d, V, x);
 }
 
-// Prompt chunk as a chain: row j of sequence b is prompt token off[b] + j at position
-// committed length + j and attends rows 0..j of the chunk.
-__global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ tokens, ChainArgs ca,
+// Prompt chunk as a chain: row j of sequence b is prompt token ca.off[b] + j at position
+// committed length + j and attends rows 0..j of the chunk. (Rows between ca.len and rm.len, if any, are rows of zeros.)
+__global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ tokens, ChainArgs ca, RowMap rm, RowMap* __restrict__ rm_dev,
                                    const int32_t* __restrict__ kv_len, int Tp, int hd, float theta,
                                    const void* __restrict__ embed, int embed_f32, int d, int V,
                                    float* __restrict__ x) {
-    const int m = blockIdx.x, b = m / Tp, j = m % Tp;
+    const int b = blockIdx.x / Tp, j = blockIdx.x % Tp, m = rm.off[b] + j;
+    if (blockIdx.x == 0 && threadIdx.x < SD_MAX_BATCH) {       // the map, for the kernels that follow
+        rm_dev->off[threadIdx.x] = rm.off[threadIdx.x];
+        rm_dev->len[threadIdx.x] = rm.len[threadIdx.x];
+        rm_dev->seq[threadIdx.x] = rm.seq[threadIdx.x];
+    }
     const bool valid = j < ca.len[b];
     int tok = valid ? min(max(tokens[ca.off[b] + j], 0), V - 1) : 0;
-    int pos = kv_len[b] + (valid ? j : 0);
+    int pos = kv_len[rm.seq[b]] + (valid ? j : 0);
     uint32_t a[SD_ANC_WORDS] = {};
     if (valid) {
         for (int w = 0; w < SD_ANC_WORDS; ++w) {
@@ -83,19 +91,21 @@ __global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ toke
     } else {
         a[j >> 5] |= 1u << (j & 31);
     }
+    if (threadIdx.x == 0)
+        for (int w = 0; w < SD_ANC_WORDS; ++w) rt.anc[(size_t)blockIdx.x * SD_ANC_WORDS + w] = a[w];
+    if (j >= rm.len[b]) return;
     if (threadIdx.x == 0) {
         rt.tok[m] = tok;
         rt.pos[m] = pos;
-        for (int w = 0; w < SD_ANC_WORDS; ++w) rt.anc[(size_t)m * SD_ANC_WORDS + w] = a[w];
     }
     for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, i, hd, theta);
     embed_row(embed, embed_f32, tok, d, x + (size_t)m * d, valid);
 }
 
-void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const int32_t* kv_len, int B,
-                             int Tp, int hd, float theta, const void* embed, int embed_f32, int d, int V, float* x,
+void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev,
+                             const int32_t* kv_len, int B, int Tp, int hd, float theta, const void* embed, int embed_f32, int d, int V, float* x,
                              hipStream_t s) {
-    hipLaunchKernelGGL(k_build_rows_chain, dim3(B * Tp), dim3(256), 0, s, rt, tokens, ca, kv_len, Tp, hd, theta,
+    hipLaunchKernelGGL(k_build_rows_chain, dim3(B * Tp), dim3(256), 0, s, rt, tokens, ca, rm, rm_dev, kv_len, Tp, hd, theta,
                        embed, embed_f32, d, V, x);
 }
 
@@ -104,21 +114,25 @@ void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs
 __global__ __launch_bounds__(NP_THREADS) void k_norm_pack(float* __restrict__ x, PartView pv,
                                                           const uint16_t* __restrict__ gain, float eps,
                                                           bf16x8* __restrict__ xn, float* __restrict__ hf, int d,
-                                                          int MB, const int32_t* __restrict__ gather) {
+                                                          int MB, int M, const int32_t* __restrict__ gather) {
     __shared__ float red[NP_THREADS / 64];
     // Eight neighbouring rows share every 128-byte line of the packed operand (a row's 16-byte piece per lane), and
     // workgroups go to the eight XCDs round-robin: workgroups b, b + 8, b + 16, .. take neighbouring rows, so that
     // a line is put together in ONE L2 and leaves it whole instead of as eight masked pieces from eight L2s.
+    // (The grid is rounded up to whole groups of 64 rows, of 32 up to one row block, where that gives half lines, when
+    // there are more than eight rows; workgroups without a row leave.)
     int m = blockIdx.x;
     if ((gridDim.x & 63) == 0) m = (m & ~63) + (m & 7) * 8 + ((m & 63) >> 3);
-    else if ((gridDim.x & 31) == 0) m = (m & ~31) + (m & 7) * 4 + ((m & 31) >> 3);      // one row block: half lines
+    else if ((gridDim.x & 31) == 0) m = (m & ~31) + (m & 7) * 4 + ((m & 31) >> 3);
+    if (m >= M) return;
     norm_pack_row<false>(x, pv, gain, eps, xn, hf, d, MB, gather ? gather[m] : m, m, red);
 }
 
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out, int M, int d,
                       int MB, const int32_t* gather, hipStream_t s) {
-    hipLaunchKernelGGL(k_norm_pack, dim3(M), dim3(NP_THREADS), 0, s, x, pv,
-                       (const uint16_t*)gain, eps, (bf16x8*)xn_packed, hf_out, d, MB, gather);
+    const int grid = M <= 8 ? M : M <= 32 ? 32 : (M + 63) / 64 * 64;
+    hipLaunchKernelGGL(k_norm_pack, dim3(grid), dim3(NP_THREADS), 0, s, x, pv,
+                       (const uint16_t*)gain, eps, (bf16x8*)xn_packed, hf_out, d, MB, M, gather);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -128,18 +142,18 @@ void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* 
 // query and key layouts put row r, dim group g of contraction step w at lane r + 32 g) and what it reads of a row and
 // slot are 64 contiguous bytes twice. (One thread per (h, a) of ONE row wrote the same bytes as 16-byte pieces 0.5-2
 // KiB apart; the values' layout is transposed, their 2-byte stores stay scattered either way.)
-__global__ void k_rope_kv(PartView pv, RowTable rt, bf16x8* __restrict__ qp, uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp,
-                          int nh, int hd, int na) {
+__global__ void k_rope_kv(PartView pv, RowTable rt, RowRef rr, bf16x8* __restrict__ qp, uint16_t* __restrict__ kt,
+                          uint16_t* __restrict__ vt, int Tp, int nh, int hd, int na) {
     const int which = blockIdx.x % 3, h = blockIdx.x / 3;     // a constant divisor: a multiplication
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int t = blockIdx.y * 32 + (lane & 31);
+    const int t = blockIdx.y * 32 + (lane & 31), b = blockIdx.z, m = rr.off(b) + min(t, rr.len(b) - 1);
     for (int a = 2 * wave + (lane >> 5); a < na; a += 8)      // hd / 16 pieces: 8 (one round) or 4 (waves 0 and 1)
-        rope_kv_item<false>(pv, rt, qp, kt, vt, Tp, nh, hd, which, h, a, t, blockIdx.z);
+        rope_kv_item<false>(pv, rt, qp, kt, vt, Tp, nh, hd, which, h, a, t, b, m);
 }
 
-void launch_rope_kv(PartView pv, RowTable rt, void* q_packed, void* kt, void* vt, int B, int Tp, int nh, int hd,
-                    hipStream_t s) {
-    hipLaunchKernelGGL(k_rope_kv, dim3(nh * 3, Tp / 32, B), dim3(256), 0, s, pv, rt, (bf16x8*)q_packed, (uint16_t*)kt,
+void launch_rope_kv(PartView pv, RowTable rt, RowRef rr, void* q_packed, void* kt, void* vt, int B, int Tp, int nh,
+                    int hd, hipStream_t s) {
+    hipLaunchKernelGGL(k_rope_kv, dim3(nh * 3, Tp / 32, B), dim3(256), 0, s, pv, rt, rr, (bf16x8*)q_packed, (uint16_t*)kt,
                        (uint16_t*)vt, Tp, nh, hd, hd / 16);
 }
 

@@ -69,10 +69,32 @@ static __host__ __device__ inline size_t vblk_index(int c, int e, int HD) {
 }
 
 // ---- per-call row table (device) -----------------------------------------------------------
+// The M rows of a pass are packed: sequence i of the pass owns rows [off[i], off[i] + len[i]) of the residual stream, of
+// every GEMM operand and of every partial sum, with no padding between sequences, so eight sequences of plain decoding
+// are 8 rows and not 256 (7B shape, four layers, GEMM time per layer 232 -> 96 us). Only attention works on 32-row blocks per sequence: its
+// queries, the tree's K/V scratch and its partials are [i][Tp], row t there is packed row off[i] + t for t < len[i] and
+// padding (never read back as a result) beyond.
+#define SD_MAX_BATCH 32
+struct RowMap {
+    int32_t off[SD_MAX_BATCH], len[SD_MAX_BATCH];   // len >= 1
+    int32_t seq[SD_MAX_BATCH];                      // sequence of the cache
+};
+// What the kernels of a layer get: every sequence of a step has the same number of rows, R (map NULL); a prompt pass leaves
+// its map in device memory. (As an argument of every launch the map's 384 bytes cost the 64-node step 1 %, read from
+// memory by every launch another 1 %: the attention launch's first addresses wait for it, 14.9 -> 15.5 us.)
+struct RowRef {
+    const RowMap* map;
+    int R;
+#ifdef __HIPCC__
+    __device__ __forceinline__ int off(int i) const { return map ? map->off[i] : i * R; }
+    __device__ __forceinline__ int len(int i) const { return map ? map->len[i] : R; }
+    __device__ __forceinline__ int seq(int i) const { return map ? map->seq[i] : i; }
+#endif
+};
 struct RowTable {
     int32_t* tok;      // [M] token id of every row (0 for padding rows)
     int32_t* pos;      // [M] position
-    uint32_t* anc;     // [M][SD_ANC_WORDS] bit i set: row may attend tree row i of its sequence
+    uint32_t* anc;     // [i][Tp][SD_ANC_WORDS] bit j set: row may attend tree row j of its sequence
     float2* cs;        // [M][head_dim/2] (cos, sin) of the rotary angle
 };
 
@@ -160,9 +182,8 @@ struct FusedArgs {
     unsigned long long* timeline;   // NULL, or [24][gridDim.x] time stamps (100 MHz): entry to each phase, end of launch
 };
 
-#define SD_MAX_BATCH 32
 #define SD_MAX_MEDUSA 15
-struct ChainArgs { int32_t off[SD_MAX_BATCH]; int32_t len[SD_MAX_BATCH]; };
+struct ChainArgs { int32_t off[SD_MAX_BATCH]; int32_t len[SD_MAX_BATCH]; };   // prompt tokens of every sequence of the pass
 struct MedusaBias { const uint16_t* p[SD_MAX_MEDUSA + 1]; };
 struct VerifyArgs {
     const int32_t *parent, *depth;      // device tree tables [T]
@@ -189,7 +210,8 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
 // ev0 / ev1 (both or neither): events that receive the kernel's own start and end time stamps,
 // for per-kernel timing without launch gaps
 // sc: deferred RMS scale of the rows (ssq NULL: none; not available at four row blocks)
-PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, hipStream_t s,
+// rows: rows that exist; the partial tiles' other rows are not written
+PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
                      hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // persistent layer kernel: G workgroups (all must be resident at once), a.MB in {1, 2, 8}
 void launch_layer(const FusedArgs& a, int G, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -202,9 +224,9 @@ void launch_reduce_selected(PartView pv, float* dst, const int32_t* sel, int B, 
 
 void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* depth, const int32_t* rank,
                             const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len,
-                            int B, int T, int Tp, int H, int topk, int hd, float theta,
+                            int B, int T, int Tp, int R, int H, int topk, int hd, float theta,
                             const void* embed, int embed_f32, int d, int V, float* x, hipStream_t s);
-void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const int32_t* kv_len,
+void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev, const int32_t* kv_len,
                              int B, int Tp, int hd, float theta, const void* embed, int embed_f32, int d, int V,
                              float* x, hipStream_t s);
 // float32 device path (f32.hip): natural row-major layouts, vector-ALU arithmetic
@@ -226,14 +248,14 @@ void launch_f32_kv_rows(float* kc, float* vc, float* k_rows, float* v_rows, int 
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out,
                       int M, int d, int MB, const int32_t* gather, hipStream_t s);
 // RMSNorm with the scale deferred: operand = x * gain, ssq_part = partial sums of squares in SkRowScale's layout
-void launch_rope_kv(PartView pv, RowTable rt, void* q_packed, void* kt, void* vt, int B, int Tp, int nh, int hd,
-                    hipStream_t s);
+void launch_rope_kv(PartView pv, RowTable rt, RowRef rr, void* q_packed, void* kt, void* vt, int B, int Tp, int nh,
+                    int hd, hipStream_t s);
 void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, const void* kt, const void* vt,
                       const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart,
-                      int B, int nh, int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep,
+                      RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep,
                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const PartView* qkv = nullptr,
                       const RowTable* rt = nullptr);
-void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, int B, int nh, int hd,
+void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s);
 void launch_swiglu_pack(PartView pv, int F, int Fpad, void* act_packed, int M, int MB, hipStream_t s);
 // output rows i*B + b in chunks of chunk_rows rows, each a packed activation of MB (last: MBlast) row blocks
@@ -260,8 +282,8 @@ void launch_build_labels(const int32_t* l0, int B, int S, int H, int32_t frag, i
                          int keep_all, int32_t* labels, hipStream_t s);
 void launch_copy_row_stats(const float4* src, float4* dst, int B, int T, int Tp, hipStream_t s);
 void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void* vc_all,
-                      const int32_t* src_slots, const int32_t* n_accept, const int32_t* n_old,
-                      int L, int B, int nh, int hd, int TB, int cap_blocks, int rows, int W, hipStream_t s);
+                      const int32_t* src_slots, const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B,
+                      int L, int B, int nh, int hd, int TB, int cap_blocks, int W, hipStream_t s);
 void launch_commit_setup(const int32_t* n_rows, int width, int B, int32_t* n_accept, int32_t* n_old, int32_t* kv_len,
                          hipStream_t s);
 void launch_kv_rows(void* kc, void* vc, void* k_rows, void* v_rows, int row0, int nrows, int nh, int hd,
@@ -271,5 +293,5 @@ void launch_copy_rows_i32(const int32_t* src, int32_t* dst, int B, int T, int Tp
 void launch_copy_head_logits(const float* src, int ld, float* dst, int V, int B, int H, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int n, hipStream_t s);
 void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s);
-void launch_prefill_commit_setup(const ChainArgs& ca, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
+void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
                                  int32_t* n_old, int32_t* kv_len, int32_t* last_row, hipStream_t s);

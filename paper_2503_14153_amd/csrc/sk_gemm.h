@@ -3,6 +3,21 @@
 #pragma once
 #include "sd_internal.h"
 
+// Stores of one row block (rows row0 .. row0 + 31) of a partial tile of `rows` rows of ldo floats (all wave-uniform). Write-through: the tiles are consumed by
+// other XCDs anyway, and lines left dirty in this XCD's L2 would only be written back at the end of the kernel,
+// lengthening it. The rows of the last row block that do not exist (plain decoding: 31 of 32) lie past the buffer
+// resource's size and the hardware drops their stores: no branch and no mask in the epilogue (written with either, the
+// 64-row launches took 0.5 us longer each although all of their rows exist). One resource per row block: 32 * ldo * 4
+// bytes at most, a 32-bit size for every projection that fits the card.
+struct TileStore {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ TileStore(float* tile, int row0, int rows, int ldo)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(tile + (size_t)row0 * ldo, 0, min(max(rows - row0, 0), 32) * ldo * 4, 0x00020000)) {}
+    __device__ __forceinline__ void put(float v, int byte_offset) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, byte_offset, 0, /*sc1*/ 16);
+    }
+};
+
 struct SkIter { int kb, ng, valid, last; };
 
 // A workgroup's walk over its unit range [u, u1) in outer iterations of R steps, without any division
@@ -62,7 +77,7 @@ struct SkGemm {
 
     const bf16x8 *Xp, *Wp, *zl;
     float* out;
-    int KB, NB, ldo, tid, wave, lane, slot0;
+    int KB, NB, ldo, rows, tid, wave, lane, slot0;
     const int32_t* slot0_at;
     size_t slot_stride, wstep;
     SkWalk walk;
@@ -71,9 +86,9 @@ struct SkGemm {
 
     __device__ __forceinline__ void setup(const bf16x8* __restrict__ Xp_, const bf16x8* __restrict__ Wp_,
                                           const bf16x8* __restrict__ zfrag, float* __restrict__ out_, int KB_, int NB_,
-                                          int ldo_, size_t slot_stride_, int upw, int rem, uint32_t kb_magic,
+                                          int ldo_, size_t slot_stride_, int rows_, int upw, int rem, uint32_t kb_magic,
                                           const int32_t* __restrict__ slot0_tab, int g, int G) {
-        Xp = Xp_; Wp = Wp_; out = out_; KB = KB_; NB = NB_; ldo = ldo_; slot_stride = slot_stride_;
+        Xp = Xp_; Wp = Wp_; out = out_; KB = KB_; NB = NB_; ldo = ldo_; slot_stride = slot_stride_; rows = rows_;
         tid = threadIdx.x; wave = tid >> 6; lane = tid & 63;
         wstep = (size_t)NB * 64;
         // Every load is unconditional and its result is used as loaded: a fragment past the end of a segment is
@@ -206,24 +221,25 @@ struct SkGemm {
                 ++nseg;
                 const int nb = cur.ng * 8 + wave;
                 if (nb < NB) {
-                    float* o = out + (size_t)slot * slot_stride + (size_t)nb * 32 + (lane & 31);
                     // the row stride and the lane's row group are made opaque here so that the row offsets
                     // m * ldo are computed where they are used: hoisted out of the loop (which the compiler
                     // does otherwise) they occupy registers for the whole kernel, 64 of them here and some
                     // 150 in the 128-row kernel
                     int gq = lane >> 5, ldo_here = ldo;
                     asm volatile("" : "+v"(gq), "+s"(ldo_here));
+                    float* tile = out + (size_t)__builtin_amdgcn_readfirstlane(slot) * slot_stride;
+                    const int col = nb * 32 + (lane & 31);
 #pragma unroll
-                    // write-through stores: the tiles are consumed by other XCDs anyway, and lines left dirty
-                    // in this XCD's L2 would only be written back at the end of the kernel, lengthening it
-                    for (int mt = 0; mt < MT; ++mt)
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const TileStore ts(tile, mt * 32, rows, ldo_here);
 #pragma unroll
                         for (int v = 0; v < 16; ++v) {
-                            int m = mt * 32 + 8 * (v >> 2) + 4 * gq + (v & 3);
+                            const int m = 8 * (v >> 2) + 4 * gq + (v & 3);
                             float val = acc[mt][v];
-                            if constexpr (SCALE) val *= lds_f[m];
-                            __hip_atomic_store(&o[(size_t)m * ldo_here], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if constexpr (SCALE) val *= lds_f[mt * 32 + m];
+                            ts.put(val, (m * ldo_here + col) * 4);
                         }
+                    }
                 }
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
