@@ -71,8 +71,10 @@ struct sd_model {
     void* xh;                                // draft-head rows of every tree row, in 256-row operand chunks
     int draft_schedule = SD_DRAFT_AFTER_ACCEPT;
     RowTable rt;
+    double* rope_freq;                       // [head_dim / 2]
     RowMap* rm_dev;                          // the row map of a prompt pass, in device memory
-    int32_t *am, *g_parent, *g_depth, *g_rank;
+    int32_t *g_parent, *g_depth, *g_rank, *fin_rows;
+    float2* best; void* ranked;                 // ranking scratch: arg-max per row and chunk, top-k per head row and chunk
     float4* row_stats;                     // [Mp]: per tree row, statistics for typical acceptance
     uint32_t* zero_stop;
     const void* zfrag;                       // 1 KiB of zeros
@@ -216,15 +218,18 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
 
     size_t wz = 0;
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
-    const size_t w_x = wtake((size_t)Mp * d * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
+    const size_t w_x = wtake((size_t)Mp * d * 4);
+    const size_t w_logits = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * m->Vpad * 4);
     const size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4), w_hrows = wtake((size_t)SD_MAX_BATCH * d * 4);
     const size_t w_xn = wtake((size_t)Mp * d * 4), w_qkv = wtake((size_t)Mp * 3 * d * 4), w_q = wtake((size_t)Mp * d * 4);
     const size_t w_attn = wtake((size_t)Mp * d * 4), w_gu = wtake((size_t)Mp * 2 * F * 4), w_act = wtake((size_t)Mp * F * 4);
     const size_t w_kt = wtake((size_t)L * Mp * d * 4), w_vt = wtake((size_t)L * Mp * d * 4);
     const size_t w_z = wtake((size_t)SD_MAX_BATCH * H * d * 4), w_xh = wtake((size_t)HBp * d * 4);
     const size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
-    const size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_am = wtake((size_t)Mp * 4), w_g = wtake(3 * 4);
-    const size_t w_rm = wtake(sizeof(RowMap));
+    const size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
+    const size_t w_best = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * rank_chunks(V) * 8);
+    const size_t w_rk = wtake((size_t)std::min(H * SD_MAX_BATCH, 256) * rank_chunks(V) * cfg->topk * 8);
+    const size_t w_rm = wtake(sizeof(RowMap)), w_freq = wtake((size_t)(hd / 2) * 8);
     const size_t w_rs = wtake((size_t)Mp * 16), w_zs = wtake((size_t)ceil_div(V, 32) * 4);
     if (e == hipSuccess) e = hipMalloc((void**)&m->work, wz);
     if (e == hipSuccess) e = hipMemsetAsync(m->work, 0, wz, s);
@@ -243,11 +248,13 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     m->f.kt = (float*)(Wk + w_kt); m->f.vt = (float*)(Wk + w_vt); m->f.z = (float*)(Wk + w_z); m->f.xh = (float*)(Wk + w_xh);
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
-    m->am = (int32_t*)(Wk + w_am);
+    m->best = (float2*)(Wk + w_best); m->ranked = Wk + w_rk; m->fin_rows = (int32_t*)(Wk + w_fin);
     m->rm_dev = (RowMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
     m->zero_stop = (uint32_t*)(Wk + w_zs);
+    m->rope_freq = (double*)(Wk + w_freq);
+    launch_rope_freqs(m->rope_freq, hd, cfg->rope_theta, s);
     launch_fill_i32(m->g_parent, -1, 1, s);
     e = hipStreamSynchronize(s);
     if (e == hipSuccess) e = hipGetLastError();
@@ -383,7 +390,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     (void)ld_max;
     m->part_floats = pf;
     m->max_parts = 65;
-    const int HBp = pow2_blocks(H * SD_MAX_BATCH > 256 ? 256 : H * SD_MAX_BATCH) * 32;
+    const int HBp = pow2_blocks(std::min((H + 1) * SD_MAX_BATCH, 256)) * 32;      // head rows of a batch, and its base rows
     size_t wz = 0;
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
     size_t w_x = wtake((size_t)Mp * d * 4), w_part = wtake(pf * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
@@ -394,8 +401,10 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     size_t w_act = wtake((size_t)Mp * F * 4), w_q = wtake((size_t)Mp * d * 4);
     size_t w_kt = wtake((size_t)L * Mp * d * 2), w_vt = wtake((size_t)L * Mp * d * 2);
     size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
-    size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_am = wtake((size_t)Mp * 4), w_g = wtake(3 * 4);
-    size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(RowMap));
+    size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
+    size_t w_best = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * rank_chunks(V) * 8);
+    size_t w_rk = wtake((size_t)std::min(H * SD_MAX_BATCH, 256) * rank_chunks(V) * cfg->topk * 8);
+    size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(RowMap)), w_freq = wtake((size_t)(hd / 2) * 8);
     size_t w_xh = wtake(align_up((size_t)H * Mp, 256) * d * 4);
     size_t w_zs = wtake((size_t)ceil_div(V, 32) * 4), w_zf = wtake(1024);
     size_t w_ssqa = wtake((size_t)align_up(d / 16, 4) * Mp * 4), w_ssqf = wtake((size_t)align_up(d / 16, 4) * Mp * 4);
@@ -443,7 +452,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     m->xh = Wk + w_xh;
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
-    m->am = (int32_t*)(Wk + w_am);
+    m->best = (float2*)(Wk + w_best); m->ranked = Wk + w_rk; m->fin_rows = (int32_t*)(Wk + w_fin);
     m->rm_dev = (RowMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
@@ -458,6 +467,8 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
         m->sync_abort = m->sync_ctr + (size_t)(L + 1) * FUSED_SYNC_WORDS;
         m->fused_ok = true;
     }
+    m->rope_freq = (double*)(Wk + w_freq);
+    launch_rope_freqs(m->rope_freq, hd, cfg->rope_theta, s);
     launch_fill_i32(m->g_parent, -1, 1, s);
     e = hipStreamSynchronize(s);
     if (e == hipSuccess) e = hipGetLastError();
@@ -993,7 +1004,6 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int 
     return last;
 }
 
-// final norm + LM head on all rows + arg-max of the first T rows of every sequence
 // ------------------------------------------------------------------------------------------ float32 pass
 // by_seq: slots, counts and old lengths are listed by sequence of the cache (else by sequence of the pass)
 static void commit_rows(sd_model* m, sd_kv* kv, bool by_seq, const int32_t* slots, const int32_t* n_acc, int Tp, int W,
@@ -1010,7 +1020,7 @@ static void commit_rows(sd_model* m, sd_kv* kv, bool by_seq, const int32_t* slot
                          c.head_dim, Tp / 32, kv->cap_blocks, W, s);
 }
 
-static void run_forward_f32(sd_model* m, sd_kv* kv, int B, int T, int Tp, bool want_lm, hipStream_t s) {
+static void run_forward_f32(sd_model* m, sd_kv* kv, int B, int Tp, bool want_lm, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int M = B * Tp, d = c.d_model, F = c.d_ffn;
     sd_model::F32& f = m->f;
@@ -1032,71 +1042,101 @@ static void run_forward_f32(sd_model* m, sd_kv* kv, int B, int T, int Tp, bool w
     if (want_lm) {
         launch_f32_rmsnorm(m->x, f.final_norm, c.rms_eps, f.xn, M, d, nullptr, s);
         launch_f32_linear(f.xn, f.lm_head, nullptr, m->logits, M, c.vocab, d, d, m->Vpad, 0, s);
-        launch_argmax(m->logits, m->Vpad, c.vocab, m->am, B, T, Tp, s);
     }
 }
+// dense float32 logits as the ranking kernels take them
+static PartView dense_logits(const sd_model* m, const float* logits) { return PartView{logits, 0, m->Vpad, nullptr, 1}; }
 
-static void run_draft_heads_f32(sd_model* m, sd_kv* kv, int B, uint32_t seq_mask, float* head_logits_out, hipStream_t s) {
+// (m->h_rows holds the final norm's output of the B rows that are drafted from)
+static void run_draft_heads_f32(sd_model* m, sd_kv* kv, int B, const SeqList& sl, float* head_logits_out, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int d = c.d_model, H = c.n_medusa;
     sd_model::F32& f = m->f;
-    launch_f32_rmsnorm(m->x, f.final_norm, c.rms_eps, m->h_rows, B, d, kv->last_row, s);
     launch_f32_linear(m->h_rows, f.medusa_w, f.medusa_b, f.z, B, H * d, d, d, H * d, 0, s);
     launch_f32_medusa_act(f.z, m->h_rows, f.xh, B, H, d, s);
     launch_f32_linear(f.xh, f.lm_head, nullptr, m->hlogits, H * B, c.vocab, d, d, m->Vpad, 0, s);
-    launch_topk(m->hlogits, m->Vpad, c.vocab, c.topk, kv->cand, B, H, seq_mask, s);
-    if (head_logits_out) launch_copy_head_logits(m->hlogits, m->Vpad, head_logits_out, c.vocab, B, H, s);
+    launch_topk(dense_logits(m, m->hlogits), 0, c.vocab, c.topk, kv->cand, B, H, sl, head_logits_out, m->ranked, s);
 }
 
+// Final norm and LM head of all M rows: partial sums of the logits.
 // (keep_h: also leaves the normalised rows in m->hf as fp32, for draft heads on every row)
-// need_logits: somebody reads m->logits afterwards (the caller's copy, sampling decoding); else only the arg-max
-static void run_lm_head(sd_model* m, PartView prev, int B, int T, int R, int M, hipStream_t s, bool keep_h, bool need_logits) {
+static PartView run_lm_head(sd_model* m, PartView prev, int M, hipStream_t s, bool keep_h) {
     const sd_config& c = m->cfg;
     const int MB = pow2_blocks(M);
     launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, keep_h ? m->hf : nullptr, M, c.d_model, MB, nullptr, s);
-    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
-    launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, c.vocab, m->am, B, T, R, s);
+    return run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
 }
 
-// The whole verifying pass: layers, and with want_lm the final norm, the LM head and the arg-max of the first T rows
-// of every sequence (logits in m->logits, arg-max in m->am). Sequence i's rows start at row i * R (R = 0: at rm.off[i],
-// prompt chunks, where the arg-max is taken of every row).
-static void run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int T, int R, int Tp, int n_hi, bool want_lm,
-                        bool keep_h, bool need_logits, hipStream_t s) {
+// The whole verifying pass: layers, and with want_lm the final norm and the LM head; returns the partial sums of the logits
+// (without want_lm: of the last down projection, still to be added to m->x). Sequence i's rows start at row i * R (R = 0:
+// at rm.off[i], prompt chunks).
+static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, bool want_lm,
+                            bool keep_h, hipStream_t s) {
     m->scratch_B = kv->B;
     m->scratch_n = B;
     for (int i = 0; i < B; ++i) m->scratch_seq[i] = rm.seq[i];
     m->scratch_Tp = Tp;
-    if (m->f32) { run_forward_f32(m, kv, B, T, Tp, want_lm, s); return; }
+    if (m->f32) { run_forward_f32(m, kv, B, Tp, want_lm, s); return dense_logits(m, m->logits); }
     const RowRef rr = {R ? nullptr : m->rm_dev, R};
-    const int am_B = R ? B : 1, am_T = R ? T : M, am_R = R ? R : M;
     if (fused_eligible(m, B * Tp)) {
         // (when the final norm's rows themselves are wanted, the last stage runs as kernels of its own)
         PartView pl = run_forward_fused(m, kv, rr, B, Tp, n_hi, want_lm && !keep_h, s);
-        if (want_lm && keep_h) run_lm_head(m, pl, am_B, am_T, am_R, M, s, true, need_logits);
-        else if (want_lm) launch_reduce_argmax(pl, need_logits ? m->logits : nullptr, m->cfg.vocab, m->am, am_B, am_T, am_R, s);
-        return;
+        return want_lm && keep_h ? run_lm_head(m, pl, M, s, true) : pl;
     }
     PartView prev = run_layers(m, kv, rr, rm, B, M, Tp, n_hi, s);
-    if (want_lm) run_lm_head(m, prev, am_B, am_T, am_R, M, s, keep_h, need_logits);
+    return want_lm ? run_lm_head(m, prev, M, s, keep_h) : prev;
 }
 
-// draft heads at row last_row[b] of every sequence -> cand (sequences in seq_mask only)
-static void run_draft_heads(sd_model* m, sd_kv* kv, int B, uint32_t seq_mask, float* head_logits_out, hipStream_t s) {
-    if (m->f32) { run_draft_heads_f32(m, kv, B, seq_mask, head_logits_out, s); return; }
+static SeqList every_sequence() {
+    SeqList sl;
+    for (int b = 0; b < SD_MAX_BATCH; ++b) sl.seq[b] = b;
+    return sl;
+}
+
+// draft heads at row last_row[b] of every sequence -> cand
+static void run_draft_heads(sd_model* m, sd_kv* kv, int B, float* head_logits_out, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int d = c.d_model, H = c.n_medusa;
+    if (m->f32) {
+        launch_f32_rmsnorm(m->x, m->f.final_norm, c.rms_eps, m->h_rows, B, d, kv->last_row, s);
+        run_draft_heads_f32(m, kv, B, every_sequence(), head_logits_out, s);
+        return;
+    }
     const PartView none = {nullptr, 0, d, nullptr, 0};
     launch_norm_pack(m->x, none, m->final_norm, c.rms_eps, m->xn, m->h_rows, B, d, 1, kv->last_row, s);
     PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, B, 1, m->KBd, m->NBmed, H * d, s);
     const int MBh = pow2_blocks(H * B);
-    launch_medusa_act(pm, m->h_rows, m->medusa_b, B, H, d, m->xn, MBh * 32, MBh, MBh, s);
+    launch_medusa_act(pm, m->h_rows, m->medusa_b, 0, B, H, d, m->xn, MBh * 32, MBh, MBh, s);
     PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, H * B, MBh, m->KBd, m->NBv, c.vocab, s);
-    // (a top-k that sums the slots itself was measured: 54 us against 5 + 22 us for these two, its few workgroups
-    // pull the partial sums too slowly)
-    launch_reduce_slots(pl, m->hlogits, H * B, s);
-    launch_topk(m->hlogits, m->Vpad, c.vocab, c.topk, kv->cand, B, H, seq_mask, s);
-    if (head_logits_out) launch_copy_head_logits(m->hlogits, m->Vpad, head_logits_out, c.vocab, B, H, s);
+    launch_topk(pl, 0, c.vocab, c.topk, kv->cand, B, H, every_sequence(), head_logits_out, m->ranked, s);
+}
+
+// The end of a pass whose drafting rows are known before its logits are (plain decoding: every row; a prompt: the last
+// row of the sequences that end, `gather`): final norm, base logits and draft heads of those n rows, with one pass of the
+// LM head for the n base rows and the n * H head rows together. Leaves the base rows' ranking in m->best; logits: or NULL.
+static void run_known_rows(sd_model* m, sd_kv* kv, PartView prev, int n, const int32_t* gather, const SeqList& sl, float* logits,
+                           int ld, float* head_logits_out, hipStream_t s) {
+    const sd_config& c = m->cfg;
+    const int d = c.d_model, H = c.n_medusa;
+    if (m->f32) {
+        launch_f32_rmsnorm(m->x, m->f.final_norm, c.rms_eps, m->h_rows, n, d, gather, s);
+        launch_f32_linear(m->h_rows, m->f.lm_head, nullptr, m->logits, n, c.vocab, d, d, m->Vpad, 0, s);
+        launch_rank_best(dense_logits(m, m->logits), 0, n, c.vocab, logits, ld, m->best, s);
+        run_draft_heads_f32(m, kv, n, sl, head_logits_out, s);
+        return;
+    }
+    launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, m->h_rows, n, d, 1, gather, s);
+    const int base = n * (H + 1) <= 256 ? 1 : 0;           // (the widest GEMM; beyond it two passes)
+    if (!base) {
+        PartView pb = run_gemm(m, m->xn, m->lm_head, m->part, n, 1, m->KBd, m->NBv, c.vocab, s);
+        launch_rank_best(pb, 0, n, c.vocab, logits, ld, m->best, s);
+    }
+    PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, n, 1, m->KBd, m->NBmed, H * d, s);
+    const int rows = n * (H + base), MBh = pow2_blocks(rows);
+    launch_medusa_act(pm, m->h_rows, m->medusa_b, base, n, H, d, m->xn, MBh * 32, MBh, MBh, s);
+    PartView pl = run_gemm(m, m->xn, m->lm_head, m->part, rows, MBh, m->KBd, m->NBv, c.vocab, s);
+    if (base) launch_rank_best(pl, 0, n, c.vocab, logits, ld, m->best, s);
+    launch_topk(pl, base * n, c.vocab, c.topk, kv->cand, n, H, sl, head_logits_out, m->ranked, s);
 }
 
 // The other schedule: the draft heads run on all M rows of the verifying pass (m->xn and m->hf
@@ -1108,7 +1148,7 @@ static void run_draft_heads_all_rows(sd_model* m, sd_kv* kv, int B, int M, float
     const int d = c.d_model, H = c.n_medusa, MB = pow2_blocks(M), R = H * M, CH = 256;
     PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, M, MB, m->KBd, m->NBmed, H * d, s);
     const int n_chunks = ceil_div(R, CH), MBlast = pow2_blocks(R - (n_chunks - 1) * CH);
-    launch_medusa_act(pm, m->hf, m->medusa_b, M, H, d, m->xh, CH, CH / 32, MBlast, s);
+    launch_medusa_act(pm, m->hf, m->medusa_b, 0, M, H, d, m->xh, CH, CH / 32, MBlast, s);
     for (int ch = 0; ch < n_chunks; ++ch) {
         const int rows = std::min(CH, R - ch * CH);
         const char* xc = (const char*)m->xh + (size_t)ch * CH * d * 4;
@@ -1116,8 +1156,7 @@ static void run_draft_heads_all_rows(sd_model* m, sd_kv* kv, int B, int M, float
                                c.vocab, s);
         launch_reduce_selected(pl, m->hlogits, kv->last_row, B, H, M, ch * CH, rows, s);
     }
-    launch_topk(m->hlogits, m->Vpad, c.vocab, c.topk, kv->cand, B, H, 0xffffffffu, s);
-    if (head_logits_out) launch_copy_head_logits(m->hlogits, m->Vpad, head_logits_out, c.vocab, B, H, s);
+    launch_topk(dense_logits(m, m->hlogits), 0, c.vocab, c.topk, kv->cand, B, H, every_sequence(), head_logits_out, m->ranked, s);
 }
 
 // ------------------------------------------------------------------------------------------ prefill
@@ -1146,8 +1185,10 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         RowMap rm;
         memset(&ca, 0, sizeof(ca));
         memset(&rm, 0, sizeof(rm));
-        int A = 0, M = 0, n_hi = 0;
-        uint32_t fin = 0;
+        SeqList fin, last;                                 // the sequences whose prompts end, and their last rows
+        memset(&fin, 0, sizeof(fin));
+        memset(&last, 0, sizeof(last));
+        int A = 0, M = 0, n_hi = 0, n_fin = 0;
         for (int b = 0; b < B; ++b)
             if (left[b] > 0 || m->f32) rm.seq[A++] = b;
         if (*std::max_element(left.begin(), left.end()) <= 0) break;
@@ -1160,13 +1201,16 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
             rm.off[i] = M;
             rm.len[i] = padded ? Tp : ca.len[i];
             M += rm.len[i];
-            if (left[b] > 0 && left[b] <= Tp) fin |= 1u << b;
+            if (left[b] > 0 && left[b] <= Tp) {            // this pass ends the prompt
+                last.seq[n_fin] = rm.off[i] + ca.len[i] - 1;
+                fin.seq[n_fin++] = b;
+            }
             n_hi = std::max(n_hi, kv->len_hi[b]);
         }
-        launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, c.rope_theta, m->embed, m->f32 ? 1 : 0,
+        launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
                                 c.d_model, c.vocab, m->x, s);
-        run_forward(m, kv, rm, A, M, Tp, 0, Tp, n_hi, fin != 0, false, false, s);
-        launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, kv->last_row, s);
+        PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, false, false, s);
+        launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
         commit_rows(m, kv, false, kv->i_slots, kv->i_nacc, Tp, Tp, s);
         for (int i = 0; i < A; ++i) {
             const int b = rm.seq[i];
@@ -1174,9 +1218,9 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
             next[b] += ca.len[i];
             left[b] -= ca.len[i];
         }
-        if (fin) {
-            launch_pick_root(m->am, kv->last_row, kv->root_tok, B, fin, s);
-            run_draft_heads(m, kv, B, fin, nullptr, s);
+        if (n_fin) {
+            run_known_rows(m, kv, prev, n_fin, m->fin_rows, fin, nullptr, 0, nullptr, s);
+            launch_pick_root(m->best, c.vocab, kv->root_tok, n_fin, fin, s);
         }
     }
     HIP_TRY(hipGetLastError());
@@ -1220,31 +1264,45 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     // everything the launch sequence depends on besides device-resident state
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
-                           c.rope_theta, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);
-    run_forward(m, kv, rm, B, M, T, R, Tp, n_hi, true, all_rows, io->logits != nullptr || ty != nullptr, s);
-    if (io->logits) launch_copy_logits(m->logits, m->Vpad, io->logits, c.vocab, B, T, R, s);
-    if (io->argmax) launch_copy_rows_i32(m->am, io->argmax, B, T, R, s);
+                           m->rope_freq, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);
+    // the logits somebody reads: the caller's dense rows [b][T][V], or (sampling decoding alone) the padded ones
+    const bool dense = R == T || B == 1;
+    float* lg = io->logits && dense ? io->logits : (io->logits || ty) ? m->logits : nullptr;
+    const int ldl = lg == m->logits ? m->Vpad : c.vocab;
+    // plain decoding drafts from the only row a sequence has: one pass of the LM head for its base and head rows
+    const bool known = T == 1 && dense && heads && !m->f32 && !fused_eligible(m, B * Tp);
+    PartView pl = run_forward(m, kv, rm, B, M, R, Tp, n_hi, !known, all_rows, s);
+    if (known) {
+        run_known_rows(m, kv, pl, B, nullptr, every_sequence(), lg, ldl, io->head_logits, s);
+    } else {
+        launch_rank_best(pl, 0, dense ? B * T : M, c.vocab, lg, ldl, m->best, s);
+        if (io->logits && !dense)
+            for (int b = 0; b < B; ++b)
+                launch_rank_best(pl, b * R, T, c.vocab, io->logits + (size_t)b * T * c.vocab, c.vocab,
+                                 m->best + (size_t)b * R * rank_chunks(c.vocab), s);
+    }
     VerifyArgs va;
     va.parent = parent; va.depth = depth; va.T = T; va.H = H; va.fallback = c.trunc_fallback;
     va.src_stride = R; va.Tp = R; va.V = c.vocab;
-    va.tok = m->rt.tok; va.am = m->am; va.stop_mask = stop_mask;
+    va.tok = m->rt.tok; va.am = nullptr; va.best = m->best; va.n_chunks = rank_chunks(c.vocab); va.am_out = io->argmax;
+    va.stop_mask = stop_mask;
     va.n_accept = n_accept; va.n_accept_raw = io->n_accept_raw; va.tokens = tokens; va.src_slots = slots;
     va.kv_len = kv->kv_len; va.n_old = kv->n_old; va.root_tok = kv->root_tok; va.last_row = kv->last_row;
     va.logits = nullptr; va.ld = 0; va.row_stats = nullptr; va.inv_temperature = 1.f;
     if (ty) {
         va.inv_temperature = 1.f / ty->temperature;
-        launch_row_stats(m->logits, m->Vpad, c.vocab, m->row_stats, B, T, R, va.inv_temperature, ty->epsilon,
+        launch_row_stats(lg, ldl, c.vocab, m->row_stats, B, T, R, va.inv_temperature, ty->epsilon,
                          ty->delta, s);
         if (ty->row_stats) launch_copy_row_stats(m->row_stats, (float4*)ty->row_stats, B, T, R, s);
-        va.logits = m->logits; va.ld = m->Vpad; va.row_stats = m->row_stats;
+        va.logits = lg; va.ld = ldl; va.row_stats = m->row_stats;
     }
     launch_verify(va, B, s);
     if (ty)      // the next root is drawn from the base distribution at the last kept node
-        launch_sample_root(m->logits, m->Vpad, c.vocab, kv->last_row, ty->u, va.inv_temperature, kv->root_tok, B,
+        launch_sample_root(lg, ldl, c.vocab, kv->last_row, ty->u, va.inv_temperature, kv->root_tok, B,
                            M, s);
     commit_rows(m, kv, false, slots, n_accept, Tp, H + 1, s);
     if (all_rows) run_draft_heads_all_rows(m, kv, B, M, io->head_logits, s);
-    else if (heads) run_draft_heads(m, kv, B, 0xffffffffu, io->head_logits, s);
+    else if (heads && !known) run_draft_heads(m, kv, B, io->head_logits, s);
     };
 
     if (m->use_graphs && !m->prof.on && !ty) {

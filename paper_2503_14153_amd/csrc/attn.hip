@@ -64,7 +64,9 @@ template <int N> static __device__ __forceinline__ void wait_vm() { asm volatile
 // the LDS area the loop reads them from), and the workgroup that reads the tree blocks first builds the tree's keys
 // and values the same way, writes them to the tree scratch (the commit stage needs them there) and reads them back
 // as blocks. One query group only (Tp = 32 * TBW). NS: the projection's slot count if the same everywhere, else 0.
-template <int HD, int TBW, int AW, int FR = 0, int NS = 0>
+// MAP: the pass's row map is in device memory (prompt passes: rr.map); else every sequence has rr.R rows, one after the
+// other, and nothing is looked up before the first addresses are known.
+template <int HD, int TBW, int AW, int FR, int NS, bool MAP>
 __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp, const bf16x8* Kc, const bf16x8* Vc,
                                                    const bf16x8* Kt, const bf16x8* Vt, const int32_t* __restrict__ kv_len,
                                                    const uint32_t* __restrict__ anc, float* __restrict__ opart,
@@ -144,7 +146,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     const int total = ntree + (has_cache ? per : 0);
     const int share = (total + 3) >> 2;
     const int jw = __builtin_amdgcn_readfirstlane(wave * share);
-    const int sq = rr.seq(b);                         // sequence of the cache
+    const int sq = MAP ? rr.map->seq[b] : b;                         // sequence of the cache
     const bf16x8* kcb = Kc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* vcb = Vc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* ktb = Kt + ((size_t)b * nh + h) * TB * BLK + lane;
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // there: no wait for the stores to the scratch, no round trip to read them back.
     bf16x8* const tkv = lds + QF * 64;                 // K blocks of the tree, then its V blocks
     const bool tree_only = FR && ntree && !has_cache;  // (workgroup-uniform)
-    const int row0 = FR ? rr.off(b) : 0, row_last = FR ? rr.len(b) - 1 : 0;       // this sequence's rows of the partial sums
+    const int row0 = MAP ? rr.map->off[b] : b * rr.R, row_last = (MAP ? rr.map->len[b] : rr.R) - 1;       // this sequence's rows of the partial sums
     auto row_of = [&](int t) { return row0 + min(t, row_last); };
     if constexpr (FR) {
         static_assert(2 * TBW * BLK <= 4 * WAVE_UNITS, "the tree blocks fit the merge area");
@@ -459,14 +461,16 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     }
 #define ATT_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (const bf16x8*)kt, (const bf16x8*)vt, \
                  kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg, rr
-#define ATT(HD_, TBW_, AW_, ...)                                                                                     \
+#define ATT_M(HD_, TBW_, AW_, FR_, NS_, MAP_)                                                                    \
     do {                                                                                                        \
         if (ev0 || ev1)                                                                                         \
-            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, ##__VA_ARGS__>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS); \
+            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS); \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, ##__VA_ARGS__>), grid, dim3(256), 0, s, ATT_ARGS);  \
+            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_>), grid, dim3(256), 0, s, ATT_ARGS); \
     } while (0)
-#define ATT2(HD_, TBW_) do { if (Tp > 128) ATT(HD_, TBW_, 8); else ATT(HD_, TBW_, 4); } while (0)
+#define ATT(HD_, TBW_, AW_, FR_, NS_)                                                                            \
+    do { if (rr.map) ATT_M(HD_, TBW_, AW_, FR_, NS_, true); else ATT_M(HD_, TBW_, AW_, FR_, NS_, false); } while (0)
+#define ATT2(HD_, TBW_) do { if (Tp > 128) ATT(HD_, TBW_, 8, 0, 0); else ATT(HD_, TBW_, 4, 0, 0); } while (0)
     PartView pv_arg = {nullptr, 0, 0, nullptr, 0};
     RowTable rt_arg = {nullptr, nullptr, nullptr, nullptr};
     if (qkv && rt && TG == 1) {
@@ -482,6 +486,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     else                { if (TBW == 2) ATT2(64, 2);  else ATT2(64, 1); }
 #undef ATT2
 #undef ATT
+#undef ATT_M
 #undef ATT_ARGS
 }
 

@@ -16,160 +16,185 @@ static __device__ inline void wave_best(float& v, int& i) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Row-wise arg-max over V columns (lowest id on ties). One workgroup of 1024 threads per row;
-// the loop is unrolled so that several 16-byte loads per thread are in flight.
-#define ARGMAX_THREADS 1024
-__global__ __launch_bounds__(ARGMAX_THREADS) void k_argmax(const float* __restrict__ logits, int ld, int V,
-                                                           int32_t* __restrict__ am, int T, int Tp) {
-    const int b = blockIdx.x / T, j = blockIdx.x % T;
-    const int m = b * Tp + j;
-    const float* row = logits + (size_t)m * ld;
-    float bv = NEG_INF;
-    int bi = 0x7fffffff;
-#pragma unroll 4
-    for (int i = threadIdx.x * 4; i < V; i += ARGMAX_THREADS * 4) {
-        float4 f = *(const float4*)(row + i);         // rows are padded to a multiple of 4 columns
-        float vals[4] = {f.x, f.y, f.z, f.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (i + e < V && better(vals[e], i + e, bv, bi)) { bv = vals[e]; bi = i + e; }
-    }
-    wave_best(bv, bi);
-    __shared__ float sv[ARGMAX_THREADS / 64];
-    __shared__ int si[ARGMAX_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        bv = threadIdx.x < ARGMAX_THREADS / 64 ? sv[threadIdx.x] : NEG_INF;
-        bi = threadIdx.x < ARGMAX_THREADS / 64 ? si[threadIdx.x] : 0x7fffffff;
-        wave_best(bv, bi);
-        if (threadIdx.x == 0) am[m] = bi;
-    }
+// Ranking of logit rows straight from the LM head's partial sums, in two stages. Stage 1, one workgroup per (row, chunk of
+// the vocabulary): a thread sums the slots of its columns (in slot order), writes the logits out where somebody wants
+// them (straight to the caller's dense rows: no padded copy, no second pass), and the workgroup finds the best entry
+// (K1: arg-max) or the best k of its chunk. Stage 2: k_verify picks a row's arg-max out of its chunks' by itself; for
+// top-k, k_topk_merge. At most 16 chunks, of NPT * 256 ids. One workgroup per row, as before, left most of the
+// chip idle (plain decoding: one workgroup, 10 us for the arg-max and 5 + 22 + 5 us for sum, top-10 and copy of four head
+// rows, which are 7 + 6 us in this form).
+// Top-k of a chunk without rounds over the chunk: the k-th best of the threads' own maxima bounds the chunk's k-th best from
+// below, so only entries at or above it (of k threads at most: k * NPT) can belong to the best k; those are listed, and
+// an entry's place is the number of better ones. "Better" = larger value, lower id on ties, so places are unique. (k
+// rounds of a reduction over the workgroup took 22 us, over single waves 11.5.) Logits of -inf are never picked.
+#define RANK_THREADS 256
+struct RankOut {
+    float* logits;         // NULL, or the summed logits: row r at logits + (map_B ? (r % map_B) * map_H + r / map_B : r) * ld
+    int ld, map_B, map_H, vec;      // vec: rows are 16-byte aligned and hold a multiple of four ids
+};
+// An entry as one 64-bit key: larger key = better (larger value, -0 like +0; lower id on ties); 0 = no entry. Compared as
+// (value, id) pairs the counting loops were branches on every entry, 27 us.
+static __device__ inline unsigned long long rank_key(float v, int id) {
+    const uint32_t u = __float_as_uint(v + 0.f);
+    return ((unsigned long long)(u & 0x80000000u ? ~u : u | 0x80000000u) << 32) | (uint32_t)~id;
 }
-
-void launch_argmax(const float* logits, int ld, int V, int32_t* am, int B, int T, int Tp, hipStream_t s) {
-    hipLaunchKernelGGL(k_argmax, dim3(B * T), dim3(ARGMAX_THREADS), 0, s, logits, ld, V, am, T, Tp);
-}
-
-// ------------------------------------------------------------------------------------------
-// The same arg-max straight from the LM-head GEMM's partial sums: a thread sums the slots of its columns (in slot
-// order, as k_reduce_slots does, so the logits are the same numbers), keeps the best, and writes the logits out
-// only when somebody wants them (WRITE: the caller asked for logits, or sampling decoding reads them). Saves a
-// launch and, without WRITE, the 8 MB write and re-read of the logits of a 64-row step.
-template <bool WRITE>
-__global__ __launch_bounds__(ARGMAX_THREADS) void k_reduce_argmax(PartView pv, float* __restrict__ logits, int V,
-                                                                  int32_t* __restrict__ am, int T, int Tp) {
-    const int b = blockIdx.x / T, j = blockIdx.x % T;
-    const int m = b * Tp + j;
-    float bv = NEG_INF;
-    int bi = 0x7fffffff;
-    for (int i = threadIdx.x * 4; i < pv.ld; i += ARGMAX_THREADS * 4) {
-        const int n = part_count(pv, i);
-        float4 a = make_float4(0, 0, 0, 0);
-        const float* p = pv.base + (size_t)m * pv.ld + i;
-#pragma unroll 4
-        for (int sp = 0; sp < n; ++sp) {
-            float4 v = *(const float4*)(p + (size_t)sp * pv.slot_stride);
-            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-        }
-        if (WRITE) *(float4*)(logits + (size_t)m * pv.ld + i) = a;
-        float vals[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (i + e < V && better(vals[e], i + e, bv, bi)) { bv = vals[e]; bi = i + e; }
+static __device__ inline int key_id(unsigned long long k) { return (int)~(uint32_t)k; }
+// how many of list[0..n) are larger than me; the list is in LDS and followed by one free entry if n is odd, which must be 0
+static __device__ inline int count_better(const unsigned long long* list, int n, unsigned long long me) {
+    int place = 0;
+    const ulonglong2* l2 = (const ulonglong2*)list;
+#pragma unroll 8
+    for (int j = 0; j < (n + 1) / 2; ++j) {
+        const ulonglong2 o = l2[j];
+        place += (o.x > me) + (o.y > me);
     }
-    wave_best(bv, bi);
-    __shared__ float sv[ARGMAX_THREADS / 64];
-    __shared__ int si[ARGMAX_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        bv = threadIdx.x < ARGMAX_THREADS / 64 ? sv[threadIdx.x] : NEG_INF;
-        bi = threadIdx.x < ARGMAX_THREADS / 64 ? si[threadIdx.x] : 0x7fffffff;
-        wave_best(bv, bi);
-        if (threadIdx.x == 0) am[m] = bi;
-    }
+    return place;
 }
-
-void launch_reduce_argmax(PartView pv, float* logits_or_null, int V, int32_t* am, int B, int T, int Tp, hipStream_t s) {
-    if (logits_or_null)
-        hipLaunchKernelGGL(k_reduce_argmax<true>, dim3(B * T), dim3(ARGMAX_THREADS), 0, s, pv, logits_or_null, V, am, T, Tp);
-    else
-        hipLaunchKernelGGL(k_reduce_argmax<false>, dim3(B * T), dim3(ARGMAX_THREADS), 0, s, pv, logits_or_null, V, am, T, Tp);
-}
-
-// ------------------------------------------------------------------------------------------
-// Per-row top-k (descending logit, ties to the lower id). One workgroup of 1024 threads per
-// row keeps the whole row in registers (thread t owns ids t, t+1024, ...); each of the k
-// rounds is a thread-local scan plus one block-wide (value, id) reduction, after which the
-// owner retires the selected element.
-#define TOPK_THREADS 1024
-template <int NPT>
-__global__ __launch_bounds__(TOPK_THREADS) void k_topk(const float* __restrict__ logits, int ld, int V, int k,
-                                                       int32_t* __restrict__ out, int B, int H, uint32_t seq_mask) {
-    const int r = blockIdx.x;                 // row r = head i * B + sequence b
-    const int i = r / B, b = r % B;
-    if (!((seq_mask >> b) & 1u)) return;
-    const float* row = logits + (size_t)r * ld;
-    const int tid = threadIdx.x;
+template <int NPT, bool K1>
+__global__ __launch_bounds__(RANK_THREADS) void k_rank_chunks(PartView pv, int row0, int V, int k, RankOut ro,
+                                                              void* __restrict__ cand) {
+    static_assert(NPT % 4 == 0, "float4 groups");
+    const int ch = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
+    [[maybe_unused]] const int wave = tid >> 6, lane = tid & 63;
+    const float* row = pv.base + (size_t)(row0 + r) * pv.ld;
+    const int c0 = ch * NPT * RANK_THREADS;
+    float* out = nullptr;
+    if (ro.logits) out = ro.logits + (size_t)(ro.map_B ? (r % ro.map_B) * ro.map_H + r / ro.map_B : r) * ro.ld;
     float v[NPT];
+    float bv = NEG_INF;
+    int bi = 0x7fffffff;
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        int c = j * TOPK_THREADS + tid;
-        v[j] = c < V ? row[c] : NEG_INF;
-    }
-    __shared__ float sv[TOPK_THREADS / 64];
-    __shared__ int si[TOPK_THREADS / 64];
-    __shared__ int chosen;
-    // thread-local best of the elements not yet retired; only the owner of a retired element rescans
-    float lbv = NEG_INF;
-    int lbi = 0x7fffffff;
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {           // ascending ids: strict > keeps the lowest id
-        int c = j * TOPK_THREADS + tid;
-        if (c < V && v[j] > lbv) { lbv = v[j]; lbi = c; }
-    }
-    for (int round = 0; round < k; ++round) {
-        float bv = lbv;
-        int bi = lbi;
-        wave_best(bv, bi);
-        if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
-        __syncthreads();
-        if (tid < 64) {
-            float wv = tid < TOPK_THREADS / 64 ? sv[tid] : NEG_INF;
-            int wi = tid < TOPK_THREADS / 64 ? si[tid] : 0x7fffffff;
-            wave_best(wv, wi);
-            if (tid == 0) {
-                chosen = wi;
-                out[((size_t)b * H + i) * k + round] = wi;
+    for (int q = 0; q < NPT / 4; ++q) {
+        const int c = c0 + (q * RANK_THREADS + tid) * 4;
+        float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c < V) {                                   // (the partial sums' rows are padded to 32 columns)
+            const int n = part_count(pv, c);
+#pragma unroll 4
+            for (int sp = 0; sp < n; ++sp) {
+                const float4 x = *(const float4*)(row + (size_t)sp * pv.slot_stride + c);
+                a.x += x.x; a.y += x.y; a.z += x.z; a.w += x.w;
             }
         }
+        const float e4[4] = {a.x, a.y, a.z, a.w};
+        if (out && c < V) {
+            if (ro.vec) *(float4*)(out + c) = a;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (c + e < V) out[c + e] = e4[e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // ascending ids: the first maximum. (The arg-max of a row of -inf is its first id; top-k never picks a -inf.)
+            v[q * 4 + e] = c + e < V ? e4[e] : NEG_INF;
+            if (K1 ? c + e < V && better(e4[e], c + e, bv, bi) : v[q * 4 + e] > bv) { bv = v[q * 4 + e]; bi = c + e; }
+        }
+    }
+    if constexpr (K1) {
+        __shared__ float2 wbest[RANK_THREADS / 64];
+        wave_best(bv, bi);
+        if (lane == 0) wbest[wave] = make_float2(bv, __int_as_float(bi));
         __syncthreads();
-        const int ch = chosen;
-        if ((ch % TOPK_THREADS) == tid) {
-            lbv = NEG_INF;
-            lbi = 0x7fffffff;
+        if (tid == 0) {
+#pragma unroll
+            for (int w = 1; w < RANK_THREADS / 64; ++w) {
+                const float2 e = wbest[w];
+                if (better(e.x, __float_as_int(e.y), bv, bi)) { bv = e.x; bi = __float_as_int(e.y); }
+            }
+            ((float2*)cand)[(size_t)r * gridDim.x + ch] = make_float2(bv, __int_as_float(bi));
+        }
+    } else {
+        __shared__ __attribute__((aligned(16))) unsigned long long own[RANK_THREADS];      // the threads' maxima
+        __shared__ __attribute__((aligned(16))) unsigned long long lst[32 * NPT + 2];      // k <= 32
+        __shared__ unsigned long long bound;
+        __shared__ int count;
+        const unsigned long long mine = bi == 0x7fffffff ? 0ull : rank_key(bv, bi);
+        own[tid] = mine;
+        if (tid == 0) { count = 0; bound = 0ull; }
+        __syncthreads();
+        // (fewer than k threads with an entry: no bound, every entry is listed)
+        if (mine && count_better(own, RANK_THREADS, mine) == k - 1) bound = mine;
+        __syncthreads();
+        const unsigned long long least = bound;
+        if (mine >= least && mine) {
 #pragma unroll
             for (int j = 0; j < NPT; ++j) {
-                if (j == ch / TOPK_THREADS) v[j] = NEG_INF;
-                int c = j * TOPK_THREADS + tid;
-                if (c < V && v[j] > lbv) { lbv = v[j]; lbi = c; }
+                const int c = c0 + ((j >> 2) * RANK_THREADS + tid) * 4 + (j & 3);
+                const unsigned long long e = rank_key(v[j], c);
+                if (v[j] > NEG_INF && e >= least) lst[atomicAdd(&count, 1)] = e;
             }
         }
+        __syncthreads();
+        const int n = count;
+        if (tid == 0) lst[n] = 0ull;                       // (an odd list is read in pairs)
+        __syncthreads();
+        unsigned long long* out_k = (unsigned long long*)cand + ((size_t)r * gridDim.x + ch) * k;
+        for (int e = tid; e < n; e += RANK_THREADS) {
+            const int place = count_better(lst, n, lst[e]);
+            if (place < k) out_k[place] = lst[e];
+        }
+        for (int e = n + tid; e < k; e += RANK_THREADS) out_k[e] = 0ull;           // a chunk of fewer than k
     }
 }
 
-void launch_topk(const float* logits, int ld, int V, int k, int32_t* out, int B, int H, uint32_t seq_mask,
-                 hipStream_t s) {
-    const int npt = (V + TOPK_THREADS - 1) / TOPK_THREADS;
-#define TOPK(N) hipLaunchKernelGGL((k_topk<N>), dim3(B * H), dim3(TOPK_THREADS), 0, s, logits, ld, V, k, out, B, H, seq_mask)
-    if (npt <= 1) TOPK(1);
-    else if (npt <= 4) TOPK(4);
-    else if (npt <= 16) TOPK(16);
-    else if (npt <= 32) TOPK(32);
-    else if (npt <= 64) TOPK(64);
-    else TOPK(160);          // vocabularies up to 163840 ids (validated at model creation)
-#undef TOPK
+// the best k of a row's n = chunks * k entries, by the same counting; row r = head i * B + b of the pass
+__global__ __launch_bounds__(RANK_THREADS) void k_topk_merge(const unsigned long long* __restrict__ cand, int n, int k,
+                                                             int32_t* __restrict__ out, int B, int H, SeqList sl) {
+    extern __shared__ __attribute__((aligned(16))) unsigned long long all[];       // n + 2 entries
+    __shared__ int found;
+    const int r = blockIdx.x, i = r / B, b = r % B, tid = threadIdx.x;
+    if (tid == 0) { found = 0; all[n] = 0ull; }
+    for (int j = tid; j < n; j += RANK_THREADS) all[j] = cand[(size_t)r * n + j];
+    __syncthreads();
+    int32_t* o = out + ((size_t)sl.seq[b] * H + i) * k;
+    for (int e = tid; e < n; e += RANK_THREADS) {
+        const unsigned long long me = all[e];
+        if (!me) continue;                             // a chunk of fewer than k
+        const int place = count_better(all, n, me);
+        if (place < k) { o[place] = key_id(me); atomicAdd(&found, 1); }
+    }
+    __syncthreads();
+    for (int e = found + tid; e < k; e += RANK_THREADS) o[e] = 0x7fffffff;      // a row of fewer than k finite logits
+}
+
+int rank_chunks(int V) {
+    const int npt = V <= 32768 ? 8 : V <= 65536 ? 16 : 40;         // 40: 163840 ids, the most a model may have
+    return (V + npt * RANK_THREADS - 1) / (npt * RANK_THREADS);
+}
+static RankOut rank_out(float* logits, int ld, int V, int map_B, int map_H) {
+    return RankOut{logits, ld, map_B, map_H, (((uintptr_t)logits & 15) == 0 && ld % 4 == 0 && V % 4 == 0) ? 1 : 0};
+}
+#define RANK(K1_, k_)                                                                                                    \
+    do {                                                                                                                 \
+        const dim3 grid(rank_chunks(V), rows);                                                                           \
+        if (V <= 32768) hipLaunchKernelGGL((k_rank_chunks<8, K1_>), grid, dim3(RANK_THREADS), 0, s, pv, row0, V, k_, ro, cand);  \
+        else if (V <= 65536) hipLaunchKernelGGL((k_rank_chunks<16, K1_>), grid, dim3(RANK_THREADS), 0, s, pv, row0, V, k_, ro, cand); \
+        else hipLaunchKernelGGL((k_rank_chunks<40, K1_>), grid, dim3(RANK_THREADS), 0, s, pv, row0, V, k_, ro, cand);    \
+    } while (0)
+void launch_rank_best(PartView pv, int row0, int rows, int V, float* logits, int ld, float2* cand, hipStream_t s) {
+    const RankOut ro = rank_out(logits, ld, V, 0, 0);
+    RANK(true, 1);
+}
+void launch_topk(PartView pv, int row0, int V, int k, int32_t* out, int B, int H, const SeqList& sl, float* head_logits,
+                 void* cand, hipStream_t s) {
+    const int rows = B * H, n = rank_chunks(V) * k;
+    const RankOut ro = rank_out(head_logits, V, V, B, H);
+    RANK(false, k);
+    hipLaunchKernelGGL(k_topk_merge, dim3(rows), dim3(RANK_THREADS), (size_t)(n + 2) * 8, s, (const unsigned long long*)cand, n, k, out, B, H, sl);
+}
+#undef RANK
+
+// a row's arg-max out of its chunks' best entries (chunks in ascending ids: the first maximum)
+static __device__ inline int best_of_chunks(const float2* __restrict__ best, int nch) {
+    float2 e[16];                                      // (16 chunks at most; past the last: the last again)
+#pragma unroll
+    for (int c = 0; c < 16; ++c) e[c] = best[min(c, nch - 1)];
+    float bv = e[0].x;
+    int bi = __float_as_int(e[0].y);
+#pragma unroll
+    for (int c = 1; c < 16; ++c)
+        if (better(e[c].x, __float_as_int(e[c].y), bv, bi)) { bv = e[c].x; bi = __float_as_int(e[c].y); }
+    return bi;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -341,9 +366,17 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
     const int b = blockIdx.x, j = threadIdx.x, T = a.T, H = a.H;
     const bool valid = j < T;
     const int32_t* tok = a.tok + (size_t)b * a.src_stride;
-    const int32_t* am = a.am + (size_t)b * a.src_stride;
     __shared__ unsigned long long matchw[NW], bestanc[NW];
-    __shared__ int wkey[NW], stopmax[NW];
+    __shared__ int wkey[NW], stopmax[NW], am_s[64 * NW];
+    // the base arg-max of every node: given, or picked out of the chunks' best entries (k_rank_chunks)
+    int amj = 0;
+    if (valid) {
+        const size_t r = (size_t)b * a.src_stride + j;
+        amj = a.best ? best_of_chunks(a.best + r * a.n_chunks, a.n_chunks) : a.am[r];
+        if (a.am_out) a.am_out[(size_t)b * T + j] = amj;
+    }
+    am_s[j] = amj;
+    __syncthreads();
     int dj = 0, tj = 0, pj = -1;
     unsigned long long anc[NW] = {};
     bool match = false;
@@ -361,7 +394,7 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
             match = false;
             if (tj >= 0 && tj < a.V) match = (a.logits[r * a.ld + tj] - st.x) * a.inv_temperature > st.w;
         } else {
-            match = tj == am[pj];
+            match = tj == am_s[pj];
         }
         for (int i = j, guard = 0; i >= 0 && guard <= H; i = a.parent[i], ++guard) anc[i >> 6] |= 1ull << (i & 63);
     }
@@ -403,7 +436,7 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
         a.tokens[(size_t)b * W + dj] = tj;
         a.src_slots[(size_t)b * W + dj] = j;
         if (dj == n_acc - 1) {
-            if (a.root_tok) a.root_tok[b] = am[j];
+            if (a.root_tok) a.root_tok[b] = amj;
             if (a.last_row) a.last_row[b] = b * a.Tp + j;
         }
     }
@@ -575,41 +608,12 @@ void launch_kv_rows(void* kc, void* vc, void* k_rows, void* v_rows, int row0, in
 
 // ------------------------------------------------------------------------------------------
 // Small copies out of the padded internal buffers into the caller's dense outputs.
-__global__ void k_copy_logits(const float* __restrict__ src, int ld, float* __restrict__ dst, int V, int T, int Tp) {
-    const int b = blockIdx.y / T, j = blockIdx.y % T;
-    const float* s = src + (size_t)(b * Tp + j) * ld;
-    float* d = dst + (size_t)(b * T + j) * V;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < V; i += gridDim.x * blockDim.x) d[i] = s[i];
-}
-void launch_copy_logits(const float* src, int ld, float* dst, int V, int B, int T, int Tp, hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_logits, dim3(16, B * T), dim3(256), 0, s, src, ld, dst, V, T, Tp);
-}
-
 __global__ void k_copy_row_stats(const float4* __restrict__ src, float4* __restrict__ dst, int B, int T, int Tp) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < B * T) dst[i] = src[(i / T) * Tp + i % T];
 }
 void launch_copy_row_stats(const float4* src, float4* dst, int B, int T, int Tp, hipStream_t s) {
     hipLaunchKernelGGL(k_copy_row_stats, dim3((B * T + 255) / 256), dim3(256), 0, s, src, dst, B, T, Tp);
-}
-
-__global__ void k_copy_rows_i32(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int B, int T, int Tp) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < B * T) dst[i] = src[(i / T) * Tp + i % T];
-}
-void launch_copy_rows_i32(const int32_t* src, int32_t* dst, int B, int T, int Tp, hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_rows_i32, dim3((B * T + 255) / 256), dim3(256), 0, s, src, dst, B, T, Tp);
-}
-
-// head logits: internal row (i*B + b) -> dst [b][i][V]
-__global__ void k_copy_head_logits(const float* __restrict__ src, int ld, float* __restrict__ dst, int V, int B, int H) {
-    const int r = blockIdx.y, i = r / B, b = r % B;
-    const float* s = src + (size_t)r * ld;
-    float* d = dst + ((size_t)b * H + i) * V;
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < V; c += gridDim.x * blockDim.x) d[c] = s[c];
-}
-void launch_copy_head_logits(const float* src, int ld, float* dst, int V, int B, int H, hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_head_logits, dim3(16, B * H), dim3(256), 0, s, src, ld, dst, V, B, H);
 }
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int n) {
@@ -629,24 +633,24 @@ void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s) {
 }
 
 // Prompt chunks commit every row: slots are the identity, the count is the chunk length. (src_slots, n_accept and n_old
-// by sequence of the pass, kv_len and last_row by sequence of the cache.)
+// by sequence of the pass, kv_len by sequence of the cache.)
 __global__ void k_prefill_commit_setup(ChainArgs ca, RowMap rm, int B, int Tp, int32_t* __restrict__ src_slots,
                                        int32_t* __restrict__ n_accept, int32_t* __restrict__ n_old,
-                                       int32_t* __restrict__ kv_len, int32_t* __restrict__ last_row) {
+                                       int32_t* __restrict__ kv_len, int32_t* __restrict__ fin_rows, int n_fin, SeqList last) {
     const int b = blockIdx.x, j = threadIdx.x;
+    if (b == 0 && j < n_fin) fin_rows[j] = last.seq[j];
     if (j < Tp) src_slots[(size_t)b * Tp + j] = j;
     if (j == 0) {
         const int sq = rm.seq[b], n = kv_len[sq];
         n_old[b] = n;
         n_accept[b] = ca.len[b];
         kv_len[sq] = n + ca.len[b];
-        if (ca.len[b] > 0) last_row[sq] = rm.off[b] + ca.len[b] - 1;
     }
 }
 void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
-                                 int32_t* n_old, int32_t* kv_len, int32_t* last_row, hipStream_t s) {
+                                 int32_t* n_old, int32_t* kv_len, int32_t* fin_rows, int n_fin, const SeqList& last, hipStream_t s) {
     hipLaunchKernelGGL(k_prefill_commit_setup, dim3(B), dim3(SD_MAX_TREE), 0, s, ca, rm, B, Tp, src_slots, n_accept, n_old,
-                       kv_len, last_row);
+                       kv_len, fin_rows, n_fin, last);
 }
 
 // commit stage alone: the count of every sequence clamped to [0, width], old length noted, new length set
@@ -664,13 +668,11 @@ void launch_commit_setup(const int32_t* n_rows, int width, int B, int32_t* n_acc
     hipLaunchKernelGGL(k_commit_setup, dim3(1), dim3(SD_MAX_BATCH), 0, s, n_rows, width, B, n_accept, n_old, kv_len);
 }
 
-// root_tok[b] = arg-max at the last prompt row, for the sequences whose prompt just ended
-__global__ void k_pick_root(const int32_t* __restrict__ am, const int32_t* __restrict__ last_row,
-                            int32_t* __restrict__ root_tok, int B, uint32_t seq_mask) {
-    int b = threadIdx.x;
-    if (b < B && ((seq_mask >> b) & 1u)) root_tok[b] = am[last_row[b]];
+// root_tok of the sequences whose prompt just ended: arg-max of their last rows' logits
+__global__ void k_pick_root(const float2* __restrict__ best, int nch, int32_t* __restrict__ root_tok, int n, SeqList sl) {
+    const int i = threadIdx.x;
+    if (i < n) root_tok[sl.seq[i]] = best_of_chunks(best + (size_t)i * nch, nch);
 }
-void launch_pick_root(const int32_t* am, const int32_t* last_row, int32_t* root_tok, int B, uint32_t seq_mask,
-                      hipStream_t s) {
-    hipLaunchKernelGGL(k_pick_root, dim3(1), dim3(SD_MAX_BATCH), 0, s, am, last_row, root_tok, B, seq_mask);
+void launch_pick_root(const float2* best, int V, int32_t* root_tok, int n, const SeqList& sl, hipStream_t s) {
+    hipLaunchKernelGGL(k_pick_root, dim3(1), dim3(SD_MAX_BATCH), 0, s, best, rank_chunks(V), root_tok, n, sl);
 }

@@ -202,23 +202,6 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
 }
 
 // ------------------------------------------------------------------------------------------
-// dst[m][c] = sum of the slots of column c (used where the consumer wants dense rows: logits)
-__global__ void k_reduce_slots(PartView pv, float* __restrict__ dst, int rows) {
-    const int c4 = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    const int m = blockIdx.y;
-    if (c4 >= pv.ld || m >= rows) return;
-    const int n = part_count(pv, c4);
-    float4 a = make_float4(0, 0, 0, 0);
-    for (int sp = 0; sp < n; ++sp) {
-        float4 v = *(const float4*)(pv.base + (size_t)sp * pv.slot_stride + (size_t)m * pv.ld + c4);
-        a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-    }
-    *(float4*)(dst + (size_t)m * pv.ld + c4) = a;
-}
-void launch_reduce_slots(PartView pv, float* dst, int rows, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_slots, dim3((pv.ld / 4 + 255) / 256, rows), dim3(256), 0, s, pv, dst, rows);
-}
-
 // Sums the slots of selected rows only: output row (i, b), i < H, b < B, is row i*M + sel[b] of a
 // row-chunked GEMM sequence; this launch covers the chunk holding rows [row0, row0 + rows) and
 // writes dst row i*B + b when that row lies in it.

@@ -6,24 +6,40 @@
 #include "row_ops.h"
 
 // ------------------------------------------------------------------------------------------
-// Rotary angle table entry, in float64 so that positions up to ~17k lose nothing.
-static __device__ inline float2 rope_cs(int pos, int i, int hd, float theta) {
-    double inv = pow((double)theta, -2.0 * (double)i / (double)hd);
+// Rotary angles in float64, so that positions up to ~17k lose nothing. The frequencies theta^(-2i/hd) are a table of the
+// model's (pow() in float64 for every row and dim was most of the row-building launch).
+__global__ void k_rope_freqs(double* __restrict__ freq, int hd, float theta) {
+    const int i = threadIdx.x;
+    if (i < hd / 2) freq[i] = pow((double)theta, -2.0 * (double)i / (double)hd);
+}
+void launch_rope_freqs(double* freq, int hd, float theta, hipStream_t s) {
+    hipLaunchKernelGGL(k_rope_freqs, dim3(1), dim3(128), 0, s, freq, hd, theta);
+}
+static __device__ inline float2 rope_cs(int pos, double freq) {
     double s, c;
-    sincos((double)pos * inv, &s, &c);
+    sincos((double)pos * freq, &s, &c);
     return make_float2((float)c, (float)s);
 }
 
-// (embed_f32: the table holds float32 instead of bfloat16)
+// (embed_f32: the table holds float32 instead of bfloat16) 16 bytes per thread and load; d is a multiple of 32
 static __device__ inline void embed_row(const void* __restrict__ embed, int embed_f32, int tok, int d,
                                         float* __restrict__ xrow, bool valid) {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
     if (embed_f32) {
-        const float* e = (const float*)embed + (size_t)tok * d;
-        for (int i = threadIdx.x; i < d; i += blockDim.x) xrow[i] = valid ? e[i] : 0.f;
+        const float4* e = (const float4*)((const float*)embed + (size_t)tok * d);
+        for (int i = threadIdx.x; i < d / 4; i += blockDim.x) ((float4*)xrow)[i] = valid ? e[i] : zero;
         return;
     }
-    const uint16_t* e = (const uint16_t*)embed + (size_t)tok * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) xrow[i] = valid ? bf16_bits_to_float(e[i]) : 0.f;
+    const uint4* e = (const uint4*)((const uint16_t*)embed + (size_t)tok * d);
+    for (int i = threadIdx.x; i < d / 8; i += blockDim.x) {
+        const uint4 q = e[i];
+        const float4 a = make_float4(__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u),
+                                     __uint_as_float(q.y << 16), __uint_as_float(q.y & 0xffff0000u));
+        const float4 c = make_float4(__uint_as_float(q.z << 16), __uint_as_float(q.z & 0xffff0000u),
+                                     __uint_as_float(q.w << 16), __uint_as_float(q.w & 0xffff0000u));
+        ((float4*)xrow)[2 * i] = valid ? a : zero;
+        ((float4*)xrow)[2 * i + 1] = valid ? c : zero;
+    }
 }
 
 // Tree assembly (paper Section III-B): node 0 = the base model's token, node j >= 1 = the
@@ -33,7 +49,7 @@ static __device__ inline void embed_row(const void* __restrict__ embed, int embe
 __global__ void k_build_rows_tree(RowTable rt, const int32_t* __restrict__ parent, const int32_t* __restrict__ depth,
                                   const int32_t* __restrict__ rank, const int32_t* __restrict__ root_tok,
                                   const int32_t* __restrict__ cand, const int32_t* __restrict__ kv_len, int T, int Tp, int R,
-                                  int H, int topk, int hd, float theta, const void* __restrict__ embed, int embed_f32,
+                                  int H, int topk, int hd, const double* __restrict__ freq, const void* __restrict__ embed, int embed_f32,
                                   int d, int V, float* __restrict__ x) {
     const int b = blockIdx.x / Tp, j = blockIdx.x % Tp, m = b * R + j;
     const bool valid = j < T;
@@ -55,22 +71,22 @@ __global__ void k_build_rows_tree(RowTable rt, const int32_t* __restrict__ paren
         rt.tok[m] = tok;
         rt.pos[m] = pos;
     }
-    for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, i, hd, theta);
+    for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, freq[i]);
     embed_row(embed, embed_f32, tok, d, x + (size_t)m * d, valid);
 }
 
 void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* depth, const int32_t* rank,
                             const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len, int B, int T, int Tp, int R,
-                            int H, int topk, int hd, float theta, const void* embed, int embed_f32, int d, int V, float* x,
+                            int H, int topk, int hd, const double* __restrict__ freq, const void* embed, int embed_f32, int d, int V, float* x,
                             hipStream_t s) {
     hipLaunchKernelGGL(k_build_rows_tree, dim3(B * Tp), dim3(256), 0, s, rt, parent, depth, rank, root_tok, cand,
-                       kv_len, T, Tp, R, H, topk, hd, theta, embed, embed_f32, d, V, x);
+                       kv_len, T, Tp, R, H, topk, hd, freq, embed, embed_f32, d, V, x);
 }
 
 // Prompt chunk as a chain: row j of sequence b is prompt token ca.off[b] + j at position
 // committed length + j and attends rows 0..j of the chunk. (Rows between ca.len and rm.len, if any, are rows of zeros.)
 __global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ tokens, ChainArgs ca, RowMap rm, RowMap* __restrict__ rm_dev,
-                                   const int32_t* __restrict__ kv_len, int Tp, int hd, float theta,
+                                   const int32_t* __restrict__ kv_len, int Tp, int hd, const double* __restrict__ freq,
                                    const void* __restrict__ embed, int embed_f32, int d, int V,
                                    float* __restrict__ x) {
     const int b = blockIdx.x / Tp, j = blockIdx.x % Tp, m = rm.off[b] + j;
@@ -98,14 +114,14 @@ __global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ toke
         rt.tok[m] = tok;
         rt.pos[m] = pos;
     }
-    for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, i, hd, theta);
+    for (int i = threadIdx.x; i < hd / 2; i += blockDim.x) rt.cs[(size_t)m * (hd / 2) + i] = rope_cs(pos, freq[i]);
     embed_row(embed, embed_f32, tok, d, x + (size_t)m * d, valid);
 }
 
 void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev,
-                             const int32_t* kv_len, int B, int Tp, int hd, float theta, const void* embed, int embed_f32, int d, int V, float* x,
+                             const int32_t* kv_len, int B, int Tp, int hd, const double* __restrict__ freq, const void* embed, int embed_f32, int d, int V, float* x,
                              hipStream_t s) {
-    hipLaunchKernelGGL(k_build_rows_chain, dim3(B * Tp), dim3(256), 0, s, rt, tokens, ca, rm, rm_dev, kv_len, Tp, hd, theta,
+    hipLaunchKernelGGL(k_build_rows_chain, dim3(B * Tp), dim3(256), 0, s, rt, tokens, ca, rm, rm_dev, kv_len, Tp, hd, freq,
                        embed, embed_f32, d, V, x);
 }
 
@@ -179,21 +195,23 @@ void launch_swiglu_pack(PartView pv, int F, int Fpad, void* act_packed, int M, i
 // operand of the shared LM-head GEMM. part columns [i*d, (i+1)*d) hold W_i h_b for row b.
 // The i*B + b output rows are laid out in chunks of `chunk_rows` rows (a power of two >= 32, or
 // >= H*B for a single operand): chunk c is a packed activation of its own, `chunk_rows * d * 2`
-// elements after the previous one, with MB row blocks (MBlast in the last chunk).
-__global__ void k_medusa_act(PartView pv, const float* __restrict__ h_rows, MedusaBias bias, int B, int H, int d,
+// elements after the previous one, with MB row blocks (MBlast in the last chunk). base = 1 (where the rows that are drafted
+// from are known before the base logits are: plain decoding, the end of a prompt): B more rows in front, the h rows
+// themselves, so that ONE pass of the LM head serves both (7B shape: a second read of 262 MB, 42 us, saved).
+__global__ void k_medusa_act(PartView pv, const float* __restrict__ h_rows, MedusaBias bias, int base, int B, int H, int d,
                              bf16x8* __restrict__ xp, int chunk_rows, int MB, int MBlast) {
     int idx = blockIdx.x * blockDim.x + threadIdx.x;
     int ng = d / 8;
-    if (idx >= H * B * ng) return;
-    int grp = idx % ng, b = (idx / ng) % B, i = idx / (ng * B);
+    if (idx >= (H + base) * B * ng) return;
+    int grp = idx % ng, b = (idx / ng) % B, i = idx / (ng * B) - base;
     float z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int nsplit = part_count(pv, i * d + grp * 8);
+    const int nsplit = i < 0 ? 0 : part_count(pv, i * d + grp * 8);
     for (int sp = 0; sp < nsplit; ++sp) {
         const float* p = pv.base + (size_t)sp * pv.slot_stride + (size_t)b * pv.ld + (size_t)i * d + grp * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) z[e] += p[e];
     }
-    const uint16_t* bi = bias.p[i];
+    const uint16_t* bi = i < 0 ? nullptr : bias.p[i];
     bf16x8 hi, lo;
     float f[8];
 #pragma unroll
@@ -202,16 +220,16 @@ __global__ void k_medusa_act(PartView pv, const float* __restrict__ h_rows, Medu
         f[e] = h_rows[(size_t)b * d + grp * 8 + e] + zz / (1.f + __expf(-zz));
     }
     split_hilo(f, hi, lo);
-    const int row = i * B + b, chunk = row / chunk_rows, last = (H * B - 1) / chunk_rows;
+    const int row = (i + base) * B + b, chunk = row / chunk_rows, last = ((H + base) * B - 1) / chunk_rows;
     const size_t u = ((size_t)chunk * chunk_rows * d * 2 + xpack_index(row - chunk * chunk_rows, grp * 8,
                                                                        chunk == last ? MBlast : MB)) >> 3;
     xp[u] = hi;
     xp[u + XPART / 8] = lo;
 }
 
-void launch_medusa_act(PartView pv, const float* h_rows, const MedusaBias& bias, int B, int H, int d, void* x_packed,
-                       int chunk_rows, int MB, int MBlast, hipStream_t s) {
-    int total = H * B * (d / 8);
-    hipLaunchKernelGGL(k_medusa_act, dim3((total + 255) / 256), dim3(256), 0, s, pv, h_rows, bias, B, H, d,
+void launch_medusa_act(PartView pv, const float* h_rows, const MedusaBias& bias, int base, int B, int H, int d,
+                       void* x_packed, int chunk_rows, int MB, int MBlast, hipStream_t s) {
+    int total = (H + base) * B * (d / 8);
+    hipLaunchKernelGGL(k_medusa_act, dim3((total + 255) / 256), dim3(256), 0, s, pv, h_rows, bias, base, B, H, d,
                        (bf16x8*)x_packed, chunk_rows, MB, MBlast);
 }

@@ -188,7 +188,10 @@ struct MedusaBias { const uint16_t* p[SD_MAX_MEDUSA + 1]; };
 struct VerifyArgs {
     const int32_t *parent, *depth;      // device tree tables [T]
     int T, H, fallback, src_stride, Tp, V;
-    const int32_t *tok, *am;            // [B][src_stride]
+    const int32_t *tok, *am;            // [B][src_stride]; am not read when best is given
+    const float2* best;                 // NULL, or [B][src_stride][n_chunks] (launch_rank_best)
+    int n_chunks;
+    int32_t* am_out;                    // [B][T] or NULL: the arg-max of every node
     const uint32_t* stop_mask;
     int32_t *n_accept, *n_accept_raw, *tokens, *src_slots;   // outputs, [B] / [B][H+1]
     int32_t *kv_len, *n_old, *root_tok, *last_row;           // carried state, may be NULL
@@ -217,17 +220,18 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
 void launch_layer(const FusedArgs& a, int G, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // how many of its workgroups the device can hold at once (0 on error)
 int fused_max_resident(int device);
-void launch_reduce_slots(PartView pv, float* dst, int rows, hipStream_t s);
 // dst row i*B + b = summed row (i*M + sel[b]) - row0 of pv when it lies in [0, rows); i < H, b < B
 void launch_reduce_selected(PartView pv, float* dst, const int32_t* sel, int B, int H, int M, int row0, int rows,
                             hipStream_t s);
 
+// freq [head_dim / 2]: rotary frequencies
+void launch_rope_freqs(double* freq, int hd, float theta, hipStream_t s);
 void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* depth, const int32_t* rank,
                             const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len,
-                            int B, int T, int Tp, int R, int H, int topk, int hd, float theta,
+                            int B, int T, int Tp, int R, int H, int topk, int hd, const double* freq,
                             const void* embed, int embed_f32, int d, int V, float* x, hipStream_t s);
 void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev, const int32_t* kv_len,
-                             int B, int Tp, int hd, float theta, const void* embed, int embed_f32, int d, int V,
+                             int B, int Tp, int hd, const double* freq, const void* embed, int embed_f32, int d, int V,
                              float* x, hipStream_t s);
 // float32 device path (f32.hip): natural row-major layouts, vector-ALU arithmetic
 void launch_f32_rmsnorm(const float* x, const float* gain, float eps, float* y, int M, int d, const int32_t* gather,
@@ -258,17 +262,21 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s);
 void launch_swiglu_pack(PartView pv, int F, int Fpad, void* act_packed, int M, int MB, hipStream_t s);
-// output rows i*B + b in chunks of chunk_rows rows, each a packed activation of MB (last: MBlast) row blocks
-void launch_medusa_act(PartView pv, const float* h_rows, const MedusaBias& bias, int B, int H, int d,
+// output rows base * B + i*B + b in chunks of chunk_rows rows, each a packed activation of MB (last: MBlast) row blocks;
+// base = 1: rows 0 .. B-1 are the h rows themselves
+void launch_medusa_act(PartView pv, const float* h_rows, const MedusaBias& bias, int base, int B, int H, int d,
                        void* x_packed, int chunk_rows, int MB, int MBlast, hipStream_t s);
-// arg-max of the first T rows of every sequence from the LM head's partial sums; logits_or_null: also write the
-// summed logits of those rows ([row][pv.ld])
-void launch_reduce_argmax(PartView pv, float* logits_or_null, int V, int32_t* am, int B, int T, int Tp, hipStream_t s);
-void launch_argmax(const float* logits, int ld, int V, int32_t* am, int B, int T, int Tp, hipStream_t s);
-void launch_topk(const float* logits, int ld, int V, int k, int32_t* out, int B, int H, uint32_t seq_mask,
-                 hipStream_t s);
-void launch_pick_root(const int32_t* am, const int32_t* last_row, int32_t* root_tok, int B, uint32_t seq_mask,
-                      hipStream_t s);
+// Ranking of logit rows from partial sums (decide.hip); cand: device scratch of rows * rank_chunks(V) * k entries (k = 1 for
+// launch_rank_best, whose result stays in it: per row and chunk {best logit, its id}); logits (or NULL): the summed rows
+// are also written there, row r at logits + r * ld, and row (b, i) at head_logits + (b * H + i) * V
+int rank_chunks(int V);
+void launch_rank_best(PartView pv, int row0, int rows, int V, float* logits, int ld, float2* cand, hipStream_t s);
+// out[seq[b]][i][0..k): ids of the largest k logits of row row0 + i * B + b, best first, lower id on ties
+struct SeqList { int32_t seq[SD_MAX_BATCH]; };
+void launch_topk(PartView pv, int row0, int V, int k, int32_t* out, int B, int H, const SeqList& sl, float* head_logits,
+                 void* cand, hipStream_t s);
+// root_tok[seq[i]] = arg-max of ranked row i
+void launch_pick_root(const float2* best, int V, int32_t* root_tok, int n, const SeqList& sl, hipStream_t s);
 void launch_verify(const VerifyArgs& a, int B, hipStream_t s);
 // per tree row: softmax statistics at a temperature and the typical-acceptance threshold (see decide.hip)
 void launch_row_stats(const float* logits, int ld, int V, float4* stats, int B, int T, int Tp, float inv_temperature,
@@ -288,10 +296,7 @@ void launch_commit_setup(const int32_t* n_rows, int width, int B, int32_t* n_acc
                          hipStream_t s);
 void launch_kv_rows(void* kc, void* vc, void* k_rows, void* v_rows, int row0, int nrows, int nh, int hd,
                     int cap_blocks, int to_cache, hipStream_t s);
-void launch_copy_logits(const float* src, int ld, float* dst, int V, int B, int T, int Tp, hipStream_t s);
-void launch_copy_rows_i32(const int32_t* src, int32_t* dst, int B, int T, int Tp, hipStream_t s);
-void launch_copy_head_logits(const float* src, int ld, float* dst, int V, int B, int H, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int n, hipStream_t s);
 void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s);
 void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
-                                 int32_t* n_old, int32_t* kv_len, int32_t* last_row, hipStream_t s);
+                                 int32_t* n_old, int32_t* kv_len, int32_t* fin_rows, int n_fin, const SeqList& last, hipStream_t s);
