@@ -23,7 +23,7 @@
  *   - dtype = SD_DTYPE_BF16: weights and cache rows are bfloat16, products run on the matrix
  *     cores with float32 accumulation: the production path, the one every performance figure is for.
  *     dtype = SD_DTYPE_F32: weights, activations and cache rows are float32 and every product is
- *     accumulated in float32 on the vector ALUs, with plain kernels: for configurations that are
+ *     taken and accumulated in float32, with plain kernels: for configurations that are
  *     specified in float32 (small ones: correctness, not speed). Same entry points, same integer
  *     stages; differences: sd_kv_write_rows / sd_kv_read_rows move float32 rows, the draft heads
  *     always run after acceptance (sd_set_draft_schedule is accepted and has no effect),

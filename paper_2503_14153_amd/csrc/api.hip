@@ -107,7 +107,8 @@ struct sd_model {
     unsigned long long* timeline = nullptr;  // caller's buffer for the layer kernel's time stamps, or NULL
     size_t timeline_launches = 0;
     int scratch_B = 0, scratch_Tp = 0;       // the tree K/V scratch as the last pass left it: its cache's batch, rows per
-    int scratch_n = 0, scratch_seq[SD_MAX_BATCH] = {};   // sequence, and the sequences that it holds, in order
+    int scratch_n = 0, scratch_seq[SD_MAX_BATCH] = {};   // sequence, and the sequences that it holds, in order; float32: the
+    int scratch_M = 0, scratch_row0[SD_MAX_BATCH] = {};  // rows of the pass and every sequence's first
     bool plan_missing = false;               // set by run_gemm if it ever had to skip a launch
     bool greedy_drafts = true;               // sd_greedy_step also runs the draft heads
     // float32 path (dtype SD_DTYPE_F32; f32.hip): weights [out][in] as float, natural activation layouts
@@ -116,7 +117,7 @@ struct sd_model {
     struct F32 {
         const float *embed, *lm_head, *final_norm, *medusa_w, *medusa_b;
         std::vector<F32Layer> layers;
-        float *xn, *qkv, *q, *attn, *gu, *act, *kt, *vt, *z, *xh;
+        float *q, *attn, *act, *kt, *vt, *xh;
     } f;
 };
 
@@ -220,11 +221,10 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
     const size_t w_x = wtake((size_t)Mp * d * 4);
     const size_t w_logits = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * m->Vpad * 4);
-    const size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4), w_hrows = wtake((size_t)SD_MAX_BATCH * d * 4);
-    const size_t w_xn = wtake((size_t)Mp * d * 4), w_qkv = wtake((size_t)Mp * 3 * d * 4), w_q = wtake((size_t)Mp * d * 4);
-    const size_t w_attn = wtake((size_t)Mp * d * 4), w_gu = wtake((size_t)Mp * 2 * F * 4), w_act = wtake((size_t)Mp * F * 4);
+    const size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4);
+    const size_t w_q = wtake((size_t)Mp * d * 4), w_attn = wtake((size_t)Mp * d * 4), w_act = wtake((size_t)Mp * F * 4);
     const size_t w_kt = wtake((size_t)L * Mp * d * 4), w_vt = wtake((size_t)L * Mp * d * 4);
-    const size_t w_z = wtake((size_t)SD_MAX_BATCH * H * d * 4), w_xh = wtake((size_t)HBp * d * 4);
+    const size_t w_xh = wtake((size_t)HBp * d * 4);
     const size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
     const size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
     const size_t w_best = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * rank_chunks(V) * 8);
@@ -242,10 +242,8 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     }
     char* Wk = m->work;
     m->x = (float*)(Wk + w_x); m->logits = (float*)(Wk + w_logits); m->hlogits = (float*)(Wk + w_hlog);
-    m->h_rows = (float*)(Wk + w_hrows);
-    m->f.xn = (float*)(Wk + w_xn); m->f.qkv = (float*)(Wk + w_qkv); m->f.q = (float*)(Wk + w_q);
-    m->f.attn = (float*)(Wk + w_attn); m->f.gu = (float*)(Wk + w_gu); m->f.act = (float*)(Wk + w_act);
-    m->f.kt = (float*)(Wk + w_kt); m->f.vt = (float*)(Wk + w_vt); m->f.z = (float*)(Wk + w_z); m->f.xh = (float*)(Wk + w_xh);
+    m->f.q = (float*)(Wk + w_q); m->f.attn = (float*)(Wk + w_attn); m->f.act = (float*)(Wk + w_act);
+    m->f.kt = (float*)(Wk + w_kt); m->f.vt = (float*)(Wk + w_vt); m->f.xh = (float*)(Wk + w_xh);
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
     m->best = (float2*)(Wk + w_best); m->ranked = Wk + w_rk; m->fin_rows = (int32_t*)(Wk + w_fin);
@@ -1012,49 +1010,45 @@ static void commit_rows(sd_model* m, sd_kv* kv, bool by_seq, const int32_t* slot
     RowMap rm;
     memset(&rm, 0, sizeof(rm));
     for (int i = 0; i < m->scratch_n; ++i) { rm.seq[i] = m->scratch_seq[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
-    if (m->f32)
-        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, c.n_layers, kv->B, c.d_model, Tp,
-                             kv->cap, W, s);
+    if (m->f32) {
+        for (int i = 0; i < m->scratch_n; ++i) rm.len[i] = m->scratch_row0[i];
+        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, m->scratch_n,
+                             c.d_model, m->scratch_M, kv->cap, W, s);
+    }
     else
         launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, m->scratch_n, c.n_heads,
                          c.head_dim, Tp / 32, kv->cap_blocks, W, s);
 }
 
-static void run_forward_f32(sd_model* m, sd_kv* kv, int B, int Tp, bool want_lm, hipStream_t s) {
+static void run_forward_f32(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, bool want_lm,
+                            hipStream_t s) {
     const sd_config& c = m->cfg;
-    const int M = B * Tp, d = c.d_model, F = c.d_ffn;
+    const int d = c.d_model, F = c.d_ffn, longest = *std::max_element(rm.len, rm.len + B);
     sd_model::F32& f = m->f;
     for (int l = 0; l < c.n_layers; ++l) {
         const sd_model::F32Layer& lw = f.layers[l];
         float* kt = f.kt + (size_t)l * M * d;
         float* vt = f.vt + (size_t)l * M * d;
-        launch_f32_rmsnorm(m->x, lw.attn_norm, c.rms_eps, f.xn, M, d, nullptr, s);
-        launch_f32_linear(f.xn, lw.wqkv, nullptr, f.qkv, M, 3 * d, d, d, 3 * d, 0, s);
-        launch_f32_rope_kv(f.qkv, m->rt, f.q, kt, vt, M, c.n_heads, c.head_dim, s);
+        launch_f32_qkv(m->x, lw.attn_norm, c.rms_eps, lw.wqkv, m->rt, f.q, kt, vt, M, c.n_heads, c.head_dim, s);
         launch_f32_attn(f.q, kv->kc32 + l * kv->layer_stride, kv->vc32 + l * kv->layer_stride, kt, vt, kv->kv_len, m->rt.anc,
-                        f.attn, B, c.n_heads, c.head_dim, Tp, kv->cap, s);
-        launch_f32_linear(f.attn, lw.wo, nullptr, m->x, M, d, d, d, d, 1, s);
-        launch_f32_rmsnorm(m->x, lw.ffn_norm, c.rms_eps, f.xn, M, d, nullptr, s);
-        launch_f32_linear(f.xn, lw.wgu, nullptr, f.gu, M, 2 * F, d, d, 2 * F, 0, s);
-        launch_f32_swiglu(f.gu, f.act, M, F, s);
-        launch_f32_linear(f.act, lw.wdown, nullptr, m->x, M, d, F, F, d, 1, s);
+                        f.attn, rr, longest, B, c.n_heads, c.head_dim, Tp, kv->cap, s);
+        launch_f32_add_linear(f.attn, lw.wo, m->x, M, d, d, s);
+        launch_f32_gate_up(m->x, lw.ffn_norm, c.rms_eps, lw.wgu, f.act, M, F, d, s);
+        launch_f32_add_linear(f.act, lw.wdown, m->x, M, d, F, s);
     }
-    if (want_lm) {
-        launch_f32_rmsnorm(m->x, f.final_norm, c.rms_eps, f.xn, M, d, nullptr, s);
-        launch_f32_linear(f.xn, f.lm_head, nullptr, m->logits, M, c.vocab, d, d, m->Vpad, 0, s);
-    }
+    if (want_lm)
+        launch_f32_norm_linear(m->x, nullptr, f.final_norm, c.rms_eps, f.lm_head, m->logits, M, c.vocab, d, m->Vpad, s);
 }
 // dense float32 logits as the ranking kernels take them
 static PartView dense_logits(const sd_model* m, const float* logits) { return PartView{logits, 0, m->Vpad, nullptr, 1}; }
 
-// (m->h_rows holds the final norm's output of the B rows that are drafted from)
-static void run_draft_heads_f32(sd_model* m, sd_kv* kv, int B, const SeqList& sl, float* head_logits_out, hipStream_t s) {
+static void run_draft_heads_f32(sd_model* m, sd_kv* kv, const int32_t* rows, int B, const SeqList& sl, float* head_logits_out,
+                                hipStream_t s) {
     const sd_config& c = m->cfg;
     const int d = c.d_model, H = c.n_medusa;
     sd_model::F32& f = m->f;
-    launch_f32_linear(m->h_rows, f.medusa_w, f.medusa_b, f.z, B, H * d, d, d, H * d, 0, s);
-    launch_f32_medusa_act(f.z, m->h_rows, f.xh, B, H, d, s);
-    launch_f32_linear(f.xh, f.lm_head, nullptr, m->hlogits, H * B, c.vocab, d, d, m->Vpad, 0, s);
+    launch_f32_heads(m->x, rows, f.final_norm, c.rms_eps, f.medusa_w, f.medusa_b, f.xh, B, H, d, s);
+    launch_f32_norm_linear(f.xh, nullptr, nullptr, 0.f, f.lm_head, m->hlogits, H * B, c.vocab, d, m->Vpad, s);
     launch_topk(dense_logits(m, m->hlogits), 0, c.vocab, c.topk, kv->cand, B, H, sl, head_logits_out, m->ranked, s);
 }
 
@@ -1074,10 +1068,11 @@ static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int
                             bool keep_h, hipStream_t s) {
     m->scratch_B = kv->B;
     m->scratch_n = B;
-    for (int i = 0; i < B; ++i) m->scratch_seq[i] = rm.seq[i];
+    m->scratch_M = M;
+    for (int i = 0; i < B; ++i) { m->scratch_seq[i] = rm.seq[i]; m->scratch_row0[i] = rm.off[i]; }
     m->scratch_Tp = Tp;
-    if (m->f32) { run_forward_f32(m, kv, B, Tp, want_lm, s); return dense_logits(m, m->logits); }
     const RowRef rr = {R ? nullptr : m->rm_dev, R};
+    if (m->f32) { run_forward_f32(m, kv, rr, rm, B, M, Tp, want_lm, s); return dense_logits(m, m->logits); }
     if (fused_eligible(m, B * Tp)) {
         // (when the final norm's rows themselves are wanted, the last stage runs as kernels of its own)
         PartView pl = run_forward_fused(m, kv, rr, B, Tp, n_hi, want_lm && !keep_h, s);
@@ -1097,11 +1092,7 @@ static SeqList every_sequence() {
 static void run_draft_heads(sd_model* m, sd_kv* kv, int B, float* head_logits_out, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int d = c.d_model, H = c.n_medusa;
-    if (m->f32) {
-        launch_f32_rmsnorm(m->x, m->f.final_norm, c.rms_eps, m->h_rows, B, d, kv->last_row, s);
-        run_draft_heads_f32(m, kv, B, every_sequence(), head_logits_out, s);
-        return;
-    }
+    if (m->f32) { run_draft_heads_f32(m, kv, kv->last_row, B, every_sequence(), head_logits_out, s); return; }
     const PartView none = {nullptr, 0, d, nullptr, 0};
     launch_norm_pack(m->x, none, m->final_norm, c.rms_eps, m->xn, m->h_rows, B, d, 1, kv->last_row, s);
     PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, B, 1, m->KBd, m->NBmed, H * d, s);
@@ -1119,10 +1110,9 @@ static void run_known_rows(sd_model* m, sd_kv* kv, PartView prev, int n, const i
     const sd_config& c = m->cfg;
     const int d = c.d_model, H = c.n_medusa;
     if (m->f32) {
-        launch_f32_rmsnorm(m->x, m->f.final_norm, c.rms_eps, m->h_rows, n, d, gather, s);
-        launch_f32_linear(m->h_rows, m->f.lm_head, nullptr, m->logits, n, c.vocab, d, d, m->Vpad, 0, s);
+        launch_f32_norm_linear(m->x, gather, m->f.final_norm, c.rms_eps, m->f.lm_head, m->logits, n, c.vocab, d, m->Vpad, s);
         launch_rank_best(dense_logits(m, m->logits), 0, n, c.vocab, logits, ld, m->best, s);
-        run_draft_heads_f32(m, kv, n, sl, head_logits_out, s);
+        run_draft_heads_f32(m, kv, gather, n, sl, head_logits_out, s);
         return;
     }
     launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, m->h_rows, n, d, 1, gather, s);
@@ -1180,7 +1170,6 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
     for (int b = 0, o = 0; b < B; ++b) { next[b] = o; o += lens[b]; }
     for (;;) {
         // The sequences that still have tokens share the pass's rows: a prompt that has ended takes none of them.
-        // (float32: all sequences, every pass.)
         ChainArgs ca;
         RowMap rm;
         memset(&ca, 0, sizeof(ca));
@@ -1190,10 +1179,10 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         memset(&last, 0, sizeof(last));
         int A = 0, M = 0, n_hi = 0, n_fin = 0;
         for (int b = 0; b < B; ++b)
-            if (left[b] > 0 || m->f32) rm.seq[A++] = b;
-        if (*std::max_element(left.begin(), left.end()) <= 0) break;
-        if (!m->f32) Tp = std::min(m->max_rows / A / 32 * 32, 256);
-        const bool padded = m->f32 || fused_eligible(m, A * Tp);        // these passes take the rows as [sequence][Tp]
+            if (left[b] > 0) rm.seq[A++] = b;
+        if (A == 0) break;
+        Tp = std::min(m->max_rows / A / 32 * 32, 256);
+        const bool padded = fused_eligible(m, A * Tp);     // that pass takes the rows as [sequence][Tp]
         for (int i = 0; i < A; ++i) {
             const int b = rm.seq[i];
             ca.len[i] = std::min(left[b], Tp);
@@ -1250,7 +1239,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     const bool heads = T > 1 || m->greedy_drafts;      // plain greedy decoding may leave the draft heads out
     // rows of a sequence lie R apart: the tree's own nodes, no padding (see RowMap), except where the pass takes them
     // as [sequence][Tp]
-    const int R = m->f32 || fused_eligible(m, B * Tp) ? Tp : T, M = B * R;
+    const int R = fused_eligible(m, B * Tp) ? Tp : T, M = B * R;
     RowMap rm;
     memset(&rm, 0, sizeof(rm));
     for (int b = 0; b < B; ++b) { rm.off[b] = b * R; rm.len[b] = R; rm.seq[b] = b; }
@@ -1270,7 +1259,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     float* lg = io->logits && dense ? io->logits : (io->logits || ty) ? m->logits : nullptr;
     const int ldl = lg == m->logits ? m->Vpad : c.vocab;
     // plain decoding drafts from the only row a sequence has: one pass of the LM head for its base and head rows
-    const bool known = T == 1 && dense && heads && !m->f32 && !fused_eligible(m, B * Tp);
+    const bool known = T == 1 && dense && heads && !fused_eligible(m, B * Tp);
     PartView pl = run_forward(m, kv, rm, B, M, R, Tp, n_hi, !known, all_rows, s);
     if (known) {
         run_known_rows(m, kv, pl, B, nullptr, every_sequence(), lg, ldl, io->head_logits, s);

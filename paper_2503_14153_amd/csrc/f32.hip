@@ -1,239 +1,319 @@
-// The float32 device path: the same speculative step with weights, activations and the KV cache held as
-// float32 and every product accumulated in float32 on the vector ALUs. It exists for configurations that are
-// specified in float32 (the small correctness configuration): shapes of that size are bound by launches, not by
-// arithmetic, so these kernels are plain (one thread per output, LDS tiles, natural row-major layouts) and make no
-// attempt at the matrix cores. The integer stages (tree assembly, arg-max, top-k, acceptance, fragment cut) and the
-// sampling statistics are the same kernels as on the bf16 path: they only ever see float32 logits.
+// The float32 device path: the same speculative step with weights, activations and the KV cache held as float32 and every
+// product accumulated in float32. It exists for configurations that are specified in float32 (the small correctness
+// configuration): shapes of that size are bound by the number of launches and by the latency of each, so the stages of a
+// layer are five launches (projections carry the norm before them and the rotary embedding, the gate or the residual add
+// after them), and a projection spreads its contraction over the eight waves of a workgroup, whose loads are all in
+// flight together. Products run on the matrix cores in float32 (v_mfma_f32_16x16x4_f32: float32 operands, float32
+// accumulation). The integer stages (tree assembly, ranking, acceptance, fragment cut) and the sampling statistics are the
+// same kernels as on the bf16 path: they only ever see float32 logits.
+// 16-node step of the small configuration (2 layers, d = 256): 470 us of kernels in 32 launches before, a projection of
+// 32 x 256 outputs over 688 inputs 69 us (one 32 x 32 tile per workgroup, contraction blocks one after the other).
 //
-// Layouts: weights [out][in]; activations [row][col]; tree scratch [layer][row][d]; cache [layer][K|V][seq][cap][d].
+// Layouts: weights [out][in]; activations [row][col], rows packed as RowMap says; tree scratch [layer][row][d]; cache
+// [layer][K|V][seq][cap][d].
 #include "sd_internal.h"
 
 // ------------------------------------------------------------------------------------------
-// y[m] = x[src] * rsqrt(mean(x[src]^2) + eps) * gain; one workgroup of 256 threads per row.
-__global__ __launch_bounds__(256) void k_f32_rmsnorm(const float* __restrict__ x, const float* __restrict__ gain, float eps,
-                                                     float* __restrict__ y, int d, const int32_t* __restrict__ gather) {
-    const int m = blockIdx.x, src = gather ? gather[m] : m;
-    const float* xr = x + (size_t)src * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d; i += 256) ss += xr[i] * xr[i];
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    __shared__ float red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+// out = epilogue(norm(X) W^T). A workgroup of eight waves owns 32 rows x two blocks of 16 columns; wave w takes the
+// contraction steps w, w + 8, .. of 16 and the waves' sums meet in LDS. Operands go from memory to the matrix cores: lane l
+// loads four consecutive inputs of row (or column) l % 16, the four products of a step take one of them each, and since
+// both operands are loaded alike, which input a product's contraction index stands for does not matter.
+// NORM: X's rows go through RMSNorm: the operand is x * gain, the sums of squares ride along, and the row's 1 / rms factor
+// is applied to the result (a product is linear in its rows).
+// The two column blocks are chosen so that a thread of the epilogue holds what belongs together:
+//   F32_STORE  columns 32t and 32t + 16: out[m][n] = v + bias[n]
+//   F32_ADD    the same, added to out (the residual stream)
+//   F32_QKV    dims i and i + hd/2 of one head: rotated at the row's position -> q; keys and values -> tree scratch
+//   F32_GATE   gate column and up column: out[m][f] = silu(gate) * up
+//   F32_HEADS  as STORE, z = v + bias: out row (n / d) * M + m, column n % d: h + silu(z), h = the normalised row
+enum { F32_STORE, F32_ADD, F32_QKV, F32_GATE, F32_HEADS };
+struct F32Linear {
+    const float *X, *gain, *W, *bias;
+    const int32_t* gather;              // or NULL: row m reads X row gather[m]
+    float eps;
+    int M, N, K, ldo;
+    float* out;
+    float *kt, *vt;                     // F32_QKV
+    const float2* cs;
+    int nh, hd;
+};
+template <int MODE, bool NORM>
+__global__ __launch_bounds__(512) void k_f32_linear(F32Linear a) {
+    constexpr int NW = 8, U = 3;        // waves; steps whose loads are issued together
+    __shared__ float red[NW][32][33];
+    __shared__ float ssq[NW][32];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, kq = (lane >> 4) * 4;
+    const int m0 = blockIdx.y * 32, t = blockIdx.x;
+    int c0 = 32 * t, c1 = c0 + 16;
+    if constexpr (MODE == F32_QKV) {
+        const int per = a.hd / 32;      // 16-column blocks of a half head
+        c0 = (t / per) * a.hd + (t % per) * 16;
+        c1 = c0 + a.hd / 2;
+    }
+    if constexpr (MODE == F32_GATE) { c0 = 16 * t; c1 = a.N / 2 + 16 * t; }
+    const float *xp[2], *wp[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {       // rows and columns past the end: the last one again, never stored
+        const int m = min(m0 + 16 * i + r16, a.M - 1), n = min((i ? c1 : c0) + r16, a.N - 1);
+        xp[i] = a.X + (size_t)(a.gather ? a.gather[m] : m) * a.K + kq;
+        wp[i] = a.W + (size_t)n * a.K + kq;
+    }
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float ss[2] = {0.f, 0.f};
+    const int S = a.K / 16;             // (d_model and d_ffn are multiples of 16)
+    for (int s0 = wave; s0 < S; s0 += NW * U) {
+        f32x4 x[U][2], w[U][2], g[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = min(s0 + NW * u, S - 1);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[u][i] = *(const f32x4*)(xp[i] + 16 * s);
+                w[u][i] = *(const f32x4*)(wp[i] + 16 * s);
+            }
+            if constexpr (NORM) g[u] = *(const f32x4*)(a.gain + 16 * s + kq);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + NW * u >= S) break;                   // wave-uniform
+            if constexpr (NORM) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { ss[i] = fmaf(x[u][i][e], x[u][i][e], ss[i]); x[u][i][e] *= g[u][e]; }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][i][e], w[u][j][e], acc[i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][16 * i + 4 * (lane >> 4) + v][16 * j + r16] = acc[i][j][v];
+        if constexpr (NORM) {
+            float q = ss[i];
+            q += __shfl_xor(q, 16);
+            q += __shfl_xor(q, 32);
+            if (lane < 16) ssq[wave][16 * i + r16] = q;
+        }
+    }
     __syncthreads();
-    const float r = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += 256) y[(size_t)m * d + i] = xr[i] * r * gain[i];
+    const int row = tid >> 4, col = tid & 15, m = m0 + row;
+    if (m >= a.M) return;
+    float v0 = 0.f, v1 = 0.f, q = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        v0 += red[w][row][col];
+        v1 += red[w][row][16 + col];
+        if constexpr (NORM) q += ssq[w][row];
+    }
+    float r = 1.f;
+    if constexpr (NORM) {
+        r = rsqrtf(q / (float)a.K + a.eps);
+        v0 *= r;
+        v1 *= r;
+    }
+    const int n0 = c0 + col, n1 = c1 + col;
+    if constexpr (MODE == F32_STORE || MODE == F32_ADD) {
+        float* o = a.out + (size_t)m * a.ldo;
+        if (n0 < a.N) o[n0] = MODE == F32_ADD ? o[n0] + v0 : v0 + (a.bias ? a.bias[n0] : 0.f);
+        if (n1 < a.N) o[n1] = MODE == F32_ADD ? o[n1] + v1 : v1 + (a.bias ? a.bias[n1] : 0.f);
+    } else if constexpr (MODE == F32_QKV) {
+        const int d = a.nh * a.hd, which = n0 / d, c = n0 - which * d, i = c % a.hd;
+        const size_t at = (size_t)m * d + c;
+        float* o = which == 0 ? a.out : which == 1 ? a.kt : a.vt;
+        if (which < 2) {
+            const float2 cs = a.cs[(size_t)m * (a.hd / 2) + i];
+            o[at] = v0 * cs.x - v1 * cs.y;
+            o[at + a.hd / 2] = v1 * cs.x + v0 * cs.y;
+        } else {
+            o[at] = v0;
+            o[at + a.hd / 2] = v1;
+        }
+    } else if constexpr (MODE == F32_GATE) {
+        a.out[(size_t)m * a.ldo + n0] = v0 / (1.f + __expf(-v0)) * v1;
+    } else {
+        const float* xr = a.X + (size_t)(a.gather ? a.gather[m] : m) * a.K;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = i ? n1 : n0;
+            if (n >= a.N) continue;
+            const int head = n / a.K, c = n - head * a.K;
+            const float z = (i ? v1 : v0) + a.bias[n];
+            a.out[((size_t)head * a.M + m) * a.ldo + c] = xr[c] * r * a.gain[c] + z / (1.f + __expf(-z));
+        }
+    }
 }
-void launch_f32_rmsnorm(const float* x, const float* gain, float eps, float* y, int M, int d, const int32_t* gather,
+
+static void launch_linear(const F32Linear& a, int mode, bool norm, hipStream_t s) {
+    const int tiles = mode == F32_GATE ? a.N / 32 : (a.N + 31) / 32;
+    const dim3 grid(tiles, (a.M + 31) / 32), block(512);
+    if (mode == F32_STORE && norm) hipLaunchKernelGGL((k_f32_linear<F32_STORE, true>), grid, block, 0, s, a);
+    else if (mode == F32_STORE) hipLaunchKernelGGL((k_f32_linear<F32_STORE, false>), grid, block, 0, s, a);
+    else if (mode == F32_ADD) hipLaunchKernelGGL((k_f32_linear<F32_ADD, false>), grid, block, 0, s, a);
+    else if (mode == F32_QKV) hipLaunchKernelGGL((k_f32_linear<F32_QKV, true>), grid, block, 0, s, a);
+    else if (mode == F32_GATE) hipLaunchKernelGGL((k_f32_linear<F32_GATE, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_f32_linear<F32_HEADS, true>), grid, block, 0, s, a);
+}
+void launch_f32_norm_linear(const float* X, const int32_t* gather, const float* gain, float eps, const float* W, float* out, int M,
+                            int N, int K, int ldo, hipStream_t s) {
+    F32Linear a = {X, gain, W, nullptr, gather, eps, M, N, K, ldo, out, nullptr, nullptr, nullptr, 0, 0};
+    launch_linear(a, F32_STORE, gain != nullptr, s);
+}
+void launch_f32_add_linear(const float* X, const float* W, float* x, int M, int N, int K, hipStream_t s) {
+    F32Linear a = {X, nullptr, W, nullptr, nullptr, 0.f, M, N, K, N, x, nullptr, nullptr, nullptr, 0, 0};
+    launch_linear(a, F32_ADD, false, s);
+}
+void launch_f32_qkv(const float* X, const float* gain, float eps, const float* W, RowTable rt, float* q, float* kt, float* vt, int M,
+                    int nh, int hd, hipStream_t s) {
+    const int d = nh * hd;
+    F32Linear a = {X, gain, W, nullptr, nullptr, eps, M, 3 * d, d, d, q, kt, vt, rt.cs, nh, hd};
+    launch_linear(a, F32_QKV, true, s);
+}
+void launch_f32_gate_up(const float* X, const float* gain, float eps, const float* W, float* act, int M, int F, int d,
                         hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_rmsnorm, dim3(M), dim3(256), 0, s, x, gain, eps, y, d, gather);
+    F32Linear a = {X, gain, W, nullptr, nullptr, eps, M, 2 * F, d, F, act, nullptr, nullptr, nullptr, 0, 0};
+    launch_linear(a, F32_GATE, true, s);
+}
+void launch_f32_heads(const float* X, const int32_t* gather, const float* gain, float eps, const float* W, const float* bias,
+                      float* out, int B, int H, int d, hipStream_t s) {
+    F32Linear a = {X, gain, W, bias, gather, eps, B, H * d, d, d, out, nullptr, nullptr, nullptr, 0, 0};
+    launch_linear(a, F32_HEADS, true, s);
 }
 
 // ------------------------------------------------------------------------------------------
-// out[m][n] (+)= sum_k X[m][k] * W[n][k] (+ bias[n]). 32 x 32 outputs per workgroup of 256 threads, contraction in
-// steps of 32 through LDS; thread (tx, ty) owns column tx of rows ty, ty+8, ty+16, ty+24 of the tile.
-// accumulate = 1: the result is added to what `out` holds (the residual stream).
-__global__ __launch_bounds__(256) void k_f32_linear(const float* __restrict__ X, const float* __restrict__ W,
-                                                    const float* __restrict__ bias, float* __restrict__ out, int M, int N,
-                                                    int K, int ldx, int ldo, int accumulate) {
-    __shared__ float xs[32][33], ws[32][33];
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = ty + 8 * r, k = k0 + tx;
-            xs[row][tx] = (m0 + row < M && k < K) ? X[(size_t)(m0 + row) * ldx + k] : 0.f;
-            ws[row][tx] = (n0 + row < N && k < K) ? W[(size_t)(n0 + row) * K + k] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int kk = 0; kk < 32; ++kk) {
-            const float w = ws[tx][kk];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = fmaf(xs[ty + 8 * r][kk], w, acc[r]);
-        }
-        __syncthreads();
-    }
-    const int n = n0 + tx;
-    if (n >= N) return;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + ty + 8 * r;
-        if (m < M) {
-            float v = acc[r] + (bias ? bias[n] : 0.f);
-            float* o = out + (size_t)m * ldo + n;
-            *o = accumulate ? *o + v : v;
-        }
-    }
-}
-void launch_f32_linear(const float* X, const float* W, const float* bias, float* out, int M, int N, int K, int ldx, int ldo,
-                       int accumulate, hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_linear, dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, s, X, W, bias, out, M, N, K, ldx,
-                       ldo, accumulate);
-}
-
-// ------------------------------------------------------------------------------------------
-// Rotary embedding of q and k at the row's position (half-split pairs), tree K/V rows to the scratch.
-// qkv [M][3d]; q [M][d]; kt, vt [M][d]; one thread per (row, head, pair index i < hd/2).
-__global__ void k_f32_rope_kv(const float* __restrict__ qkv, RowTable rt, float* __restrict__ q, float* __restrict__ kt,
-                              float* __restrict__ vt, int M, int nh, int hd) {
-    const int half = hd / 2, d = nh * hd;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)M * nh * half) return;
-    const int i = (int)(idx % half), h = (int)((idx / half) % nh), m = (int)(idx / ((size_t)half * nh));
-    const float2 cs = rt.cs[(size_t)m * half + i];
-    const float* row = qkv + (size_t)m * 3 * d;
-    const int c = h * hd + i;
-    const float q1 = row[c], q2 = row[c + half], k1 = row[d + c], k2 = row[d + c + half];
-    q[(size_t)m * d + c] = q1 * cs.x - q2 * cs.y;
-    q[(size_t)m * d + c + half] = q2 * cs.x + q1 * cs.y;
-    kt[(size_t)m * d + c] = k1 * cs.x - k2 * cs.y;
-    kt[(size_t)m * d + c + half] = k2 * cs.x + k1 * cs.y;
-    vt[(size_t)m * d + c] = row[2 * d + c];
-    vt[(size_t)m * d + c + half] = row[2 * d + c + half];
-}
-void launch_f32_rope_kv(const float* qkv, RowTable rt, float* q, float* kt, float* vt, int M, int nh, int hd, hipStream_t s) {
-    const size_t total = (size_t)M * nh * (hd / 2);
-    hipLaunchKernelGGL(k_f32_rope_kv, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, qkv, rt, q, kt, vt, M, nh, hd);
-}
-
-// ------------------------------------------------------------------------------------------
-// Tree-masked attention of one (sequence, head, tree row): softmax over the committed rows 0..n-1 and the tree rows
-// in the row's ancestor set, in chunks of 256 keys with a running maximum. 128 threads: each computes the scores of
-// two keys of a chunk, then thread e accumulates output dim e.
-#define F32A_CHUNK 256
-__global__ __launch_bounds__(128) void k_f32_attn(const float* __restrict__ q, const float* __restrict__ kc,
+// Tree-masked attention of one (sequence, head, row): softmax over the committed rows 0 .. n-1 and the tree rows in the
+// row's ancestor set. The keys are dealt to the four waves in chunks of 64, one key per lane for the scores, one or two
+// output dims per lane for the values, running maximum per wave; the waves merge through LDS.
+template <int HD>
+__global__ __launch_bounds__(256) void k_f32_attn(const float* __restrict__ q, const float* __restrict__ kc,
                                                   const float* __restrict__ vc, const float* __restrict__ kt,
                                                   const float* __restrict__ vt, const int32_t* __restrict__ kv_len,
-                                                  const uint32_t* __restrict__ anc, float* __restrict__ out, int nh,
-                                                  int hd, int Tp, int cap, float scale) {
-    const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z, m = b * Tp + t, d = nh * hd, tid = threadIdx.x;
-    const int n = kv_len[b], total = n + Tp;
-    const float* qr = q + (size_t)m * d + h * hd;
-    const float* kcb = kc + (size_t)b * cap * d + h * hd;
-    const float* vcb = vc + (size_t)b * cap * d + h * hd;
-    const float* ktb = kt + (size_t)b * Tp * d + h * hd;
-    const float* vtb = vt + (size_t)b * Tp * d + h * hd;
-    const uint32_t* am = anc + (size_t)m * SD_ANC_WORDS;
-    __shared__ float p[F32A_CHUNK], qs[128], red[2];
-    if (tid < hd) qs[tid] = qr[tid];
+                                                  const uint32_t* __restrict__ anc, float* __restrict__ out, RowRef rr, int nh,
+                                                  int Tp, int cap, float scale) {
+    constexpr int ND = HD / 64;         // output dims per lane
+    const int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z, d = nh * HD, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int len = rr.len(b);
+    if (t >= len) return;
+    const int row0 = rr.off(b), m = row0 + t, sq = rr.seq(b), n = kv_len[sq], total = n + len;
+    __shared__ __attribute__((aligned(16))) float qs[HD];
+    __shared__ float mo[4][HD], ml[4][2];
+    if (tid < HD) qs[tid] = q[(size_t)m * d + h * HD + tid];
     __syncthreads();
-    float mrun = -__builtin_inff(), lrun = 0.f, o = 0.f;
-    for (int c0 = 0; c0 < total; c0 += F32A_CHUNK) {
-        float sc[2];
+    const float* kcb = kc + (size_t)sq * cap * d + h * HD;
+    const float* vcb = vc + (size_t)sq * cap * d + h * HD;
+    const float* ktb = kt + (size_t)row0 * d + h * HD;
+    const float* vtb = vt + (size_t)row0 * d + h * HD;
+    const uint32_t* am = anc + ((size_t)b * Tp + t) * SD_ANC_WORDS;
+    const float NINF = -__builtin_inff();
+    float mrun = NINF, lrun = 0.f, o[ND];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int i = c0 + tid + 128 * u;
-            bool vis = i < n;
-            const float* kr = kcb + (size_t)i * d;
-            if (i >= n && i < total) {
-                const int j = i - n;
-                vis = (am[j >> 5] >> (j & 31)) & 1u;
-                kr = ktb + (size_t)j * d;
-            }
-            float s = -__builtin_inff();
-            if (vis) {
-                s = 0.f;
-                for (int e = 0; e < hd; ++e) s = fmaf(qs[e], kr[e], s);
-                s *= scale;
-            }
-            sc[u] = s;
+    for (int e = 0; e < ND; ++e) o[e] = 0.f;
+    for (int c0 = wave * 64; c0 < total; c0 += 256) {
+        const int i = c0 + lane;
+        bool vis = i < n;
+        const float* kr = kcb + (size_t)min(i, max(n - 1, 0)) * d;
+        if (i >= n) {
+            const int j = min(i - n, len - 1);
+            vis = i < total && ((am[j >> 5] >> (j & 31)) & 1u);
+            kr = ktb + (size_t)j * d;
         }
-        float mx = fmaxf(sc[0], sc[1]);
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < HD; e += 4) {
+            const f32x4 k4 = *(const f32x4*)(kr + e), q4 = *(const f32x4*)(qs + e);
+            s = fmaf(q4[0], k4[0], s); s = fmaf(q4[1], k4[1], s); s = fmaf(q4[2], k4[2], s); s = fmaf(q4[3], k4[3], s);
+        }
+        s = vis ? s * scale : NINF;
+        float mx = s;
         for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-        if ((tid & 63) == 0) red[tid >> 6] = mx;
-        __syncthreads();
-        mx = fmaxf(red[0], red[1]);
         const float mnew = fmaxf(mrun, mx);
-        __syncthreads();                                   // red is reused below
-        if (mnew == -__builtin_inff()) continue;           // nothing visible so far (uniform over the workgroup)
-        const float alpha = mrun == -__builtin_inff() ? 0.f : __expf(mrun - mnew);
-        float ps = 0.f;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float e = sc[u] == -__builtin_inff() ? 0.f : __expf(sc[u] - mnew);
-            p[tid + 128 * u] = e;
-            ps += e;
-        }
+        if (mnew == NINF) continue;                        // nothing visible so far (uniform over the wave)
+        const float alpha = mrun == NINF ? 0.f : __expf(mrun - mnew);
+        const float p = s == NINF ? 0.f : __expf(s - mnew);
+        float ps = p;
         for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-        if ((tid & 63) == 0) red[tid >> 6] = ps;
-        __syncthreads();
-        lrun = lrun * alpha + red[0] + red[1];
-        o *= alpha;
-        if (tid < hd) {
-            const int lim = min(F32A_CHUNK, total - c0);
-            for (int jj = 0; jj < lim; ++jj) {
-                const float w = p[jj];
-                if (w != 0.f) {
-                    const int i = c0 + jj;
-                    const float* vr = i < n ? vcb + (size_t)i * d : vtb + (size_t)(i - n) * d;
-                    o = fmaf(w, vr[tid], o);
-                }
+        lrun = lrun * alpha + ps;
+        mrun = mnew;
+#pragma unroll
+        for (int e = 0; e < ND; ++e) o[e] *= alpha;
+        for (int j0 = 0; j0 < min(64, total - c0); j0 += 16) {
+            float x[16][ND];                               // sixteen keys' values requested before the first is used
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {                 // (past the end: the last key again, weight 0)
+                const int k = min(c0 + j0 + j, total - 1);
+                const float* vr = k < n ? vcb + (size_t)k * d : vtb + (size_t)(k - n) * d;
+#pragma unroll
+                for (int e = 0; e < ND; ++e) x[j][e] = vr[lane + 64 * e];
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), j0 + j));
+#pragma unroll
+                for (int e = 0; e < ND; ++e)               // (what is not visible never counts, not even as 0 x NaN)
+                    o[e] = fmaf(w, w != 0.f ? x[j][e] : 0.f, o[e]);
             }
         }
-        mrun = mnew;
-        __syncthreads();                                   // p and red are rewritten by the next chunk
     }
-    if (tid < hd) out[(size_t)m * d + h * hd + tid] = lrun > 0.f ? o / lrun : 0.f;
+#pragma unroll
+    for (int e = 0; e < ND; ++e) mo[wave][lane + 64 * e] = o[e];
+    if (lane == 0) { ml[wave][0] = mrun; ml[wave][1] = lrun; }
+    __syncthreads();
+    if (tid < HD) {
+        float M = NINF, L = 0.f, v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) M = fmaxf(M, ml[w][0]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = ml[w][0] == NINF ? 0.f : __expf(ml[w][0] - M);
+            L += f * ml[w][1];
+            v += f * mo[w][tid];
+        }
+        out[(size_t)m * d + h * HD + tid] = L > 0.f ? v / L : 0.f;
+    }
 }
 void launch_f32_attn(const float* q, const float* kc, const float* vc, const float* kt, const float* vt,
-                     const int32_t* kv_len, const uint32_t* anc, float* out, int B, int nh, int hd, int Tp, int cap,
-                     hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_attn, dim3(Tp, nh, B), dim3(128), 0, s, q, kc, vc, kt, vt, kv_len, anc, out, nh, hd, Tp, cap,
-                       1.f / sqrtf((float)hd));
+                     const int32_t* kv_len, const uint32_t* anc, float* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
+                     int cap, hipStream_t s) {
+    const dim3 grid(longest, nh, B);
+    const float scale = 1.f / sqrtf((float)hd);
+    if (hd == 128)
+        hipLaunchKernelGGL(k_f32_attn<128>, grid, dim3(256), 0, s, q, kc, vc, kt, vt, kv_len, anc, out, rr, nh, Tp, cap, scale);
+    else
+        hipLaunchKernelGGL(k_f32_attn<64>, grid, dim3(256), 0, s, q, kc, vc, kt, vt, kv_len, anc, out, rr, nh, Tp, cap, scale);
 }
 
 // ------------------------------------------------------------------------------------------
-// act[m][f] = silu(gu[m][f]) * gu[m][F + f]
-__global__ void k_f32_swiglu(const float* __restrict__ gu, float* __restrict__ act, int M, int F) {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)M * F) return;
-    const int f = (int)(idx % F), m = (int)(idx / F);
-    const float g = gu[(size_t)m * 2 * F + f], u = gu[(size_t)m * 2 * F + F + f];
-    act[idx] = g / (1.f + __expf(-g)) * u;
-}
-void launch_f32_swiglu(const float* gu, float* act, int M, int F, hipStream_t s) {
-    const size_t total = (size_t)M * F;
-    hipLaunchKernelGGL(k_f32_swiglu, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, gu, act, M, F);
-}
-
-// ------------------------------------------------------------------------------------------
-// Draft heads: row (i, b) = h_b + silu(z[b][i*d ..]) (z already holds W_i h_b + bias_i)
-__global__ void k_f32_medusa_act(const float* __restrict__ z, const float* __restrict__ h, float* __restrict__ out, int B,
-                                 int H, int d) {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)H * B * d) return;
-    const int c = (int)(idx % d), b = (int)((idx / d) % B), i = (int)(idx / ((size_t)d * B));
-    const float zz = z[(size_t)b * H * d + (size_t)i * d + c];
-    out[idx] = h[(size_t)b * d + c] + zz / (1.f + __expf(-zz));
-}
-void launch_f32_medusa_act(const float* z, const float* h, float* out, int B, int H, int d, hipStream_t s) {
-    const size_t total = (size_t)H * B * d;
-    hipLaunchKernelGGL(k_f32_medusa_act, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, z, h, out, B, H, d);
-}
-
-// ------------------------------------------------------------------------------------------
-// Commit: tree row src_slots[b][j] -> cache row n_old[b] + j for j < n_accept[b], every layer, K and V.
-// grid (row j, layer * B + b), 256 threads over the d columns.
+// Commit: row src_slots[list][j] of pass sequence i -> cache row n_old[list] + j of sequence rm.seq[i], for j < n_accept[list],
+// list = rm.off[i], every layer, K and V. The sequence's rows start at scratch row rm.len[i]; slots past the scratch's last
+// row are clamped. grid (row j, layer * B + i), 256 threads over the d columns.
 __global__ void k_f32_kv_commit(const float* __restrict__ kt, const float* __restrict__ vt, float* __restrict__ kc,
                                 float* __restrict__ vc, const int32_t* __restrict__ src_slots,
-                                const int32_t* __restrict__ n_accept, const int32_t* __restrict__ n_old, int B, int d,
-                                int Tp, int cap, int W, size_t layer_stride_t, size_t layer_stride_c) {
-    const int j = blockIdx.x, l = blockIdx.y / B, b = blockIdx.y % B;
-    if (j >= min(n_accept[b], W)) return;
-    const int src = min(max(src_slots[(size_t)b * W + j], 0), Tp - 1), dst = n_old[b] + j;
-    const size_t so = l * layer_stride_t + ((size_t)b * Tp + src) * d, dofs = l * layer_stride_c + ((size_t)b * cap + dst) * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) {
-        kc[dofs + c] = kt[so + c];
-        vc[dofs + c] = vt[so + c];
+                                const int32_t* __restrict__ n_accept, const int32_t* __restrict__ n_old, RowMap rm, int B, int d,
+                                int rows, int cap, int W, size_t layer_stride_t, size_t layer_stride_c) {
+    const int j = blockIdx.x, l = blockIdx.y / B, i = blockIdx.y % B, lst = rm.off[i];
+    if (j >= min(n_accept[lst], W)) return;
+    const int src = min(rm.len[i] + max(src_slots[(size_t)lst * W + j], 0), rows - 1), dst = n_old[lst] + j;
+    const size_t so = l * layer_stride_t + (size_t)src * d, dofs = l * layer_stride_c + ((size_t)rm.seq[i] * cap + dst) * d;
+    for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
+        *(f32x4*)(kc + dofs + c) = *(const f32x4*)(kt + so + c);
+        *(f32x4*)(vc + dofs + c) = *(const f32x4*)(vt + so + c);
     }
 }
 void launch_f32_kv_commit(const float* kt, const float* vt, float* kc, float* vc, const int32_t* src_slots,
-                          const int32_t* n_accept, const int32_t* n_old, int L, int B, int d, int Tp, int cap, int W,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_kv_commit, dim3(W, L * B), dim3(256), 0, s, kt, vt, kc, vc, src_slots, n_accept, n_old, B, d, Tp,
-                       cap, W, (size_t)B * Tp * d, (size_t)B * cap * d);
+                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B, int L, int B, int d, int rows,
+                          int cap, int W, hipStream_t s) {
+    hipLaunchKernelGGL(k_f32_kv_commit, dim3(W, L * B), dim3(64), 0, s, kt, vt, kc, vc, src_slots, n_accept, n_old, rm, B, d, rows,
+                       cap, W, (size_t)rows * d, (size_t)kv_B * cap * d);
 }
 
 // natural-layout rows [nrows][d] <-> cache rows of one sequence and layer

@@ -234,19 +234,24 @@ void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs
                              int B, int Tp, int hd, const double* freq, const void* embed, int embed_f32, int d, int V,
                              float* x, hipStream_t s);
 // float32 device path (f32.hip): natural row-major layouts, vector-ALU arithmetic
-void launch_f32_rmsnorm(const float* x, const float* gain, float eps, float* y, int M, int d, const int32_t* gather,
+// out = norm(X[gather]) W^T (gain NULL: no norm); x += X W^T
+void launch_f32_norm_linear(const float* X, const int32_t* gather, const float* gain, float eps, const float* W, float* out, int M,
+                            int N, int K, int ldo, hipStream_t s);
+void launch_f32_add_linear(const float* X, const float* W, float* x, int M, int N, int K, hipStream_t s);
+// norm, QKV projection, rotary embedding: q [M][d], keys and values to the tree scratch
+void launch_f32_qkv(const float* X, const float* gain, float eps, const float* W, RowTable rt, float* q, float* kt, float* vt, int M,
+                    int nh, int hd, hipStream_t s);
+void launch_f32_gate_up(const float* X, const float* gain, float eps, const float* W, float* act, int M, int F, int d,
                         hipStream_t s);
-void launch_f32_linear(const float* X, const float* W, const float* bias, float* out, int M, int N, int K, int ldx, int ldo,
-                       int accumulate, hipStream_t s);
-void launch_f32_rope_kv(const float* qkv, RowTable rt, float* q, float* kt, float* vt, int M, int nh, int hd, hipStream_t s);
+// out row i * B + b = h_b + silu(W_i h_b + bias_i), h_b = norm(X[gather[b]])
+void launch_f32_heads(const float* X, const int32_t* gather, const float* gain, float eps, const float* W, const float* bias,
+                      float* out, int B, int H, int d, hipStream_t s);
 void launch_f32_attn(const float* q, const float* kc, const float* vc, const float* kt, const float* vt,
-                     const int32_t* kv_len, const uint32_t* anc, float* out, int B, int nh, int hd, int Tp, int cap,
-                     hipStream_t s);
-void launch_f32_swiglu(const float* gu, float* act, int M, int F, hipStream_t s);
-void launch_f32_medusa_act(const float* z, const float* h, float* out, int B, int H, int d, hipStream_t s);
+                     const int32_t* kv_len, const uint32_t* anc, float* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
+                     int cap, hipStream_t s);
 void launch_f32_kv_commit(const float* kt, const float* vt, float* kc, float* vc, const int32_t* src_slots,
-                          const int32_t* n_accept, const int32_t* n_old, int L, int B, int d, int Tp, int cap, int W,
-                          hipStream_t s);
+                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B, int L, int B, int d, int rows,
+                          int cap, int W, hipStream_t s);
 void launch_f32_kv_rows(float* kc, float* vc, float* k_rows, float* v_rows, int row0, int nrows, int d, int to_cache,
                         hipStream_t s);
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out,
