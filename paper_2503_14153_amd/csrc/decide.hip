@@ -274,10 +274,11 @@ void launch_row_stats(const float* logits, int ld, int V, float4* stats, int B, 
 // ------------------------------------------------------------------------------------------
 // Sampling decoding, the next root: the smallest token id whose cumulative probability under
 // softmax(logits[last_row] / temperature) exceeds u. One workgroup of 16 waves per sequence.
-// Wave w owns the contiguous ids [w*S, (w+1)*S) and sums their weights exp((l - max)/temp) with
-// coalesced loads; the wave whose segment holds the target u * total then walks it 64 ids at a
-// time with a wave-wide inclusive scan. Sums are in fp64, so the draw only differs from an
-// exact one when u lies within fp32 rounding of the weights of a boundary of the CDF.
+// Wave w owns the contiguous ids [w*S, (w+1)*S), lane l of group j the id w*S + 64 j + l, read once into registers for the
+// maximum and the weights exp((l - max)/temp). The wave whose segment holds the target u * total leaves its weights in
+// LDS, where every lane sums a whole group of 64 in id order; one scan over the groups and one inside the group found
+// give the id. (Walking the segment group by group, a scan each, took 22 us at 32 k ids; this form 8.) Sums are in fp64,
+// so the draw only differs from an exact one when u lies within fp32 rounding of the weights of a boundary of the CDF.
 static __device__ inline double wave_incl_scan_f64(double v, int lane) {
     for (int o = 1; o < 64; o <<= 1) {
         double t = __shfl_up(v, o);
@@ -285,6 +286,7 @@ static __device__ inline double wave_incl_scan_f64(double v, int lane) {
     }
     return v;
 }
+template <int NPT>                                     // groups of a wave, at most
 __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restrict__ logits, int ld, int V,
                                                             const int32_t* __restrict__ last_row,
                                                             const float* __restrict__ u, float inv_temperature,
@@ -299,26 +301,36 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
     const float* row = logits + (size_t)r * ld;
     __shared__ float smax[NW];
     __shared__ double wsum[NW];
+    __shared__ float ws[NPT * 65];                     // one wave's weights, [group][64 + 1]
+    const int S = ((V + NW - 1) / NW + 63) & ~63;      // segment length, a multiple of the wave size
+    const int s0 = min(wave * S, V), s1 = min(s0 + S, V);
+    float v[NPT];
     float mx = NEG_INF;
-#pragma unroll 4
-    for (int c = tid; c < V; c += RS_THREADS) mx = fmaxf(mx, row[c]);
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const int c = s0 + j * 64 + lane;
+        v[j] = c < s1 ? row[c] : NEG_INF;
+        mx = fmaxf(mx, v[j]);
+    }
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if (lane == 0) smax[wave] = mx;
     __syncthreads();
     mx = smax[0];
     for (int w = 1; w < NW; ++w) mx = fmaxf(mx, smax[w]);
-    const int S = ((V + NW - 1) / NW + 63) & ~63;      // segment length, a multiple of the wave size
-    const int s0 = min(wave * S, V), s1 = min(s0 + S, V);
     double part = 0.0;
-#pragma unroll 4
-    for (int c = s0 + lane; c < s1; c += 64) part += (double)__expf((row[c] - mx) * inv_temperature);
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const float e = s0 + j * 64 + lane < s1 ? __expf((v[j] - mx) * inv_temperature) : 0.f;
+        v[j] = e;
+        part += (double)e;
+    }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
     if (lane == 0) wsum[wave] = part;
     __syncthreads();
     double total = 0.0;
     for (int w = 0; w < NW; ++w) total += wsum[w];
     const double target = (double)u[b] * total;
-    // the segment that holds the target; if rounding leaves none, the last one that has any mass, walked to its end
+    // the segment that holds the target; if rounding leaves none, the last one that has any mass, taken to its end
     int seg = -1, last_mass = 0;
     double base = 0.0, acc = 0.0;
     for (int w = 0; w < NW; ++w) {
@@ -328,16 +340,33 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
     }
     const bool to_end = seg < 0;
     if (to_end) seg = last_mass;
-    if (wave != seg) return;
-    int pick = -1, last_pos = s0;
-    for (int c0 = s0; c0 < s1 && pick < 0; c0 += 64) {
-        const int c = c0 + lane;
-        const double e = c < s1 ? (double)__expf((row[c] - mx) * inv_temperature) : 0.0;
-        const double cum = base + wave_incl_scan_f64(e, lane);
-        const unsigned long long pos = __ballot(e > 0.0);
-        if (pos) last_pos = c0 + 63 - __builtin_clzll(pos);
-        const unsigned long long hit = __ballot(!to_end && cum > target);
-        if (hit) pick = c0 + __builtin_ctzll(hit);
+    if (wave != seg) return;                           // (the rest is this wave's alone: no barrier follows)
+    int last_pos = s0;                                 // the last id with mass
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        ws[j * 65 + lane] = v[j];
+        const unsigned long long pos = __ballot(v[j] > 0.f);
+        if (pos) last_pos = s0 + j * 64 + 63 - __builtin_clzll(pos);
+    }
+    __builtin_amdgcn_wave_barrier();
+    int pick = -1;
+    const int groups = (s1 - s0 + 63) / 64;
+    for (int g0 = 0; g0 < groups && pick < 0 && !to_end; g0 += 64) {
+        double gsum = 0.0;
+        if (g0 + lane < groups)
+#pragma unroll 16
+            for (int i = 0; i < 64; ++i) gsum += (double)ws[(g0 + lane) * 65 + i];
+        const double cum = base + wave_incl_scan_f64(gsum, lane);
+        const unsigned long long hit = __ballot(g0 + lane < groups && cum > target);
+        if (hit) {
+            const int gl = __builtin_ctzll(hit), g = g0 + gl;
+            const double before = gl ? __shfl(cum, gl - 1) : base;
+            const double e = (double)ws[g * 65 + lane];
+            const unsigned long long in = __ballot(before + wave_incl_scan_f64(e, lane) > target);
+            const unsigned long long mass = __ballot(e > 0.0);
+            // (the two sums of a group may differ in the last bit: then its last id with mass)
+            pick = s0 + g * 64 + (in ? __builtin_ctzll(in) : 63 - __builtin_clzll(mass));
+        }
         base = __shfl(cum, 63);
     }
     if (lane == 0) root_tok[b] = pick >= 0 ? pick : last_pos;
@@ -345,8 +374,15 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
 
 void launch_sample_root(const float* logits, int ld, int V, const int32_t* last_row, const float* u,
                         float inv_temperature, int32_t* root_tok, int B, int n_rows, hipStream_t s) {
-    hipLaunchKernelGGL(k_sample_root, dim3(B), dim3(RS_THREADS), 0, s, logits, ld, V, last_row, u, inv_temperature,
-                       root_tok, n_rows);
+    const int npt = (((V + RS_THREADS / 64 - 1) / (RS_THREADS / 64) + 63) & ~63) / 64;
+#define SR(N) hipLaunchKernelGGL((k_sample_root<N>), dim3(B), dim3(RS_THREADS), 0, s, logits, ld, V, last_row, u, inv_temperature, \
+                                 root_tok, n_rows)
+    if (npt <= 4) SR(4);
+    else if (npt <= 16) SR(16);
+    else if (npt <= 32) SR(32);
+    else if (npt <= 64) SR(64);
+    else SR(160);                                      // 163840 ids
+#undef SR
 }
 
 // ------------------------------------------------------------------------------------------
@@ -482,6 +518,7 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 //     neighbouring rows is 16 bytes further on, so eight lanes write 128 contiguous bytes).
 // Every piece has one owner, and only this workgroup touches this layer's blocks of its (sequence, head).
 #define KVC_THREADS 512
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 static __device__ inline int vgroup_of(int c) { return (c >> 5) * 4 + ((c >> 4) & 1) * 2 + ((c >> 2) & 1); }
 __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const uint16_t* __restrict__ kt, const uint16_t* __restrict__ vt, uint16_t* __restrict__ kc,
@@ -509,7 +546,6 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const size_t toff0 = ((size_t)b * nh + h) * TB * (32 * hd);
     const size_t coff0 = ((size_t)rm.seq[b] * nh + h) * cap_blocks * (32 * hd);
     const int EB = hd / 32, KP = hd / 64;                  // wave tasks per 16-row half (values), per 8 rows (keys)
-    typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const uint32_t need = s_need;
     const int half0 = n >> 4, nV = (((n + a - 1) >> 4) - half0 + 1) * EB;
@@ -584,26 +620,89 @@ void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void
 }
 
 // ------------------------------------------------------------------------------------------
-// Natural-layout rows [nrows][nh][hd] <-> one sequence's cache blocks of one layer.
-__global__ void k_kv_rows(uint16_t* __restrict__ kc, uint16_t* __restrict__ vc, uint16_t* __restrict__ k_rows,
-                          uint16_t* __restrict__ v_rows, int row0, int nh, int hd, int cap_blocks, int to_cache) {
-    const int r = blockIdx.x, h = blockIdx.y, e = threadIdx.x;
-    const size_t nat = ((size_t)r * nh + h) * hd + e;
-    const size_t hoff = (size_t)h * cap_blocks * (32 * hd);
-    const size_t ki = hoff + kblk_index(row0 + r, e, hd), vi = hoff + vblk_index(row0 + r, e, hd);
-    if (to_cache) {
-        kc[ki] = k_rows[nat];
-        vc[vi] = v_rows[nat];
-    } else {
-        k_rows[nat] = kc[ki];
-        v_rows[nat] = vc[vi];
+// Natural-layout rows [nrows][nh][hd] <-> one sequence's cache blocks of one layer: bytes moved once, so a workgroup owns
+// one 32-row block of one head and everything moves in 16-byte pieces. Keys keep their pieces (a row's eight dims), eight
+// lanes on neighbouring rows, so that both sides are whole 128-byte runs; a value piece holds one dim of eight rows, so
+// the block is turned through LDS, and a piece some of whose rows are not asked for is read, patched and written back
+// by its one owner. (One thread per element and two-byte accesses took 17.8 us for 1003 rows at the 7B shape, 1.8 TB/s;
+// this form 8 us.) VEC: the caller's arrays are 16-byte aligned; else they are read and written by elements.
+template <bool VEC>
+static __device__ __forceinline__ u16x8 load_piece(const uint16_t* p) {
+    if constexpr (VEC) return *(const u16x8*)p;
+    u16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = p[i];
+    return v;
+}
+template <bool VEC>
+static __device__ __forceinline__ void store_piece(uint16_t* p, const u16x8& v) {
+    if constexpr (VEC) { *(u16x8*)p = v; return; }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = v[i];
+}
+template <int HD, bool TO_CACHE, bool VEC>
+__global__ __launch_bounds__(256) void k_kv_rows(uint16_t* __restrict__ kc, uint16_t* __restrict__ vc, uint16_t* __restrict__ k_rows,
+                                                 uint16_t* __restrict__ v_rows, int row0, int nrows, int nh, int cap_blocks) {
+    constexpr int PC = HD / 8;                         // pieces of a row
+    __shared__ __attribute__((aligned(16))) uint16_t tile[32][HD + 8];
+    const int blk = (row0 >> 5) + blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    const size_t hoff = (size_t)h * cap_blocks * (32 * HD);
+    const int first = blk * 32 - row0;                 // natural row of the block's row 0 (negative: before the range)
+    auto nat = [&](int r) { return ((size_t)(first + r) * nh + h) * HD; };
+    auto asked = [&](int r) { return first + r >= 0 && first + r < nrows; };
+    if constexpr (TO_CACHE) {                          // values of the rows asked for -> LDS
+        for (int i = tid; i < 32 * PC; i += 256) {
+            const int r = i / PC, e = (i % PC) * 8;
+            if (asked(r)) *(u16x8*)&tile[r][e] = load_piece<VEC>(v_rows + nat(r) + e);
+        }
+    }
+    for (int i = tid; i < 32 * PC; i += 256) {         // keys: eight rows x eight pieces per wave
+        const int r = ((i >> 6) & 3) * 8 + (i & 7), e = ((i >> 8) * 8 + ((i >> 3) & 7)) * 8;
+        if (!asked(r)) continue;
+        uint16_t* c = kc + hoff + kblk_index(blk * 32 + r, e, HD);
+        if constexpr (TO_CACHE) *(u16x8*)c = load_piece<VEC>(k_rows + nat(r) + e);
+        else store_piece<VEC>(k_rows + nat(r) + e, *(const u16x8*)c);
+    }
+    if constexpr (TO_CACHE) __syncthreads();
+    for (int i = tid; i < 32 * PC; i += 256) {         // value pieces in cache order: half, 32-dim block, quad, dim
+        const int er = i & 31, g = (i >> 5) & 1, eb = (i >> 6) % (HD / 32), p = (i >> 6) / (HD / 32), e = eb * 32 + er;
+        const int r0 = p * 16 + g * 4;                 // the piece's rows: r0 + {0..3, 8..11}
+        uint16_t* c = vc + hoff + vblk_index(blk * 32 + r0, e, HD);
+        bool any = false, all = true;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) { const bool a = asked(r0 + (q >> 2) * 8 + (q & 3)); any |= a; all &= a; }
+        if (!any) continue;
+        u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (!TO_CACHE || !all) v = *(const u16x8*)c;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int r = r0 + (q >> 2) * 8 + (q & 3);
+            if constexpr (TO_CACHE) { if (asked(r)) v[q] = tile[r][e]; }
+            else tile[r][e] = v[q];
+        }
+        if constexpr (TO_CACHE) *(u16x8*)c = v;
+    }
+    if constexpr (!TO_CACHE) {
+        __syncthreads();
+        for (int i = tid; i < 32 * PC; i += 256) {
+            const int r = i / PC, e = (i % PC) * 8;
+            if (asked(r)) store_piece<VEC>(v_rows + nat(r) + e, *(const u16x8*)&tile[r][e]);
+        }
     }
 }
 
 void launch_kv_rows(void* kc, void* vc, void* k_rows, void* v_rows, int row0, int nrows, int nh, int hd,
                     int cap_blocks, int to_cache, hipStream_t s) {
-    hipLaunchKernelGGL(k_kv_rows, dim3(nrows, nh), dim3(hd), 0, s, (uint16_t*)kc, (uint16_t*)vc, (uint16_t*)k_rows,
-                       (uint16_t*)v_rows, row0, nh, hd, cap_blocks, to_cache);
+    const dim3 grid((row0 + nrows - 1) / 32 - row0 / 32 + 1, nh);
+    const bool vec = ((((uintptr_t)k_rows) | ((uintptr_t)v_rows)) & 15) == 0;
+#define KV_ROWS(HD_, TO_, VEC_)                                                                                        \
+    hipLaunchKernelGGL((k_kv_rows<HD_, TO_, VEC_>), grid, dim3(256), 0, s, (uint16_t*)kc, (uint16_t*)vc,              \
+                       (uint16_t*)k_rows, (uint16_t*)v_rows, row0, nrows, nh, cap_blocks)
+#define KV_ROWS2(HD_, TO_) do { if (vec) KV_ROWS(HD_, TO_, true); else KV_ROWS(HD_, TO_, false); } while (0)
+    if (hd == 128) { if (to_cache) KV_ROWS2(128, true); else KV_ROWS2(128, false); }
+    else           { if (to_cache) KV_ROWS2(64, true);  else KV_ROWS2(64, false); }
+#undef KV_ROWS2
+#undef KV_ROWS
 }
 
 // ------------------------------------------------------------------------------------------
