@@ -846,7 +846,13 @@ static bool have_plans(const sd_model* m, int M, int B, bool heads, bool all_row
 // builds the tree's keys and values itself (one query group of two blocks: split_ok), one per tree block, so that the
 // building is shared by two workgroups.
 struct AttnGeom { int ncparts, per, tree_sep, nparts; };
-static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool split_ok = false) {
+// ragged: the sequences' lengths (host's bounds) add up to less than four fifths of B times the longest.
+static bool ragged_lengths(const sd_kv* kv, const int32_t* seq, int B, int n_hi) {
+    long long sum = 0;
+    for (int i = 0; i < B; ++i) sum += kv->len_hi[seq ? seq[i] : i];
+    return sum * 5 < 4ll * n_hi * B;
+}
+static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool split_ok = false, bool ragged = false) {
     const int nblk = ceil_div(n_hi, 32);
     const int TB = Tp / 32, TG = (TB % 2 == 0) ? TB / 2 : TB;
     const int groups = B * m->cfg.n_heads * TG;
@@ -855,6 +861,17 @@ static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool s
     if (P > m->max_parts) P = m->max_parts;
     AttnGeom g;
     if (nblk == 0) { g.ncparts = 0; g.per = 1; g.tree_sep = 1; g.nparts = 1; return g; }
+    // A batch with one workgroup per (sequence, head) lasts as long as its longest sequence: when the lengths are ragged,
+    // two parts that share every sequence's own blocks evenly (per = 0). Launch at eight 7B-shaped sequences of 1024 - 4096
+    // rows: plain decoding 88 -> 78 us, 32-node trees 88 -> 82; one of 4096 beside seven of 32 rows 56 -> 36; but eight of
+    // 2560 rows 74.6 -> 77.6, so not where they are alike. (Three and four parts 85 and 95 us: one workgroup of this
+    // kernel fits a compute unit, and held to 128 registers, so that two fit, it spills: 107 us.)
+    if (P == 1 && TB == 1 && ragged && nblk >= 8) {
+        g.tree_sep = 0;
+        g.ncparts = g.nparts = 2;
+        g.per = 0;
+        return g;
+    }
     const int by_work = ceil_div(nblk, 4);                 // at least one block per wave
     const int ntp = (split_ok && TB == 2 && P >= 3) ? 2 : 1;
     // The tree keeps parts of its own while the cache parts are short: up to eight blocks per cache part, or, when a
@@ -881,7 +898,7 @@ static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool s
 static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, hipStream_t s) {
     const sd_config& c = m->cfg;
     const int MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
-    const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, /*split_ok=*/Tp == 64);   // (one query group of two blocks)
+    const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, /*split_ok=*/Tp == 64, ragged_lengths(kv, rm.seq, B, n_hi));
     PartView prev = {nullptr, 0, d, nullptr, 0};
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
     for (int l = 0; l < c.n_layers; ++l) {
@@ -898,8 +915,8 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         // (16 k rows: attention 55 -> 64 us): there the stage stays a launch of its own. Where every (sequence, head) has
         // ONE workgroup (a batch that fills the chip) all workgroups carry the same extra work, none is a straggler, and
         // the launch saved is worth more than it costs (batch of eight 32-node trees: attention 65.4 -> 72.8 us, the
-        // 11.8 us launch gone, step -0.8 %).
-        const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1);
+        // 11.8 us launch gone, step -0.8 %); so it is with the two even parts of a ragged batch, whose second takes the tree.
+        const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1 || ag.per == 0);
         if (!fr) launch_rope_kv(pq, m->rt, rr, m->q, kt, vt, B, Tp, nh, hd, s);
         // algorithmic bytes: one read of K and V of the committed rows (upper bound n_hi) + tree rows
         const int pa = prof_claim(m, PROF_ATTN, (double)B * (n_hi + Tp) * 2.0 * d * 2.0);
@@ -1295,7 +1312,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     };
 
     if (m->use_graphs && !m->prof.on && !ty) {
-        const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, Tp == 64);
+        const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, Tp == 64, ragged_lengths(kv, nullptr, B, n_hi));
         std::vector<uint64_t> key = {kv->uid, tree_uid, (uint64_t)(uintptr_t)parent, (uint64_t)T, (uint64_t)Tp,
                                      (uint64_t)ag.ncparts, (uint64_t)(ag.per * 4 + ag.tree_sep), (uint64_t)(uintptr_t)stop_mask,
                                      (uint64_t)(uintptr_t)n_accept, (uint64_t)(uintptr_t)tokens,

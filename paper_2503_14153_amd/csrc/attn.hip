@@ -66,7 +66,9 @@ template <int N> static __device__ __forceinline__ void wait_vm() { asm volatile
 // as blocks. One query group only (Tp = 32 * TBW). NS: the projection's slot count if the same everywhere, else 0.
 // MAP: the pass's row map is in device memory (prompt passes: rr.map); else every sequence has rr.R rows, one after the
 // other, and nothing is looked up before the first addresses are known.
-template <int HD, int TBW, int AW, int FR, int NS, bool MAP>
+// EVEN: every sequence's blocks are split evenly over its ncparts parts (ragged batches, see attn_geometry); else part p
+// starts at block p * per and its first blocks are requested before the length is known.
+template <int HD, int TBW, int AW, int FR, int NS, bool MAP, bool EVEN>
 __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp, const bf16x8* Kc, const bf16x8* Vc,
                                                    const bf16x8* Kt, const bf16x8* Vt, const int32_t* __restrict__ kv_len,
                                                    const uint32_t* __restrict__ anc, float* __restrict__ opart,
@@ -141,12 +143,21 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     }
 
     // The part's items: its tree blocks first, then its cache blocks; wave w owns items
-    // [w*share, (w+1)*share). Which of them exist depends on the sequence length, known later.
-    const int c0 = part * per;
-    const int total = ntree + (has_cache ? per : 0);
+    // [w*share, (w+1)*share). Which of them exist depends on the sequence length, known later; or (EVEN) the length is
+    // waited for here and this sequence's own blocks are what its parts share evenly.
+    const int sq = MAP ? rr.map->seq[b] : b;           // sequence of the cache
+    const int n = kv_len[sq];
+    const int nblk = (n + 31) >> 5;
+    int here = per;                                    // cache blocks of this part, at most
+    int c0 = part * per;
+    if constexpr (EVEN) {
+        const int each = max(1, (int)__umulhi((uint32_t)(nblk + ncparts - 1), (uint32_t)per));       // per = ceil(2^32 / ncparts)
+        c0 = part * each;
+        here = max(0, min(each, nblk - c0));
+    }
+    const int total = max(1, ntree + (has_cache ? here : 0));
     const int share = (total + 3) >> 2;
     const int jw = __builtin_amdgcn_readfirstlane(wave * share);
-    const int sq = MAP ? rr.map->seq[b] : b;                         // sequence of the cache
     const bf16x8* kcb = Kc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* vcb = Vc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* ktb = Kt + ((size_t)b * nh + h) * TB * BLK + lane;
@@ -154,11 +165,11 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // item -> block address, always inside the tree scratch or the cache allocation
     auto kaddr = [&](int j) -> const bf16x8* {
         j = min(j, total - 1);
-        return (j < ntree) ? ktb + (size_t)(tb0 + j) * BLK : kcb + (size_t)min(c0 + j - ntree, cap_blocks - 1) * BLK;
+        return (j < ntree) ? ktb + (size_t)(tb0 + j) * BLK : kcb + (size_t)max(0, min(c0 + j - ntree, cap_blocks - 1)) * BLK;
     };
     auto vaddr = [&](int j) -> const bf16x8* {
         j = min(j, total - 1);
-        return (j < ntree) ? vtb + (size_t)(tb0 + j) * BLK : vcb + (size_t)min(c0 + j - ntree, cap_blocks - 1) * BLK;
+        return (j < ntree) ? vtb + (size_t)(tb0 + j) * BLK : vcb + (size_t)max(0, min(c0 + j - ntree, cap_blocks - 1)) * BLK;
     };
     // FR: a workgroup whose items are tree blocks only (the tree has a part of its own) keeps the blocks it builds in
     // LDS too (in the area the final merge uses, which is idle until the loop is over) and reads its operands from
@@ -239,9 +250,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
         for (int i = 0; i < QW; ++i) lds_dma16(qsrc + (wave * QW + i) * 64, myq_addr + i * 1024);
     }
 
-    const int n = kv_len[sq];
-    const int nblk = (n + 31) >> 5;
-    const int ncache = has_cache ? max(0, min(per, nblk - c0)) : 0;
+    const int ncache = has_cache ? max(0, min(here, nblk - c0)) : 0;
     const int nit = __builtin_amdgcn_readfirstlane(max(0, min(share, ntree + ncache - jw)));       // this wave's items [jw, jw + nit)
 
     f32x16 O[TBW][EB];
@@ -450,6 +459,8 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     const int TB = Tp / 32;
     const int TBW = (TB % 2 == 0) ? 2 : 1;
     const int nparts = ncparts + tree_sep, TG = TB / TBW;     // tree_sep: number of parts with tree blocks only
+    const bool even = per == 0;                        // (one query block per sequence only, see attn_geometry)
+    if (even) per = (int)(uint32_t)((0x100000000ull + ncparts - 1) / ncparts);
     dim3 grid(nparts, nh * TG, B);
     int xcd_stride = 0;
     if (TG > 1) {                                      // query groups of one head on one XCD (see the kernel)
@@ -461,12 +472,17 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     }
 #define ATT_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (const bf16x8*)kt, (const bf16x8*)vt, \
                  kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg, rr
-#define ATT_M(HD_, TBW_, AW_, FR_, NS_, MAP_)                                                                    \
+#define ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_)                                                             \
     do {                                                                                                        \
         if (ev0 || ev1)                                                                                         \
-            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS); \
+            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS); \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_>), grid, dim3(256), 0, s, ATT_ARGS); \
+            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ATT_ARGS); \
+    } while (0)
+#define ATT_M(HD_, TBW_, AW_, FR_, NS_, MAP_)                                                                    \
+    do {                                                                                                        \
+        if (TBW_ == 1 && AW_ == 4 && even) ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, (TBW_ == 1 && AW_ == 4));       \
+        else ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, false);                                                       \
     } while (0)
 #define ATT(HD_, TBW_, AW_, FR_, NS_)                                                                            \
     do { if (rr.map) ATT_M(HD_, TBW_, AW_, FR_, NS_, true); else ATT_M(HD_, TBW_, AW_, FR_, NS_, false); } while (0)
@@ -487,6 +503,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 #undef ATT2
 #undef ATT
 #undef ATT_M
+#undef ATT_E
 #undef ATT_ARGS
 }
 
