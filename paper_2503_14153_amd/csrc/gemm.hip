@@ -68,8 +68,9 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int nb_offset,
 // Loads of one wave return in order, so an activation load queues behind the HBM loads issued
 // before it: chunks are therefore fetched one ring-length (R steps) ahead, by all threads, and
 // parked in registers until the chunk before them has been consumed.
+// (At most 128 registers, 94 in use: the next workgroup can start on a compute unit while this one ends.)
 template <int MT>
-__global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_gemm_sk(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
+__global__ __launch_bounds__(512, 4) void k_gemm_sk(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                     const bf16x8* __restrict__ zfrag, float* __restrict__ out,
                                                     int KB, int NB, int ldo, size_t slot_stride, int rows, int upw, int rem,
                                                     uint32_t kb_magic, const int32_t* __restrict__ slot0_tab) {

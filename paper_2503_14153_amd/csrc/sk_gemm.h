@@ -65,14 +65,17 @@ static __device__ inline SkIter sk_walk_next(SkWalk& w, int KB) {
 template <int MT>
 struct SkGemm {
     static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_sk_rows only");
-    // ring depth. Eight row blocks: the 128 accumulators leave two waves per SIMD room for a ring of
-    // 4 steps (210 registers), and a step then holds 16 MFMAs, so 4 steps cover the same time as 16 do
-    // with two row blocks (rings of 6 and 8 steps measured slower: 62.3 and 62.8 us against 59.8)
-    static constexpr int R = MT == 8 ? 4 : 16;
-    static constexpr int XK = 8 / MT;                // contraction blocks per chunk
+    // Ring depth R, and XK contraction blocks per activation chunk (a barrier each). A shallow ring: what a wave holds in
+    // flight when its stream ends is still to be multiplied then, and a workgroup's steps are padded to a multiple of R.
+    // Depth 16 (chunks of 8 / MT) kept more bytes in flight and was slower: down projection of the 7B shape (43 steps a
+    // workgroup) 25.6 -> 22.2 us at 64 rows and 20.8 -> 16.4 at 1 row, O 14.7 -> 13.6, QKV 26.6 -> 25.9; full step of the
+    // 64-node tree 4849 (16), 4768 (8), 4690 (4, chunks of 4), 4682 (6, chunks of 2), 4620 us (4, chunks of 2), 5405
+    // (2). With eight row blocks a step holds 16 MFMAs and rings of 6 and 8 measured slower too.
+    static constexpr int R = 4;
+    static constexpr int XK = MT == 8 ? 1 : 2;      // contraction blocks per chunk
     static constexpr int CPI = R / XK;               // chunks per outer iteration (2 or 4)
-    static constexpr int XF = 16;                    // fragments per chunk = XK * MT * 2
-    static constexpr int XP = XF * 64 / 512;         // 16-byte pieces per thread per chunk = 2
+    static constexpr int XF = XK * MT * 2;           // fragments per chunk
+    static constexpr int XP = (XF * 64 + 511) / 512; // 16-byte pieces per thread per chunk (one row block: half the threads)
     static constexpr int PER_KB = MT * 2 * 64;       // 16-byte units of the row blocks per contraction block
 
     const bf16x8 *Xp, *Wp, *zl;
@@ -148,7 +151,8 @@ struct SkGemm {
         bf16x8(*xs)[XF * 64] = (bf16x8(*)[XF * 64])xs_flat;
         auto xstore = [&](const bf16x8(&src)[XP], int buf) {
 #pragma unroll
-            for (int p = 0; p < XP; ++p) xs[buf][p * 512 + tid] = src[p];
+            for (int p = 0; p < XP; ++p)
+                if (XF >= 8 || tid < XF * 64) xs[buf][p * 512 + tid] = src[p];
         };
         f32x16 acc[MT];
 #pragma unroll
@@ -185,7 +189,7 @@ struct SkGemm {
             // (the barrier below, before the first MFMA, also publishes the factors)
         }
 
-        int nseg = 0;
+        int nseg = 0, odd = 0;
         xstore(xr[0], 0);
         xload(xr[0], nxt, 0);
         __syncthreads();
@@ -199,8 +203,8 @@ struct SkGemm {
                     const int i = c * XK + j;                         // ring slot (compile-time)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) {
-                        bf16x8 hi = xs[c & 1][((j * MT + mt) * 2) * 64 + lane];
-                        bf16x8 lo = xs[c & 1][((j * MT + mt) * 2 + 1) * 64 + lane];
+                        bf16x8 hi = xs[(c + odd) & 1][((j * MT + mt) * 2) * 64 + lane];
+                        bf16x8 lo = xs[(c + odd) & 1][((j * MT + mt) * 2 + 1) * 64 + lane];
                         acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, w[i], acc[mt], 0, 0, 0);
                         acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, w[i], acc[mt], 0, 0, 0);
                     }
@@ -209,7 +213,7 @@ struct SkGemm {
                 // the chunk consumed next goes to the other buffer; its register slot is refilled
                 // with the chunk one outer iteration further on
                 const int nc = (c + 1) % CPI;
-                xstore(xr[nc], (c + 1) & 1);
+                xstore(xr[nc], (c + 1 + odd) & 1);
                 if (c + 1 < CPI) xload(xr[nc], nxt, c + 1);
                 else xload(xr[nc], nx2, 0);
                 __syncthreads();
@@ -247,6 +251,7 @@ struct SkGemm {
                     for (int v = 0; v < 16; ++v) acc[mt][v] = 0.f;
             }
             if (nxt.valid == 0) break;
+            odd ^= CPI & 1;
             cur = nxt;
             nxt = nx2;
             nx2 = sk_walk_next<R>(walk, KB);
