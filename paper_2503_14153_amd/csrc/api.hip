@@ -65,7 +65,7 @@ struct sd_model {
     MedusaBias medusa_b;
     std::vector<LayerW> layers;
     // workspace
-    float *x, *part, *logits, *hlogits, *hf, *h_rows, *opart;
+    float *x, *part, *part2, *logits, *hlogits, *hf, *h_rows, *opart;
     float2* mlpart;
     void *xn, *attn_x, *act, *q, *kt, *vt;
     void* xh;                                // draft-head rows of every tree row, in 256-row operand chunks
@@ -360,7 +360,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     const int Mp = m->MBmax * 32, nh = cfg->n_heads, hd = cfg->head_dim;
     const int ld_max = std::max(std::max(3 * d, 2 * m->Fpad), H * d);
     // launch plans for every GEMM shape this model can issue
-    size_t pf = 0;
+    size_t pf = 0, pf2 = 0;                                // (pf2: the down projection's, whose launch reads the gate/up one's)
     std::vector<int32_t> cnt_all;
     std::vector<size_t> cnt_off;
     {
@@ -383,6 +383,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
                 cnt_all.insert(cnt_all.end(), slot0.begin(), slot0.end());
                 m->plans.push_back(pl);
                 pf = std::max(pf, (size_t)pl.slots_max * (mb * 32) * (size_t)sh[1] * 32);
+                if (mb == 1 && sh[0] == m->KBf && sh[1] == m->NBo) pf2 = (size_t)pl.slots_max * 32 * (size_t)sh[1] * 32;
             }
     }
     (void)ld_max;
@@ -391,7 +392,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     const int HBp = pow2_blocks(std::min((H + 1) * SD_MAX_BATCH, 256)) * 32;      // head rows of a batch, and its base rows
     size_t wz = 0;
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
-    size_t w_x = wtake((size_t)Mp * d * 4), w_part = wtake(pf * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
+    size_t w_x = wtake((size_t)Mp * d * 4), w_part = wtake(pf * 4), w_part2 = wtake(pf2 * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
     size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4), w_hf = wtake((size_t)Mp * d * 4);
     size_t w_hrows = wtake((size_t)SD_MAX_BATCH * d * 4);
     size_t w_opart = wtake((size_t)Mp * nh * m->max_parts * hd * 4), w_ml = wtake((size_t)Mp * nh * m->max_parts * 8);
@@ -442,7 +443,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
         return fail(SD_ERR_HIP, "workspace clear: %s", hipGetErrorString(e));
     }
     char* Wk = m->work;
-    m->x = (float*)(Wk + w_x); m->part = (float*)(Wk + w_part); m->logits = (float*)(Wk + w_logits);
+    m->x = (float*)(Wk + w_x); m->part = (float*)(Wk + w_part); m->part2 = (float*)(Wk + w_part2); m->logits = (float*)(Wk + w_logits);
     m->hlogits = (float*)(Wk + w_hlog); m->hf = (float*)(Wk + w_hf); m->h_rows = (float*)(Wk + w_hrows);
     m->opart = (float*)(Wk + w_opart); m->mlpart = (float2*)(Wk + w_ml);
     m->xn = Wk + w_xn; m->attn_x = Wk + w_attn; m->act = Wk + w_act; m->q = Wk + w_q;
@@ -820,6 +821,12 @@ static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out
     return launch_gemm(*p, Xp, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
 }
 
+static PartView run_gemm_few(sd_model* m, const GemmPlan* p, const FewSrc& src, const void* Wp, float* out, int rows, int n_real,
+                             hipStream_t s) {
+    const int pi = prof_claim(m, PROF_GEMM, (double)n_real * p->KB * 16 * 2);
+    return launch_gemm_few(*p, src, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
+}
+
 // Every GEMM shape a pass over M rows issues (and, with heads = true, the draft heads after it, in the
 // schedule given) has a launch plan: checked by the entry points before anything is enqueued.
 static bool have_plans(const sd_model* m, int M, int B, bool heads, bool all_rows) {
@@ -901,6 +908,10 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
     const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, /*split_ok=*/Tp == 64, ragged_lengths(kv, rm.seq, B, n_hi));
     PartView prev = {nullptr, 0, d, nullptr, 0};
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
+    // a handful of rows: the O and down projections make their operands themselves (k_gemm_few; steps only, whose rows lie
+    // rr.R apart)
+    const GemmPlan *plan_o = m->find_plan(MB, m->KBd, m->NBo), *plan_dn = m->find_plan(MB, m->KBf, m->NBo);
+    const bool few_o = rr.map == nullptr && plan_o && few_ok(*plan_o, M), few_dn = plan_dn && few_ok(*plan_dn, M);
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW& lw = m->layers[l];
         launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
@@ -923,12 +934,23 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kt, vt, kv->kv_len,
                          m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
                          prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
-        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, *std::max_element(rm.len, rm.len + B), B, nh, hd, Tp, ag.nparts, MB, s);
-        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
+        PartView po;
+        if (few_o) {
+            FewSrc fs = {PartView{nullptr, 0, 0, nullptr, 0}, 0, m->opart, m->mlpart, nh, hd, Tp, ag.nparts, rr.R};
+            po = run_gemm_few(m, m->find_plan(MB, m->KBd, m->NBo), fs, lw.wo, m->part, M, d, s);
+        } else {
+            launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, *std::max_element(rm.len, rm.len + B), B, nh, hd, Tp, ag.nparts, MB, s);
+            po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
+        }
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
-        launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
-        prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
+        if (few_dn) {
+            FewSrc fs = {pg, m->Fpad, nullptr, nullptr, 0, 0, 0, 0, 0};
+            prev = run_gemm_few(m, m->find_plan(MB, m->KBf, m->NBo), fs, lw.wdown, m->part2, M, d, s);
+        } else {
+            launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
+            prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
+        }
     }
     return prev;
 }

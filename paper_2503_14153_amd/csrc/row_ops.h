@@ -265,16 +265,20 @@ static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const Ro
 // act = silu(gate) * up from the gate/up partials (gate in columns [0,F), up in [Fpad, Fpad+F)).
 // One item = (row m, group of 8 columns grp < F / 8).
 template <bool WT>
-static __device__ __forceinline__ void swiglu_item(const PartView& pv, int F, int Fpad, bf16x8* __restrict__ act, int MB,
-                                                   int m, int grp) {
+static __device__ __forceinline__ void swiglu_values(const PartView& pv, int Fpad, int m, int grp, float (&f)[8]) {
     float gsum[8] = {0, 0, 0, 0, 0, 0, 0, 0}, usum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int ng_ = part_count(pv, grp * 8), nu_ = part_count(pv, Fpad + grp * 8);
     add_slots8<WT>(gsum, pv.base + (size_t)m * pv.ld + grp * 8, pv.slot_stride, ng_);
     add_slots8<WT>(usum, pv.base + (size_t)m * pv.ld + Fpad + grp * 8, pv.slot_stride, nu_);
-    bf16x8 hi, lo;
-    float f[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) f[i] = gsum[i] / (1.f + __expf(-gsum[i])) * usum[i];
+}
+template <bool WT>
+static __device__ __forceinline__ void swiglu_item(const PartView& pv, int F, int Fpad, bf16x8* __restrict__ act, int MB,
+                                                   int m, int grp) {
+    bf16x8 hi, lo;
+    float f[8];
+    swiglu_values<WT>(pv, Fpad, m, grp, f);
     split_hilo(f, hi, lo);
     const size_t u = xpack_index(m, grp * 8, MB) >> 3;
     store_frag16<WT>(act + u, hi);
@@ -286,13 +290,14 @@ static __device__ __forceinline__ void swiglu_item(const PartView& pv, int F, in
 // the packed bf16 operand of the O-projection (row m). The parts are read in batches of eight whose loads are all
 // issued before any is used (a part index past the end re-reads the last part with weight zero, so no load
 // sits behind a branch).
-template <bool WT>
-static __device__ __forceinline__ void attn_merge_item(const float* __restrict__ opart, const float2* __restrict__ mlpart,
-                                                       bf16x8* __restrict__ xp, int nh, int hd, int Tp, int nparts, int MB,
-                                                       int b, int h, int t, int m, int e8) {
+static __device__ __forceinline__ void attn_merge_values(const float* __restrict__ opart, const float2* __restrict__ mlpart,
+                                                         int nh, int hd, int Tp, int nparts, int b, int h, int t, int e8,
+                                                         float (&o)[8]) {
     constexpr int PB = 8;
     size_t base = ((size_t)b * nh + h) * nparts;
-    float M = NEG_INF_F, den = 0.f, o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    float M = NEG_INF_F, den = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = 0.f;
     for (int p0 = 0; p0 < nparts; p0 += PB) {
         float2 ml[PB];
         float4 a[PB], c[PB];
@@ -323,9 +328,16 @@ static __device__ __forceinline__ void attn_merge_item(const float* __restrict__
         M = Mb;
     }
     float inv = den > 0.f ? 1.f / den : 0.f;
-    bf16x8 hi, lo;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] *= inv;
+}
+template <bool WT>
+static __device__ __forceinline__ void attn_merge_item(const float* __restrict__ opart, const float2* __restrict__ mlpart,
+                                                       bf16x8* __restrict__ xp, int nh, int hd, int Tp, int nparts, int MB,
+                                                       int b, int h, int t, int m, int e8) {
+    bf16x8 hi, lo;
+    float o[8];
+    attn_merge_values(opart, mlpart, nh, hd, Tp, nparts, b, h, t, e8, o);
     split_hilo(o, hi, lo);
     const int k = h * hd + e8 * 8;
     const size_t u = xpack_index(m, k, MB) >> 3;

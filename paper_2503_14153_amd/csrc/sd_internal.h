@@ -216,6 +216,18 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
 // rows: rows that exist; the partial tiles' other rows are not written
 PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
                      hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// At most FEW_ROWS rows: the projection makes its operand itself, from what the launch before it would have packed (the
+// gate/up projection's partial sums, or the attention parts), so that launch is not needed. few_ok: the plan's workgroups
+// have one segment each, of FEW_STEPS contraction blocks at most.
+#define FEW_ROWS 2
+#define FEW_STEPS 96
+struct FewSrc {
+    PartView gu; int Fpad;                                            // down projection: silu(gate) * up
+    const float* opart; const float2* mlpart; int nh, hd, Tp, nparts, R;   // O projection: merged attention output, row m = b * R + t
+};
+bool few_ok(const GemmPlan& p, int rows);
+PartView launch_gemm_few(const GemmPlan& p, const FewSrc& src, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
+                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // persistent layer kernel: G workgroups (all must be resident at once), a.MB in {1, 2, 8}
 void launch_layer(const FusedArgs& a, int G, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // how many of its workgroups the device can hold at once (0 on error)
