@@ -340,10 +340,10 @@ def main():
         "cpu_baseline": cpu,
     }
     if shape.dtype == "f32":
-        # the float32 path: plain vector-ALU kernels, launch-bound at this size; no per-kernel events are taken
+        # the float32 path: launch-bound at this size; no per-kernel events are taken
         Tp = (T + 31) // 32 * 32
         flops = 2.0 * Tp * weight_bytes(shape, 1) / 2.0
-        res["roofline"] = {"kernel": "k_f32_linear (whole step; float32 vector-ALU path, launch-bound at this size)",
+        res["roofline"] = {"kernel": "k_f32_linear (whole step; float32 path, launch-bound at this size)",
                            "bound": "alu", "achieved": flops / (ms_per_step * 1e-3) / 1e12, "peak": 157.3,
                            "unit": "TFLOP/s", "frac": flops / (ms_per_step * 1e-3) / 1e12 / 157.3, "traffic": None}
         res["attention"] = None

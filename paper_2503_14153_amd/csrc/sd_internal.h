@@ -71,9 +71,9 @@ static __host__ __device__ inline size_t vblk_index(int c, int e, int HD) {
 // ---- per-call row table (device) -----------------------------------------------------------
 // The M rows of a pass are packed: sequence i of the pass owns rows [off[i], off[i] + len[i]) of the residual stream, of
 // every GEMM operand and of every partial sum, with no padding between sequences, so eight sequences of plain decoding
-// are 8 rows and not 256 (7B shape, four layers, GEMM time per layer 232 -> 96 us). Only attention works on 32-row blocks per sequence: its
-// queries, the tree's K/V scratch and its partials are [i][Tp], row t there is packed row off[i] + t for t < len[i] and
-// padding (never read back as a result) beyond.
+// are 8 rows and not 256 (7B shape, GEMM launches per layer 232 -> 86 us). Only attention works on 32-row blocks per
+// sequence: its queries, the tree's K/V scratch and its partials are [i][Tp], row t there is packed row off[i] + t for
+// t < len[i] and padding (never read back as a result) beyond. (float32 path: the scratch is packed too.)
 #define SD_MAX_BATCH 32
 struct RowMap {
     int32_t off[SD_MAX_BATCH], len[SD_MAX_BATCH];   // len >= 1
@@ -245,7 +245,7 @@ void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* d
 void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev, const int32_t* kv_len,
                              int B, int Tp, int hd, const double* freq, const void* embed, int embed_f32, int d, int V,
                              float* x, hipStream_t s);
-// float32 device path (f32.hip): natural row-major layouts, vector-ALU arithmetic
+// float32 device path (f32.hip): natural row-major layouts, float32 products
 // out = norm(X[gather]) W^T (gain NULL: no norm); x += X W^T
 void launch_f32_norm_linear(const float* X, const int32_t* gather, const float* gain, float eps, const float* W, float* out, int M,
                             int N, int K, int ldo, hipStream_t s);
