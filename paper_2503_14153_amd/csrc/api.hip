@@ -1334,7 +1334,8 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     };
 
     if (m->use_graphs && !m->prof.on && !ty) {
-        const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, Tp == 64, ragged_lengths(kv, nullptr, B, n_hi));
+        // (float32 attention has no parts: nothing of its launches depends on the lengths that the host knows)
+        const AttnGeom ag = m->f32 ? AttnGeom{} : attn_geometry(m, B, Tp, n_hi, Tp == 64, ragged_lengths(kv, nullptr, B, n_hi));
         std::vector<uint64_t> key = {kv->uid, tree_uid, (uint64_t)(uintptr_t)parent, (uint64_t)T, (uint64_t)Tp,
                                      (uint64_t)ag.ncparts, (uint64_t)(ag.per * 4 + ag.tree_sep), (uint64_t)(uintptr_t)stop_mask,
                                      (uint64_t)(uintptr_t)n_accept, (uint64_t)(uintptr_t)tokens,
