@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "sd_internal.h"
+#include "attn_geom.h"
 
 // ------------------------------------------------------------------------------------------ errors
 static thread_local char g_err[512] = "";
@@ -844,68 +845,30 @@ static bool have_plans(const sd_model* m, int M, int B, bool heads, bool all_row
     return ok;
 }
 
-// How the attention of one step is cut into workgroups (one resident per compute unit: the kernel
-// takes the whole LDS). A group is one (sequence, head, query-block group); it gets `ncparts` cache
-// parts of `per` 32-row blocks each, sized from the host's bound on the sequence lengths, and the
-// tree blocks go to a part of their own while the chip has room for it (short contexts) or to the
-// last cache part (long contexts).
-// tree_sep: parts that hold tree blocks only: 0 (the last cache part takes them), 1, or, when the attention launch
-// builds the tree's keys and values itself (one query group of two blocks: split_ok), one per tree block, so that the
-// building is shared by two workgroups.
-struct AttnGeom { int ncparts, per, tree_sep, nparts; };
+// Does a pass over M rows run through the persistent layer kernel?
+static bool fused_eligible(const sd_model* m, int M) {
+    if (m->f32) return false;
+    const int MB = pow2_blocks(M);
+    return m->use_fused && m->fused_ok && (MB == 1 || MB == 2 || MB == 8);
+}
 // ragged: the sequences' lengths (host's bounds) add up to less than four fifths of B times the longest.
 static bool ragged_lengths(const sd_kv* kv, const int32_t* seq, int B, int n_hi) {
     long long sum = 0;
     for (int i = 0; i < B; ++i) sum += kv->len_hi[seq ? seq[i] : i];
     return sum * 5 < 4ll * n_hi * B;
 }
-static AttnGeom attn_geometry(const sd_model* m, int B, int Tp, int n_hi, bool split_ok = false, bool ragged = false) {
-    const int nblk = ceil_div(n_hi, 32);
-    const int TB = Tp / 32, TG = (TB % 2 == 0) ? TB / 2 : TB;
-    const int groups = B * m->cfg.n_heads * TG;
-    int P = 256 / groups;                                  // parts per group that fit the chip at once
-    if (P < 1) P = 1;
-    if (P > m->max_parts) P = m->max_parts;
-    AttnGeom g;
-    if (nblk == 0) { g.ncparts = 0; g.per = 1; g.tree_sep = 1; g.nparts = 1; return g; }
-    // A batch with one workgroup per (sequence, head) lasts as long as its longest sequence: when the lengths are ragged,
-    // two parts that share every sequence's own blocks evenly (per = 0). Launch at eight 7B-shaped sequences of 1024 - 4096
-    // rows: plain decoding 88 -> 78 us, 32-node trees 88 -> 82; one of 4096 beside seven of 32 rows 56 -> 36; but eight of
-    // 2560 rows 74.6 -> 77.6, so not where they are alike. (Three and four parts 85 and 95 us: one workgroup of this
-    // kernel fits a compute unit, and held to 128 registers, so that two fit, it spills: 107 us.)
-    if (P == 1 && TB == 1 && ragged && nblk >= 8) {
-        g.tree_sep = 0;
-        g.ncparts = g.nparts = 2;
-        g.per = 0;
-        return g;
-    }
-    const int by_work = ceil_div(nblk, 4);                 // at least one block per wave
-    const int ntp = (split_ok && TB == 2 && P >= 3) ? 2 : 1;
-    // The tree keeps parts of its own while the cache parts are short: up to eight blocks per cache part, or, when a
-    // single sequence has the chip (eight parts per head, of which the tree's one or two idle while the others stream),
-    // up to forty: there the launch without the rotary stage before it wins up to ~8 k rows (64-node tree, step at
-    // 1.5 / 3 / 6 k rows: 5.18 -> 5.06, 5.25 -> 5.20, 5.55 -> 5.47 ms; at 16 k rows 6.40 -> 6.45, so not there).
-    const int short_mult = P >= 8 ? 40 : 8;
-    if (P >= 2 && nblk <= short_mult * (P - ntp)) {        // short: the tree beside the cache parts
-        // (two blocks per wave before another part is opened: every part repeats the queries' set-up and adds a term
-        // to the merge; 7B shape, 64-node tree over 512-1800 rows: attention launch 18.4 -> 16.8 us, step -1 %)
-        const int by_two = ceil_div(nblk, 8);
-        g.tree_sep = ntp;
-        g.ncparts = P - ntp < by_two ? P - ntp : by_two;
-    } else {
-        g.tree_sep = 0;
-        g.ncparts = P < by_work ? P : by_work;
-    }
-    g.per = ceil_div(nblk, g.ncparts);
-    g.ncparts = ceil_div(nblk, g.per);
-    g.nparts = g.ncparts + g.tree_sep;
-    return g;
+// The geometry that the pass over B sequences of Tp rows will launch: worked out once per pass, launched, and part of the
+// key under which the pass is captured. (float32 attention has no parts: none of its launches depends on n_hi.)
+static AttnGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int Tp, int n_hi) {
+    if (m->f32) return AttnGeom{};
+    return attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
+                                 ragged_lengths(kv, seq, B, n_hi));
 }
 
-static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, hipStream_t s) {
+static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, const AttnGeom& ag,
+                           hipStream_t s) {
     const sd_config& c = m->cfg;
     const int MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
-    const AttnGeom ag = attn_geometry(m, B, Tp, n_hi, /*split_ok=*/Tp == 64, ragged_lengths(kv, rm.seq, B, n_hi));
     PartView prev = {nullptr, 0, d, nullptr, 0};
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
     // a handful of rows: the O and down projections make their operands themselves (k_gemm_few; steps only, whose rows lie
@@ -969,18 +932,13 @@ static FusedGemm fused_gemm(const sd_model* m, int MB, int KB, int NB, const voi
     g.sc = NO_SCALE;
     return g;
 }
-static bool fused_eligible(const sd_model* m, int M) {
-    if (m->f32) return false;
-    const int MB = pow2_blocks(M);
-    return m->use_fused && m->fused_ok && (MB == 1 || MB == 2 || MB == 8);
-}
 // Layers 0..L-1 and, with want_lm, the final norm and the LM-head GEMM, whose partial sums the returned view
 // describes (without want_lm: the last down projection's, still to be added to m->x).
 // (Its phases take the rows as [sequence][Tp]: the row map says off[i] = i * Tp.)
-static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int Tp, int n_hi, bool want_lm, hipStream_t s) {
+static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int Tp, int n_hi, const AttnGeom& ag, bool want_lm,
+                                  hipStream_t s) {
     const sd_config& c = m->cfg;
     const int M = B * Tp, MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32, L = c.n_layers;
-    const AttnGeom ag = attn_geometry(m, B, Tp, n_hi);
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;
     launch_fill_i32((int32_t*)m->sync_ctr, 0, (L + 1) * FUSED_SYNC_WORDS, s);
     m->fused_dirty = true;
@@ -1103,8 +1061,8 @@ static PartView run_lm_head(sd_model* m, PartView prev, int M, hipStream_t s, bo
 // The whole verifying pass: layers, and with want_lm the final norm and the LM head; returns the partial sums of the logits
 // (without want_lm: of the last down projection, still to be added to m->x). Sequence i's rows start at row i * R (R = 0:
 // at rm.off[i], prompt chunks).
-static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, bool want_lm,
-                            bool keep_h, hipStream_t s) {
+static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, const AttnGeom& ag,
+                            bool want_lm, bool keep_h, hipStream_t s) {
     m->scratch_B = kv->B;
     m->scratch_n = B;
     m->scratch_M = M;
@@ -1114,10 +1072,10 @@ static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int
     if (m->f32) { run_forward_f32(m, kv, rr, rm, B, M, Tp, want_lm, s); return dense_logits(m, m->logits); }
     if (fused_eligible(m, B * Tp)) {
         // (when the final norm's rows themselves are wanted, the last stage runs as kernels of its own)
-        PartView pl = run_forward_fused(m, kv, rr, B, Tp, n_hi, want_lm && !keep_h, s);
+        PartView pl = run_forward_fused(m, kv, rr, B, Tp, n_hi, ag, want_lm && !keep_h, s);
         return want_lm && keep_h ? run_lm_head(m, pl, M, s, true) : pl;
     }
-    PartView prev = run_layers(m, kv, rr, rm, B, M, Tp, n_hi, s);
+    PartView prev = run_layers(m, kv, rr, rm, B, M, Tp, n_hi, ag, s);
     return want_lm ? run_lm_head(m, prev, M, s, keep_h) : prev;
 }
 
@@ -1237,7 +1195,8 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         }
         launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
                                 c.d_model, c.vocab, m->x, s);
-        PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, false, false, s);
+        const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
+        PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
         launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
         commit_rows(m, kv, false, kv->i_slots, kv->i_nacc, Tp, Tp, s);
         for (int i = 0; i < A; ++i) {
@@ -1289,7 +1248,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     int32_t* slots = io->src_slots ? io->src_slots : kv->i_slots;
     const int32_t* cand = io->forced_cand ? io->forced_cand : kv->cand;
 
-    // everything the launch sequence depends on besides device-resident state
+    const AttnGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
                            m->rope_freq, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);
@@ -1299,7 +1258,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     const int ldl = lg == m->logits ? m->Vpad : c.vocab;
     // plain decoding drafts from the only row a sequence has: one pass of the LM head for its base and head rows
     const bool known = T == 1 && dense && heads && !fused_eligible(m, B * Tp);
-    PartView pl = run_forward(m, kv, rm, B, M, R, Tp, n_hi, !known, all_rows, s);
+    PartView pl = run_forward(m, kv, rm, B, M, R, Tp, n_hi, ag, !known, all_rows, s);
     if (known) {
         run_known_rows(m, kv, pl, B, nullptr, every_sequence(), lg, ldl, io->head_logits, s);
     } else {
@@ -1334,10 +1293,9 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     };
 
     if (m->use_graphs && !m->prof.on && !ty) {
-        // (float32 attention has no parts: nothing of its launches depends on the lengths that the host knows)
-        const AttnGeom ag = m->f32 ? AttnGeom{} : attn_geometry(m, B, Tp, n_hi, Tp == 64, ragged_lengths(kv, nullptr, B, n_hi));
+        // everything the launch sequence depends on besides device-resident state
         std::vector<uint64_t> key = {kv->uid, tree_uid, (uint64_t)(uintptr_t)parent, (uint64_t)T, (uint64_t)Tp,
-                                     (uint64_t)ag.ncparts, (uint64_t)(ag.per * 4 + ag.tree_sep), (uint64_t)(uintptr_t)stop_mask,
+                                     (uint64_t)ag.ncparts, (uint64_t)ag.per, (uint64_t)ag.tree_sep, (uint64_t)(uintptr_t)stop_mask,
                                      (uint64_t)(uintptr_t)n_accept, (uint64_t)(uintptr_t)tokens,
                                      (uint64_t)(uintptr_t)slots, (uint64_t)(uintptr_t)io->n_accept_raw,
                                      (uint64_t)(uintptr_t)io->logits, (uint64_t)(uintptr_t)io->argmax,

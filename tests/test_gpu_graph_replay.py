@@ -43,3 +43,50 @@ def test_float32_steps_replay(sd, T):
     model.set_graph_mode(False)
     for a, b in zip(got[False], got[True]):
         assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
+
+
+def _wide(sd, B, T, cap, max_rows):
+    """32 heads over a tiny model, a cache full of known rows, random drafts."""
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=32, head_dim=128, d_model=4096, d_ffn=256)
+    model = sd.Model(shape, wl.make_weights(shape, device="cuda"), max_rows)
+    kv = sd.KVCache(model, B, cap)
+    rows = [[[wl.synthetic_kv_rows(3, f"{t}{b}.{layer}", (cap, 32, 128), "bf16", "cuda") for t in "kv"]
+             for layer in range(shape.n_layers)] for b in range(B)]
+    g = np.random.default_rng(8)
+    draft = g.integers(shape.vocab, size=B), g.integers(shape.vocab, size=(B, shape.n_medusa, shape.topk))
+    words = torch.zeros((shape.vocab + 31) // 32, dtype=torch.int32, device="cuda")
+    tree = sd.Tree(*wl.default_tree(T, shape.n_medusa, shape.topk), shape.n_medusa, shape.topk)
+    return model, kv, words, tree, draft, rows
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("B,T,lens", [
+    (8, 32, [256, 288, 257, 320, 600, 256]),             # one workgroup per (sequence, head), ragged: even parts or one part
+    (1, 64, [1568, 1728, 1600, 1569, 1760]),             # a tree of two blocks: in parts of its own or not
+    (1, 32, [40, 41, 256, 257, 1100])])
+def test_replayed_steps_follow_the_cache_length(sd, B, T, lens, fused):
+    """A step captured at one length and replayed at others, in both directions across the edges of 32-row blocks: every
+    committed row counts."""
+    model, kv, words, tree, draft, rows = _wide(sd, B, T, max(lens) + 8, 256)
+    others = [40, 1, 33, 64, 7, 100, 31][:B - 1]
+    model.set_fused(fused)
+    got = {}
+    for graphs in (False, True):
+        model.set_graph_mode(graphs)
+        out, res = None, []
+        for n in lens + lens:
+            for b in range(B):                             # (a step overwrites the rows that it commits)
+                for layer, (k, v) in enumerate(rows[b]):
+                    kv.write_rows(layer, b, 0, k, v)
+            kv.set_len([n] + others)
+            kv.set_draft(*draft)
+            out = sd.spec_step(model, kv, tree, words, want_logits=True, out=out)
+            torch.cuda.synchronize()
+            res.append((out.logits.clone(), out.tokens.clone(), kv.len()))
+            _ = (out.logits * 2).sum().item()              # unrelated eager work between replays
+        got[graphs] = res
+    model.set_graph_mode(False)
+    for i, (a, b) in enumerate(zip(got[False], got[True])):
+        assert torch.isfinite(b[0]).all()
+        assert torch.equal(a[0], b[0]), f"call {i}, length {(lens + lens)[i]}: the replay's logits are not the eager step's"
+        assert torch.equal(a[1], b[1]) and a[2] == b[2]
