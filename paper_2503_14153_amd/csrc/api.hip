@@ -55,6 +55,13 @@ struct Profile {
     size_t used = 0;                         // pairs used
 };
 
+// What a pass leaves in the tree K/V scratch: its cache's batch, rows per sequence, and the sequences that it holds, in
+// order; float32: the rows of the pass and every sequence's first.
+struct ScratchRows {
+    int B = 0, Tp = 0, M = 0, n = 0;
+    int seq[SD_MAX_BATCH] = {}, row0[SD_MAX_BATCH] = {};
+};
+
 struct sd_model {
     sd_config cfg;
     Profile prof;
@@ -107,9 +114,7 @@ struct sd_model {
     unsigned long long sync_timeout_ticks = 5000000ull;     // 50 ms of the 100 MHz counter
     unsigned long long* timeline = nullptr;  // caller's buffer for the layer kernel's time stamps, or NULL
     size_t timeline_launches = 0;
-    int scratch_B = 0, scratch_Tp = 0;       // the tree K/V scratch as the last pass left it: its cache's batch, rows per
-    int scratch_n = 0, scratch_seq[SD_MAX_BATCH] = {};   // sequence, and the sequences that it holds, in order; float32: the
-    int scratch_M = 0, scratch_row0[SD_MAX_BATCH] = {};  // rows of the pass and every sequence's first
+    ScratchRows scratch;                     // as the last pass left it
     bool plan_missing = false;               // set by run_gemm if it ever had to skip a launch
     bool greedy_drafts = true;               // sd_greedy_step also runs the draft heads
     // float32 path (dtype SD_DTYPE_F32; f32.hip): weights [out][in] as float, natural activation layouts
@@ -1001,20 +1006,20 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int 
 
 // ------------------------------------------------------------------------------------------ float32 pass
 // by_seq: slots, counts and old lengths are listed by sequence of the cache (else by sequence of the pass)
-static void commit_rows(sd_model* m, sd_kv* kv, bool by_seq, const int32_t* slots, const int32_t* n_acc, int Tp, int W,
-                        hipStream_t s) {
+static void commit_rows(sd_model* m, sd_kv* kv, const ScratchRows& sc, bool by_seq, const int32_t* slots, const int32_t* n_acc,
+                        int W, hipStream_t s) {
     const sd_config& c = m->cfg;
     RowMap rm;
     memset(&rm, 0, sizeof(rm));
-    for (int i = 0; i < m->scratch_n; ++i) { rm.seq[i] = m->scratch_seq[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
+    for (int i = 0; i < sc.n; ++i) { rm.seq[i] = sc.seq[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
     if (m->f32) {
-        for (int i = 0; i < m->scratch_n; ++i) rm.len[i] = m->scratch_row0[i];
-        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, m->scratch_n,
-                             c.d_model, m->scratch_M, kv->cap, W, s);
+        for (int i = 0; i < sc.n; ++i) rm.len[i] = sc.row0[i];
+        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, sc.n,
+                             c.d_model, sc.M, kv->cap, W, s);
     }
     else
-        launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, m->scratch_n, c.n_heads,
-                         c.head_dim, Tp / 32, kv->cap_blocks, W, s);
+        launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, sc.n, c.n_heads,
+                         c.head_dim, sc.Tp / 32, kv->cap_blocks, W, s);
 }
 
 static void run_forward_f32(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, bool want_lm,
@@ -1058,16 +1063,18 @@ static PartView run_lm_head(sd_model* m, PartView prev, int M, hipStream_t s, bo
     return run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
 }
 
+static ScratchRows scratch_of_pass(const sd_kv* kv, const RowMap& rm, int n, int M, int Tp) {
+    ScratchRows sc;
+    sc.B = kv->B; sc.Tp = Tp; sc.M = M; sc.n = n;
+    for (int i = 0; i < n; ++i) { sc.seq[i] = rm.seq[i]; sc.row0[i] = rm.off[i]; }
+    return sc;
+}
+
 // The whole verifying pass: layers, and with want_lm the final norm and the LM head; returns the partial sums of the logits
 // (without want_lm: of the last down projection, still to be added to m->x). Sequence i's rows start at row i * R (R = 0:
 // at rm.off[i], prompt chunks).
 static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, const AttnGeom& ag,
                             bool want_lm, bool keep_h, hipStream_t s) {
-    m->scratch_B = kv->B;
-    m->scratch_n = B;
-    m->scratch_M = M;
-    for (int i = 0; i < B; ++i) { m->scratch_seq[i] = rm.seq[i]; m->scratch_row0[i] = rm.off[i]; }
-    m->scratch_Tp = Tp;
     const RowRef rr = {R ? nullptr : m->rm_dev, R};
     if (m->f32) { run_forward_f32(m, kv, rr, rm, B, M, Tp, want_lm, s); return dense_logits(m, m->logits); }
     if (fused_eligible(m, B * Tp)) {
@@ -1198,7 +1205,8 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
         PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
         launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
-        commit_rows(m, kv, false, kv->i_slots, kv->i_nacc, Tp, Tp, s);
+        m->scratch = scratch_of_pass(kv, rm, A, M, Tp);
+        commit_rows(m, kv, m->scratch, false, kv->i_slots, kv->i_nacc, Tp, s);
         for (int i = 0; i < A; ++i) {
             const int b = rm.seq[i];
             kv->len_hi[b] += ca.len[i];
@@ -1249,6 +1257,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     const int32_t* cand = io->forced_cand ? io->forced_cand : kv->cand;
 
     const AttnGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
+    const ScratchRows scratch = scratch_of_pass(kv, rm, B, M, Tp);
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
                            m->rope_freq, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);
@@ -1287,7 +1296,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     if (ty)      // the next root is drawn from the base distribution at the last kept node
         launch_sample_root(lg, ldl, c.vocab, kv->last_row, ty->u, va.inv_temperature, kv->root_tok, B,
                            M, s);
-    commit_rows(m, kv, false, slots, n_accept, Tp, H + 1, s);
+    commit_rows(m, kv, scratch, false, slots, n_accept, H + 1, s);
     if (all_rows) run_draft_heads_all_rows(m, kv, B, M, io->head_logits, s);
     else if (heads && !known) run_draft_heads(m, kv, B, io->head_logits, s);
     };
@@ -1325,6 +1334,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     } else {
         enqueue(s);
     }
+    m->scratch = scratch;                              // (of a replayed step too: passes may have run since its capture)
     HIP_TRY(hipGetLastError());
     if (m->plan_missing) return fail(SD_ERR_STATE, "%s: a GEMM launch plan was missing", who);
     for (int b = 0; b < B; ++b) kv->len_hi[b] += (T == 1) ? 1 : H + 1;
@@ -1346,17 +1356,17 @@ extern "C" int sd_kv_commit_rows(sd_model* m, sd_kv* kv, const int32_t* src_slot
                                  void* stream) {
     if (!m || !kv || !src_slots || !n_rows) return fail(SD_ERR_NULL, "sd_kv_commit_rows: NULL argument");
     if (kv->m != m) return fail(SD_ERR_STATE, "sd_kv_commit_rows: cache belongs to another model");
-    if (m->scratch_B != kv->B || m->scratch_Tp < 32)
+    if (m->scratch.B != kv->B || m->scratch.Tp < 32)
         return fail(SD_ERR_STATE, "sd_kv_commit_rows: no pass over a batch of %d has left tree rows to commit", kv->B);
-    if (width < 1 || width > m->scratch_Tp)
-        return fail(SD_ERR_SHAPE, "sd_kv_commit_rows: width must be in 1..%d (the rows of the last pass)", m->scratch_Tp);
+    if (width < 1 || width > m->scratch.Tp)
+        return fail(SD_ERR_SHAPE, "sd_kv_commit_rows: width must be in 1..%d (the rows of the last pass)", m->scratch.Tp);
     for (int b = 0; b < kv->B; ++b)
         if (kv->len_hi[b] + width > kv->cap)
             return fail(SD_ERR_KV_FULL, "sd_kv_commit_rows: sequence %d may exceed the cache (len <= %d, cap %d)", b,
                         kv->len_hi[b], kv->cap);
     hipStream_t s = (hipStream_t)stream;
     launch_commit_setup(n_rows, width, kv->B, kv->i_nacc, kv->n_old, kv->kv_len, s);
-    commit_rows(m, kv, true, src_slots, kv->i_nacc, m->scratch_Tp, width, s);
+    commit_rows(m, kv, m->scratch, true, src_slots, kv->i_nacc, width, s);
     HIP_TRY(hipGetLastError());
     for (int b = 0; b < kv->B; ++b) kv->len_hi[b] += width;
     return SD_OK;

@@ -90,3 +90,52 @@ def test_replayed_steps_follow_the_cache_length(sd, B, T, lens, fused):
         assert torch.isfinite(b[0]).all()
         assert torch.equal(a[0], b[0]), f"call {i}, length {(lens + lens)[i]}: the replay's logits are not the eager step's"
         assert torch.equal(a[1], b[1]) and a[2] == b[2]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_rows_of_a_replayed_step_can_be_committed(sd, dtype):
+    """sd_kv_commit_rows after a replay takes the rows of the step that was replayed, whatever passes ran since its capture: a
+    ragged prompt whose last pass held one sequence, a step of another tree."""
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype=dtype)
+    model = sd.Model(shape, {k: v.cuda() for k, v in wl.make_weights(shape).items()}, 256)
+    B, cap = 4, 160
+    trees = [sd.Tree(*wl.default_tree(T, shape.n_medusa, shape.topk), shape.n_medusa, shape.topk) for T in (5, 9)]
+    words = torch.zeros((shape.vocab + 31) // 32, dtype=torch.int32, device="cuda")
+    lens = [100, 3, 17, 40]
+    prompt = torch.from_numpy(wl.zipf_prompt(shape.vocab, sum(lens))).cuda()
+    g = np.random.default_rng(8)
+    draft = g.integers(shape.vocab, size=B), g.integers(shape.vocab, size=(B, shape.n_medusa, shape.topk))
+    slots = torch.tensor([[0, 4], [3, 1], [2, 2], [4, 0]], dtype=torch.int32, device="cuda")
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+
+    def step(kv, tree, out):
+        kv.set_len(lens)
+        kv.set_draft(*draft)
+        return sd.spec_step(model, kv, tree, words, out=out)
+
+    def committed(kv):
+        kv.set_len(lens)
+        sd.kv_commit_rows(model, kv, slots, two)
+        assert kv.len() == [n + 2 for n in lens]
+        return [t.clone() for b in range(B) for layer in range(shape.n_layers) for t in kv.read_rows(layer, b, lens[b], 2)]
+
+    got = {}
+    for graphs in (False, True):
+        model.set_graph_mode(graphs)
+        kv = sd.KVCache(model, B, cap)
+        sd.prefill(model, kv, prompt, lens)
+        outs, res = [None, None], []
+        for i in (0, 1):
+            outs[i] = step(kv, trees[i], outs[i])          # captures
+        for i in (0, 1, 0):
+            kv.set_len([0] * B)
+            sd.prefill(model, kv, prompt, lens)
+            step(kv, trees[i], outs[i])
+            res.append(committed(kv))
+        for i in (1, 0):                                   # and straight after the other tree's step
+            step(kv, trees[i], outs[i])
+            res.append(committed(kv))
+        got[graphs] = res
+    model.set_graph_mode(False)
+    for a, b in zip(got[False], got[True]):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
