@@ -209,7 +209,8 @@ int sd_verify_tree(const sd_tree* tree, int32_t batch, int32_t n_medusa, int32_t
 /* Commit of key/value rows alone (the last stage of a step, Section III-B: the accepted tokens become part of the
  * sequence): for every sequence b of `kv`, rows src_slots[b][0 .. n_rows[b]) of the tree rows that the LAST step or
  * prefill chunk of this model over this cache's batch computed are appended to the cache, in that order, and the
- * committed length grows by n_rows[b] (clamped to 0 .. width). src_slots: dev [batch][width], tree row numbers
+ * committed length grows by n_rows[b] (clamped to 0 .. width). A sequence that that pass did not hold (its prompt had
+ * ended in an earlier chunk of the same sd_prefill) has no such rows: its n_rows[b] counts as 0. src_slots: dev [batch][width], tree row numbers
  * below the last pass's padded tree size (clamped); n_rows: dev [batch]. Keys are copied as they are (they were
  * rotated for the position depth(node) after the old length: only meaningful when row j has depth j). SD_ERR_STATE
  * without such a pass, SD_ERR_SHAPE for a bad width, SD_ERR_KV_FULL judged on width rows per sequence.              */

@@ -1365,10 +1365,13 @@ extern "C" int sd_kv_commit_rows(sd_model* m, sd_kv* kv, const int32_t* src_slot
             return fail(SD_ERR_KV_FULL, "sd_kv_commit_rows: sequence %d may exceed the cache (len <= %d, cap %d)", b,
                         kv->len_hi[b], kv->cap);
     hipStream_t s = (hipStream_t)stream;
-    launch_commit_setup(n_rows, width, kv->B, kv->i_nacc, kv->n_old, kv->kv_len, s);
+    uint32_t held = 0;                                 // a sequence that the pass did not hold has no rows to commit
+    for (int i = 0; i < m->scratch.n; ++i) held |= 1u << m->scratch.seq[i];
+    launch_commit_setup(n_rows, width, held, kv->B, kv->i_nacc, kv->n_old, kv->kv_len, s);
     commit_rows(m, kv, m->scratch, true, src_slots, kv->i_nacc, width, s);
     HIP_TRY(hipGetLastError());
-    for (int b = 0; b < kv->B; ++b) kv->len_hi[b] += width;
+    for (int b = 0; b < kv->B; ++b)
+        if ((held >> b) & 1u) kv->len_hi[b] += width;
     return SD_OK;
 }
 

@@ -752,19 +752,20 @@ void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, i
                        kv_len, fin_rows, n_fin, last);
 }
 
-// commit stage alone: the count of every sequence clamped to [0, width], old length noted, new length set
-__global__ void k_commit_setup(const int32_t* __restrict__ n_rows, int width, int B, int32_t* __restrict__ n_accept,
+// commit stage alone: the count of every sequence clamped to [0, width] (0 where bit b of `held` is not set: the last pass
+// left no rows of it), old length noted, new length set
+__global__ void k_commit_setup(const int32_t* __restrict__ n_rows, int width, uint32_t held, int B, int32_t* __restrict__ n_accept,
                                int32_t* __restrict__ n_old, int32_t* __restrict__ kv_len) {
     const int b = threadIdx.x;
     if (b >= B) return;
-    const int a = min(max(n_rows[b], 0), width), n = kv_len[b];
+    const int a = (held >> b) & 1u ? min(max(n_rows[b], 0), width) : 0, n = kv_len[b];
     n_accept[b] = a;
     n_old[b] = n;
     kv_len[b] = n + a;
 }
-void launch_commit_setup(const int32_t* n_rows, int width, int B, int32_t* n_accept, int32_t* n_old, int32_t* kv_len,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(k_commit_setup, dim3(1), dim3(SD_MAX_BATCH), 0, s, n_rows, width, B, n_accept, n_old, kv_len);
+void launch_commit_setup(const int32_t* n_rows, int width, uint32_t held, int B, int32_t* n_accept, int32_t* n_old,
+                         int32_t* kv_len, hipStream_t s) {
+    hipLaunchKernelGGL(k_commit_setup, dim3(1), dim3(SD_MAX_BATCH), 0, s, n_rows, width, held, B, n_accept, n_old, kv_len);
 }
 
 // root_tok of the sequences whose prompt just ended: arg-max of their last rows' logits
