@@ -210,10 +210,11 @@ int sd_verify_tree(const sd_tree* tree, int32_t batch, int32_t n_medusa, int32_t
  * sequence): for every sequence b of `kv`, rows src_slots[b][0 .. n_rows[b]) of the tree rows that the LAST step or
  * prefill chunk of this model over this cache's batch computed are appended to the cache, in that order, and the
  * committed length grows by n_rows[b] (clamped to 0 .. width). A sequence that that pass did not hold (its prompt had
- * ended in an earlier chunk of the same sd_prefill) has no such rows: its n_rows[b] counts as 0. src_slots: dev [batch][width], tree row numbers
- * below the last pass's padded tree size (clamped); n_rows: dev [batch]. Keys are copied as they are (they were
- * rotated for the position depth(node) after the old length: only meaningful when row j has depth j). SD_ERR_STATE
- * without such a pass, SD_ERR_SHAPE for a bad width, SD_ERR_KV_FULL judged on width rows per sequence.              */
+ * ended in an earlier chunk of the same sd_prefill) has no such rows: its n_rows[b] counts as 0. src_slots: dev
+ * [batch][width], row numbers of that pass: tree nodes, or prompt tokens of its chunk; a number at or past the
+ * sequence's own rows stands for its last row, a negative one for row 0. n_rows: dev [batch]. Keys are copied as they
+ * are (they were rotated for the position depth(node) after the old length: only meaningful when row j has depth j).
+ * SD_ERR_STATE without such a pass, SD_ERR_SHAPE for a bad width, SD_ERR_KV_FULL judged on width rows per sequence. */
 int sd_kv_commit_rows(sd_model* m, sd_kv* kv, const int32_t* src_slots, const int32_t* n_rows, int32_t width,
                       void* stream);
 

@@ -55,11 +55,12 @@ struct Profile {
     size_t used = 0;                         // pairs used
 };
 
-// What a pass leaves in the tree K/V scratch: its cache's batch, rows per sequence, and the sequences that it holds, in
-// order; float32: the rows of the pass and every sequence's first.
+// What a pass leaves in the tree K/V scratch: its cache's batch, padded rows per sequence, and the sequences that it holds,
+// in order, each with its own rows (tree nodes, prompt tokens); float32: the rows of the pass and every sequence's first.
 struct ScratchRows {
     int B = 0, Tp = 0, M = 0, n = 0;
-    int seq[SD_MAX_BATCH] = {}, row0[SD_MAX_BATCH] = {};
+    int seq[SD_MAX_BATCH] = {}, len[SD_MAX_BATCH] = {};
+    SeqList row0 = {};
 };
 
 struct sd_model {
@@ -1009,14 +1010,12 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int 
 static void commit_rows(sd_model* m, sd_kv* kv, const ScratchRows& sc, bool by_seq, const int32_t* slots, const int32_t* n_acc,
                         int W, hipStream_t s) {
     const sd_config& c = m->cfg;
-    RowMap rm;
+    RowMap rm;                                         // (off: entry of the lists)
     memset(&rm, 0, sizeof(rm));
-    for (int i = 0; i < sc.n; ++i) { rm.seq[i] = sc.seq[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
-    if (m->f32) {
-        for (int i = 0; i < sc.n; ++i) rm.len[i] = sc.row0[i];
-        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, sc.n,
+    for (int i = 0; i < sc.n; ++i) { rm.seq[i] = sc.seq[i]; rm.len[i] = sc.len[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
+    if (m->f32)
+        launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, sc.row0, kv->B, c.n_layers, sc.n,
                              c.d_model, sc.M, kv->cap, W, s);
-    }
     else
         launch_kv_commit(m->kt, m->vt, kv->kc, kv->vc, slots, n_acc, kv->n_old, rm, kv->B, c.n_layers, sc.n, c.n_heads,
                          c.head_dim, sc.Tp / 32, kv->cap_blocks, W, s);
@@ -1063,10 +1062,11 @@ static PartView run_lm_head(sd_model* m, PartView prev, int M, hipStream_t s, bo
     return run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
 }
 
-static ScratchRows scratch_of_pass(const sd_kv* kv, const RowMap& rm, int n, int M, int Tp) {
+// len: real rows of sequence i (NULL: T each)
+static ScratchRows scratch_of_pass(const sd_kv* kv, const RowMap& rm, int n, int M, int Tp, const int32_t* len, int T) {
     ScratchRows sc;
     sc.B = kv->B; sc.Tp = Tp; sc.M = M; sc.n = n;
-    for (int i = 0; i < n; ++i) { sc.seq[i] = rm.seq[i]; sc.row0[i] = rm.off[i]; }
+    for (int i = 0; i < n; ++i) { sc.seq[i] = rm.seq[i]; sc.row0.seq[i] = rm.off[i]; sc.len[i] = len ? len[i] : T; }
     return sc;
 }
 
@@ -1205,7 +1205,7 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
         PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
         launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
-        m->scratch = scratch_of_pass(kv, rm, A, M, Tp);
+        m->scratch = scratch_of_pass(kv, rm, A, M, Tp, ca.len, 0);
         commit_rows(m, kv, m->scratch, false, kv->i_slots, kv->i_nacc, Tp, s);
         for (int i = 0; i < A; ++i) {
             const int b = rm.seq[i];
@@ -1257,7 +1257,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     const int32_t* cand = io->forced_cand ? io->forced_cand : kv->cand;
 
     const AttnGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
-    const ScratchRows scratch = scratch_of_pass(kv, rm, B, M, Tp);
+    const ScratchRows scratch = scratch_of_pass(kv, rm, B, M, Tp, nullptr, T);
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
                            m->rope_freq, m->embed, m->f32 ? 1 : 0, c.d_model, c.vocab, m->x, s);

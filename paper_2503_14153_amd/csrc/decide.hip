@@ -501,7 +501,7 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 // every layer and head. A kept node at chain index j was rotated for position n_old + j
 // already (depth = chain index), so this is a pure copy.
 // grid: x = head, y = sequence b of the pass that filled the scratch (sequence rm.seq[b] of the cache, entry rm.off[b] of
-// src_slots, n_accept and n_old), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
+// src_slots, n_accept and n_old; slots past its own rm.len[b] rows give the last of them), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
 // whole 16-byte pieces that lie side by side in the cache:
 //   values: a 16-byte piece of the value layout holds one dim of EIGHT rows (a "group": of a 16-row half of a block,
 //     the four rows of one quad and of the quad two further on), so a row cannot move as a piece, and a piece
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const int a = min(n_accept[lst], W);                            // <= SD_MAX_TREE < KVC_THREADS
     if (a <= 0) return;
     const int n = n_old[lst];
-    const int slot = tid < a ? min(max(src_slots[(size_t)lst * W + tid], 0), TB * 32 - 1) : 0;
+    const int slot = tid < a ? min(max(src_slots[(size_t)lst * W + tid], 0), rm.len[b] - 1) : 0;
     if (tid == 0) s_need = 0;
     __syncthreads();
     if (tid < a) {

@@ -294,15 +294,15 @@ void launch_f32_attn(const float* q, const float* kc, const float* vc, const flo
 
 // ------------------------------------------------------------------------------------------
 // Commit: row src_slots[list][j] of pass sequence i -> cache row n_old[list] + j of sequence rm.seq[i], for j < n_accept[list],
-// list = rm.off[i], every layer, K and V. The sequence's rows start at scratch row rm.len[i]; slots past the scratch's last
-// row are clamped. grid (row j, layer * B + i), 256 threads over the d columns.
+// list = rm.off[i], every layer, K and V. The sequence owns rm.len[i] scratch rows from row0.seq[i] on; a slot past them gives
+// its last one, never another sequence's row. grid (row j, layer * B + i), 64 threads over the d columns.
 __global__ void k_f32_kv_commit(const float* __restrict__ kt, const float* __restrict__ vt, float* __restrict__ kc,
                                 float* __restrict__ vc, const int32_t* __restrict__ src_slots,
-                                const int32_t* __restrict__ n_accept, const int32_t* __restrict__ n_old, RowMap rm, int B, int d,
-                                int rows, int cap, int W, size_t layer_stride_t, size_t layer_stride_c) {
+                                const int32_t* __restrict__ n_accept, const int32_t* __restrict__ n_old, RowMap rm, SeqList row0,
+                                int B, int d, int cap, int W, size_t layer_stride_t, size_t layer_stride_c) {
     const int j = blockIdx.x, l = blockIdx.y / B, i = blockIdx.y % B, lst = rm.off[i];
     if (j >= min(n_accept[lst], W)) return;
-    const int src = min(rm.len[i] + max(src_slots[(size_t)lst * W + j], 0), rows - 1), dst = n_old[lst] + j;
+    const int src = row0.seq[i] + min(max(src_slots[(size_t)lst * W + j], 0), rm.len[i] - 1), dst = n_old[lst] + j;
     const size_t so = l * layer_stride_t + (size_t)src * d, dofs = l * layer_stride_c + ((size_t)rm.seq[i] * cap + dst) * d;
     for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
         *(f32x4*)(kc + dofs + c) = *(const f32x4*)(kt + so + c);
@@ -310,9 +310,9 @@ __global__ void k_f32_kv_commit(const float* __restrict__ kt, const float* __res
     }
 }
 void launch_f32_kv_commit(const float* kt, const float* vt, float* kc, float* vc, const int32_t* src_slots,
-                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B, int L, int B, int d, int rows,
-                          int cap, int W, hipStream_t s) {
-    hipLaunchKernelGGL(k_f32_kv_commit, dim3(W, L * B), dim3(64), 0, s, kt, vt, kc, vc, src_slots, n_accept, n_old, rm, B, d, rows,
+                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, const SeqList& row0, int kv_B, int L,
+                          int B, int d, int rows, int cap, int W, hipStream_t s) {
+    hipLaunchKernelGGL(k_f32_kv_commit, dim3(W, L * B), dim3(64), 0, s, kt, vt, kc, vc, src_slots, n_accept, n_old, rm, row0, B, d,
                        cap, W, (size_t)rows * d, (size_t)kv_B * cap * d);
 }
 

@@ -79,6 +79,7 @@ struct RowMap {
     int32_t off[SD_MAX_BATCH], len[SD_MAX_BATCH];   // len >= 1
     int32_t seq[SD_MAX_BATCH];                      // sequence of the cache
 };
+struct SeqList { int32_t seq[SD_MAX_BATCH]; };      // one number per sequence of a pass
 // What the kernels of a layer get: every sequence of a step has the same number of rows, R (map NULL); a prompt pass leaves
 // its map in device memory. (As an argument of every launch the map's 384 bytes cost the 64-node step 1 %, read from
 // memory by every launch another 1 %: the attention launch's first addresses wait for it, 14.9 -> 15.5 us.)
@@ -262,8 +263,8 @@ void launch_f32_attn(const float* q, const float* kc, const float* vc, const flo
                      const int32_t* kv_len, const uint32_t* anc, float* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
                      int cap, hipStream_t s);
 void launch_f32_kv_commit(const float* kt, const float* vt, float* kc, float* vc, const int32_t* src_slots,
-                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B, int L, int B, int d, int rows,
-                          int cap, int W, hipStream_t s);
+                          const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, const SeqList& row0, int kv_B, int L,
+                          int B, int d, int rows, int cap, int W, hipStream_t s);
 void launch_f32_kv_rows(float* kc, float* vc, float* k_rows, float* v_rows, int row0, int nrows, int d, int to_cache,
                         hipStream_t s);
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out,
@@ -289,7 +290,6 @@ void launch_medusa_act(PartView pv, const float* h_rows, const MedusaBias& bias,
 int rank_chunks(int V);
 void launch_rank_best(PartView pv, int row0, int rows, int V, float* logits, int ld, float2* cand, hipStream_t s);
 // out[seq[b]][i][0..k): ids of the largest k logits of row row0 + i * B + b, best first, lower id on ties
-struct SeqList { int32_t seq[SD_MAX_BATCH]; };
 void launch_topk(PartView pv, int row0, int V, int k, int32_t* out, int B, int H, const SeqList& sl, float* head_logits,
                  void* cand, hipStream_t s);
 // root_tok[seq[i]] = arg-max of ranked row i
@@ -306,6 +306,8 @@ void launch_sample_root(const float* logits, int ld, int V, const int32_t* last_
 void launch_build_labels(const int32_t* l0, int B, int S, int H, int32_t frag, int32_t pad, int32_t ignore,
                          int keep_all, int32_t* labels, hipStream_t s);
 void launch_copy_row_stats(const float4* src, float4* dst, int B, int T, int Tp, hipStream_t s);
+// commit: entry i of the pass is sequence rm.seq[i] of the cache and entry rm.off[i] of the lists; it has rm.len[i] rows, to which
+// slots are clamped (float32: from row row0.seq[i] of the scratch on)
 void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void* vc_all,
                       const int32_t* src_slots, const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B,
                       int L, int B, int nh, int hd, int TB, int cap_blocks, int W, hipStream_t s);
