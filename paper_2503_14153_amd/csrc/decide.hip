@@ -274,8 +274,8 @@ void launch_row_stats(const float* logits, int ld, int V, float4* stats, int B, 
 // ------------------------------------------------------------------------------------------
 // Sampling decoding, the next root: the smallest token id whose cumulative probability under
 // softmax(logits[last_row] / temperature) exceeds u. One workgroup of 16 waves per sequence.
-// Wave w owns the contiguous ids [w*S, (w+1)*S), lane l of group j the id w*S + 64 j + l, read once into registers for the
-// maximum and the weights exp((l - max)/temp). The wave whose segment holds the target u * total leaves its weights in
+// Wave w owns the contiguous ids [w*S, (w+1)*S), lane l of group j the id w*S + 64 j + l: the
+// maximum, then the weights exp((l - max)/temp). The weights of the segment that holds the target u * total go to
 // LDS, where every lane sums a whole group of 64 in id order; one scan over the groups and one inside the group found
 // give the id. (Walking the segment group by group, a scan each, took 22 us at 32 k ids; this form 8.) Sums are in fp64,
 // so the draw only differs from an exact one when u lies within fp32 rounding of the weights of a boundary of the CDF.
@@ -286,7 +286,13 @@ static __device__ inline double wave_incl_scan_f64(double v, int lane) {
     }
     return v;
 }
-template <int NPT>                                     // groups of a wave, at most
+// NPT: groups of a wave, at most. KEEP: the weights stay in registers, up to 65536 ids (64 of them per lane: 14 registers
+// spill, and reading the row twice is slower all the same: 12.6 against 15.1 us at 65536 ids, level at 33000); beyond, where 160 would spill 237
+// registers, the row is read again from the caches for the sum, sixteen groups' loads in flight, and all waves fetch the
+// segment that holds the target, so that no wave is left alone with it. One row / eight rows of 100000, 128256 and
+// 163840 ids: 23 / 24, 26 / 27, 32 / 32 us; spilled 42 / 43, 45 / 46, 47 / 47; walking the segment a scan per 64 ids
+// 26 / 50, 35 / 65, 74 / 80 (the longer, the further into its segment the draw falls).
+template <int NPT, bool KEEP>
 __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restrict__ logits, int ld, int V,
                                                             const int32_t* __restrict__ last_row,
                                                             const float* __restrict__ u, float inv_temperature,
@@ -301,28 +307,40 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
     const float* row = logits + (size_t)r * ld;
     __shared__ float smax[NW];
     __shared__ double wsum[NW];
-    __shared__ float ws[NPT * 65];                     // one wave's weights, [group][64 + 1]
+    __shared__ float ws[NPT * 65];                     // one segment's weights, [group][64 + 1]
     const int S = ((V + NW - 1) / NW + 63) & ~63;      // segment length, a multiple of the wave size
-    const int s0 = min(wave * S, V), s1 = min(s0 + S, V);
-    float v[NPT];
-    float mx = NEG_INF;
+    int s0 = min(wave * S, V), s1 = min(s0 + S, V);
+    constexpr int U = KEEP ? NPT : 16;                 // groups whose loads are issued together
+    int groups = (s1 - s0 + 63) / 64;
+    float v[U];
+    auto load = [&](int j0) {                          // groups j0 .. j0 + U - 1 of this wave's segment
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int c = s0 + j * 64 + lane;
-        v[j] = c < s1 ? row[c] : NEG_INF;
-        mx = fmaxf(mx, v[j]);
+        for (int j = 0; j < U; ++j) {
+            const int c = s0 + (j0 + j) * 64 + lane;
+            if constexpr (KEEP) v[j] = c < s1 ? row[c] : NEG_INF;
+            else v[j] = row[min(c, V - 1)];
+        }
+    };
+    float mx = NEG_INF;
+    for (int j0 = 0; j0 < (KEEP ? 1 : groups); j0 += U) {
+        load(j0);
+#pragma unroll
+        for (int j = 0; j < U; ++j) mx = fmaxf(mx, KEEP || s0 + (j0 + j) * 64 + lane < s1 ? v[j] : NEG_INF);
     }
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if (lane == 0) smax[wave] = mx;
     __syncthreads();
     mx = smax[0];
     for (int w = 1; w < NW; ++w) mx = fmaxf(mx, smax[w]);
+    auto weight = [&](int j0, int j) { return s0 + (j0 + j) * 64 + lane < s1 ? __expf((v[j] - mx) * inv_temperature) : 0.f; };
     double part = 0.0;
+    for (int j0 = 0; j0 < (KEEP ? 1 : groups); j0 += U) {
+        if constexpr (!KEEP) load(j0);
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const float e = s0 + j * 64 + lane < s1 ? __expf((v[j] - mx) * inv_temperature) : 0.f;
-        v[j] = e;
-        part += (double)e;
+        for (int j = 0; j < U; ++j) {
+            v[j] = weight(j0, j);
+            part += (double)v[j];
+        }
     }
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
     if (lane == 0) wsum[wave] = part;
@@ -340,17 +358,41 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
     }
     const bool to_end = seg < 0;
     if (to_end) seg = last_mass;
-    if (wave != seg) return;                           // (the rest is this wave's alone: no barrier follows)
-    int last_pos = s0;                                 // the last id with mass
+    int last_pos;                                      // the last id with mass
+    if constexpr (KEEP) {
+        if (wave != seg) return;                       // (the rest is this wave's alone: no barrier follows)
+        last_pos = s0;
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        ws[j * 65 + lane] = v[j];
-        const unsigned long long pos = __ballot(v[j] > 0.f);
-        if (pos) last_pos = s0 + j * 64 + 63 - __builtin_clzll(pos);
+        for (int j = 0; j < NPT; ++j) {
+            ws[j * 65 + lane] = v[j];
+            const unsigned long long pos = __ballot(v[j] > 0.f);
+            if (pos) last_pos = s0 + j * 64 + 63 - __builtin_clzll(pos);
+        }
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        // every wave fetches its share of that segment's groups; the draw is the first wave's
+        __shared__ int last;
+        s0 = min(seg * S, V);
+        s1 = min(s0 + S, V);
+        groups = (s1 - s0 + 63) / 64;
+        if (tid == 0) last = s0;
+        __syncthreads();
+        float x[NPT / NW];
+#pragma unroll
+        for (int i = 0; i < NPT / NW; ++i) x[i] = row[min(s0 + (wave + i * NW) * 64 + lane, V - 1)];
+#pragma unroll
+        for (int i = 0; i < NPT / NW; ++i) {
+            const int g = wave + i * NW, c = s0 + g * 64 + lane;
+            const float e = c < s1 ? __expf((x[i] - mx) * inv_temperature) : 0.f;
+            if (g < groups) ws[g * 65 + lane] = e;
+            const unsigned long long pos = __ballot(e > 0.f);
+            if (pos && lane == 0) atomicMax(&last, s0 + g * 64 + 63 - __builtin_clzll(pos));
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        last_pos = last;
     }
-    __builtin_amdgcn_wave_barrier();
     int pick = -1;
-    const int groups = (s1 - s0 + 63) / 64;
     for (int g0 = 0; g0 < groups && pick < 0 && !to_end; g0 += 64) {
         double gsum = 0.0;
         if (g0 + lane < groups)
@@ -375,13 +417,13 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
 void launch_sample_root(const float* logits, int ld, int V, const int32_t* last_row, const float* u,
                         float inv_temperature, int32_t* root_tok, int B, int n_rows, hipStream_t s) {
     const int npt = (((V + RS_THREADS / 64 - 1) / (RS_THREADS / 64) + 63) & ~63) / 64;
-#define SR(N) hipLaunchKernelGGL((k_sample_root<N>), dim3(B), dim3(RS_THREADS), 0, s, logits, ld, V, last_row, u, inv_temperature, \
-                                 root_tok, n_rows)
-    if (npt <= 4) SR(4);
-    else if (npt <= 16) SR(16);
-    else if (npt <= 32) SR(32);
-    else if (npt <= 64) SR(64);
-    else SR(160);                                      // 163840 ids
+#define SR(N, KEEP_) hipLaunchKernelGGL((k_sample_root<N, KEEP_>), dim3(B), dim3(RS_THREADS), 0, s, logits, ld, V, last_row, u, \
+                                        inv_temperature, root_tok, n_rows)
+    if (npt <= 4) SR(4, true);
+    else if (npt <= 16) SR(16, true);
+    else if (npt <= 32) SR(32, true);
+    else if (npt <= 64) SR(64, true);
+    else SR(160, false);                               // 163840 ids
 #undef SR
 }
 
