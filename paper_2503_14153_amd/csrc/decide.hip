@@ -399,12 +399,14 @@ __global__ __launch_bounds__(RS_THREADS) void k_sample_root(const float* __restr
 #pragma unroll 16
             for (int i = 0; i < 64; ++i) gsum += (double)ws[(g0 + lane) * 65 + i];
         const double cum = base + wave_incl_scan_f64(gsum, lane);
-        const unsigned long long hit = __ballot(g0 + lane < groups && cum > target);
+        // (a group without mass is never the one: its place in the scan can round past the target that the sum before it,
+        // the same number exactly, does not pass)
+        const unsigned long long hit = __ballot(gsum > 0.0 && cum > target);
         if (hit) {
             const int gl = __builtin_ctzll(hit), g = g0 + gl;
             const double before = gl ? __shfl(cum, gl - 1) : base;
             const double e = (double)ws[g * 65 + lane];
-            const unsigned long long in = __ballot(before + wave_incl_scan_f64(e, lane) > target);
+            const unsigned long long in = __ballot(e > 0.0 && before + wave_incl_scan_f64(e, lane) > target);
             const unsigned long long mass = __ballot(e > 0.0);
             // (the two sums of a group may differ in the last bit: then its last id with mass)
             pick = s0 + g * 64 + (in ? __builtin_ctzll(in) : 63 - __builtin_clzll(mass));

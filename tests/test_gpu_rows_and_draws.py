@@ -62,3 +62,20 @@ def test_draws_fall_into_their_interval(vocab):
         r, u = i // len(us), float(us[i % len(us)])
         assert 0 <= t < vocab and p[r, t] > 0
         assert (F[r, t - 1] if t else 0.0) - 2e-5 <= u < F[r, t] + 2e-5
+
+
+@pytest.mark.parametrize("vocab,stride", [(32016, 3 * 64), (32016, 67), (65537, 5 * 64), (163840, 1000)])
+def test_draws_over_rows_that_are_mostly_masked(vocab, stride):
+    """One id in `stride` has mass (groups of 64 ids without any in between): every draw is an id that has, and the one whose
+    interval holds u (bound as above)."""
+    import paper_2503_14153_amd as sd
+    g = torch.Generator(device="cuda").manual_seed(stride)
+    logits = torch.full((1, vocab), -float("inf"), device="cuda")
+    logits[0, 7::stride] = torch.randn(len(range(7, vocab, stride)), generator=g, device="cuda") * 3
+    us = torch.cat([torch.rand(2000, generator=g, device="cuda"), torch.tensor([0.0, 0.5, 1 - 2 ** -24], device="cuda")])
+    rows = torch.zeros(len(us), device="cuda", dtype=torch.int32)
+    got = sd.sample_tokens(logits, rows, us, 0.8).cpu().numpy()
+    F = np.cumsum(torch.softmax(logits.double() / 0.8, -1).cpu().numpy()[0])
+    u = us.cpu().numpy()
+    assert (got >= 7).all() and (got < vocab).all() and ((got - 7) % stride == 0).all()
+    assert (F[got - 1] - 2e-5 <= u).all() and (u < F[got] + 2e-5).all()
