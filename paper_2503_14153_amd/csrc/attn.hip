@@ -459,7 +459,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     const int TB = Tp / 32;
     const int TBW = (TB % 2 == 0) ? 2 : 1;
     const int nparts = ncparts + tree_sep, TG = TB / TBW;     // tree_sep: number of parts with tree blocks only
-    const bool even = per == 0;                        // (one query block per sequence only, see attn_geometry)
+    const bool even = per == 0;                        // (one query block per sequence, built in this launch: see attn_geometry)
     if (even) per = (int)(uint32_t)((0x100000000ull + ncparts - 1) / ncparts);
     dim3 grid(nparts, nh * TG, B);
     int xcd_stride = 0;
@@ -481,7 +481,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
     } while (0)
 #define ATT_M(HD_, TBW_, AW_, FR_, NS_, MAP_)                                                                    \
     do {                                                                                                        \
-        if (TBW_ == 1 && AW_ == 4 && even) ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, (TBW_ == 1 && AW_ == 4));       \
+        if (TBW_ == 1 && FR_ == 1 && even) ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, (TBW_ == 1 && FR_ == 1));       \
         else ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, false);                                                       \
     } while (0)
 #define ATT(HD_, TBW_, AW_, FR_, NS_)                                                                            \

@@ -21,11 +21,11 @@
 // NORM: X's rows go through RMSNorm: the operand is x * gain, the sums of squares ride along, and the row's 1 / rms factor
 // is applied to the result (a product is linear in its rows).
 // The two column blocks are chosen so that a thread of the epilogue holds what belongs together:
-//   F32_STORE  columns 32t and 32t + 16: out[m][n] = v + bias[n]
+//   F32_STORE  columns 32t and 32t + 16: out[m][n] = v
 //   F32_ADD    the same, added to out (the residual stream)
 //   F32_QKV    dims i and i + hd/2 of one head: rotated at the row's position -> q; keys and values -> tree scratch
 //   F32_GATE   gate column and up column: out[m][f] = silu(gate) * up
-//   F32_HEADS  as STORE, z = v + bias: out row (n / d) * M + m, column n % d: h + silu(z), h = the normalised row
+//   F32_HEADS  as STORE, z = v + bias[n]: out row (n / d) * M + m, column n % d: h + silu(z), h = the normalised row
 enum { F32_STORE, F32_ADD, F32_QKV, F32_GATE, F32_HEADS };
 struct F32Linear {
     const float *X, *gain, *W, *bias;
@@ -125,8 +125,8 @@ __global__ __launch_bounds__(512) void k_f32_linear(F32Linear a) {
     const int n0 = c0 + col, n1 = c1 + col;
     if constexpr (MODE == F32_STORE || MODE == F32_ADD) {
         float* o = a.out + (size_t)m * a.ldo;
-        if (n0 < a.N) o[n0] = MODE == F32_ADD ? o[n0] + v0 : v0 + (a.bias ? a.bias[n0] : 0.f);
-        if (n1 < a.N) o[n1] = MODE == F32_ADD ? o[n1] + v1 : v1 + (a.bias ? a.bias[n1] : 0.f);
+        if (n0 < a.N) o[n0] = MODE == F32_ADD ? o[n0] + v0 : v0;
+        if (n1 < a.N) o[n1] = MODE == F32_ADD ? o[n1] + v1 : v1;
     } else if constexpr (MODE == F32_QKV) {
         const int d = a.nh * a.hd, which = n0 / d, c = n0 - which * d, i = c % a.hd;
         const size_t at = (size_t)m * d + c;

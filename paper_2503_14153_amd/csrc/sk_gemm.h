@@ -64,7 +64,7 @@ static __device__ inline SkIter sk_walk_next(SkWalk& w, int KB) {
 // A workgroup (or a whole launch) without units: has_work() is false, the other calls do nothing.
 template <int MT>
 struct SkGemm {
-    static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_sk_rows only");
+    static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_rows only");
     // Ring depth R, and XK contraction blocks per activation chunk (a barrier each). A shallow ring: what a wave holds in
     // flight when its stream ends is still to be multiplied then, and a workgroup's steps are padded to a multiple of R.
     // Depth 16 (chunks of 8 / MT) kept more bytes in flight and was slower: down projection of the 7B shape (43 steps a
@@ -74,6 +74,7 @@ struct SkGemm {
     static constexpr int R = 4;
     static constexpr int XK = MT == 8 ? 1 : 2;      // contraction blocks per chunk
     static constexpr int CPI = R / XK;               // chunks per outer iteration (2 or 4)
+    static_assert(CPI % 2 == 0, "chunk c of every iteration is in LDS buffer c & 1");
     static constexpr int XF = XK * MT * 2;           // fragments per chunk
     static constexpr int XP = (XF * 64 + 511) / 512; // 16-byte pieces per thread per chunk (one row block: half the threads)
     static constexpr int PER_KB = MT * 2 * 64;       // 16-byte units of the row blocks per contraction block
@@ -189,7 +190,7 @@ struct SkGemm {
             // (the barrier below, before the first MFMA, also publishes the factors)
         }
 
-        int nseg = 0, odd = 0;
+        int nseg = 0;
         xstore(xr[0], 0);
         xload(xr[0], nxt, 0);
         __syncthreads();
@@ -203,8 +204,8 @@ struct SkGemm {
                     const int i = c * XK + j;                         // ring slot (compile-time)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) {
-                        bf16x8 hi = xs[(c + odd) & 1][((j * MT + mt) * 2) * 64 + lane];
-                        bf16x8 lo = xs[(c + odd) & 1][((j * MT + mt) * 2 + 1) * 64 + lane];
+                        bf16x8 hi = xs[c & 1][((j * MT + mt) * 2) * 64 + lane];
+                        bf16x8 lo = xs[c & 1][((j * MT + mt) * 2 + 1) * 64 + lane];
                         acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, w[i], acc[mt], 0, 0, 0);
                         acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, w[i], acc[mt], 0, 0, 0);
                     }
@@ -213,7 +214,7 @@ struct SkGemm {
                 // the chunk consumed next goes to the other buffer; its register slot is refilled
                 // with the chunk one outer iteration further on
                 const int nc = (c + 1) % CPI;
-                xstore(xr[nc], (c + 1 + odd) & 1);
+                xstore(xr[nc], (c + 1) & 1);
                 if (c + 1 < CPI) xload(xr[nc], nxt, c + 1);
                 else xload(xr[nc], nx2, 0);
                 __syncthreads();
@@ -251,7 +252,6 @@ struct SkGemm {
                     for (int v = 0; v < 16; ++v) acc[mt][v] = 0.f;
             }
             if (nxt.valid == 0) break;
-            odd ^= CPI & 1;
             cur = nxt;
             nxt = nx2;
             nx2 = sk_walk_next<R>(walk, KB);
