@@ -1310,7 +1310,8 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
                                      (uint64_t)(uintptr_t)io->logits, (uint64_t)(uintptr_t)io->argmax,
                                      (uint64_t)(uintptr_t)io->head_logits, (uint64_t)(uintptr_t)cand,
                                      (uint64_t)m->draft_schedule, (uint64_t)heads,
-                                     (uint64_t)(m->use_fused ? 1 : 0) | ((uint64_t)m->sync_timeout_ticks << 1)};
+                                     (uint64_t)(m->use_fused ? 1 : 0) | ((uint64_t)m->sync_timeout_ticks << 1),
+                                     (uint64_t)(uintptr_t)m->timeline, (uint64_t)m->timeline_launches};
         hipGraphExec_t exec = nullptr;
         for (const sd_model::StepGraph& g : m->graphs)
             if (g.key == key) { exec = g.exec; break; }

@@ -139,3 +139,28 @@ def test_rows_of_a_replayed_step_can_be_committed(sd, dtype):
     model.set_graph_mode(False)
     for a, b in zip(got[False], got[True]):
         assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_replays_write_the_timeline_only_while_it_is_set(sd):
+    """The buffer of sd_set_layer_timeline is the caller's only while it is set: a step captured with it must not be replayed
+    after it was taken away, nor one captured without it while it is there."""
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16")
+    model = sd.Model(shape, {k: v.cuda() for k, v in wl.make_weights(shape).items()}, 32)
+    kv = sd.KVCache(model, 1, 128)
+    words = torch.zeros((shape.vocab + 31) // 32, dtype=torch.int32, device="cuda")
+    tree = sd.Tree(*wl.default_tree(16, shape.n_medusa, shape.topk), shape.n_medusa, shape.topk)
+    kv.set_draft([1], np.arange(shape.n_medusa * shape.topk).reshape(1, shape.n_medusa, shape.topk))
+    buf = torch.zeros((shape.n_layers + 1, 24, 256), dtype=torch.int64, device="cuda")
+    model.set_fused(True)
+    model.set_graph_mode(True)
+    out = None
+    for on in (False, True, False, True, True):
+        buf.zero_()
+        model.set_layer_timeline(buf if on else None)
+        kv.set_len([40])
+        out = sd.spec_step(model, kv, tree, words, out=out)
+        torch.cuda.synchronize()
+        assert bool(buf.any()) == on
+    model.set_layer_timeline(None)
+    model.set_graph_mode(False)
+    assert kv.len() == [40 + int(out.n_accept[0])]
