@@ -281,10 +281,13 @@ int sd_set_draft_schedule(sd_model* m, int32_t schedule);
  * step is still lossless, its drafts are merely stale. Returns SD_ERR_NULL for a NULL model.             */
 int sd_set_greedy_drafts(sd_model* m, int32_t on);
 
-/* The persistent layer kernel (on by default where the device can hold its 256 workgroups of 512 threads at once,
- * and for passes of 32, 64 or 256 rows): all stages of the verifying pass between two attention launches run as
- * phases of one launch, separated by barriers across the grid, instead of one launch per stage; results are
- * bit-identical either way. sd_set_fused(m, 0) selects one launch per stage.
+/* The persistent layer kernel (off by default; on = 1 takes effect where the device can hold its 256 workgroups of 512
+ * threads at once, on a bfloat16 model, for passes whose padded rows make 32, 64 or 256): all stages of the verifying
+ * pass between two attention launches run as phases of one launch, separated by barriers across the grid, instead of
+ * one launch per stage (on = 0, the faster of the two). The two agree to float32 rounding, not bit for bit: the norms
+ * apply their factor after the product instead of before it, rows are padded to [sequence][32 k] instead of packed,
+ * and ragged batches split their attention differently, so sums are taken in another order and a bfloat16 rounding of
+ * a key or value can fall the other way.
  * Every wait of that kernel is bounded (default 50 ms; sd_set_sync_timeout: 0 .. 10 s, in microseconds). If a
  * wait runs out, the kernel still ends, the outputs enqueued since are invalid, and the next sd_kv_len on a cache
  * of this model returns SD_ERR_HIP once (after which decoding can go on, e.g. with sd_set_fused(m, 0)).           */

@@ -1442,7 +1442,7 @@ extern "C" int sd_verify_tree_typical(const sd_tree* tree, int32_t batch, int32_
     memset(&va, 0, sizeof(va));
     va.parent = tree->parent; va.depth = tree->depth; va.T = T; va.H = tree->H; va.fallback = trunc_fallback;
     va.src_stride = T; va.Tp = tree->Tp; va.V = vocab;
-    va.tok = tok; va.am = tok; va.stop_mask = stop_mask;      // am is not read under typical acceptance
+    va.tok = tok; va.am = tok; va.stop_mask = stop_mask;      // (am decides nothing under typical acceptance; it is read, so it must be readable)
     va.n_accept = n_accept; va.n_accept_raw = n_accept_raw; va.tokens = tokens; va.src_slots = src_slots;
     va.logits = logits; va.ld = vocab; va.row_stats = (const float4*)row_stats; va.inv_temperature = 1.f / temperature;
     launch_verify(va, batch, s);
@@ -1504,7 +1504,7 @@ extern "C" int sd_verify_tree_typical_static(const sd_tree* tree, int32_t batch,
     memset(&va, 0, sizeof(va));
     va.parent = tree->parent; va.depth = tree->depth; va.T = T; va.H = tree->H; va.fallback = trunc_fallback;
     va.src_stride = T; va.Tp = tree->Tp; va.V = vocab;
-    va.tok = tok; va.am = tok; va.stop_mask = stop_mask;      // am is not read under typical acceptance
+    va.tok = tok; va.am = tok; va.stop_mask = stop_mask;      // (am decides nothing under typical acceptance; it is read, so it must be readable)
     va.n_accept = n_accept; va.n_accept_raw = n_accept_raw; va.tokens = tokens; va.src_slots = src_slots;
     va.logits = logits; va.ld = vocab; va.row_stats = stats; va.inv_temperature = 1.f / temperature;
     launch_verify(va, batch, s);

@@ -24,7 +24,7 @@ static inline AttnGeom attn_geometry(int n_heads, int max_parts, int B, int Tp, 
     // two parts that share every sequence's own blocks evenly (per = 0). Launch at eight 7B-shaped sequences of 1024 - 4096
     // rows: plain decoding 88 -> 78 us, 32-node trees 88 -> 82; one of 4096 beside seven of 32 rows 56 -> 36; but eight of
     // 2560 rows 74.6 -> 77.6, so not where they are alike. (Three and four parts 85 and 95 us: one workgroup of this
-    // kernel fits a compute unit, and held to 128 registers, so that two fit, it spills: 107 us.)
+    // kernel fits a compute unit, and held to 256 registers, so that two fit, it spills: 107 us.)
     if (P == 1 && TB == 1 && ragged && nblk >= 8) {
         g.tree_sep = 0;
         g.ncparts = g.nparts = 2;

@@ -298,7 +298,7 @@ void launch_reduce_selected(PartView pv, float* dst, const int32_t* sel, int B, 
 }
 
 // ------------------------------------------------------------------------------------------
-#define SK_MAX_WG 256       // one workgroup of 8 waves per CU
+#define SK_MAX_WG 256       // one workgroup of 8 waves per CU (at 94 registers k_gemm_sk leaves room for two: not tried as a plan)
 #ifndef SK_SMALL_U
 #define SK_SMALL_U (16 * SK_MAX_WG * 2)   // (column groups x contraction blocks) up to which half the workgroups are used
 #endif
@@ -339,8 +339,10 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     p->slot0_dev = nullptr;
     p->NG = (NB + 7) / 8;
     const int U = p->NG * KB;
-    int G = U / 16;                                   // at least one ring length of steps each
+    int G = U / 16;                                   // at least 16 steps each
     if (G > SK_MAX_WG) G = SK_MAX_WG;
+    // (The figures below were taken with a weight ring 16 steps deep. With the ring of 4, looked at again: balanced over 256
+    // workgroups plain decoding is 5 % slower, the O projection on 256 workgroups level.)
     // Prefer a split in which no workgroup's range crosses a column group: s workgroups per group with s a divisor
     // of KB. Every workgroup then has ONE segment, writes its partial tile once, at the end of its stream, and a
     // group has exactly s slots. With ranges that straddle groups a workgroup stores a tile in the middle of its

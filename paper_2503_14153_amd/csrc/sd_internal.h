@@ -269,7 +269,6 @@ void launch_f32_kv_rows(float* kc, float* vc, float* k_rows, float* v_rows, int 
                         hipStream_t s);
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out,
                       int M, int d, int MB, const int32_t* gather, hipStream_t s);
-// RMSNorm with the scale deferred: operand = x * gain, ssq_part = partial sums of squares in SkRowScale's layout
 void launch_rope_kv(PartView pv, RowTable rt, RowRef rr, void* q_packed, void* kt, void* vt, int B, int Tp, int nh,
                     int hd, hipStream_t s);
 void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, const void* kt, const void* vt,

@@ -3,12 +3,12 @@
 #pragma once
 #include "sd_internal.h"
 
-// Stores of one row block (rows row0 .. row0 + 31) of a partial tile of `rows` rows of ldo floats (all wave-uniform). Write-through: the tiles are consumed by
-// other XCDs anyway, and lines left dirty in this XCD's L2 would only be written back at the end of the kernel,
-// lengthening it. The rows of the last row block that do not exist (plain decoding: 31 of 32) lie past the buffer
-// resource's size and the hardware drops their stores: no branch and no mask in the epilogue (written with either, the
-// 64-row launches took 0.5 us longer each although all of their rows exist). One resource per row block: 32 * ldo * 4
-// bytes at most, a 32-bit size for every projection that fits the card.
+// Stores of one row block (rows row0 .. row0 + 31) of a partial tile of `rows` rows of ldo floats (all wave-uniform).
+// Write-through: the tiles are consumed by other XCDs anyway, and lines left dirty in this XCD's L2 would only be written
+// back at the end of the kernel, lengthening it. The rows of the last row block that do not exist (plain decoding: 31 of
+// 32) lie past the buffer resource's size and the hardware drops their stores: no branch and no mask in the epilogue
+// (written with either, the 64-row launches took 0.5 us longer each although all of their rows exist). One resource per
+// row block: 32 * ldo * 4 bytes at most, a 32-bit size for every projection that fits the card.
 struct TileStore {
     __amdgpu_buffer_rsrc_t rsrc;
     __device__ __forceinline__ TileStore(float* tile, int row0, int rows, int ldo)
@@ -50,7 +50,7 @@ static __device__ inline SkIter sk_walk_next(SkWalk& w, int KB) {
     return r;
 }
 
-// LDS the GEMM needs: two activation chunks of 16 fragments, and (for a GEMM that applies the deferred RMS scale
+// LDS the GEMM needs: two activation chunks of up to 16 fragments, and (for a GEMM that applies the deferred RMS scale
 // of its rows) the per-row factors and the scratch of their reduction
 #define SK_LDS_UNITS (2 * 16 * 64)
 #define SK_LDS_SCALE_FLOATS (256 + 512)
@@ -67,10 +67,11 @@ struct SkGemm {
     static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_rows only");
     // Ring depth R, and XK contraction blocks per activation chunk (a barrier each). A shallow ring: what a wave holds in
     // flight when its stream ends is still to be multiplied then, and a workgroup's steps are padded to a multiple of R.
-    // Depth 16 (chunks of 8 / MT) kept more bytes in flight and was slower: down projection of the 7B shape (43 steps a
-    // workgroup) 25.6 -> 22.2 us at 64 rows and 20.8 -> 16.4 at 1 row, O 14.7 -> 13.6, QKV 26.6 -> 25.9; full step of the
-    // 64-node tree 4849 (16), 4768 (8), 4690 (4, chunks of 4), 4682 (6, chunks of 2), 4620 us (4, chunks of 2), 5405
-    // (2). With eight row blocks a step holds 16 MFMAs and rings of 6 and 8 measured slower too.
+    // Depth 16 (chunks of 8 / MT) keeps more bytes in flight and is slower: down projection of the 7B shape (43 steps a
+    // workgroup) 25.6 -> 22.2 us at 64 rows and 20.8 -> 16.4 at 1 row, O 14.7 -> 13.6, QKV 26.6 -> 25.9; in turn on one
+    // box, the full step of the 64-node tree 4850 -> 4739 us, four layers over 16384 rows 992 -> 976, eight sequences of
+    // plain decoding 925 -> 906. Depth 8 lies between, 6 is level with 4, 2 is 17 % slower. With eight row blocks a step
+    // holds 16 MFMAs and rings of 6 and 8 measured slower too.
     static constexpr int R = 4;
     static constexpr int XK = MT == 8 ? 1 : 2;      // contraction blocks per chunk
     static constexpr int CPI = R / XK;               // chunks per outer iteration (2 or 4)
