@@ -1010,9 +1010,12 @@ static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int 
 static void commit_rows(sd_model* m, sd_kv* kv, const ScratchRows& sc, bool by_seq, const int32_t* slots, const int32_t* n_acc,
                         int W, hipStream_t s) {
     const sd_config& c = m->cfg;
-    RowMap rm;                                         // (off: entry of the lists)
+    // Entry of the lists and last row in one word: read from another line of the arguments, the last row costs the bfloat16
+    // kernel 0.2 us of a step's 6.6.
+    static_assert(SD_MAX_BATCH <= 256, "an entry fits 8 bits");
+    RowMap rm;
     memset(&rm, 0, sizeof(rm));
-    for (int i = 0; i < sc.n; ++i) { rm.seq[i] = sc.seq[i]; rm.len[i] = sc.len[i]; rm.off[i] = by_seq ? rm.seq[i] : i; }
+    for (int i = 0; i < sc.n; ++i) { rm.seq[i] = sc.seq[i]; rm.off[i] = (by_seq ? sc.seq[i] : i) + 256 * (sc.len[i] - 1); }
     if (m->f32)
         launch_f32_kv_commit(m->f.kt, m->f.vt, kv->kc32, kv->vc32, slots, n_acc, kv->n_old, rm, sc.row0, kv->B, c.n_layers, sc.n,
                              c.d_model, sc.M, kv->cap, W, s);

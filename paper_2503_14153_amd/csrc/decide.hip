@@ -544,8 +544,8 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 // Commit the kept nodes' K/V rows: tree-scratch row src_slots[j] -> cache row n_old + j, for
 // every layer and head. A kept node at chain index j was rotated for position n_old + j
 // already (depth = chain index), so this is a pure copy.
-// grid: x = head, y = sequence b of the pass that filled the scratch (sequence rm.seq[b] of the cache, entry rm.off[b] of
-// src_slots, n_accept and n_old; slots past its own rm.len[b] rows give the last of them), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
+// grid: x = head, y = sequence b of the pass that filled the scratch (sequence rm.seq[b] of the cache; rm.off[b] = entry of
+// src_slots, n_accept and n_old + 256 * its last scratch row, which a slot past it stands for), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
 // whole 16-byte pieces that lie side by side in the cache:
 //   values: a 16-byte piece of the value layout holds one dim of EIGHT rows (a "group": of a 16-row half of a block,
 //     the four rows of one quad and of the quad two further on), so a row cannot move as a piece, and a piece
@@ -556,7 +556,7 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 //     has new rows, where one does not, was measured and is slower, short lists included). The new rows' elements
 //     come from a copy in LDS of the scratch groups that hold a kept row, fetched once as whole pieces: picked out
 //     of global memory two bytes at a time they cost a cache lookup per element and lane, eight times the lookups
-//     of everything else here (mirror_groups = 0: no room for that copy, the elements are gathered from global
+//     of everything else here (MIRROR = false: no room for that copy, the elements are gathered from global
 //     memory).
 //   keys: a row's 16-byte pieces move as they are; one task = 8 rows x 8 pieces, rows fastest (the same piece of
 //     neighbouring rows is 16 bytes further on, so eight lanes write 128 contiguous bytes).
@@ -564,27 +564,27 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 #define KVC_THREADS 512
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 static __device__ inline int vgroup_of(int c) { return (c >> 5) * 4 + ((c >> 4) & 1) * 2 + ((c >> 2) & 1); }
+template <bool MIRROR>
 __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const uint16_t* __restrict__ kt, const uint16_t* __restrict__ vt, uint16_t* __restrict__ kc,
     uint16_t* __restrict__ vc, const int32_t* __restrict__ src_slots, const int32_t* __restrict__ n_accept,
-    const int32_t* __restrict__ n_old, RowMap rm, int nh, int hd, int TB, int cap_blocks, int W, int mirror_groups,
-    int L, int lpw, size_t layer_stride_t, size_t layer_stride_c) {
+    const int32_t* __restrict__ n_old, RowMap rm, int nh, int hd, int TB, int cap_blocks, int W, int L, int lpw, size_t layer_stride_t, size_t layer_stride_c) {
     extern __shared__ __align__(16) uint16_t kvc_mirror[];          // [kept group][hd / 32][32 dims][8 rows]
     __shared__ int s_slots[SD_MAX_TREE];
     __shared__ uint32_t s_need;
     const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int l0 = blockIdx.z * lpw, l1 = min(l0 + lpw, L);
     const int wave = tid >> 6, lane = tid & 63;
-    const int lst = rm.off[b];                                      // whose list, count and old length these are
+    const int lst = rm.off[b] & 255, last = rm.off[b] >> 8;         // whose list, count and old length these are; its last row
     const int a = min(n_accept[lst], W);                            // <= SD_MAX_TREE < KVC_THREADS
     if (a <= 0) return;
     const int n = n_old[lst];
-    const int slot = tid < a ? min(max(src_slots[(size_t)lst * W + tid], 0), rm.len[b] - 1) : 0;
+    const int slot = tid < a ? min(max(src_slots[(size_t)lst * W + tid], 0), last) : 0;
     if (tid == 0) s_need = 0;
     __syncthreads();
     if (tid < a) {
         s_slots[tid] = slot;
-        if (mirror_groups) atomicOr(&s_need, 1u << vgroup_of(slot));
+        if constexpr (MIRROR) atomicOr(&s_need, 1u << vgroup_of(slot));
     }
     __syncthreads();
     const size_t toff0 = ((size_t)b * nh + h) * TB * (32 * hd);
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     // then goes through its layers (the same number of times for every wave: all of them reach the barriers).
     for (int l = l0; l < l1; ++l) {
         const size_t toff = l * layer_stride_t + toff0, coff = l * layer_stride_c + coff0;
-        if (mirror_groups) {                               // (at most min(a, groups of the scratch) <= mirror_groups bits)
+        if constexpr (MIRROR) {                            // (the launch has room for min(W, groups of the scratch) groups)
             if (l > l0) __syncthreads();                   // the previous layer's readers are done
             for (int i = tid; i < TB * 4 * EB * 32; i += KVC_THREADS) {
                 const int grp = i / (EB * 32), eb = (i >> 5) % EB, er = i & 31;
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {              // (any kept row's element where the piece's row stays)
                     const int c = s_slots[min(max((q >> 2) * 8 + (q & 3) - lo, 0), a - 1)];
-                    if (mirror_groups) {
+                    if constexpr (MIRROR) {
                         const int cs = __popc(need & ((1u << vgroup_of(c)) - 1u));
                         g[q] = kvc_mirror[((cs * EB + eb) * 32 + er) * 8 + ((c >> 3) & 1) * 4 + (c & 3)];
                     } else {
@@ -653,14 +653,17 @@ void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void
                       int TB, int cap_blocks, int W, hipStream_t s) {
     size_t lst = (size_t)B * nh * TB * 32 * hd, lsc = (size_t)kv_B * nh * cap_blocks * 32 * hd;
     // LDS copy of the scratch groups (8 rows x hd) with a kept row: at most one per row, at most all of them
-    int groups = W < TB * 4 ? W : TB * 4;
-    size_t mirror = (size_t)groups * 8 * hd * 2;
-    if (mirror > 60 * 1024) { groups = 0; mirror = 0; }  // (eight-block scratch at head_dim 128, 31 rows or more)
+    const int groups = W < TB * 4 ? W : TB * 4;
+    const size_t mirror = (size_t)groups * 8 * hd * 2;
     int lpw = (int)((size_t)B * nh * L / 1024);            // layers per workgroup: one while the launch is small
     lpw = lpw < 1 ? 1 : lpw > L ? L : lpw;
-    hipLaunchKernelGGL(k_kv_commit, dim3(nh, B, (L + lpw - 1) / lpw), dim3(KVC_THREADS), mirror, s,
-                       (const uint16_t*)kt_all, (const uint16_t*)vt_all, (uint16_t*)kc_all, (uint16_t*)vc_all, src_slots,
-                       n_accept, n_old, rm, nh, hd, TB, cap_blocks, W, groups, L, lpw, lst, lsc);
+#define KVC(MIRROR_, lds_)                                                                                                  \
+    hipLaunchKernelGGL(k_kv_commit<MIRROR_>, dim3(nh, B, (L + lpw - 1) / lpw), dim3(KVC_THREADS), lds_, s,                 \
+                       (const uint16_t*)kt_all, (const uint16_t*)vt_all, (uint16_t*)kc_all, (uint16_t*)vc_all, src_slots,  \
+                       n_accept, n_old, rm, nh, hd, TB, cap_blocks, W, L, lpw, lst, lsc)
+    if (mirror <= 60 * 1024) KVC(true, mirror);
+    else KVC(false, 0);                                    // (eight-block scratch at head_dim 128, 31 rows or more)
+#undef KVC
 }
 
 // ------------------------------------------------------------------------------------------

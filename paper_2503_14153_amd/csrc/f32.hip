@@ -294,15 +294,15 @@ void launch_f32_attn(const float* q, const float* kc, const float* vc, const flo
 
 // ------------------------------------------------------------------------------------------
 // Commit: row src_slots[list][j] of pass sequence i -> cache row n_old[list] + j of sequence rm.seq[i], for j < n_accept[list],
-// list = rm.off[i], every layer, K and V. The sequence owns rm.len[i] scratch rows from row0.seq[i] on; a slot past them gives
-// its last one, never another sequence's row. grid (row j, layer * B + i), 64 threads over the d columns.
+// every layer, K and V; rm.off[i] = list + 256 * the sequence's last row. Its rows start at scratch row row0.seq[i]; a slot past
+// the last gives the last, never another sequence's row. grid (row j, layer * B + i), 64 threads over the d columns.
 __global__ void k_f32_kv_commit(const float* __restrict__ kt, const float* __restrict__ vt, float* __restrict__ kc,
                                 float* __restrict__ vc, const int32_t* __restrict__ src_slots,
                                 const int32_t* __restrict__ n_accept, const int32_t* __restrict__ n_old, RowMap rm, SeqList row0,
                                 int B, int d, int cap, int W, size_t layer_stride_t, size_t layer_stride_c) {
-    const int j = blockIdx.x, l = blockIdx.y / B, i = blockIdx.y % B, lst = rm.off[i];
+    const int j = blockIdx.x, l = blockIdx.y / B, i = blockIdx.y % B, lst = rm.off[i] & 255;
     if (j >= min(n_accept[lst], W)) return;
-    const int src = row0.seq[i] + min(max(src_slots[(size_t)lst * W + j], 0), rm.len[i] - 1), dst = n_old[lst] + j;
+    const int src = row0.seq[i] + min(max(src_slots[(size_t)lst * W + j], 0), rm.off[i] >> 8), dst = n_old[lst] + j;
     const size_t so = l * layer_stride_t + (size_t)src * d, dofs = l * layer_stride_c + ((size_t)rm.seq[i] * cap + dst) * d;
     for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
         *(f32x4*)(kc + dofs + c) = *(const f32x4*)(kt + so + c);

@@ -305,8 +305,8 @@ void launch_sample_root(const float* logits, int ld, int V, const int32_t* last_
 void launch_build_labels(const int32_t* l0, int B, int S, int H, int32_t frag, int32_t pad, int32_t ignore,
                          int keep_all, int32_t* labels, hipStream_t s);
 void launch_copy_row_stats(const float4* src, float4* dst, int B, int T, int Tp, hipStream_t s);
-// commit: entry i of the pass is sequence rm.seq[i] of the cache and entry rm.off[i] of the lists; it has rm.len[i] rows, to which
-// slots are clamped (float32: from row row0.seq[i] of the scratch on)
+// commit: sequence i of the pass is sequence rm.seq[i] of the cache; rm.off[i] = its entry of the lists + 256 * its last row, to
+// which slots are clamped (float32: counted from row row0.seq[i] of the scratch)
 void launch_kv_commit(const void* kt_all, const void* vt_all, void* kc_all, void* vc_all,
                       const int32_t* src_slots, const int32_t* n_accept, const int32_t* n_old, const RowMap& rm, int kv_B,
                       int L, int B, int nh, int hd, int TB, int cap_blocks, int W, hipStream_t s);
