@@ -8,11 +8,11 @@
 //           from memory into a per-wave ring of four 8 KiB slots in LDS (global_load_lds_dwordx4) and is read
 //           from there: the other way to stage K/V or weight tiles; 32 KiB in flight per wave, twice `stream`'s
 // and what the ingredients of the weight-streaming GEMM cost beside the bare weight stream:
-//   sd_calib parts <NB> <KB> [reps]   a projection with NB column blocks of 32 and KB contraction blocks of 16, in
-//           the GEMM's launch shape and unit walk (256 workgroups of 8 waves, ring of 16 fragments per wave),
-//           weights never touched before (a fresh region per launch): the stream alone, + the partial-tile
-//           stores of a 64-row pass at every segment end, + the activation chunks (L2 -> registers -> LDS, a
-//           barrier per chunk), + both. No arithmetic: the figures bound what the real kernel can reach.
+//   sd_calib parts <NB> <KB> [reps] [workgroups]   a projection with NB column blocks of 32 and KB contraction blocks
+//           of 16, in the GEMM's launch shape and unit walk (that many workgroups of 8 waves, 256 unless given; ring of
+//           4 fragments per wave), weights never touched before (a fresh region per launch): the stream alone, + the
+//           partial-tile stores of a 64-row pass at every segment end, + the activation chunks (two contraction
+//           blocks, L2 -> registers -> LDS, a barrier per chunk), + both. No arithmetic.
 //   sd_calib ratio [reps]             the weight stream of a 384 MiB matrix while every thread also reads x:w
 //           times as many bytes from a 1 MiB buffer that stays in L2 (x:w = 0 .. 4): what an operand costs that
 //           is shared by fewer waves
@@ -102,39 +102,42 @@ template <int STORES, int XCHUNKS>
 __global__ __launch_bounds__(512) void k_calib_parts(const u4* __restrict__ w, int NB, int KB, const u4* __restrict__ x,
                                                      float* __restrict__ out, int ldo, size_t slot_stride, int nslots,
                                                      unsigned* __restrict__ sink) {
-    __shared__ u4 xs[2][1024];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = blockIdx.x;
+    constexpr int R = 4, XK = 2;                         // ring; contraction blocks per activation chunk
+    __shared__ u4 xs[2][512];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = blockIdx.x, G = gridDim.x;
     const int U = NB / 8 * KB;                           // units: (column group of 8 blocks, contraction block)
-    const int u0 = (int)((long long)g * U / 256), u1 = (int)((long long)(g + 1) * U / 256);
+    const int u0 = (int)((long long)g * U / G), u1 = (int)((long long)(g + 1) * U / G);
     auto addr = [&](int u) {                             // fragment of this wave in unit u ([kb][nb] layout)
         if (u >= u1) u = u1 - 1;
         const int ng = u / KB, kb = u - ng * KB;
         return w + ((size_t)kb * NB + ng * 8 + wave) * 64 + lane;
     };
-    u4 ring[16];
+    auto chunk = [&](int u) { return x[(size_t)(u % KB) * 256 + tid]; };     // of a 64-row two-term operand: 8 KiB
+    u4 xr[R / XK], ring[R];
+    if (XCHUNKS)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) ring[i] = __builtin_nontemporal_load(addr(u0 + i));
+        for (int c = 0; c < R / XK; ++c) xr[c] = chunk(u0 + c * XK);
+#pragma unroll
+    for (int i = 0; i < R; ++i) ring[i] = __builtin_nontemporal_load(addr(u0 + i));
     u4 acc = {0, 0, 0, 0};
     int slot = g % nslots;
-    for (int u = u0; u < u1; u += 16) {
+    for (int u = u0; u < u1; u += R) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            if (XCHUNKS) {                               // a chunk of 8 contraction blocks of a 64-row operand: 16 KiB
-                const int kb = (u + c * 8) % KB;
-                u4 a = x[(size_t)kb * 128 + tid], b = x[(size_t)kb * 128 + 512 + tid];
-                xs[c][tid] = a;
-                xs[c][512 + tid] = b;
+        for (int c = 0; c < R / XK; ++c) {
+            if (XCHUNKS) {                               // fetched one ring ahead, as the GEMM does
+                xs[c & 1][tid] = xr[c];
+                xr[c] = chunk(u + R + c * XK);
                 __syncthreads();
-                acc ^= xs[c][(tid * 7) & 1023];
+                acc ^= xs[c & 1][(tid * 7) & 511];
             }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int i = c * 8 + j;
+            for (int j = 0; j < XK; ++j) {
+                const int i = c * XK + j;
                 acc ^= ring[i];
-                ring[i] = __builtin_nontemporal_load(addr(u + 16 + i));
+                ring[i] = __builtin_nontemporal_load(addr(u + R + i));
             }
         }
-        const int ng_now = u / KB, ng_next = (u + 16 < u1) ? (u + 16) / KB : -1;
+        const int ng_now = u / KB, ng_next = (u + R < u1) ? (u + R) / KB : -1;
         if (STORES && ng_now != ng_next) {               // a segment ends: this wave's 64 x 32 floats, write-through
             float* o = out + (size_t)slot * slot_stride + (size_t)(ng_now * 8 + wave) * 32 + (lane & 31);
             const int gq = lane >> 5;
@@ -182,21 +185,22 @@ __global__ __launch_bounds__(512) void k_calib_ratio(const u4* __restrict__ w, s
 
 #define CK(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) { fprintf(stderr, "%s: %s\n", #x, hipGetErrorString(e_)); return 1; } } while (0)
 
-static int run_parts(int NB, int KB, int reps) {
-    if (NB < 8 || NB % 8 || KB < 16 || KB > 4096 || (size_t)NB * KB > (1u << 20)) {
-        fprintf(stderr, "parts: NB must be a multiple of 8, 16 <= KB <= 4096, NB * KB <= 2^20\n");
+static int run_parts(int NB, int KB, int reps, int G) {
+    if (NB < 8 || NB % 8 || KB < 16 || KB > 4096 || (size_t)NB * KB > (1u << 20) || reps < 1 || G < 1 || G > 256 || NB / 8 * KB < G) {
+        fprintf(stderr, "parts: NB must be a multiple of 8, 16 <= KB <= 4096, NB * KB <= 2^20, 1 .. 256 workgroups\n");
         return 2;
     }
     const size_t bytes = (size_t)NB * KB * 1024, step = (bytes + (2u << 20)) & ~((size_t)(2u << 20) - 1);
     const size_t pool = step * (size_t)(reps + 2) < (12ull << 30) ? step * (size_t)(reps + 2) : (12ull << 30);
     const int nslots = 16, ldo = NB * 32;
+    const size_t xbytes = (size_t)(KB + 2) * 4096;       // the chunk of the last contraction block ends one block further on
     const size_t slot_stride = (size_t)64 * ldo;
     char *wbuf, *xbuf;
     float* out;
     unsigned* sink;
-    CK(hipMalloc(&wbuf, pool)); CK(hipMalloc(&xbuf, 9u << 20)); CK(hipMalloc(&out, nslots * slot_stride * 4));
+    CK(hipMalloc(&wbuf, pool)); CK(hipMalloc(&xbuf, xbytes)); CK(hipMalloc(&out, nslots * slot_stride * 4));
     CK(hipMalloc(&sink, 4));
-    CK(hipMemset(wbuf, 1, pool)); CK(hipMemset(xbuf, 2, 9u << 20)); CK(hipMemset(out, 0, nslots * slot_stride * 4));
+    CK(hipMemset(wbuf, 1, pool)); CK(hipMemset(xbuf, 2, xbytes)); CK(hipMemset(out, 0, nslots * slot_stride * 4));
     hipEvent_t e0, e1;
     CK(hipEventCreate(&e0)); CK(hipEventCreate(&e1));
     const char* names[4] = {"weight stream alone", "+ partial-tile stores", "+ activation chunks", "+ stores + chunks"};
@@ -207,7 +211,7 @@ static int run_parts(int NB, int KB, int reps) {
             if (off + bytes > pool) off = 0;
             const u4* wp = (const u4*)(wbuf + off);
             CK(hipEventRecord(e0));
-#define PARTS(S, X) hipLaunchKernelGGL((k_calib_parts<S, X>), dim3(256), dim3(512), 0, 0, wp, NB, KB, (const u4*)xbuf, out, ldo, slot_stride, nslots, sink)
+#define PARTS(S, X) hipLaunchKernelGGL((k_calib_parts<S, X>), dim3(G), dim3(512), 0, 0, wp, NB, KB, (const u4*)xbuf, out, ldo, slot_stride, nslots, sink)
             if (var == 0) PARTS(0, 0); else if (var == 1) PARTS(1, 0); else if (var == 2) PARTS(0, 1); else PARTS(1, 1);
 #undef PARTS
             CK(hipEventRecord(e1)); CK(hipEventSynchronize(e1));
@@ -251,10 +255,11 @@ static int run_ratio(int reps) {
 }
 
 int main(int argc, char** argv) {
-    if (argc >= 4 && !strcmp(argv[1], "parts")) return run_parts(atoi(argv[2]), atoi(argv[3]), argc > 4 ? atoi(argv[4]) : 10);
+    if (argc >= 4 && !strcmp(argv[1], "parts")) return run_parts(atoi(argv[2]), atoi(argv[3]), argc > 4 ? atoi(argv[4]) : 10,
+                                                                       argc > 5 ? atoi(argv[5]) : 256);
     if (argc >= 2 && !strcmp(argv[1], "ratio")) return run_ratio(argc > 2 ? atoi(argv[2]) : 4);
     if (argc < 3) {
-        fprintf(stderr, "usage: sd_calib copy|read|stream|ldsstream <MiB> [reps] | parts <NB> <KB> [reps] | ratio [reps]\n");
+        fprintf(stderr, "usage: sd_calib copy|read|stream|ldsstream <MiB> [reps] | parts <NB> <KB> [reps] [workgroups] | ratio [reps]\n");
         return 2;
     }
     const bool copy = !strcmp(argv[1], "copy"), stream = !strcmp(argv[1], "stream"), ldsstream = !strcmp(argv[1], "ldsstream");
