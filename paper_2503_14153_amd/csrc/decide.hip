@@ -545,8 +545,8 @@ void launch_verify(const VerifyArgs& a, int B, hipStream_t s) {
 // every layer and head. A kept node at chain index j was rotated for position n_old + j
 // already (depth = chain index), so this is a pure copy.
 // grid: x = head, y = sequence b of the pass that filled the scratch (sequence rm.seq[b] of the cache; rm.off[b] = entry of
-// src_slots, n_accept and n_old + 256 * its last scratch row, which a slot past it stands for), z = layer; eight waves that share a list of wave-sized tasks, every task a run of
-// whole 16-byte pieces that lie side by side in the cache:
+// src_slots, n_accept and n_old + 256 * its last scratch row, which a slot past it stands for), z = layer; eight waves
+// that share a list of wave-sized tasks, every task a run of whole 16-byte pieces that lie side by side in the cache:
 //   values: a 16-byte piece of the value layout holds one dim of EIGHT rows (a "group": of a 16-row half of a block,
 //     the four rows of one quad and of the quad two further on), so a row cannot move as a piece, and a piece
 //     written in parts (2-byte elements, or its 8-byte halves from two workgroups) leaves the memory partial lines.
@@ -568,7 +568,8 @@ template <bool MIRROR>
 __global__ __launch_bounds__(KVC_THREADS) void k_kv_commit(
     const uint16_t* __restrict__ kt, const uint16_t* __restrict__ vt, uint16_t* __restrict__ kc,
     uint16_t* __restrict__ vc, const int32_t* __restrict__ src_slots, const int32_t* __restrict__ n_accept,
-    const int32_t* __restrict__ n_old, RowMap rm, int nh, int hd, int TB, int cap_blocks, int W, int L, int lpw, size_t layer_stride_t, size_t layer_stride_c) {
+    const int32_t* __restrict__ n_old, RowMap rm, int nh, int hd, int TB, int cap_blocks, int W, int L, int lpw,
+    size_t layer_stride_t, size_t layer_stride_c) {
     extern __shared__ __align__(16) uint16_t kvc_mirror[];          // [kept group][hd / 32][32 dims][8 rows]
     __shared__ int s_slots[SD_MAX_TREE];
     __shared__ uint32_t s_need;
