@@ -32,6 +32,8 @@ extern "C" const char* sd_version(void) { return "libspecdec 0.1 (gfx950)"; }
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+static inline int pow2_blocks(int rows);
+static inline int prompt_blocks(int rows) { return rows <= 256 ? pow2_blocks(rows) : ceil_div(rows, 32); }   // of a prompt pass
 static inline int pow2_blocks(int rows) {   // 32-row blocks, rounded up to 1, 2, 4 or 8
     int mb = ceil_div(rows, 32), p = 1;
     while (p < mb) p *= 2;
@@ -63,6 +65,10 @@ struct ScratchRows {
     SeqList row0 = {};
 };
 
+// Prompt passes of more than 256 rows: packed rows at most, and rows padded to [chunk][Tp] at most.
+#define PROMPT_ROWS 1024
+#define PROMPT_PADDED 2048
+
 struct sd_model {
     sd_config cfg;
     Profile prof;
@@ -81,7 +87,11 @@ struct sd_model {
     int draft_schedule = SD_DRAFT_AFTER_ACCEPT;
     RowTable rt;
     double* rope_freq;                       // [head_dim / 2]
-    RowMap* rm_dev;                          // the row map of a prompt pass, in device memory
+    PassMap* rm_dev;                         // the row map of a prompt pass, in device memory
+    int prompt_rows = 0;                     // rows of the largest prompt pass; above 256 its plans and buffers exist:
+    std::vector<GemmPlan> prompt_plans;      // of 9 .. prompt_rows / 32 row blocks
+    std::vector<double> prompt_cost;         // [row blocks]: modelled cycles of a layer of a pass of that many (0: none)
+    void *ktp = nullptr, *vtp = nullptr;     // one layer's keys and values of such a pass, [chunk][head][blocks]
     int32_t *g_parent, *g_depth, *g_rank, *fin_rows;
     float2* best; void* ranked;                 // ranking scratch: arg-max per row and chunk, top-k per head row and chunk
     float4* row_stats;                     // [Mp]: per tree row, statistics for typical acceptance
@@ -100,6 +110,8 @@ struct sd_model {
     // (have_plans) before they enqueue anything, so a miss here cannot happen after that check
     const GemmPlan* find_plan(int MB, int KB, int NB) const {
         for (const GemmPlan& p : plans)
+            if (p.MB == MB && p.KB == KB && p.NB == NB) return &p;
+        for (const GemmPlan& p : prompt_plans)
             if (p.MB == MB && p.KB == KB && p.NB == NB) return &p;
         return nullptr;
     }
@@ -236,7 +248,7 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     const size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
     const size_t w_best = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * rank_chunks(V) * 8);
     const size_t w_rk = wtake((size_t)std::min(H * SD_MAX_BATCH, 256) * rank_chunks(V) * cfg->topk * 8);
-    const size_t w_rm = wtake(sizeof(RowMap)), w_freq = wtake((size_t)(hd / 2) * 8);
+    const size_t w_rm = wtake(sizeof(PassMap)), w_freq = wtake((size_t)(hd / 2) * 8);
     const size_t w_rs = wtake((size_t)Mp * 16), w_zs = wtake((size_t)ceil_div(V, 32) * 4);
     if (e == hipSuccess) e = hipMalloc((void**)&m->work, wz);
     if (e == hipSuccess) e = hipMemsetAsync(m->work, 0, wz, s);
@@ -254,7 +266,7 @@ static int create_f32(const sd_config* cfg, const sd_weights* w, int max_rows, h
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
     m->best = (float2*)(Wk + w_best); m->ranked = Wk + w_rk; m->fin_rows = (int32_t*)(Wk + w_fin);
-    m->rm_dev = (RowMap*)(Wk + w_rm);
+    m->rm_dev = (PassMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
     m->zero_stop = (uint32_t*)(Wk + w_zs);
@@ -395,22 +407,45 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     }
     (void)ld_max;
     m->part_floats = pf;
+    // Prompts: passes of up to 1024 rows (a model of max_rows > 128 has the room for prompt passes of 256). One layer's
+    // cost of a pass in modelled cycles decides how a prompt is cut (prompt_passes); up to 256 rows it is that of the
+    // passes above.
+    size_t pf_prompt = pf;
+    m->prompt_rows = m->MBmax == 8 ? PROMPT_ROWS : max_rows;
+    if (m->MBmax == 8) {
+        const int shapes[4][2] = {{m->KBd, m->NBqkv}, {m->KBd, m->NBo}, {m->KBd, m->NBgu}, {m->KBf, m->NBo}};
+        m->prompt_cost.assign(PROMPT_ROWS / 32 + 1, 0.0);
+        for (int mb = 1; mb <= PROMPT_ROWS / 32; ++mb)
+            for (const int* sh : shapes) {
+                GemmPlan pl;
+                double cycles = 0;
+                gemm_plan_prompt(&pl, mb, sh[0], sh[1], &cycles);
+                // (a pass of one or two row blocks streams the weights: 2.2 KB a cycle and 10000 cycles a launch)
+                m->prompt_cost[mb] += mb <= 2 ? (double)sh[0] * sh[1] * 1024 / 2200 + 10000 : cycles;
+                if (mb <= 8) continue;
+                m->prompt_plans.push_back(pl);
+                pf_prompt = std::max(pf_prompt, (size_t)pl.S * mb * 32 * (size_t)sh[1] * 32);
+            }
+    }
+    // rows of the buffers that a pass fills: packed rows, and rows padded to whole chunks (attention's side)
+    const int Mr = std::max(m->MBmax * 32, m->MBmax == 8 ? PROMPT_ROWS : 0), Mc = std::max(m->MBmax * 32, m->MBmax == 8 ? PROMPT_PADDED : 0);
     m->max_parts = 65;
     const int HBp = pow2_blocks(std::min((H + 1) * SD_MAX_BATCH, 256)) * 32;      // head rows of a batch, and its base rows
     size_t wz = 0;
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
-    size_t w_x = wtake((size_t)Mp * d * 4), w_part = wtake(pf * 4), w_part2 = wtake(pf2 * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
+    size_t w_x = wtake((size_t)Mr * d * 4), w_part = wtake(pf_prompt * 4), w_part2 = wtake(pf2 * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
     size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4), w_hf = wtake((size_t)Mp * d * 4);
     size_t w_hrows = wtake((size_t)SD_MAX_BATCH * d * 4);
     size_t w_opart = wtake((size_t)Mp * nh * m->max_parts * hd * 4), w_ml = wtake((size_t)Mp * nh * m->max_parts * 8);
-    size_t w_xn = wtake((size_t)std::max(Mp, HBp) * d * 4), w_attn = wtake((size_t)Mp * d * 4);
-    size_t w_act = wtake((size_t)Mp * F * 4), w_q = wtake((size_t)Mp * d * 4);
+    size_t w_xn = wtake((size_t)std::max(Mr, HBp) * d * 4), w_attn = wtake((size_t)Mr * d * 4);
+    size_t w_act = wtake((size_t)Mr * F * 4), w_q = wtake((size_t)Mc * d * 4);
     size_t w_kt = wtake((size_t)L * Mp * d * 2), w_vt = wtake((size_t)L * Mp * d * 2);
-    size_t w_tok = wtake((size_t)Mp * 4), w_pos = wtake((size_t)Mp * 4), w_anc = wtake((size_t)Mp * SD_ANC_WORDS * 4);
-    size_t w_cs = wtake((size_t)Mp * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
+    size_t w_ktp = wtake(Mc > Mp ? (size_t)Mc * d * 2 : 0), w_vtp = wtake(Mc > Mp ? (size_t)Mc * d * 2 : 0);
+    size_t w_tok = wtake((size_t)Mr * 4), w_pos = wtake((size_t)Mr * 4), w_anc = wtake((size_t)Mc * SD_ANC_WORDS * 4);
+    size_t w_cs = wtake((size_t)Mr * (hd / 2) * 8), w_g = wtake(3 * 4), w_fin = wtake(SD_MAX_BATCH * 4);
     size_t w_best = wtake((size_t)std::max(Mp, SD_MAX_BATCH) * rank_chunks(V) * 8);
     size_t w_rk = wtake((size_t)std::min(H * SD_MAX_BATCH, 256) * rank_chunks(V) * cfg->topk * 8);
-    size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(RowMap)), w_freq = wtake((size_t)(hd / 2) * 8);
+    size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(PassMap)), w_freq = wtake((size_t)(hd / 2) * 8);
     size_t w_xh = wtake(align_up((size_t)H * Mp, 256) * d * 4);
     size_t w_zs = wtake((size_t)ceil_div(V, 32) * 4), w_zf = wtake(1024);
     size_t w_ssqa = wtake((size_t)align_up(d / 16, 4) * Mp * 4), w_ssqf = wtake((size_t)align_up(d / 16, 4) * Mp * 4);
@@ -455,11 +490,12 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     m->opart = (float*)(Wk + w_opart); m->mlpart = (float2*)(Wk + w_ml);
     m->xn = Wk + w_xn; m->attn_x = Wk + w_attn; m->act = Wk + w_act; m->q = Wk + w_q;
     m->kt = Wk + w_kt; m->vt = Wk + w_vt;
+    m->ktp = Wk + w_ktp; m->vtp = Wk + w_vtp;
     m->xh = Wk + w_xh;
     m->rt.tok = (int32_t*)(Wk + w_tok); m->rt.pos = (int32_t*)(Wk + w_pos); m->rt.anc = (uint32_t*)(Wk + w_anc);
     m->rt.cs = (float2*)(Wk + w_cs);
     m->best = (float2*)(Wk + w_best); m->ranked = Wk + w_rk; m->fin_rows = (int32_t*)(Wk + w_fin);
-    m->rm_dev = (RowMap*)(Wk + w_rm);
+    m->rm_dev = (PassMap*)(Wk + w_rm);
     m->row_stats = (float4*)(Wk + w_rs);
     m->g_parent = (int32_t*)(Wk + w_g); m->g_depth = m->g_parent + 1; m->g_rank = m->g_parent + 2;
     m->zero_stop = (uint32_t*)(Wk + w_zs);
@@ -1157,10 +1193,212 @@ static void run_draft_heads_all_rows(sd_model* m, sd_kv* kv, int B, int M, float
 }
 
 // ------------------------------------------------------------------------------------------ prefill
+// A prompt pass holds the next tokens of every sequence whose prompt has not ended, up to 256 rows in all and Tp per sequence
+// (a prompt that has ended takes no rows).
+struct PromptChunk { int b, tok, len, before; bool ends; };   // sequence, first token, tokens, rows earlier in the launch, ends its prompt
+struct PromptPass { int Tp, M; std::vector<PromptChunk> chunks; };
+static std::vector<PromptPass> cut_prompts(const sd_model* m, const int32_t* lens, int B) {
+    std::vector<int> next(B), left(lens, lens + B);
+    for (int b = 0, o = 0; b < B; ++b) { next[b] = o; o += lens[b]; }
+    std::vector<PromptPass> passes;
+    for (;;) {
+        int A = 0;
+        for (int b = 0; b < B; ++b) A += left[b] > 0;
+        if (A == 0) return passes;
+        PromptPass p;
+        p.Tp = std::min(m->max_rows / A / 32 * 32, 256);       // (the widest GEMM of a pass on its own)
+        p.M = 0;
+        for (int b = 0; b < B; ++b) {
+            if (left[b] <= 0) continue;
+            const int n = std::min(left[b], p.Tp);
+            p.chunks.push_back({b, next[b], n, 0, n == left[b]});
+            next[b] += n;
+            left[b] -= n;
+            p.M += n;
+        }
+        passes.push_back(p);
+    }
+}
+
+// The chunks of passes[0 .. n) as one launch sequence takes them: chunks of a sequence that follow one another joined up to
+// 256 rows, those of passes[n - 1] left alone where a later commit is to find them (keep).
+static std::vector<PromptChunk> joined_chunks(const PromptPass* passes, int n, bool keep, int* Tp) {
+    std::vector<PromptChunk> v;
+    int done[SD_MAX_BATCH] = {};                           // rows of the sequence so far
+    *Tp = 0;
+    for (int i = 0; i < n; ++i)
+        for (const PromptChunk& c : passes[i].chunks) {
+            PromptChunk* last = nullptr;                   // the sequence's latest
+            for (PromptChunk& e : v)
+                if (e.b == c.b) last = &e;
+            if (last && !(keep && i == n - 1) && last->len + c.len <= 256) {
+                last->len += c.len;
+                last->ends = c.ends;
+            } else {
+                v.push_back(c);
+                v.back().before = done[c.b];
+            }
+            done[c.b] += c.len;
+        }
+    for (const PromptChunk& c : v) *Tp = std::max(*Tp, ceil_div(c.len, 32) * 32);
+    return v;
+}
+
+// How many passes from passes[i] on run as one: as many as its buffers hold, the last of them only if the model of the GEMMs'
+// cost (and 60000 cycles for a layer's other launches) says that a pass of its own is not cheaper (a short remainder).
+static size_t passes_together(const sd_model* m, const std::vector<PromptPass>& passes, size_t i) {
+    if (m->prompt_rows <= 256 || fused_eligible(m, 256)) return 1;
+    auto cost = [&](int rows) { return m->prompt_cost[prompt_blocks(rows)] + 60000.0; };
+    size_t k = 0;
+    int M = 0;
+    while (i + k < passes.size() && M + passes[i + k].M <= m->prompt_rows) {
+        int Tp;
+        const std::vector<PromptChunk> v = joined_chunks(&passes[i], (int)k + 1, i + k + 1 == passes.size(), &Tp);
+        if (k > 0 && (v.size() > SD_MAX_BATCH || (int)v.size() * Tp > PROMPT_PADDED)) break;
+        M += passes[i + k].M;
+        ++k;
+    }
+    if (k > 1 && cost(M) > cost(M - passes[i + k - 1].M) + cost(passes[i + k - 1].M)) --k;
+    return std::max<size_t>(k, 1);
+}
+
+// The sequences whose prompts end with these chunks: their last rows (of the pass), and themselves.
+static int ending_rows(const std::vector<PromptChunk>& chunks, const RowMap& rm, SeqList* last, SeqList* fin) {
+    int n = 0;
+    for (size_t i = 0; i < chunks.size(); ++i)
+        if (chunks[i].ends) {
+            last->seq[n] = rm.off[i] + chunks[i].len - 1;
+            fin->seq[n++] = chunks[i].b;
+        }
+    return n;
+}
+
+// What the ended prompts' sequences carry into their first step.
+static void draft_from_prompts(sd_model* m, sd_kv* kv, PartView prev, int n_fin, const SeqList& fin, hipStream_t s) {
+    if (!n_fin) return;
+    run_known_rows(m, kv, prev, n_fin, m->fin_rows, fin, nullptr, 0, nullptr, s);
+    launch_pick_root(m->best, m->cfg.vocab, kv->root_tok, n_fin, fin, s);
+}
+
+static void run_prompt_pass(sd_model* m, sd_kv* kv, const int32_t* tokens, const PromptPass& p, hipStream_t s) {
+    const sd_config& c = m->cfg;
+    const int A = (int)p.chunks.size(), Tp = p.Tp;
+    ChainArgs ca;
+    RowMap rm;
+    SeqList fin, last;
+    memset(&ca, 0, sizeof(ca));
+    memset(&rm, 0, sizeof(rm));
+    memset(&fin, 0, sizeof(fin));
+    memset(&last, 0, sizeof(last));
+    int M = 0, n_hi = 0;
+    const bool padded = fused_eligible(m, A * Tp);         // that pass takes the rows as [sequence][Tp]
+    for (int i = 0; i < A; ++i) {
+        const PromptChunk& ch = p.chunks[i];
+        ca.len[i] = ch.len;
+        ca.off[i] = ch.tok;
+        rm.seq[i] = ch.b;
+        rm.off[i] = M;
+        rm.len[i] = padded ? Tp : ch.len;
+        M += rm.len[i];
+        n_hi = std::max(n_hi, kv->len_hi[ch.b]);
+    }
+    const int n_fin = ending_rows(p.chunks, rm, &last, &fin);
+    launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
+                            c.d_model, c.vocab, m->x, s);
+    const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
+    PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
+    launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
+    m->scratch = scratch_of_pass(kv, rm, A, M, Tp, ca.len, 0);
+    commit_rows(m, kv, m->scratch, false, kv->i_slots, kv->i_nacc, Tp, s);
+    for (const PromptChunk& ch : p.chunks) kv->len_hi[ch.b] += ch.len;
+    draft_from_prompts(m, kv, prev, n_fin, fin, s);
+}
+
+// Several passes (more than 256 rows) as one: every projection reads its weights once and has rows enough to fill the chip
+// without cutting the contraction into partial sums. Attention takes the chunks as sequences of their own: a chunk attends
+// the committed rows and its sequence's earlier chunks from the cache, where the rotary stage of the layer has put them, and
+// its own rows from the pass's scratch. So the rows are committed layer by layer and nothing is left to commit at the end; what
+// sd_kv_commit_rows may ask for afterwards, the rows of the last pass, goes to the model's scratch as if that pass had
+// run by itself (last: it is the last of the call).
+static void run_prompt_passes(sd_model* m, sd_kv* kv, const int32_t* tokens, const PromptPass* passes, int n, bool is_last,
+                              hipStream_t s) {
+    const sd_config& c = m->cfg;
+    const int d = c.d_model, nh = c.n_heads, hd = c.head_dim;
+    int Tp;
+    const std::vector<PromptChunk> chunks = joined_chunks(passes, n, is_last, &Tp);
+    const int V = (int)chunks.size(), keep = is_last ? V - (int)passes[n - 1].chunks.size() : V, keep_Tp = passes[n - 1].Tp;
+    ChainArgs ca, sum;
+    RowMap rm, seqs;
+    SeqList fin, last;
+    memset(&ca, 0, sizeof(ca));
+    memset(&sum, 0, sizeof(sum));
+    memset(&rm, 0, sizeof(rm));
+    memset(&seqs, 0, sizeof(seqs));
+    memset(&fin, 0, sizeof(fin));
+    memset(&last, 0, sizeof(last));
+    int M = 0, n_hi = 0, longest = 0, A = 0;
+    for (int i = 0; i < V; ++i) {
+        const PromptChunk& ch = chunks[i];
+        ca.len[i] = rm.len[i] = ch.len;
+        ca.off[i] = ch.tok;
+        ca.before[i] = ch.before;
+        rm.seq[i] = ch.b;
+        rm.off[i] = M;
+        M += ch.len;
+        n_hi = std::max(n_hi, kv->len_hi[ch.b] + ch.before);
+        longest = std::max(longest, ch.len);
+        int a = 0;
+        while (a < A && seqs.seq[a] != ch.b) ++a;
+        if (a == A) seqs.seq[A++] = ch.b;
+        sum.len[a] += ch.len;
+    }
+    const int n_fin = ending_rows(chunks, rm, &last, &fin), MB = prompt_blocks(M);
+    launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, V, Tp, hd, m->rope_freq, m->embed, 0, d, c.vocab, m->x, s);
+    const RowRef rr = {m->rm_dev, 0};
+    // (parts: what the partials' buffer holds)
+    const AttnGeom ag = attn_geometry(nh, std::min(m->max_parts, m->MBmax * 32 * m->max_parts / (V * Tp)), V, Tp, n_hi, false, false);
+    const int keep_A = V - keep, keep_TB = keep_Tp / 32;
+    const size_t keep_stride = (size_t)keep_A * nh * keep_TB * 32 * hd;
+    PartView prev = {nullptr, 0, d, nullptr, 0};
+    for (int l = 0; l < c.n_layers; ++l) {
+        const LayerW& lw = m->layers[l];
+        launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
+        PartView pq = run_gemm(m, m->xn, lw.wqkv, m->part, M, MB, m->KBd, m->NBqkv, 3 * d, s);
+        const KvSinks sinks = {kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kv->cap_blocks,
+                               (uint16_t*)m->kt + l * keep_stride, (uint16_t*)m->vt + l * keep_stride, keep, keep_TB};
+        launch_rope_kv(pq, m->rt, rr, m->q, m->ktp, m->vtp, V, Tp, nh, hd, s, &sinks);
+        const int pa = prof_claim(m, PROF_ATTN, (double)V * (n_hi + Tp) * 2.0 * d * 2.0);
+        launch_tree_attn(m->q, sinks.kc, sinks.vc, m->ktp, m->vtp, kv->kv_len, m->rt.anc, m->opart, m->mlpart, rr, V, nh, hd, Tp,
+                         kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1));
+        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, V, nh, hd, Tp, ag.nparts, MB, s);
+        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
+        launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
+        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
+        launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
+        prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
+    }
+    launch_prefill_commit_setup(sum, seqs, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
+    if (is_last) {                                         // (else a later pass of this call sets it)
+        RowMap kr;
+        ChainArgs kl;
+        memset(&kr, 0, sizeof(kr));
+        memset(&kl, 0, sizeof(kl));
+        int kM = 0;
+        for (int i = 0; i < keep_A; ++i) {
+            kr.seq[i] = rm.seq[keep + i];
+            kr.off[i] = kM;
+            kl.len[i] = rm.len[keep + i];
+            kM += kl.len[i];
+        }
+        m->scratch = scratch_of_pass(kv, kr, keep_A, kM, keep_Tp, kl.len, 0);
+    }
+    for (const PromptChunk& ch : chunks) kv->len_hi[ch.b] += ch.len;
+    draft_from_prompts(m, kv, prev, n_fin, fin, s);
+}
+
 extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const int32_t* lens, void* stream) {
     if (!m || !kv || !tokens || !lens) return fail(SD_ERR_NULL, "sd_prefill: NULL argument");
     if (kv->m != m) return fail(SD_ERR_STATE, "sd_prefill: cache belongs to another model");
-    const sd_config& c = m->cfg;
     const int B = kv->B;
     hipStream_t s = (hipStream_t)stream;
     int Tp = (m->max_rows / B) / 32 * 32;
@@ -1173,53 +1411,12 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
     for (int rows = 32; rows <= 256; rows *= 2)            // every row count a pass can come down to
         if (pow2_blocks(rows) <= m->MBmax && !have_plans(m, rows, B, true, false))
             return fail(SD_ERR_STATE, "sd_prefill: no launch plan for %d rows (internal inconsistency)", rows);
-    std::vector<int> next(B), left(lens, lens + B);        // first prompt token not yet enqueued, how many are left
-    for (int b = 0, o = 0; b < B; ++b) { next[b] = o; o += lens[b]; }
-    for (;;) {
-        // The sequences that still have tokens share the pass's rows: a prompt that has ended takes none of them.
-        ChainArgs ca;
-        RowMap rm;
-        memset(&ca, 0, sizeof(ca));
-        memset(&rm, 0, sizeof(rm));
-        SeqList fin, last;                                 // the sequences whose prompts end, and their last rows
-        memset(&fin, 0, sizeof(fin));
-        memset(&last, 0, sizeof(last));
-        int A = 0, M = 0, n_hi = 0, n_fin = 0;
-        for (int b = 0; b < B; ++b)
-            if (left[b] > 0) rm.seq[A++] = b;
-        if (A == 0) break;
-        Tp = std::min(m->max_rows / A / 32 * 32, 256);
-        const bool padded = fused_eligible(m, A * Tp);     // that pass takes the rows as [sequence][Tp]
-        for (int i = 0; i < A; ++i) {
-            const int b = rm.seq[i];
-            ca.len[i] = std::min(left[b], Tp);
-            ca.off[i] = next[b];
-            rm.off[i] = M;
-            rm.len[i] = padded ? Tp : ca.len[i];
-            M += rm.len[i];
-            if (left[b] > 0 && left[b] <= Tp) {            // this pass ends the prompt
-                last.seq[n_fin] = rm.off[i] + ca.len[i] - 1;
-                fin.seq[n_fin++] = b;
-            }
-            n_hi = std::max(n_hi, kv->len_hi[b]);
-        }
-        launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
-                                c.d_model, c.vocab, m->x, s);
-        const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
-        PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
-        launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
-        m->scratch = scratch_of_pass(kv, rm, A, M, Tp, ca.len, 0);
-        commit_rows(m, kv, m->scratch, false, kv->i_slots, kv->i_nacc, Tp, s);
-        for (int i = 0; i < A; ++i) {
-            const int b = rm.seq[i];
-            kv->len_hi[b] += ca.len[i];
-            next[b] += ca.len[i];
-            left[b] -= ca.len[i];
-        }
-        if (n_fin) {
-            run_known_rows(m, kv, prev, n_fin, m->fin_rows, fin, nullptr, 0, nullptr, s);
-            launch_pick_root(m->best, c.vocab, kv->root_tok, n_fin, fin, s);
-        }
+    const std::vector<PromptPass> passes = cut_prompts(m, lens, B);
+    for (size_t i = 0; i < passes.size();) {
+        const size_t k = passes_together(m, passes, i);
+        if (k > 1) run_prompt_passes(m, kv, tokens, &passes[i], (int)k, i + k == passes.size(), s);
+        else run_prompt_pass(m, kv, tokens, passes[i], s);
+        i += k;
     }
     HIP_TRY(hipGetLastError());
     if (m->plan_missing) return fail(SD_ERR_STATE, "sd_prefill: a GEMM launch plan was missing");

@@ -117,6 +117,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
         h = hb % nh;
         b = hb / nh;
     }
+    if (MAP && tg * TBW * 32 >= rr.map->len[b]) return;   // prompt passes: no rows in this query group, nothing reads its parts
     bf16x8* qs = lds;
     const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16x8*)lds);
     const uint32_t myq_addr = __builtin_amdgcn_readfirstlane(lds_addr + wave * QW * 1024);
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // [w*share, (w+1)*share). Which of them exist depends on the sequence length, known later; or (EVEN) the length is
     // waited for here and this sequence's own blocks are what its parts share evenly.
     const int sq = MAP ? rr.map->seq[b] : b;           // sequence of the cache
-    const int n = kv_len[sq];
+    const int n = MAP ? rr.map->ctx[b] : kv_len[sq];   // rows before this pass's, or this chunk's, own
     const int nblk = (n + 31) >> 5;
     int here = per;                                    // cache blocks of this part, at most
     int c0 = part * per;

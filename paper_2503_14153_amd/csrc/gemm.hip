@@ -16,6 +16,8 @@
 // cores idle most of the time in an HBM-bound kernel, each activation enters as a two-term
 // bf16 expansion x = hi + lo (two MFMAs per weight fragment), which keeps ~16 mantissa bits
 // of x and makes the product exact up to fp32 accumulation.
+#include <string.h>
+
 #include "sd_internal.h"
 #include "sk_gemm.h"
 #include "row_ops.h"
@@ -174,10 +176,16 @@ __global__ __launch_bounds__(512, 4) void k_gemm_few(FewSrc src, const bf16x8* _
 // unit has not taken yet (24 loads of 1 KiB per step at once held every wave's next MFMAs back).
 // Measured per step at 256 rows, column groups of six blocks (768 MFMA cycles): 1230 cycles with write, barrier,
 // read, MFMA in sequence; 1075 with the hand-over pipelined; 1030 with the loads spread as well.
-template <int MT, int CG>
+//
+// TILED (prompt passes of more than 256 rows): the pass is RT tiles of MT row blocks, a workgroup takes one tile of one
+// column group and segment. Workgroups go to the XCDs round-robin, so the RT tiles of a (column group, segment) are dealt to
+// one XCD, next to one another: the weights come from memory once and the other tiles find them in that XCD's L2. A last
+// tile that reaches past the operand's MB row blocks repeats its last one; those products are not stored.
+template <int MT, int CG, bool TILED>
 __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                       const bf16x8* __restrict__ zfrag, float* __restrict__ out,
-                                                      int KB, int NB, int ldo, size_t slot_stride, int rows, int S) {
+                                                      int KB, int NB, int ldo, size_t slot_stride, int rows, int S, int MB_,
+                                                      int RT, int n_combo) {
     static_assert((MT == 4 || MT == 8) && (CG * MT) % 16 == 0 && CG <= 8, "row blocks / column group");
     constexpr int R = 4;                                // ring depth in steps; even (the LDS buffer of step i is i & 1)
     constexpr int CPW = CG * MT / 8;                    // column blocks per wave: 8 waves cover MT rows x CG columns
@@ -185,14 +193,22 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
     __shared__ bf16x8 ws[2][CG * 64];                   // the weight fragments of two consecutive steps
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int r = wave % MT, ch = wave / MT;
-    const int ng = blockIdx.x / S, seg = blockIdx.x - ng * S;
+    int combo = blockIdx.x, tile = 0;                   // combo: column group and segment
+    if constexpr (TILED) {
+        const int q = blockIdx.x >> 3;                  // (of this XCD's workgroups)
+        tile = q % RT;
+        combo = (q / RT) * 8 + (blockIdx.x & 7);
+        if (combo >= n_combo) return;                   // (workgroup-uniform, before any barrier)
+    }
+    const int MB = TILED ? MB_ : MT, rb = tile * MT + r;   // this wave's row block
+    const int ng = combo / S, seg = combo - ng * S;
     const int n = KB / S, kb0 = seg * n;                // this workgroup's steps: contraction blocks [kb0, kb0 + n)
     const bool loader = wave < CG;
     int nbw = ng * CG + wave;
     if (nbw >= NB) nbw = NB - 1;                        // (a ragged last group: a duplicate fragment, never stored)
-    const size_t wstep = (size_t)NB * 64, xstep = (size_t)MT * 2 * 64;
+    const size_t wstep = (size_t)NB * 64, xstep = (size_t)MB * 2 * 64;
     const bf16x8* wp = Wp + ((size_t)kb0 * NB + nbw) * 64 + lane;
-    const bf16x8* xp = Xp + ((size_t)kb0 * MT + r) * 2 * 64 + lane;
+    const bf16x8* xp = Xp + ((size_t)kb0 * MB + (TILED ? min(rb, MB - 1) : rb)) * 2 * 64 + lane;
     const bf16x8* zl = zfrag + lane;                    // steps past n read zeros (no weight bytes, idle MFMA work)
 
     f32x16 acc[CPW];
@@ -256,7 +272,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
     }
     int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
     asm volatile("" : "+v"(gq), "+s"(ldo_here));
-    const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(r) * 32, rows, ldo_here);
+    const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(rb) * 32, rows, ldo_here);
 #pragma unroll
     for (int j = 0; j < CPW; ++j) {
         const int nb = ng * CG + ch * CPW + j;
@@ -333,6 +349,33 @@ static void gemm_plan_rows(GemmPlan* p) {
     if (p->S > p->slots_max) p->slots_max = p->S;
 }
 
+// Prompt passes of more than 256 rows: tiles of eight or four row blocks, the cost of gemm_plan_rows over all of them, and
+// 6000 cycles (launch, first loads, stores) per round of workgroups. With this many rows there is one segment or two, where
+// 256 rows need four to eight to fill the chip, so the partial tiles all but disappear; the weights are read once per pass.
+// 7B shape, a prompt of 1500 tokens through four layers: 6641 us in six passes of up to 256 rows, 5649 in passes of 1024 and
+// 476. The launches themselves run at what the card's power allows for dense data, 0.97-1.05 PFLOP/s of two-term work at
+// 256 and at 1024 rows alike (1.26-1.36 with operands of zeros): what is saved lies between them.
+void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles) {
+    memset(p, 0, sizeof(*p));
+    p->MB = MB; p->KB = KB; p->NB = NB;
+    static const int widths8[] = {8, 6, 4}, widths4[] = {8, 4};
+    double best = 0;
+    for (int MT = 8; MT >= 4; MT /= 2)
+        for (int wi = 0; wi < (MT == 8 ? 3 : 2); ++wi) {
+            const int CG = MT == 8 ? widths8[wi] : widths4[wi], groups = (NB + CG - 1) / CG, RT = (MB + MT - 1) / MT;
+            for (int S = 1; S <= 4 && S <= KB; ++S) {
+                if (KB % S) continue;
+                const int rounds = (groups * S * RT + SK_MAX_WG - 1) / SK_MAX_WG, steps = (KB / S + 3) / 4 * 4;
+                const double tile_bytes = (double)S * MB * 32 * NB * 32 * 4;
+                const double cost = rounds * (steps * (16.0 * CG * MT + 300.0) + 6000.0) + 2.0 * tile_bytes / 2500.0;
+                if (p->CG == 0 || cost < best) { best = cost; p->CG = CG; p->S = S; p->MT = MT; p->RT = RT; }
+            }
+        }
+    p->slots = p->slots_max = p->S;
+    p->uniform = 1;
+    *cycles = best;
+}
+
 void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int32_t* slot0_host) {
     p->MB = MB; p->KB = KB; p->NB = NB;
     p->cnt_dev = nullptr;
@@ -381,6 +424,7 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     for (int ng = 0; ng < p->NG; ++ng) p->uniform &= (cnt_host[ng] == slots);
     p->CG = 0;
     p->S = 0;
+    p->RT = p->MT = 0;
     p->slots_max = slots;
     if (MB >= 4) gemm_plan_rows(p);
 }
@@ -403,25 +447,31 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
             hipLaunchKernelGGL(KERNEL_, dim3(p.G), dim3(THREADS_), 0, s, SK_ARGS, ##__VA_ARGS__);          \
     } while (0)
     if (p.CG) {                                        // four / eight row blocks: the aligned split of k_gemm_rows
-        const int G = (p.NB + p.CG - 1) / p.CG * p.S;
+        const int combos = (p.NB + p.CG - 1) / p.CG * p.S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
         pv.cnt = nullptr;
         pv.nmax = p.S;
-#define ROWS_LAUNCH(MT_, CG_)                                                                              \
+#define ROWS_LAUNCH(MT_, CG_, TILED_)                                                                      \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
-            hipExtLaunchKernelGGL((k_gemm_rows<MT_, CG_>), dim3(G), dim3(512), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
-                                  (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S); \
+            hipExtLaunchKernelGGL((k_gemm_rows<MT_, CG_, TILED_>), dim3(G), dim3(512), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
+                                  (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, \
+                                  p.MB, p.RT, combos);                                                     \
         else                                                                                               \
-            hipLaunchKernelGGL((k_gemm_rows<MT_, CG_>), dim3(G), dim3(512), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S);   \
+            hipLaunchKernelGGL((k_gemm_rows<MT_, CG_, TILED_>), dim3(G), dim3(512), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
+                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos); \
     } while (0)
-        const int key = p.MB * 10 + p.CG;
-        if (key == 88) ROWS_LAUNCH(8, 8);
-        else if (key == 86) ROWS_LAUNCH(8, 6);
-        else if (key == 84) ROWS_LAUNCH(8, 4);
-        else if (key == 48) ROWS_LAUNCH(4, 8);
-        else if (key == 44) ROWS_LAUNCH(4, 4);
-        else pv.nmax = 0;                              // gemm_plan_rows makes no other: nothing launched, nothing to read
+        const int key = (p.RT ? 100 + p.MT * 10 : p.MB * 10) + p.CG;
+        if (key == 88) ROWS_LAUNCH(8, 8, false);
+        else if (key == 86) ROWS_LAUNCH(8, 6, false);
+        else if (key == 84) ROWS_LAUNCH(8, 4, false);
+        else if (key == 48) ROWS_LAUNCH(4, 8, false);
+        else if (key == 44) ROWS_LAUNCH(4, 4, false);
+        else if (key == 188) ROWS_LAUNCH(8, 8, true);
+        else if (key == 186) ROWS_LAUNCH(8, 6, true);
+        else if (key == 184) ROWS_LAUNCH(8, 4, true);
+        else if (key == 148) ROWS_LAUNCH(4, 8, true);
+        else if (key == 144) ROWS_LAUNCH(4, 4, true);
+        else pv.nmax = 0;                              // the planners make no other: nothing launched, nothing to read
 #undef ROWS_LAUNCH
         return pv;
     }

@@ -177,12 +177,13 @@ static __device__ __forceinline__ void norm_tile(float* __restrict__ x, const Pa
 // NS > 0: every column group of the QKV projection has NS slots (its plan says so): all loads in a straight line.
 // q_unit0: subtracted from the 16-byte unit index of the query fragments (a caller that keeps one head's queries in a
 // buffer of its own, e.g. in LDS, passes that head's offset). k_copy / v_copy: if not NULL, this head's key / value
-// blocks are written there as well (block layouts, offsets within the head).
+// blocks are written there as well (block layouts, offsets within the head); k_copy2 / v_copy2 the same, as row t2.
 template <bool BATCH, int NS = 0>
 static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const RowTable& rt, bf16x8* __restrict__ qp,
                                                     uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp, int nh,
                                                     int hd, int which, int h, int a, int t, int b, int m, size_t q_unit0 = 0,
-                                                    uint16_t* k_copy = nullptr, uint16_t* v_copy = nullptr) {
+                                                    uint16_t* k_copy = nullptr, uint16_t* v_copy = nullptr,
+                                                    uint16_t* k_copy2 = nullptr, uint16_t* v_copy2 = nullptr, int t2 = 0) {
     const int d = nh * hd, half = hd / 2;
     const int col0 = which * d + h * hd + a * 8;
     const float* p0 = pv.base + (size_t)m * pv.ld + col0;
@@ -229,6 +230,10 @@ static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const Ro
                 v_copy[vblk_index(t, a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w1);
                 v_copy[vblk_index(t, half + a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w2);
             }
+            if (v_copy2) {
+                v_copy2[vblk_index(t2, a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w1);
+                v_copy2[vblk_index(t2, half + a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w2);
+            }
         }
         return;
     }
@@ -257,6 +262,10 @@ static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const Ro
         if (k_copy) {
             ((bf16x8*)k_copy)[kblk_index(t, a * 8, hd) >> 3] = k1;
             ((bf16x8*)k_copy)[kblk_index(t, half + a * 8, hd) >> 3] = k2;
+        }
+        if (k_copy2) {
+            ((bf16x8*)k_copy2)[kblk_index(t2, a * 8, hd) >> 3] = k1;
+            ((bf16x8*)k_copy2)[kblk_index(t2, half + a * 8, hd) >> 3] = k2;
         }
     }
 }

@@ -84,8 +84,9 @@ void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* d
 }
 
 // Prompt chunk as a chain: row j of sequence b is prompt token ca.off[b] + j at position
-// committed length + j and attends rows 0..j of the chunk. (Rows between ca.len and rm.len, if any, are rows of zeros.)
-__global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ tokens, ChainArgs ca, RowMap rm, RowMap* __restrict__ rm_dev,
+// committed length + ca.before[b] + j and attends rows 0..j of the chunk. (Rows between ca.len and rm.len, if any, are rows
+// of zeros.)
+__global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ tokens, ChainArgs ca, RowMap rm, PassMap* __restrict__ rm_dev,
                                    const int32_t* __restrict__ kv_len, int Tp, int hd, const double* __restrict__ freq,
                                    const void* __restrict__ embed, int embed_f32, int d, int V,
                                    float* __restrict__ x) {
@@ -94,10 +95,11 @@ __global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ toke
         rm_dev->off[threadIdx.x] = rm.off[threadIdx.x];
         rm_dev->len[threadIdx.x] = rm.len[threadIdx.x];
         rm_dev->seq[threadIdx.x] = rm.seq[threadIdx.x];
+        rm_dev->ctx[threadIdx.x] = kv_len[rm.seq[threadIdx.x]] + ca.before[threadIdx.x];
     }
     const bool valid = j < ca.len[b];
     int tok = valid ? min(max(tokens[ca.off[b] + j], 0), V - 1) : 0;
-    int pos = kv_len[rm.seq[b]] + (valid ? j : 0);
+    int pos = kv_len[rm.seq[b]] + ca.before[b] + (valid ? j : 0);
     uint32_t a[SD_ANC_WORDS] = {};
     if (valid) {
         for (int w = 0; w < SD_ANC_WORDS; ++w) {
@@ -118,7 +120,7 @@ __global__ void k_build_rows_chain(RowTable rt, const int32_t* __restrict__ toke
     embed_row(embed, embed_f32, tok, d, x + (size_t)m * d, valid);
 }
 
-void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev,
+void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, PassMap* rm_dev,
                              const int32_t* kv_len, int B, int Tp, int hd, const double* __restrict__ freq, const void* embed, int embed_f32, int d, int V, float* x,
                              hipStream_t s) {
     hipLaunchKernelGGL(k_build_rows_chain, dim3(B * Tp), dim3(256), 0, s, rt, tokens, ca, rm, rm_dev, kv_len, Tp, hd, freq,
@@ -158,19 +160,47 @@ void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* 
 // query and key layouts put row r, dim group g of contraction step w at lane r + 32 g) and what it reads of a row and
 // slot are 64 contiguous bytes twice. (One thread per (h, a) of ONE row wrote the same bytes as 16-byte pieces 0.5-2
 // KiB apart; the values' layout is transposed, their 2-byte stores stay scattered either way.)
+// SINKS: a prompt pass of several chunks per sequence. Its keys and values go to the cache here, because the attention
+// launch that follows reads the earlier chunks' from there (rows that exist only; bytes of a 16-byte value piece may come
+// from several workgroups, which is safe: each writes its own).
+template <bool SINKS>
 __global__ void k_rope_kv(PartView pv, RowTable rt, RowRef rr, bf16x8* __restrict__ qp, uint16_t* __restrict__ kt,
-                          uint16_t* __restrict__ vt, int Tp, int nh, int hd, int na) {
+                          uint16_t* __restrict__ vt, int Tp, int nh, int hd, int na, KvSinks sk) {
     const int which = blockIdx.x % 3, h = blockIdx.x / 3;     // a constant divisor: a multiplication
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int t = blockIdx.y * 32 + (lane & 31), b = blockIdx.z, m = rr.off(b) + min(t, rr.len(b) - 1);
-    for (int a = 2 * wave + (lane >> 5); a < na; a += 8)      // hd / 16 pieces: 8 (one round) or 4 (waves 0 and 1)
-        rope_kv_item<false>(pv, rt, qp, kt, vt, Tp, nh, hd, which, h, a, t, b, m);
+    if constexpr (SINKS) {
+        const size_t head = (size_t)32 * hd;
+        uint16_t *k1 = nullptr, *v1 = nullptr, *k2 = nullptr, *v2 = nullptr;
+        int t2 = 0;
+        if (t < rr.len(b)) {
+            const size_t at = ((size_t)rr.seq(b) * nh + h) * sk.cap_blocks * head;
+            k2 = sk.kc + at;
+            v2 = sk.vc + at;
+            t2 = rr.map->ctx[b] + t;
+            if (b >= sk.keep) {
+                const size_t ka = ((size_t)(b - sk.keep) * nh + h) * sk.keep_TB * head;
+                k1 = sk.kk + ka;
+                v1 = sk.vk + ka;
+            }
+        }
+        for (int a = 2 * wave + (lane >> 5); a < na; a += 8)
+            rope_kv_item<false>(pv, rt, qp, kt, vt, Tp, nh, hd, which, h, a, t, b, m, 0, k1, v1, k2, v2, t2);
+    } else {
+        for (int a = 2 * wave + (lane >> 5); a < na; a += 8)  // hd / 16 pieces: 8 (one round) or 4 (waves 0 and 1)
+            rope_kv_item<false>(pv, rt, qp, kt, vt, Tp, nh, hd, which, h, a, t, b, m);
+    }
 }
 
 void launch_rope_kv(PartView pv, RowTable rt, RowRef rr, void* q_packed, void* kt, void* vt, int B, int Tp, int nh,
-                    int hd, hipStream_t s) {
-    hipLaunchKernelGGL(k_rope_kv, dim3(nh * 3, Tp / 32, B), dim3(256), 0, s, pv, rt, rr, (bf16x8*)q_packed, (uint16_t*)kt,
-                       (uint16_t*)vt, Tp, nh, hd, hd / 16);
+                    int hd, hipStream_t s, const KvSinks* sinks) {
+    const dim3 grid(nh * 3, Tp / 32, B);
+    if (sinks)
+        hipLaunchKernelGGL(k_rope_kv<true>, grid, dim3(256), 0, s, pv, rt, rr, (bf16x8*)q_packed, (uint16_t*)kt, (uint16_t*)vt, Tp,
+                           nh, hd, hd / 16, *sinks);
+    else
+        hipLaunchKernelGGL(k_rope_kv<false>, grid, dim3(256), 0, s, pv, rt, rr, (bf16x8*)q_packed, (uint16_t*)kt, (uint16_t*)vt, Tp,
+                           nh, hd, hd / 16, KvSinks{});
 }
 
 // ------------------------------------------------------------------------------------------

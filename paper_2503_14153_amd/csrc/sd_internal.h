@@ -80,11 +80,14 @@ struct RowMap {
     int32_t seq[SD_MAX_BATCH];                      // sequence of the cache
 };
 struct SeqList { int32_t seq[SD_MAX_BATCH]; };      // one number per sequence of a pass
+// The map of a prompt pass in device memory. ctx: rows that sequence i's rows attend besides their own (the committed ones,
+// and the sequence's rows earlier in the same pass, which are in the cache by the time attention runs).
+struct PassMap { int32_t off[SD_MAX_BATCH], len[SD_MAX_BATCH], seq[SD_MAX_BATCH], ctx[SD_MAX_BATCH]; };
 // What the kernels of a layer get: every sequence of a step has the same number of rows, R (map NULL); a prompt pass leaves
 // its map in device memory. (As an argument of every launch the map's 384 bytes cost the 64-node step 1 %, read from
 // memory by every launch another 1 %: the attention launch's first addresses wait for it, 14.9 -> 15.5 us.)
 struct RowRef {
-    const RowMap* map;
+    const PassMap* map;
     int R;
 #ifdef __HIPCC__
     __device__ __forceinline__ int off(int i) const { return map ? map->off[i] : i * R; }
@@ -133,6 +136,8 @@ struct GemmPlan {
                              // split into S segments of the contraction (workgroup = group * S + segment, slot =
                              // segment); 0 for one and two row blocks. The fields above then describe the balanced
                              // split that the persistent layer kernel walks at eight row blocks.
+    int RT, MT;              // prompt passes of more than 256 rows: RT tiles of MT row blocks each (MB = all of them), one
+                             // workgroup per tile, column group and segment; 0 otherwise
     int slots_max;           // slots the output buffer must hold for either
     int32_t* cnt_dev;        // [NG] contributors per column group (device)
     int32_t* slot0_dev;      // [G] slot of every workgroup's first segment (device)
@@ -184,7 +189,11 @@ struct FusedArgs {
 };
 
 #define SD_MAX_MEDUSA 15
-struct ChainArgs { int32_t off[SD_MAX_BATCH]; int32_t len[SD_MAX_BATCH]; };   // prompt tokens of every sequence of the pass
+// prompt tokens of every sequence of the pass; before: rows of the same sequence earlier in this pass
+struct ChainArgs { int32_t off[SD_MAX_BATCH]; int32_t len[SD_MAX_BATCH]; int32_t before[SD_MAX_BATCH]; };
+// Where the rotary stage of a prompt pass of several chunks puts keys and values besides the pass's own scratch: the cache
+// (one layer's planes), and for sequences keep .. of the pass the scratch that a later commit reads ([i - keep][keep_TB blocks]).
+struct KvSinks { uint16_t *kc, *vc; int cap_blocks; uint16_t *kk, *vk; int keep, keep_TB; };
 struct MedusaBias { const uint16_t* p[SD_MAX_MEDUSA + 1]; };
 struct VerifyArgs {
     const int32_t *parent, *depth;      // device tree tables [T]
@@ -209,6 +218,8 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int nb_offset,
 // fills every field of the plan except cnt_dev; cnt_host receives the per-group counts
 // cnt_host [>= ceil(NB/8)] and slot0_host [>= 256] receive the tables the device copies hold
 void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int32_t* slot0_host);
+// the plan of a prompt pass of MB > 8 row blocks (no tables); cycles: its modelled cost
+void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles);
 // out must hold plan.slots * (MB*32) * (NB*32) floats; zfrag: 1 KiB of zeros (device);
 // returns the view consumers read
 // ev0 / ev1 (both or neither): events that receive the kernel's own start and end time stamps,
@@ -243,7 +254,7 @@ void launch_build_rows_tree(RowTable rt, const int32_t* parent, const int32_t* d
                             const int32_t* root_tok, const int32_t* cand, const int32_t* kv_len,
                             int B, int T, int Tp, int R, int H, int topk, int hd, const double* freq,
                             const void* embed, int embed_f32, int d, int V, float* x, hipStream_t s);
-void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, RowMap* rm_dev, const int32_t* kv_len,
+void launch_build_rows_chain(RowTable rt, const int32_t* tokens, const ChainArgs& ca, const RowMap& rm, PassMap* rm_dev, const int32_t* kv_len,
                              int B, int Tp, int hd, const double* freq, const void* embed, int embed_f32, int d, int V,
                              float* x, hipStream_t s);
 // float32 device path (f32.hip): natural row-major layouts, float32 products
@@ -270,7 +281,7 @@ void launch_f32_kv_rows(float* kc, float* vc, float* k_rows, float* v_rows, int 
 void launch_norm_pack(float* x, PartView pv, const void* gain, float eps, void* xn_packed, float* hf_out,
                       int M, int d, int MB, const int32_t* gather, hipStream_t s);
 void launch_rope_kv(PartView pv, RowTable rt, RowRef rr, void* q_packed, void* kt, void* vt, int B, int Tp, int nh,
-                    int hd, hipStream_t s);
+                    int hd, hipStream_t s, const KvSinks* sinks = nullptr);
 void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, const void* kt, const void* vt,
                       const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart,
                       RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep,
