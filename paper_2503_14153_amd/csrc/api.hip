@@ -80,7 +80,7 @@ struct sd_model {
     MedusaBias medusa_b;
     std::vector<LayerW> layers;
     // workspace
-    float *x, *part, *part2, *logits, *hlogits, *hf, *h_rows, *opart;
+    float *x, *part, *logits, *hlogits, *hf, *h_rows, *opart;
     float2* mlpart;
     void *xn, *attn_x, *act, *q, *kt, *vt;
     void* xh;                                // draft-head rows of every tree row, in 256-row operand chunks
@@ -379,7 +379,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     const int Mp = m->MBmax * 32, nh = cfg->n_heads, hd = cfg->head_dim;
     const int ld_max = std::max(std::max(3 * d, 2 * m->Fpad), H * d);
     // launch plans for every GEMM shape this model can issue
-    size_t pf = 0, pf2 = 0;                                // (pf2: the down projection's, whose launch reads the gate/up one's)
+    size_t pf = 0;
     std::vector<int32_t> cnt_all;
     std::vector<size_t> cnt_off;
     {
@@ -402,7 +402,6 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
                 cnt_all.insert(cnt_all.end(), slot0.begin(), slot0.end());
                 m->plans.push_back(pl);
                 pf = std::max(pf, (size_t)pl.slots_max * (mb * 32) * (size_t)sh[1] * 32);
-                if (mb == 1 && sh[0] == m->KBf && sh[1] == m->NBo) pf2 = (size_t)pl.slots_max * 32 * (size_t)sh[1] * 32;
             }
     }
     (void)ld_max;
@@ -433,7 +432,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     const int HBp = pow2_blocks(std::min((H + 1) * SD_MAX_BATCH, 256)) * 32;      // head rows of a batch, and its base rows
     size_t wz = 0;
     auto wtake = [&](size_t bytes) { size_t o = wz; wz = align_up(wz + bytes, 256); return o; };
-    size_t w_x = wtake((size_t)Mr * d * 4), w_part = wtake(pf_prompt * 4), w_part2 = wtake(pf2 * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
+    size_t w_x = wtake((size_t)Mr * d * 4), w_part = wtake(pf_prompt * 4), w_logits = wtake((size_t)Mp * m->Vpad * 4);
     size_t w_hlog = wtake((size_t)HBp * m->Vpad * 4), w_hf = wtake((size_t)Mp * d * 4);
     size_t w_hrows = wtake((size_t)SD_MAX_BATCH * d * 4);
     size_t w_opart = wtake((size_t)Mp * nh * m->max_parts * hd * 4), w_ml = wtake((size_t)Mp * nh * m->max_parts * 8);
@@ -485,7 +484,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
         return fail(SD_ERR_HIP, "workspace clear: %s", hipGetErrorString(e));
     }
     char* Wk = m->work;
-    m->x = (float*)(Wk + w_x); m->part = (float*)(Wk + w_part); m->part2 = (float*)(Wk + w_part2); m->logits = (float*)(Wk + w_logits);
+    m->x = (float*)(Wk + w_x); m->part = (float*)(Wk + w_part); m->logits = (float*)(Wk + w_logits);
     m->hlogits = (float*)(Wk + w_hlog); m->hf = (float*)(Wk + w_hf); m->h_rows = (float*)(Wk + w_hrows);
     m->opart = (float*)(Wk + w_opart); m->mlpart = (float2*)(Wk + w_ml);
     m->xn = Wk + w_xn; m->attn_x = Wk + w_attn; m->act = Wk + w_act; m->q = Wk + w_q;
@@ -864,10 +863,49 @@ static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out
     return launch_gemm(*p, Xp, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
 }
 
-static PartView run_gemm_few(sd_model* m, const GemmPlan* p, const FewSrc& src, const void* Wp, float* out, int rows, int n_real,
-                             hipStream_t s) {
-    const int pi = prof_claim(m, PROF_GEMM, (double)n_real * p->KB * 16 * 2);
-    return launch_gemm_few(*p, src, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
+// ---- a handful of rows (few.hip): no packed operands, no partial sums
+// Do M rows against a packed matrix of KB x NB fragments go that way?
+static bool few_rows(int M, int KB, int NB) { return M <= FEW_ROWS && (uint64_t)KB * NB < (1ull << 22); }
+static FewLinear few_linear(const float* X, int ldx, const void* W, int KB, int NB, int M, int units, float* out, int ldo) {
+    FewLinear a;
+    memset(&a, 0, sizeof(a));
+    a.X = X; a.ldx = ldx; a.W = (const bf16x8*)W; a.KB = KB; a.NB = NB; a.M = M; a.n_units = units; a.out = out; a.ldo = ldo;
+    return a;
+}
+static FewLinear few_norm_linear(const sd_model* m, const void* gain, const int32_t* gather, const void* W, int NB, int M, int units,
+                                 float* out, int ldo) {
+    FewLinear a = few_linear(m->x, m->cfg.d_model, W, m->KBd, NB, M, units, out, ldo);
+    a.gain = (const uint16_t*)gain; a.eps = m->cfg.rms_eps; a.gather = gather;
+    return a;
+}
+template <class F>
+static void few_launch(sd_model* m, int n_real, int KB, F&& launch) {
+    const int pi = prof_claim(m, PROF_GEMM, (double)n_real * KB * 16 * 2);
+    launch(prof_ev(m, pi, 0), prof_ev(m, pi, 1));
+}
+// LM head of `rows` rows of X (through the final norm, or as they are): dense logits
+static PartView few_lm_head(sd_model* m, const float* X, const float* row_scale, bool norm, int rows, hipStream_t s) {
+    FewLinear a = norm ? few_norm_linear(m, m->final_norm, nullptr, m->lm_head, m->NBv, rows, m->NBv * 2, m->part, m->Vpad)
+                       : few_linear(X, m->cfg.d_model, m->lm_head, m->KBd, m->NBv, rows, m->NBv * 2, m->part, m->Vpad);
+    a.row_scale = row_scale;
+    few_launch(m, m->cfg.vocab, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_store(a, s, e0, e1); });
+    return PartView{m->part, 0, m->Vpad, nullptr, 1};
+}
+// Draft heads (and with base the rows themselves in front) at rows gather[b] of the residual stream, and the LM head of all
+// of those rows: the partial sums of its logits.
+static PartView few_drafts(sd_model* m, const int32_t* gather, int base, int n, hipStream_t s) {
+    const int H = m->cfg.n_medusa, d = m->cfg.d_model, rows = n * (H + base), MB = pow2_blocks(rows);
+    const bool wide = !few_rows(rows, m->KBd, m->NBv);
+    FewLinear a = few_norm_linear(m, m->final_norm, gather, m->medusa_w, m->NBmed, n, m->NBmed * 2, (float*)m->xn, d);
+    a.base = base;
+    a.scale_out = m->h_rows;
+    if (wide) { a.packed = (bf16x8*)m->xn; a.MB = MB; }
+    few_launch(m, H * d, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_heads(a, m->medusa_b, s, e0, e1); });
+    if (wide) return run_gemm(m, m->xn, m->lm_head, m->part, rows, MB, m->KBd, m->NBv, m->cfg.vocab, s);
+    return few_lm_head(m, (const float*)m->xn, m->h_rows, false, rows, s);
+}
+static bool few_layers(const sd_model* m, int M) {
+    return M <= FEW_LAYER_ROWS && few_rows(M, m->KBd, m->NBgu) && few_rows(M, m->KBd, m->NBqkv) && few_rows(M, m->KBf, m->NBo);
 }
 
 // Every GEMM shape a pass over M rows issues (and, with heads = true, the draft heads after it, in the
@@ -913,14 +951,18 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
     const int MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
     PartView prev = {nullptr, 0, d, nullptr, 0};
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
-    // a handful of rows: the O and down projections make their operands themselves (k_gemm_few; steps only, whose rows lie
-    // rr.R apart)
-    const GemmPlan *plan_o = m->find_plan(MB, m->KBd, m->NBo), *plan_dn = m->find_plan(MB, m->KBf, m->NBo);
-    const bool few_o = rr.map == nullptr && plan_o && few_ok(*plan_o, M), few_dn = plan_dn && few_ok(*plan_dn, M);
+    const int longest = *std::max_element(rm.len, rm.len + B);
+    const bool few = few_layers(m, M);
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW& lw = m->layers[l];
-        launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
-        PartView pq = run_gemm(m, m->xn, lw.wqkv, m->part, M, MB, m->KBd, m->NBqkv, 3 * d, s);
+        PartView pq = {m->part, 0, 3 * d, nullptr, 1};
+        if (few) {
+            const FewLinear a = few_norm_linear(m, lw.attn_norm, nullptr, lw.wqkv, m->NBqkv, M, 3 * d / 16, m->part, 3 * d);
+            few_launch(m, 3 * d, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_store(a, s, e0, e1); });
+        } else {
+            launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
+            pq = run_gemm(m, m->xn, lw.wqkv, m->part, M, MB, m->KBd, m->NBqkv, 3 * d, s);
+        }
         uint16_t* kt = (uint16_t*)m->kt + l * t_stride;
         uint16_t* vt = (uint16_t*)m->vt + l * t_stride;
         // With one query group per head (trees of up to 64 nodes, plain decoding, short prompt chunks) the attention
@@ -939,23 +981,30 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kt, vt, kv->kv_len,
                          m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
                          prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
-        PartView po;
-        if (few_o) {
-            FewSrc fs = {PartView{nullptr, 0, 0, nullptr, 0}, 0, m->opart, m->mlpart, nh, hd, Tp, ag.nparts, rr.R};
-            po = run_gemm_few(m, m->find_plan(MB, m->KBd, m->NBo), fs, lw.wo, m->part, M, d, s);
-        } else {
-            launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, *std::max_element(rm.len, rm.len + B), B, nh, hd, Tp, ag.nparts, MB, s);
-            po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
+        if (few) {
+            FewLinear a = few_linear(nullptr, 0, lw.wo, m->KBd, m->NBo, M, d / 16, m->x, d);
+            a.Xp = (const bf16x8*)m->attn_x;
+            if (rr.map == nullptr && few_merges(M, d)) {      // the projection merges the attention parts itself
+                a.opart = m->opart; a.mlpart = m->mlpart; a.nh = nh; a.hd = hd; a.Tp = Tp; a.nparts = ag.nparts; a.R = rr.R;
+            } else {
+                launch_attn_merge_few(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, s);
+            }
+            few_launch(m, d, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
+            a = few_norm_linear(m, lw.ffn_norm, nullptr, lw.wgu, m->NBgu, M, c.d_ffn / 16, nullptr, 0);
+            a.up = m->Fpad / 16;
+            a.packed = (bf16x8*)m->act;
+            few_launch(m, 2 * c.d_ffn, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_swiglu(a, s, e0, e1); });
+            a = few_linear(nullptr, 0, lw.wdown, m->KBf, m->NBo, M, d / 16, m->x, d);
+            a.Xp = (const bf16x8*)m->act;
+            few_launch(m, d, m->KBf, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
+            continue;                                  // (prev stays empty: the residual stream is complete)
         }
+        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s);
+        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
-        if (few_dn) {
-            FewSrc fs = {pg, m->Fpad, nullptr, nullptr, 0, 0, 0, 0, 0};
-            prev = run_gemm_few(m, m->find_plan(MB, m->KBf, m->NBo), fs, lw.wdown, m->part2, M, d, s);
-        } else {
-            launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
-            prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
-        }
+        launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
+        prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
     }
     return prev;
 }
@@ -1097,6 +1146,7 @@ static void run_draft_heads_f32(sd_model* m, sd_kv* kv, const int32_t* rows, int
 static PartView run_lm_head(sd_model* m, PartView prev, int M, hipStream_t s, bool keep_h) {
     const sd_config& c = m->cfg;
     const int MB = pow2_blocks(M);
+    if (!keep_h && prev.nmax == 0 && few_rows(M, m->KBd, m->NBv)) return few_lm_head(m, nullptr, nullptr, true, M, s);
     launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, keep_h ? m->hf : nullptr, M, c.d_model, MB, nullptr, s);
     return run_gemm(m, m->xn, m->lm_head, m->part, M, MB, m->KBd, m->NBv, c.vocab, s);
 }
@@ -1137,6 +1187,11 @@ static void run_draft_heads(sd_model* m, sd_kv* kv, int B, float* head_logits_ou
     const int d = c.d_model, H = c.n_medusa;
     if (m->f32) { run_draft_heads_f32(m, kv, kv->last_row, B, every_sequence(), head_logits_out, s); return; }
     const PartView none = {nullptr, 0, d, nullptr, 0};
+    if (few_rows(B, m->KBd, m->NBmed)) {
+        const PartView pl = few_drafts(m, kv->last_row, 0, B, s);
+        launch_topk(pl, 0, c.vocab, c.topk, kv->cand, B, H, every_sequence(), head_logits_out, m->ranked, s);
+        return;
+    }
     launch_norm_pack(m->x, none, m->final_norm, c.rms_eps, m->xn, m->h_rows, B, d, 1, kv->last_row, s);
     PartView pm = run_gemm(m, m->xn, m->medusa_w, m->part, B, 1, m->KBd, m->NBmed, H * d, s);
     const int MBh = pow2_blocks(H * B);
@@ -1156,6 +1211,12 @@ static void run_known_rows(sd_model* m, sd_kv* kv, PartView prev, int n, const i
         launch_f32_norm_linear(m->x, gather, m->f.final_norm, c.rms_eps, m->f.lm_head, m->logits, n, c.vocab, d, m->Vpad, s);
         launch_rank_best(dense_logits(m, m->logits), 0, n, c.vocab, logits, ld, m->best, s);
         run_draft_heads_f32(m, kv, gather, n, sl, head_logits_out, s);
+        return;
+    }
+    if (prev.nmax == 0 && few_rows(n, m->KBd, m->NBmed) && n * (H + 1) <= 256) {
+        const PartView pl = few_drafts(m, gather, 1, n, s);
+        launch_rank_best(pl, 0, n, c.vocab, logits, ld, m->best, s);
+        launch_topk(pl, n, c.vocab, c.topk, kv->cand, n, H, sl, head_logits_out, m->ranked, s);
         return;
     }
     launch_norm_pack(m->x, prev, m->final_norm, c.rms_eps, m->xn, m->h_rows, n, d, 1, gather, s);

@@ -494,7 +494,13 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
         pv_arg = *qkv;
         rt_arg = *rt;
         const bool four = qkv->cnt == nullptr && qkv->nmax == 4;     // the aligned QKV plan of the 7B and 13B shapes
-#define ATT_FR(HD_, TBW_) do { if (four) ATT(HD_, TBW_, 4, 1, 4); else ATT(HD_, TBW_, 4, 1, 0); } while (0)
+        const bool one = qkv->cnt == nullptr && qkv->nmax == 1 && TBW == 1;      // a handful of rows (few.hip)
+#define ATT_FR(HD_, TBW_)                                                                                        \
+    do {                                                                                                        \
+        if (four) ATT(HD_, TBW_, 4, 1, 4);                                                                       \
+        else if (one) ATT(HD_, TBW_, 4, 1, (TBW_ == 1 ? 1 : 0));                                                 \
+        else ATT(HD_, TBW_, 4, 1, 0);                                                                            \
+    } while (0)
         if (hd == 128) { if (TBW == 2) ATT_FR(128, 2); else ATT_FR(128, 1); }
         else           { if (TBW == 2) ATT_FR(64, 2);  else ATT_FR(64, 1); }
 #undef ATT_FR
@@ -511,18 +517,36 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 // ------------------------------------------------------------------------------------------
 // Merge the split-KV partials and emit the packed bf16 operand of the O-projection (body: row_ops.h).
 // one thread per (seq, head, query t, 8 consecutive output dims), grid (chunks of t x dims, head, seq)
+// FEW: a handful of rows, as few.hip's ready-made operand
+template <bool FEW>
 __global__ void k_attn_merge(const float* __restrict__ opart, const float2* __restrict__ mlpart,
                              bf16x8* __restrict__ xp, RowRef rr, int nh, int hd, int e8_shift, int Tp, int nparts, int MB) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;      // hd / 8 = 1 << e8_shift pieces per query row
     const int e8 = idx & ((1 << e8_shift) - 1), t = idx >> e8_shift;
-    const int b = blockIdx.z;
+    const int b = blockIdx.z, h = blockIdx.y;
     if (t >= rr.len(b)) return;
-    attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, MB, b, /*h=*/blockIdx.y, t, rr.off(b) + t, e8);
+    if constexpr (FEW) {
+        float o[8];
+        bf16x8 hi, lo;
+        attn_merge_values(opart, mlpart, nh, hd, Tp, nparts, b, h, t, e8, o);
+        split_hilo(o, hi, lo);
+        const int u = few_unit(rr.off(b) + t, (h << e8_shift) + e8);
+        xp[u] = hi;
+        xp[u + 8] = lo;
+    } else {
+        attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, MB, b, h, t, rr.off(b) + t, e8);
+    }
 }
 
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s) {
     const int e8_shift = hd == 128 ? 4 : 3;            // head_dim is 128 or 64
-    hipLaunchKernelGGL(k_attn_merge, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
+    hipLaunchKernelGGL(k_attn_merge<false>, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
                        (bf16x8*)x_packed, rr, nh, hd, e8_shift, Tp, nparts, MB);
+}
+void launch_attn_merge_few(const float* opart, const float2* mlpart, void* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
+                            int nparts, hipStream_t s) {
+    const int e8_shift = hd == 128 ? 4 : 3;
+    hipLaunchKernelGGL(k_attn_merge<true>, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
+                       (bf16x8*)out, rr, nh, hd, e8_shift, Tp, nparts, 0);
 }

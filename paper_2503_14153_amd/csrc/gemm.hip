@@ -20,7 +20,6 @@
 
 #include "sd_internal.h"
 #include "sk_gemm.h"
-#include "row_ops.h"
 
 // ------------------------------------------------------------------------------------------
 // Re-tile a row-major bf16 matrix W[N][K] into fragment order (see sd_internal.h).
@@ -83,74 +82,6 @@ __global__ __launch_bounds__(512, 4) void k_gemm_sk(const bf16x8* __restrict__ X
     gm.issue_x();                                      // the short L2 loads first: a wave's loads return in order
     gm.issue_ring();
     gm.template run<false>(xs, SkRowScale{nullptr, 0, 0.f, 0.f}, nullptr);
-}
-
-// ------------------------------------------------------------------------------------------
-// One or two rows (plain decoding): the same split and the same sums, but the operand of a workgroup's segment is so small
-// that the workgroup makes it itself, straight into LDS, while its first weights are on their way, and then streams
-// without a barrier. SRC: 1 = SwiGLU of the gate/up projection's partial sums, 2 = merge of the attention parts. Bound by
-// the weight stream and the launches around it: the launch that packed the operand (4.7 us and a gap) is gone, twice a
-// layer (7B shape, four layers, one row: step 614 -> 592 us). Every row costs the down projection's workgroups 1.2 us more
-// of that work (28.7 us at eight rows against 16.4 + 4.8), so beyond two rows the operand comes from memory.
-template <int SRC>
-__global__ __launch_bounds__(512, 4) void k_gemm_few(FewSrc src, const bf16x8* __restrict__ Wp, const bf16x8* __restrict__ zfrag,
-                                                     float* __restrict__ out, int KB, int NB, int ldo, size_t slot_stride,
-                                                     int rows, int n, uint32_t kb_magic, const int32_t* __restrict__ slot0_tab) {
-    constexpr int R = 4, F = FEW_ROWS;                 // ring depth (8: 600 us)
-    __shared__ bf16x8 xs[FEW_STEPS * 4 * F];           // [step][hi, lo][column group][row]
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int u = blockIdx.x * n;                      // first unit: n units each, all of one column group
-    const int ng = KB == 1 ? u : (int)__umulhi((uint32_t)u, kb_magic), kb0 = u - ng * KB;
-    const int nb = ng * 8 + wave;
-    const size_t wstep = (size_t)NB * 64;
-    const bf16x8* wp = Wp + ((size_t)kb0 * NB + min(nb, NB - 1)) * 64 + lane;
-    const bf16x8* zl = zfrag + lane;
-    bf16x8 w[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) w[i] = __builtin_nontemporal_load(i < n ? wp + (size_t)i * wstep : zl);
-    int zero = 0;
-    asm volatile("" : "+v"(zero));                     // (a vector load: nothing waits for it before the end)
-    const int slot = slot0_tab[blockIdx.x + zero];
-    static_assert(FEW_ROWS == 2, "rows are told apart by one bit");
-    const int rsh = rows - 1;
-    for (int i = tid; i < (2 * n) << rsh; i += 512) {  // item: row m, eight columns
-        const int m = i & ((1 << rsh) - 1), piece = i >> rsh, k8 = kb0 * 2 + piece;
-        float f[8];
-        if constexpr (SRC == 1) {
-            swiglu_values<true>(src.gu, src.Fpad, m, k8, f);
-        } else {
-            const int e8s = src.hd == 128 ? 4 : 3, b = m / src.R;
-            attn_merge_values(src.opart, src.mlpart, src.nh, src.hd, src.Tp, src.nparts, b, k8 >> e8s, m - b * src.R,
-                              k8 & ((1 << e8s) - 1), f);
-        }
-        bf16x8 hi, lo;
-        split_hilo(f, hi, lo);
-        bf16x8* d = xs + (piece >> 1) * (4 * F) + (piece & 1) * F + m;
-        d[0] = hi;
-        d[2 * F] = lo;
-    }
-    __syncthreads();
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    const bf16x8* xl = xs + (lane >> 5) * F + (lane & (F - 1));        // (rows 2 .. 31 repeat: products nobody reads)
-    for (int s0 = 0; s0 < n; s0 += R) {
-        wp += R * wstep;
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int s = min(s0 + i, n - 1);          // past the end: zero weights on the last operand
-            const bf16x8 hi = xl[s * (4 * F)], lo = xl[s * (4 * F) + 2 * F];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, w[i], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, w[i], acc, 0, 0, 0);
-            w[i] = __builtin_nontemporal_load(s0 + R + i < n ? wp + (size_t)i * wstep : zl);
-        }
-    }
-    if (nb < NB) {
-        const TileStore ts(out + (size_t)__builtin_amdgcn_readfirstlane(slot) * slot_stride, 0, rows, ldo);
-#pragma unroll
-        for (int v = 0; v < F; ++v)                    // rows 4 (lane / 32) + v
-            ts.put(acc[v], ((4 * (lane >> 5) + v) * ldo + nb * 32 + (lane & 31)) * 4);
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -485,31 +416,5 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
     }
 #undef SK_LAUNCH
 #undef SK_ARGS
-    return pv;
-}
-
-bool few_ok(const GemmPlan& p, int rows) {
-    return p.MB == 1 && rows <= FEW_ROWS && p.rem == 0 && p.KB % p.upw == 0 && p.upw <= FEW_STEPS;
-}
-PartView launch_gemm_few(const GemmPlan& p, const FewSrc& src, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
-                         hipEvent_t ev0, hipEvent_t ev1) {
-    PartView pv;
-    pv.base = out;
-    pv.ld = p.NB * 32;
-    pv.slot_stride = (size_t)32 * pv.ld;
-    pv.cnt = p.uniform ? nullptr : p.cnt_dev;
-    pv.nmax = p.slots;
-    const uint32_t kb_magic = (uint32_t)((0x100000000ull + (uint64_t)p.KB - 1) / (uint64_t)p.KB);
-#define FEW(SRC_)                                                                                                        \
-    do {                                                                                                                 \
-        if (ev0 || ev1)                                                                                                  \
-            hipExtLaunchKernelGGL((k_gemm_few<SRC_>), dim3(p.G), dim3(512), 0, s, ev0, ev1, 0, src, (const bf16x8*)Wp,   \
-                                  (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.upw, kb_magic, p.slot0_dev); \
-        else                                                                                                             \
-            hipLaunchKernelGGL((k_gemm_few<SRC_>), dim3(p.G), dim3(512), 0, s, src, (const bf16x8*)Wp, (const bf16x8*)zfrag, out, \
-                               p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.upw, kb_magic, p.slot0_dev);                   \
-    } while (0)
-    if (src.opart) FEW(2); else FEW(1);
-#undef FEW
     return pv;
 }

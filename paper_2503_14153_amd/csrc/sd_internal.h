@@ -228,18 +228,37 @@ void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles);
 // rows: rows that exist; the partial tiles' other rows are not written
 PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
                      hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// At most FEW_ROWS rows: the projection makes its operand itself, from what the launch before it would have packed (the
-// gate/up projection's partial sums, or the attention parts), so that launch is not needed. few_ok: the plan's workgroups
-// have one segment each, of FEW_STEPS contraction blocks at most.
-#define FEW_ROWS 2
-#define FEW_STEPS 96
-struct FewSrc {
-    PartView gu; int Fpad;                                            // down projection: silu(gate) * up
-    const float* opart; const float2* mlpart; int nh, hd, Tp, nparts, R;   // O projection: merged attention output, row m = b * R + t
+// A handful of rows (few.hip): float32 rows in, every column finished by one workgroup, no partial sums.
+struct FewLinear {
+    const float* X; int ldx;                                          // rows [M][ldx] (row m: gather[m] if given)
+    const int32_t* gather;
+    const bf16x8* Xp;                                                 // or the ready-made operand (add), M <= FEW_LAYER_ROWS
+    const uint16_t* gain; float eps;                                  // RMSNorm of the rows, or NULL
+    const bf16x8* W; int KB, NB;                                        // packed weights, KB * NB KiB < 4 GiB
+    int M, n_units;                                                   // M <= FEW_ROWS; columns / 16 (pairs, if gate and up)
+    int up;                                                           // first up block, in units of 16 columns
+    float* out; int ldo;
+    bf16x8* packed; int MB;                                           // results as an operand instead: swiglu: ready-made for
+                                                                      // add; heads (or NULL): of a GEMM of MB row blocks
+    const float* row_scale;                                           // store: factor of every row's result, or NULL
+    int base; float* scale_out;                                       // heads: 1 = the rows h themselves come first, as x * gain
+                                                                      // whose factor goes to scale_out (heads' rows: 1), so that
+                                                                      // their products are the bits that norm(X) gives
+    const float* opart; const float2* mlpart;                         // or NULL: the rows are the merged attention parts,
+    int nh, hd, Tp, nparts, R;                                        // row m = b * R + t; few_merges(M, d)
 };
-bool few_ok(const GemmPlan& p, int rows);
-PartView launch_gemm_few(const GemmPlan& p, const FewSrc& src, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
-                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+#define FEW_ROWS 16
+#define FEW_LAYER_ROWS 8         // layers (add, swiglu): one product takes both terms
+#define FEW_MERGE_ROWS 2         // (every workgroup merges all of the rows, 8 bytes of LDS per input)
+static inline bool few_merges(int M, int d) { return M <= FEW_MERGE_ROWS && d <= 6144; }
+// 16-byte unit of (row m, inputs 8 k8 ..) in the ready-made operand: hi terms; the lo terms lie 8 units further
+static __host__ __device__ inline int few_unit(int m, int k8) { return (k8 >> 2) * 64 + (k8 & 3) * 16 + m; }
+// out = X W^T (through RMSNorm if gain is given); out += X W^T; out = silu(gate) * up of norm(X); draft heads: rows
+// [base + head][M] of h + silu(W_head h + bias), h = norm(X)
+void launch_few_store(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_few_add(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_few_swiglu(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_few_heads(const FewLinear& a, const MedusaBias& bias, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // persistent layer kernel: G workgroups (all must be resident at once), a.MB in {1, 2, 8}
 void launch_layer(const FusedArgs& a, int G, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // how many of its workgroups the device can hold at once (0 on error)
@@ -289,6 +308,9 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
                       const RowTable* rt = nullptr);
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s);
+// the same, as few.hip's ready-made operand
+void launch_attn_merge_few(const float* opart, const float2* mlpart, void* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
+                            int nparts, hipStream_t s);
 void launch_swiglu_pack(PartView pv, int F, int Fpad, void* act_packed, int M, int MB, hipStream_t s);
 // output rows base * B + i*B + b in chunks of chunk_rows rows, each a packed activation of MB (last: MBlast) row blocks;
 // base = 1: rows 0 .. B-1 are the h rows themselves
