@@ -931,21 +931,25 @@ static bool fused_eligible(const sd_model* m, int M) {
     const int MB = pow2_blocks(M);
     return m->use_fused && m->fused_ok && (MB == 1 || MB == 2 || MB == 8);
 }
-// ragged: the sequences' lengths (host's bounds) add up to less than four fifths of B times the longest.
-static bool ragged_lengths(const sd_kv* kv, const int32_t* seq, int B, int n_hi) {
-    long long sum = 0;
-    for (int i = 0; i < B; ++i) sum += kv->len_hi[seq ? seq[i] : i];
-    return sum * 5 < 4ll * n_hi * B;
-}
 // The geometry that the pass over B sequences of Tp rows will launch: worked out once per pass, launched, and part of the
 // key under which the pass is captured. (float32 attention has no parts: none of its launches depends on n_hi.)
-static AttnGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int Tp, int n_hi) {
-    if (m->f32) return AttnGeom{};
-    return attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
-                                 ragged_lengths(kv, seq, B, n_hi));
+struct PassGeom : AttnGeom { AttnSplit split; };
+static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int Tp, int n_hi) {
+    PassGeom g = {};
+    if (m->f32) return g;
+    // (a batch is cut sequence by sequence once its longest one has 256 rows)
+    static_cast<AttnGeom&>(g) = attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
+                                                      B > 1 && n_hi >= 256);
+    if (g.per == 0) {
+        int len[SD_MAX_BATCH];
+        for (int i = 0; i < B; ++i) len[i] = kv->len_hi[seq ? seq[i] : i];
+        g.split = attn_split(m->cfg.n_heads, B, len);
+        g.ncparts = g.nparts = g.split.max_parts;
+    }
+    return g;
 }
 
-static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, const AttnGeom& ag,
+static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, const PassGeom& ag,
                            hipStream_t s) {
     const sd_config& c = m->cfg;
     const int MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32;
@@ -973,21 +977,25 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         // (16 k rows: attention 55 -> 64 us): there the stage stays a launch of its own. Where every (sequence, head) has
         // ONE workgroup (a batch that fills the chip) all workgroups carry the same extra work, none is a straggler, and
         // the launch saved is worth more than it costs (batch of eight 32-node trees: attention 65.4 -> 72.8 us, the
-        // 11.8 us launch gone, step -0.8 %); so it is with the two even parts of a ragged batch, whose second takes the tree.
-        const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1 || ag.per == 0);
+        // 11.8 us launch gone, step -0.8 %); so it is with the parts of a batch that is cut sequence by sequence, the last of
+        // which takes the tree.
+        const AttnSplit* split = ag.split.n ? &ag.split : nullptr;
+        const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1 || split);
         if (!fr) launch_rope_kv(pq, m->rt, rr, m->q, kt, vt, B, Tp, nh, hd, s);
         // algorithmic bytes: one read of K and V of the committed rows (upper bound n_hi) + tree rows
         const int pa = prof_claim(m, PROF_ATTN, (double)B * (n_hi + Tp) * 2.0 * d * 2.0);
         launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kt, vt, kv->kv_len,
                          m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
-                         prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
+                         prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr, split);
         if (few) {
             FewLinear a = few_linear(nullptr, 0, lw.wo, m->KBd, m->NBo, M, d / 16, m->x, d);
             a.Xp = (const bf16x8*)m->attn_x;
             if (rr.map == nullptr && few_merges(M, d)) {      // the projection merges the attention parts itself
                 a.opart = m->opart; a.mlpart = m->mlpart; a.nh = nh; a.hd = hd; a.Tp = Tp; a.nparts = ag.nparts; a.R = rr.R;
+                for (int& own : a.own) own = ag.nparts;
+                for (int i = 0; i < ag.split.n; ++i) a.own[ag.split.slot[i] & 255] = ag.split.slot[i] >> 16;
             } else {
-                launch_attn_merge_few(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, s);
+                launch_attn_merge_few(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, s, split);
             }
             few_launch(m, d, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
             a = few_norm_linear(m, lw.ffn_norm, nullptr, lw.wgu, m->NBgu, M, c.d_ffn / 16, nullptr, 0);
@@ -999,7 +1007,7 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
             few_launch(m, d, m->KBf, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
             continue;                                  // (prev stays empty: the residual stream is complete)
         }
-        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s);
+        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
         PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
@@ -1026,7 +1034,7 @@ static FusedGemm fused_gemm(const sd_model* m, int MB, int KB, int NB, const voi
 // Layers 0..L-1 and, with want_lm, the final norm and the LM-head GEMM, whose partial sums the returned view
 // describes (without want_lm: the last down projection's, still to be added to m->x).
 // (Its phases take the rows as [sequence][Tp]: the row map says off[i] = i * Tp.)
-static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int Tp, int n_hi, const AttnGeom& ag, bool want_lm,
+static PartView run_forward_fused(sd_model* m, sd_kv* kv, RowRef rr, int B, int Tp, int n_hi, const PassGeom& ag, bool want_lm,
                                   hipStream_t s) {
     const sd_config& c = m->cfg;
     const int M = B * Tp, MB = pow2_blocks(M), d = c.d_model, nh = c.n_heads, hd = c.head_dim, TB = Tp / 32, L = c.n_layers;
@@ -1162,7 +1170,7 @@ static ScratchRows scratch_of_pass(const sd_kv* kv, const RowMap& rm, int n, int
 // The whole verifying pass: layers, and with want_lm the final norm and the LM head; returns the partial sums of the logits
 // (without want_lm: of the last down projection, still to be added to m->x). Sequence i's rows start at row i * R (R = 0:
 // at rm.off[i], prompt chunks).
-static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, const AttnGeom& ag,
+static PartView run_forward(sd_model* m, sd_kv* kv, const RowMap& rm, int B, int M, int R, int Tp, int n_hi, const PassGeom& ag,
                             bool want_lm, bool keep_h, hipStream_t s) {
     const RowRef rr = {R ? nullptr : m->rm_dev, R};
     if (m->f32) { run_forward_f32(m, kv, rr, rm, B, M, Tp, want_lm, s); return dense_logits(m, m->logits); }
@@ -1366,7 +1374,7 @@ static void run_prompt_pass(sd_model* m, sd_kv* kv, const int32_t* tokens, const
     const int n_fin = ending_rows(p.chunks, rm, &last, &fin);
     launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
                             c.d_model, c.vocab, m->x, s);
-    const AttnGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
+    const PassGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
     PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
     launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
     m->scratch = scratch_of_pass(kv, rm, A, M, Tp, ca.len, 0);
@@ -1417,7 +1425,7 @@ static void run_prompt_passes(sd_model* m, sd_kv* kv, const int32_t* tokens, con
     launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, V, Tp, hd, m->rope_freq, m->embed, 0, d, c.vocab, m->x, s);
     const RowRef rr = {m->rm_dev, 0};
     // (parts: what the partials' buffer holds)
-    const AttnGeom ag = attn_geometry(nh, std::min(m->max_parts, m->MBmax * 32 * m->max_parts / (V * Tp)), V, Tp, n_hi, false, false);
+    const AttnGeom ag = attn_geometry(nh, std::min(m->max_parts, m->MBmax * 32 * m->max_parts / (V * Tp)), V, Tp, n_hi, false);
     const int keep_A = V - keep, keep_TB = keep_Tp / 32;
     const size_t keep_stride = (size_t)keep_A * nh * keep_TB * 32 * hd;
     PartView prev = {nullptr, 0, d, nullptr, 0};
@@ -1517,7 +1525,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     int32_t* slots = io->src_slots ? io->src_slots : kv->i_slots;
     const int32_t* cand = io->forced_cand ? io->forced_cand : kv->cand;
 
-    const AttnGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
+    const PassGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
     const ScratchRows scratch = scratch_of_pass(kv, rm, B, M, Tp, nullptr, T);
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,
@@ -1573,6 +1581,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
                                      (uint64_t)m->draft_schedule, (uint64_t)heads,
                                      (uint64_t)(m->use_fused ? 1 : 0) | ((uint64_t)m->sync_timeout_ticks << 1),
                                      (uint64_t)(uintptr_t)m->timeline, (uint64_t)m->timeline_launches};
+        key.insert(key.end(), ag.split.slot, ag.split.slot + ag.split.n);
         hipGraphExec_t exec = nullptr;
         for (const sd_model::StepGraph& g : m->graphs)
             if (g.key == key) { exec = g.exec; break; }

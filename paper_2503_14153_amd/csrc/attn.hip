@@ -15,7 +15,10 @@
 //   * the cache range is split over workgroups (split-KV) and over the four waves of each;
 //     the waves merge through LDS, the workgroups' partial (max, sum, O) triples are merged
 //     by a second small kernel, which also emits the packed bf16 operand of the O-projection.
+#include <type_traits>
+
 #include "sd_internal.h"
+#include "attn_geom.h"
 #include "row_ops.h"
 
 #define NEG_INF (-__builtin_inff())
@@ -68,13 +71,16 @@ template <int N> static __device__ __forceinline__ void wait_vm() { asm volatile
 // other, and nothing is looked up before the first addresses are known.
 // EVEN: every sequence's blocks are split evenly over its ncparts parts (ragged batches, see attn_geometry); else part p
 // starts at block p * per and its first blocks are requested before the length is known.
+struct NoSplit {};
 template <int HD, int TBW, int AW, int FR, int NS, bool MAP, bool EVEN>
-__global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp, const bf16x8* Kc, const bf16x8* Vc,
+__global__ __launch_bounds__(256, TBW == 1 ? 2 : 1) void k_tree_attn(const bf16x8* __restrict__ Qp, const bf16x8* Kc, const bf16x8* Vc,
                                                    const bf16x8* Kt, const bf16x8* Vt, const int32_t* __restrict__ kv_len,
                                                    const uint32_t* __restrict__ anc, float* __restrict__ opart,
                                                    float2* __restrict__ mlpart, int nh, int Tp, int cap_blocks,
                                                    int ncparts, int per, int tree_sep, float scale_log2,
-                                                   int xcd_stride, int nseq, PartView pv, RowTable rt, RowRef rr) {
+                                                   int xcd_stride, int nseq, PartView pv, RowTable rt, RowRef rr,
+                                                   std::conditional_t<EVEN, AttnSplit, NoSplit> split) {
+    constexpr int RB = TBW == 1 ? 1 : 2;
     constexpr int KK = HD / 16;        // contraction steps of QK^T = K fragments per block
     constexpr int EB = HD / 32;        // 32-wide output blocks of PV
     constexpr int NV = 2 * EB;         // V fragments per block
@@ -90,7 +96,15 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     const int TB = Tp / 32, TG = TB / TBW;
     const int nparts = ncparts + tree_sep;             // tree_sep: parts that hold tree blocks only (0, 1, or one per block)
     int part, h, tg, b;
-    if (xcd_stride == 0) {                             // grid (part, head x query group, sequence)
+    int own = ncparts;                                 // EVEN: parts of this sequence
+    if constexpr (EVEN) {                              // grid (head, entry), or (entry, head)
+        h = xcd_stride < 0 ? blockIdx.x : blockIdx.y;
+        const uint32_t e = split.slot[xcd_stride < 0 ? blockIdx.y : blockIdx.x];
+        tg = 0;
+        b = e & 255;
+        part = (e >> 8) & 255;
+        own = e >> 16;
+    } else if (xcd_stride == 0) {                      // grid (part, head x query group, sequence)
         part = blockIdx.x;
         h = blockIdx.y / TG;
         tg = blockIdx.y % TG;
@@ -126,7 +140,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // part, or, when every tree block has a part of its own (tree_sep >= 2, one query group), block part - ncparts.
     const bool split_tree = tree_sep >= 2;
     const int tb0 = (split_tree && part >= ncparts) ? part - ncparts : 0;
-    const int ntree = split_tree ? (part >= ncparts ? 1 : 0) : ((part == nparts - 1) ? tg * TBW + TBW : 0);
+    const int ntree = split_tree ? (part >= ncparts ? 1 : 0) : ((part == (EVEN ? own : nparts) - 1) ? tg * TBW + TBW : 0);
 
     // ancestor words of this lane's query rows: only the part with the tree blocks masks by them
     static_assert(SD_ANC_WORDS == 8 && (AW == 4 || AW == 8), "one or two 16-byte loads per row");
@@ -152,7 +166,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     int here = per;                                    // cache blocks of this part, at most
     int c0 = part * per;
     if constexpr (EVEN) {
-        const int each = max(1, (int)__umulhi((uint32_t)(nblk + ncparts - 1), (uint32_t)per));       // per = ceil(2^32 / ncparts)
+        const int each = max(1, (nblk + own - 1) / own);
         c0 = part * each;
         here = max(0, min(each, nblk - c0));
     }
@@ -212,7 +226,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
             }
         }
     }
-    bf16x8 kr[2][KK], vr[2][NV];
+    bf16x8 kr[RB][KK], vr[RB][NV];
     auto request_k = [&](bf16x8(&kd)[KK], int j) {
         const bf16x8* kp = kaddr(j);
 #pragma unroll
@@ -233,7 +247,15 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
 #pragma unroll
         for (int i = 0; i < NV; ++i) vd[i] = vp[i * 64];
     };
-    if (!tree_only) { request_k(kr[0], jw); request_v(vr[0], jw); request_k(kr[1], jw + 1); request_v(vr[1], jw + 1); }
+    const auto first_blocks = [&]() {
+        if (!tree_only)
+#pragma unroll
+            for (int r = 0; r < RB; ++r) { request_k(kr[r], jw + r); request_v(vr[r], jw + r); }
+    };
+    // EVEN: their addresses wait for the length; the projection's sums do not, and loads return in order. With one slot of
+    // them (a handful of rows) they go first (73.5 -> 72.6 us at eight sequences); with four it costs more (81 -> 83).
+    constexpr bool LATE = EVEN && NS == 1;
+    if constexpr (!LATE) first_blocks();
     if constexpr (FR) {                                // queries of this head, built here, -> LDS
         constexpr int NA = HD / 16;
         const size_t q_unit0 = ((size_t)b * nh + h) * TB * (KK * 2 * 64);
@@ -250,6 +272,7 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
 #pragma unroll
         for (int i = 0; i < QW; ++i) lds_dma16(qsrc + (wave * QW + i) * 64, myq_addr + i * 1024);
     }
+    if constexpr (LATE) first_blocks();
 
     const int ncache = has_cache ? max(0, min(here, nblk - c0)) : 0;
     const int nit = __builtin_amdgcn_readfirstlane(max(0, min(share, ntree + ncache - jw)));       // this wave's items [jw, jw + nit)
@@ -376,20 +399,21 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     // the loop in two copies, so that each has loads of one kind in a straight line (a branch around a load makes the
     // compiler wait for everything in flight)
     auto run_items = [&](auto&& req_k, auto&& req_v) {
-        for (int it = 0; it < nit; it += 2) {
+        for (int it = 0; it < nit; it += RB) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
+            for (int r = 0; r < RB; ++r) {
                 const bool live = it + r < nit;
                 f32x16 S[TBW];
                 if (live) qk(kr[r], S);
-                req_k(kr[r], jw + min(it + r + 2, nit - 1));   // past the wave's last item: that item again
+                req_k(kr[r], jw + min(it + r + RB, nit - 1));   // past the wave's last item: that item again
                 if (live) softmax_pv(vr[r], S, it + r);
-                req_v(vr[r], jw + min(it + r + 2, nit - 1));
+                req_v(vr[r], jw + min(it + r + RB, nit - 1));
             }
         }
     };
     if (FR && tree_only) {
-        lds_k(kr[0], jw); lds_v(vr[0], jw); lds_k(kr[1], jw + 1); lds_v(vr[1], jw + 1);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) { lds_k(kr[r], jw + r); lds_v(vr[r], jw + r); }
         if (nit > 0) run_items(lds_k, lds_v);
     } else if (nit > 0) {
         run_items(request_k, request_v);
@@ -431,9 +455,10 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
             L += sc[w] * lw[w];
         }
         const int t = (tg * TBW + tb) * 32 + tl;
+        if (t > row_last) continue;                    // a padding row: nobody reads it (plain decoding: 31 of 32)
         const size_t row = (((size_t)b * nh + h) * nparts + part) * Tp + t;
         if (eb == 0) {
-            const float ltot = L + __shfl_xor(L, 32);
+            const float ltot = L + __shfl_xor(L, 32);    // (the other lane of the row is here too)
             if (g == 0) mlpart[row] = make_float2(M, ltot);
         }
         float* o = opart + row * HD;
@@ -450,18 +475,22 @@ __global__ __launch_bounds__(256) void k_tree_attn(const bf16x8* __restrict__ Qp
     }
 }
 
+template <bool EVEN>
+static std::conditional_t<EVEN, AttnSplit, NoSplit> att_split(const AttnSplit* s) {
+    if constexpr (EVEN) return *s; else return NoSplit{};
+}
+// split: NULL, or how the sequences of a batch of one query block each are cut (then ncparts is its max_parts, tree_sep 0)
 // qkv: NULL (the queries and the tree's keys / values were made by launch_rope_kv), or the QKV projection's partial
 // sums: then this launch makes them itself (one query group only: Tp <= 64), and `rt` gives the rotation table
 void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, const void* kt, const void* vt,
                       const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart, RowRef rr, int B, int nh,
                       int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep, hipStream_t s, hipEvent_t ev0,
-                      hipEvent_t ev1, const PartView* qkv, const RowTable* rt) {
+                      hipEvent_t ev1, const PartView* qkv, const RowTable* rt, const AttnSplit* split) {
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
     const int TB = Tp / 32;
     const int TBW = (TB % 2 == 0) ? 2 : 1;
     const int nparts = ncparts + tree_sep, TG = TB / TBW;     // tree_sep: number of parts with tree blocks only
-    const bool even = per == 0;                        // (one query block per sequence, built in this launch: see attn_geometry)
-    if (even) per = (int)(uint32_t)((0x100000000ull + ncparts - 1) / ncparts);
+    const bool even = split != nullptr;                // (one query block per sequence, built in this launch)
     dim3 grid(nparts, nh * TG, B);
     int xcd_stride = 0;
     if (TG > 1) {                                      // query groups of one head on one XCD (see the kernel)
@@ -471,14 +500,21 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
         xcd_stride = -1;
         grid = dim3(nh, nparts, B);
     }
+    if (even) {
+        xcd_stride = nh % 8 == 0 ? -1 : 0;
+        grid = xcd_stride ? dim3(nh, split->n) : dim3(split->n, nh);
+    }
 #define ATT_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (const bf16x8*)kt, (const bf16x8*)vt, \
                  kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg, rr
 #define ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_)                                                             \
-    do {                                                                                                        \
+    do {                                                                                                         \
+                                                                                                        \
         if (ev0 || ev1)                                                                                         \
-            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS); \
+            hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS, \
+                                  att_split<EVEN_>(split)); \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ATT_ARGS); \
+            hipLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ATT_ARGS, \
+                               att_split<EVEN_>(split)); \
     } while (0)
 #define ATT_M(HD_, TBW_, AW_, FR_, NS_, MAP_)                                                                    \
     do {                                                                                                        \
@@ -517,36 +553,54 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 // ------------------------------------------------------------------------------------------
 // Merge the split-KV partials and emit the packed bf16 operand of the O-projection (body: row_ops.h).
 // one thread per (seq, head, query t, 8 consecutive output dims), grid (chunks of t x dims, head, seq)
+// of: the parts of every sequence, if they differ
+struct PartsOf {
+    uint32_t w[SD_MAX_BATCH / 8];                      // four bits per sequence; 0: nparts
+    __device__ __forceinline__ int operator()(int b, int nparts) const {
+        const int p = (w[b >> 3] >> (4 * (b & 7))) & 15;
+        return p ? p : nparts;
+    }
+};
+static PartsOf parts_of(const AttnSplit* s) {
+    PartsOf of = {};
+    for (int i = 0; s && i < s->n; ++i) {              // (every entry of a sequence says the same)
+        const uint32_t b = s->slot[i] & 255, parts = s->slot[i] >> 16;
+        of.w[b >> 3] |= parts << (4 * (b & 7));
+    }
+    return of;
+}
 // FEW: a handful of rows, as few.hip's ready-made operand
 template <bool FEW>
 __global__ void k_attn_merge(const float* __restrict__ opart, const float2* __restrict__ mlpart,
-                             bf16x8* __restrict__ xp, RowRef rr, int nh, int hd, int e8_shift, int Tp, int nparts, int MB) {
+                             bf16x8* __restrict__ xp, RowRef rr, int nh, int hd, int e8_shift, int Tp, int nparts, PartsOf of,
+                             int MB) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;      // hd / 8 = 1 << e8_shift pieces per query row
     const int e8 = idx & ((1 << e8_shift) - 1), t = idx >> e8_shift;
     const int b = blockIdx.z, h = blockIdx.y;
     if (t >= rr.len(b)) return;
+    const int own = of(b, nparts);
     if constexpr (FEW) {
         float o[8];
         bf16x8 hi, lo;
-        attn_merge_values(opart, mlpart, nh, hd, Tp, nparts, b, h, t, e8, o);
+        attn_merge_values(opart, mlpart, nh, hd, Tp, nparts, own, b, h, t, e8, o);
         split_hilo(o, hi, lo);
         const int u = few_unit(rr.off(b) + t, (h << e8_shift) + e8);
         xp[u] = hi;
         xp[u + 8] = lo;
     } else {
-        attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, MB, b, h, t, rr.off(b) + t, e8);
+        attn_merge_item<false>(opart, mlpart, xp, nh, hd, Tp, nparts, own, MB, b, h, t, rr.off(b) + t, e8);
     }
 }
 
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
-                       int Tp, int nparts, int MB, hipStream_t s) {
+                       int Tp, int nparts, int MB, hipStream_t s, const AttnSplit* split) {
     const int e8_shift = hd == 128 ? 4 : 3;            // head_dim is 128 or 64
     hipLaunchKernelGGL(k_attn_merge<false>, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
-                       (bf16x8*)x_packed, rr, nh, hd, e8_shift, Tp, nparts, MB);
+                       (bf16x8*)x_packed, rr, nh, hd, e8_shift, Tp, nparts, parts_of(split), MB);
 }
 void launch_attn_merge_few(const float* opart, const float2* mlpart, void* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
-                            int nparts, hipStream_t s) {
+                            int nparts, hipStream_t s, const AttnSplit* split) {
     const int e8_shift = hd == 128 ? 4 : 3;
     hipLaunchKernelGGL(k_attn_merge<true>, dim3((longest * (hd / 8) + 255) / 256, nh, B), dim3(256), 0, s, opart, mlpart,
-                       (bf16x8*)out, rr, nh, hd, e8_shift, Tp, nparts, 0);
+                       (bf16x8*)out, rr, nh, hd, e8_shift, Tp, nparts, parts_of(split), 0);
 }

@@ -1,5 +1,6 @@
 // Plain host arithmetic on sizes: no HIP in here.
 #pragma once
+#include <stdint.h>
 
 // How the attention of a pass is cut into workgroups (one resident per compute unit: the kernel
 // takes the whole LDS). A group is one (sequence, head, query-block group); it gets `ncparts` cache
@@ -10,7 +11,7 @@
 // builds the tree's keys and values itself (one query group of two blocks: split_ok), one per tree block, so that the
 // building is shared by two workgroups.
 struct AttnGeom { int ncparts, per, tree_sep, nparts; };
-static inline AttnGeom attn_geometry(int n_heads, int max_parts, int B, int Tp, int n_hi, bool split_ok, bool ragged) {
+static inline AttnGeom attn_geometry(int n_heads, int max_parts, int B, int Tp, int n_hi, bool split_ok) {
     auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
     const int nblk = ceil_div(n_hi, 32);
     const int TB = Tp / 32, TG = (TB % 2 == 0) ? TB / 2 : TB;
@@ -20,17 +21,6 @@ static inline AttnGeom attn_geometry(int n_heads, int max_parts, int B, int Tp, 
     if (P > max_parts) P = max_parts;
     AttnGeom g;
     if (nblk == 0) { g.ncparts = 0; g.per = 1; g.tree_sep = 1; g.nparts = 1; return g; }
-    // A batch with one workgroup per (sequence, head) lasts as long as its longest sequence: when the lengths are ragged,
-    // two parts that share every sequence's own blocks evenly (per = 0). Launch at eight 7B-shaped sequences of 1024 - 4096
-    // rows: plain decoding 88 -> 78 us, 32-node trees 88 -> 82; one of 4096 beside seven of 32 rows 56 -> 36; but eight of
-    // 2560 rows 74.6 -> 77.6, so not where they are alike. (Three and four parts 85 and 95 us: one workgroup of this
-    // kernel fits a compute unit, and held to 256 registers, so that two fit, it spills: 107 us.)
-    if (P == 1 && TB == 1 && ragged && nblk >= 8) {
-        g.tree_sep = 0;
-        g.ncparts = g.nparts = 2;
-        g.per = 0;
-        return g;
-    }
     const int by_work = ceil_div(nblk, 4);                 // at least one block per wave
     const int ntp = (split_ok && TB == 2 && P >= 3) ? 2 : 1;
     // The tree keeps parts of its own while the cache parts are short: up to eight blocks per cache part, or, when a
@@ -55,7 +45,62 @@ static inline AttnGeom attn_geometry(int n_heads, int max_parts, int B, int Tp, 
 }
 
 // The geometry of a pass. The persistent layer kernel (fused) keeps the rotary stage as a phase of its own, so none of the
-// rules that rest on the attention launch building the tree's keys itself apply there: no second tree part, no even parts.
+// rules that rest on the attention launch building the tree's keys itself apply there: no second tree part, no parts per
+// sequence. ragged: a batch whose sequences are to be cut one by one, if they have one query block each: per = 0 says that
+// attn_split tells how (two parts, or more or fewer).
 static inline AttnGeom attn_geometry_of_pass(bool fused, int n_heads, int max_parts, int B, int Tp, int n_hi, bool ragged) {
-    return attn_geometry(n_heads, max_parts, B, Tp, n_hi, !fused && Tp == 64, !fused && ragged);
+    if (ragged && !fused && Tp == 32) return AttnGeom{2, 0, 0, 2};
+    return attn_geometry(n_heads, max_parts, B, Tp, n_hi, !fused && Tp == 64);
+}
+
+// Batches of one query block per sequence (trees of up to 32 nodes, plain decoding): every sequence gets parts in proportion
+// to its length, and shares its own blocks, as many as the device says it has, evenly among them. One entry per (sequence, part),
+// each a workgroup per head; n = 0: not used.
+#define ATTN_SPLIT_MAX 64
+struct AttnSplit {
+    uint32_t slot[ATTN_SPLIT_MAX];       // sequence | part << 8 | parts of the sequence << 16
+    int n, max_parts;                    // entries; parts of the sequence that has the most
+};
+// The smallest block count per part, q >= 8 (two a wave), with which the parts of all sequences number `want` at most.
+static inline int attn_parts(int len, int q) {
+    const int parts = ((len + 31) / 32 + q - 1) / q;
+    return parts < 1 ? 1 : parts > 15 ? 15 : parts;
+}
+static inline int attn_split_q(int B, const int* len, int want) {
+    for (int q = 8;; ++q) {
+        int total = 0;
+        for (int b = 0; b < B; ++b) total += attn_parts(len[b], q);
+        if (total <= want || q >= 1 << 20) return q;
+    }
+}
+// len: the host's bounds. One workgroup per compute unit, or two (both fit; no more: a second round costs more than any
+// balance gains), whichever the measured pace says is sooner done: a launch takes 9.4 us, 2.5 more with two per unit, and the
+// longer of its bytes (2.73 ns a block) and the blocks of its longest workgroup (0.5 us each alone on a unit, 0.8 beside
+// another). 7B shape, plain decoding, one / two per unit, us: eight sequences of 2656 rows 67.4 / 69.9; of 1024 32.1 / 35.9;
+// of 1024 - 4096 80 / 75 (79 with two even parts each, as it was); five of 150 - 2100 25.4 / 27.8 (32); three per unit 84.
+static inline AttnSplit attn_split(int n_heads, int B, const int* len) {
+    AttnSplit s = {};
+    double best = 0;
+    int best_q = 1;
+    for (int k = 1; k <= 2; ++k) {
+        int want = 256 * k / n_heads;
+        if (want > ATTN_SPLIT_MAX) want = ATTN_SPLIT_MAX;
+        if (want < B) want = B;
+        const int q = attn_split_q(B, len, want);
+        int longest = 0, blocks = 0;
+        for (int b = 0; b < B; ++b) {
+            const int nb = (len[b] + 31) / 32, parts = attn_parts(len[b], q), each = (nb + parts - 1) / parts;
+            blocks += nb;
+            if (each > longest) longest = each;
+        }
+        const double stream = blocks * n_heads * 2.73, chain = longest * (k == 1 ? 500.0 : 800.0);
+        const double cost = 9400.0 + 2500.0 * (k - 1) + (stream > chain ? stream : chain);
+        if (k == 1 || cost < best) { best = cost; best_q = q; }
+    }
+    for (int b = 0; b < B; ++b) {
+        const int parts = attn_parts(len[b], best_q);
+        if (parts > s.max_parts) s.max_parts = parts;
+        for (int p = 0; p < parts; ++p) s.slot[s.n++] = (uint32_t)b | (uint32_t)p << 8 | (uint32_t)parts << 16;
+    }
+    return s;
 }

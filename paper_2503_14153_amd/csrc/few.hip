@@ -66,7 +66,7 @@ static __device__ __forceinline__ void few_body(const FewLinear& a, const Medusa
         for (int i = tid; i < a.M * per; i += NW * 64) {
             const int m = i / per, k8 = i - m * per, b = m / a.R;
             float f[8];
-            attn_merge_values(a.opart, a.mlpart, a.nh, a.hd, a.Tp, a.nparts, b, k8 >> e8s, m - b * a.R, k8 & ((1 << e8s) - 1), f);
+            attn_merge_values(a.opart, a.mlpart, a.nh, a.hd, a.Tp, a.nparts, b ? a.own[1] : a.own[0], b, k8 >> e8s, m - b * a.R, k8 & ((1 << e8s) - 1), f);
             bf16x8 hi, lo;
             split_hilo(f, hi, lo);
             merged[k8 * (2 * FEW_MERGE_ROWS) + m] = hi;

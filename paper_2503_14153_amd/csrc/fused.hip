@@ -126,7 +126,7 @@ __global__ __launch_bounds__(512, MT == 8 ? 1 : 2) void k_layer(const FusedArgs 
             for (unsigned item = gw; item < total; item += GW) {
                 const unsigned kbh = item % nk, r1 = item / nk, tblk = r1 % TB, r2 = r1 / TB;
                 const unsigned h = r2 % (unsigned)a.nh, b = r2 / (unsigned)a.nh;
-                attn_merge_item<true>(a.opart, a.mlpart, a.att, a.nh, a.hd, a.Tp, a.nparts, MB, b, h,
+                attn_merge_item<true>(a.opart, a.mlpart, a.att, a.nh, a.hd, a.Tp, a.nparts, a.nparts, MB, b, h,
                                       tblk * 32 + (lane & 31), b * a.Tp + tblk * 32 + (lane & 31), kbh * 2 + (lane >> 5));
             }
         });

@@ -298,12 +298,12 @@ static __device__ __forceinline__ void swiglu_item(const PartView& pv, int F, in
 // Merge the split-KV partials of one (sequence b, head h, query t, 8 consecutive output dims e8) and emit
 // the packed bf16 operand of the O-projection (row m). The parts are read in batches of eight whose loads are all
 // issued before any is used (a part index past the end re-reads the last part with weight zero, so no load
-// sits behind a branch).
+// sits behind a branch). nparts of the stride parts that the batch's partials leave room for are this sequence's.
 static __device__ __forceinline__ void attn_merge_values(const float* __restrict__ opart, const float2* __restrict__ mlpart,
-                                                         int nh, int hd, int Tp, int nparts, int b, int h, int t, int e8,
+                                                         int nh, int hd, int Tp, int stride, int nparts, int b, int h, int t, int e8,
                                                          float (&o)[8]) {
     constexpr int PB = 8;
-    size_t base = ((size_t)b * nh + h) * nparts;
+    size_t base = ((size_t)b * nh + h) * stride;
     float M = NEG_INF_F, den = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = 0.f;
@@ -342,11 +342,11 @@ static __device__ __forceinline__ void attn_merge_values(const float* __restrict
 }
 template <bool WT>
 static __device__ __forceinline__ void attn_merge_item(const float* __restrict__ opart, const float2* __restrict__ mlpart,
-                                                       bf16x8* __restrict__ xp, int nh, int hd, int Tp, int nparts, int MB,
+                                                       bf16x8* __restrict__ xp, int nh, int hd, int Tp, int stride, int nparts, int MB,
                                                        int b, int h, int t, int m, int e8) {
     bf16x8 hi, lo;
     float o[8];
-    attn_merge_values(opart, mlpart, nh, hd, Tp, nparts, b, h, t, e8, o);
+    attn_merge_values(opart, mlpart, nh, hd, Tp, stride, nparts, b, h, t, e8, o);
     split_hilo(o, hi, lo);
     const int k = h * hd + e8 * 8;
     const size_t u = xpack_index(m, k, MB) >> 3;

@@ -246,6 +246,7 @@ struct FewLinear {
                                                                       // their products are the bits that norm(X) gives
     const float* opart; const float2* mlpart;                         // or NULL: the rows are the merged attention parts,
     int nh, hd, Tp, nparts, R;                                        // row m = b * R + t; few_merges(M, d)
+    int own[2];                                                       // parts of sequence b (of nparts)
 };
 #define FEW_ROWS 16
 #define FEW_LAYER_ROWS 8         // layers (add, swiglu): one product takes both terms
@@ -305,12 +306,12 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
                       const int32_t* kv_len, const uint32_t* anc, float* opart, float2* mlpart,
                       RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep,
                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const PartView* qkv = nullptr,
-                      const RowTable* rt = nullptr);
+                      const RowTable* rt = nullptr, const struct AttnSplit* split = nullptr);
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
-                       int Tp, int nparts, int MB, hipStream_t s);
+                       int Tp, int nparts, int MB, hipStream_t s, const AttnSplit* split = nullptr);
 // the same, as few.hip's ready-made operand
 void launch_attn_merge_few(const float* opart, const float2* mlpart, void* out, RowRef rr, int longest, int B, int nh, int hd, int Tp,
-                            int nparts, hipStream_t s);
+                            int nparts, hipStream_t s, const AttnSplit* split = nullptr);
 void launch_swiglu_pack(PartView pv, int F, int Fpad, void* act_packed, int M, int MB, hipStream_t s);
 // output rows base * B + i*B + b in chunks of chunk_rows rows, each a packed activation of MB (last: MBlast) row blocks;
 // base = 1: rows 0 .. B-1 are the h rows themselves
