@@ -48,6 +48,7 @@ struct LayerW {
 
 // Optional per-launch timing of the two bandwidth-bound kernel classes with HIP events on the
 // caller's stream (sd_profile_begin / sd_profile_end).
+enum { KW_QKV, KW_O, KW_DOWN };      // sd_model::kw
 enum { PROF_GEMM = 0, PROF_ATTN = 1, PROF_CLASSES = 2 };
 struct Profile {
     bool on = false;
@@ -89,6 +90,7 @@ struct sd_model {
     double* rope_freq;                       // [head_dim / 2]
     PassMap* rm_dev;                         // the row map of a prompt pass, in device memory
     int prompt_rows = 0;                     // rows of the largest prompt pass; above 256 its plans and buffers exist:
+    KwPlan kw[2][3];                         // 16, 32 rows; QKV, O, down projection
     std::vector<GemmPlan> prompt_plans;      // of 9 .. prompt_rows / 32 row blocks
     std::vector<double> prompt_cost;         // [row blocks]: modelled cycles of a layer of a pass of that many (0: none)
     void *ktp = nullptr, *vtp = nullptr;     // one layer's keys and values of such a pass, [chunk][head][blocks]
@@ -406,6 +408,14 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     }
     (void)ld_max;
     m->part_floats = pf;
+    for (int r = 0; r < 2; ++r) {
+        const int shapes[3][2] = {{m->KBd, m->NBqkv}, {m->KBd, m->NBo}, {m->KBf, m->NBo}};
+        for (int i = 0; i < 3; ++i) {
+            const int rows = 16 << r, KB = shapes[i][0], NB = shapes[i][1];
+            m->kw[r][i] = (uint64_t)KB * NB < (1ull << 22) ? kw_plan(rows, KB, NB) : KwPlan{0, 0, 0};
+            pf = std::max(pf, (size_t)m->kw[r][i].S * rows * (size_t)NB * 32);
+        }
+    }
     // Prompts: passes of up to 1024 rows (a model of max_rows > 128 has the room for prompt passes of 256). One layer's
     // cost of a pass in modelled cycles decides how a prompt is cut (prompt_passes); up to 256 rows it is that of the
     // passes above.
@@ -949,6 +959,18 @@ static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t*
     return g;
 }
 
+// A projection of a pass of M rows: k_gemm_kw where the pass has a plan for it (kw: or NULL), else the split over column groups.
+static PartView run_projection(sd_model* m, const KwPlan* kw, const void* X, const void* W, int M, int MB, int KB, int NB, int n_real,
+                               hipStream_t s) {
+    if (!kw || !kw->C) return run_gemm(m, X, W, m->part, M, MB, KB, NB, n_real, s);
+    KwLinear a;
+    memset(&a, 0, sizeof(a));
+    a.X = X; a.W = W; a.KB = KB; a.NB = NB; a.M = M; a.S = kw->S; a.n_units = NB * 2; a.out = m->part; a.ldo = NB * 32;
+    a.slot_stride = (size_t)kw->RT * 16 * a.ldo;
+    few_launch(m, n_real, KB, [&](hipEvent_t e0, hipEvent_t e1) { launch_gemm_kw(*kw, a, s, e0, e1); });
+    return PartView{m->part, a.slot_stride, a.ldo, nullptr, kw->S};
+}
+
 static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, int B, int M, int Tp, int n_hi, const PassGeom& ag,
                            hipStream_t s) {
     const sd_config& c = m->cfg;
@@ -957,6 +979,8 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
     const size_t t_stride = (size_t)B * nh * TB * 32 * hd;     // elements per layer of tree scratch
     const int longest = *std::max_element(rm.len, rm.len + B);
     const bool few = few_layers(m, M);
+    const KwPlan* kw = M <= 32 ? m->kw[M <= 16 ? 0 : 1] : nullptr;
+    const auto plan = [&](int which) { return kw ? kw + which : nullptr; };
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW& lw = m->layers[l];
         PartView pq = {m->part, 0, 3 * d, nullptr, 1};
@@ -965,7 +989,7 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
             few_launch(m, 3 * d, m->KBd, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_store(a, s, e0, e1); });
         } else {
             launch_norm_pack(m->x, prev, lw.attn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
-            pq = run_gemm(m, m->xn, lw.wqkv, m->part, M, MB, m->KBd, m->NBqkv, 3 * d, s);
+            pq = run_projection(m, plan(KW_QKV), m->xn, lw.wqkv, M, MB, m->KBd, m->NBqkv, 3 * d, s);
         }
         uint16_t* kt = (uint16_t*)m->kt + l * t_stride;
         uint16_t* vt = (uint16_t*)m->vt + l * t_stride;
@@ -1008,11 +1032,11 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
             continue;                                  // (prev stays empty: the residual stream is complete)
         }
         launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
-        PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
+        PartView po = run_projection(m, plan(KW_O), m->attn_x, lw.wo, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
         launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
-        prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
+        prev = run_projection(m, plan(KW_DOWN), m->act, lw.wdown, M, MB, m->KBf, m->NBo, d, s);
     }
     return prev;
 }

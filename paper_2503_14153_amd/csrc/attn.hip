@@ -530,10 +530,12 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
         pv_arg = *qkv;
         rt_arg = *rt;
         const bool four = qkv->cnt == nullptr && qkv->nmax == 4;     // the aligned QKV plan of the 7B and 13B shapes
+        const bool two = qkv->cnt == nullptr && qkv->nmax == 2;      // ... and of gemm_kw.hip's
         const bool one = qkv->cnt == nullptr && qkv->nmax == 1 && TBW == 1;      // a handful of rows (few.hip)
 #define ATT_FR(HD_, TBW_)                                                                                        \
     do {                                                                                                        \
         if (four) ATT(HD_, TBW_, 4, 1, 4);                                                                       \
+        else if (two) ATT(HD_, TBW_, 4, 1, 2);                                                                   \
         else if (one) ATT(HD_, TBW_, 4, 1, (TBW_ == 1 ? 1 : 0));                                                 \
         else ATT(HD_, TBW_, 4, 1, 0);                                                                            \
     } while (0)

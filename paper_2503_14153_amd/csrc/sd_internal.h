@@ -260,6 +260,15 @@ void launch_few_store(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullpt
 void launch_few_add(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_few_swiglu(const FewLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 void launch_few_heads(const FewLinear& a, const MedusaBias& bias, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// 9 to 32 rows, the contraction over the waves of a workgroup and S segments (gemm_kw.hip)
+struct KwPlan { int C, S, RT; };                                      // column blocks of 16 (0: not that way), segments, tiles of 16 rows
+KwPlan kw_plan(int M, int KB, int NB);
+struct KwLinear {
+    const void *X, *W;                                                // packed operands; KB * NB KiB < 4 GiB
+    int KB, NB, M, S, n_units;                                        // n_units: columns / 16
+    float* out; int ldo; size_t slot_stride;                          // partial sums [S][row][ldo]
+};
+void launch_gemm_kw(const KwPlan& p, const KwLinear& a, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // persistent layer kernel: G workgroups (all must be resident at once), a.MB in {1, 2, 8}
 void launch_layer(const FusedArgs& a, int G, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // how many of its workgroups the device can hold at once (0 on error)
