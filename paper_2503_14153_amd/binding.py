@@ -244,7 +244,9 @@ class KVCache:
         s = self.model.shape
         cand = torch.as_tensor(cand, dtype=torch.int32).reshape(self.batch, s.n_medusa, s.topk).cuda().contiguous()
         _check(lib().sd_kv_set_draft(self.handle, root_tok.data_ptr(), cand.data_ptr(), _stream()))
-        torch.cuda.current_stream().synchronize()      # the temporaries above die with this frame
+        # read in the order of the current stream: memory that was allocated for another one must not be handed out before
+        for t in (root_tok, cand):
+            t.record_stream(torch.cuda.current_stream())
 
     def get_draft(self):
         s = self.model.shape

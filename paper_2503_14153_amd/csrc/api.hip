@@ -736,8 +736,8 @@ extern "C" int sd_kv_set_len(sd_kv* kv, const int32_t* len, void* stream) {
     if (!kv || !len) return fail(SD_ERR_NULL, "sd_kv_set_len: NULL argument");
     for (int b = 0; b < kv->B; ++b)
         if (len[b] < 0 || len[b] > kv->cap) return fail(SD_ERR_SHAPE, "sd_kv_set_len: length %d out of range", len[b]);
-    HIP_TRY(hipMemcpyAsync(kv->kv_len, len, kv->B * 4, hipMemcpyHostToDevice, (hipStream_t)stream));
-    HIP_TRY(hipStreamSynchronize((hipStream_t)stream));   // `len` may be a temporary of the caller
+    launch_set_i32(len, kv->kv_len, kv->B, (hipStream_t)stream);
+    HIP_TRY(hipGetLastError());
     for (int b = 0; b < kv->B; ++b) kv->len_hi[b] = len[b];
     return SD_OK;
 }
@@ -774,8 +774,7 @@ extern "C" int sd_kv_read_rows(sd_kv* kv, int32_t layer, int32_t seq, int32_t ro
 extern "C" int sd_kv_set_draft(sd_kv* kv, const int32_t* root_tok, const int32_t* cand, void* stream) {
     if (!kv || !root_tok || !cand) return fail(SD_ERR_NULL, "sd_kv_set_draft: NULL argument");
     const sd_config& c = kv->m->cfg;
-    launch_copy_i32(root_tok, kv->root_tok, kv->B, (hipStream_t)stream);
-    launch_copy_i32(cand, kv->cand, kv->B * c.n_medusa * c.topk, (hipStream_t)stream);
+    launch_copy_i32(root_tok, kv->root_tok, kv->B, cand, kv->cand, kv->B * c.n_medusa * c.topk, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     kv->has_draft = true;
     return SD_OK;
@@ -783,8 +782,7 @@ extern "C" int sd_kv_set_draft(sd_kv* kv, const int32_t* root_tok, const int32_t
 extern "C" int sd_kv_get_draft(sd_kv* kv, int32_t* root_tok, int32_t* cand, void* stream) {
     if (!kv || !root_tok || !cand) return fail(SD_ERR_NULL, "sd_kv_get_draft: NULL argument");
     const sd_config& c = kv->m->cfg;
-    launch_copy_i32(kv->root_tok, root_tok, kv->B, (hipStream_t)stream);
-    launch_copy_i32(kv->cand, cand, kv->B * c.n_medusa * c.topk, (hipStream_t)stream);
+    launch_copy_i32(kv->root_tok, root_tok, kv->B, kv->cand, cand, kv->B * c.n_medusa * c.topk, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return SD_OK;
 }

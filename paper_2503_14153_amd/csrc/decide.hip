@@ -771,12 +771,25 @@ void launch_fill_i32(int32_t* p, int32_t v, int n, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_i32, dim3((n + 255) / 256), dim3(256), 0, s, p, v, n);
 }
 
-__global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+// two arrays in one launch (a sequence's root token and its candidates: bound by the launch)
+__global__ void k_copy_i32(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int n, const int32_t* __restrict__ src2,
+                           int32_t* __restrict__ dst2, int n2) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) dst[i] = src[i];
+    if (i < n2) dst2[i] = src2[i];
 }
-void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s) {
-    hipLaunchKernelGGL(k_copy_i32, dim3((n + 255) / 256), dim3(256), 0, s, src, dst, n);
+void launch_copy_i32(const int32_t* src, int32_t* dst, int n, const int32_t* src2, int32_t* dst2, int n2, hipStream_t s) {
+    const int most = n > n2 ? n : n2;
+    hipLaunchKernelGGL(k_copy_i32, dim3((most + 255) / 256), dim3(256), 0, s, src, dst, n, src2, dst2, n2);
+}
+// dst[0 .. n) = the values, which travel with the launch: nothing of the caller's is read later
+__global__ void k_set_i32(SeqList v, int32_t* __restrict__ dst, int n) {
+    if (threadIdx.x < n) dst[threadIdx.x] = v.seq[threadIdx.x];
+}
+void launch_set_i32(const int32_t* v, int32_t* dst, int n, hipStream_t s) {
+    SeqList l = {};
+    for (int i = 0; i < n; ++i) l.seq[i] = v[i];
+    hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(SD_MAX_BATCH), 0, s, l, dst, n);
 }
 
 // Prompt chunks commit every row: slots are the identity, the count is the chunk length. (src_slots, n_accept and n_old

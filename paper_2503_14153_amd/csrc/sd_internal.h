@@ -359,6 +359,7 @@ void launch_commit_setup(const int32_t* n_rows, int width, uint32_t held, int B,
 void launch_kv_rows(void* kc, void* vc, void* k_rows, void* v_rows, int row0, int nrows, int nh, int hd,
                     int cap_blocks, int to_cache, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int n, hipStream_t s);
-void launch_copy_i32(const int32_t* src, int32_t* dst, int n, hipStream_t s);
+void launch_copy_i32(const int32_t* src, int32_t* dst, int n, const int32_t* src2, int32_t* dst2, int n2, hipStream_t s);
+void launch_set_i32(const int32_t* v, int32_t* dst, int n, hipStream_t s);      // v: host, n <= SD_MAX_BATCH
 void launch_prefill_commit_setup(const ChainArgs& ca, const RowMap& rm, int B, int Tp, int32_t* src_slots, int32_t* n_accept,
                                  int32_t* n_old, int32_t* kv_len, int32_t* fin_rows, int n_fin, const SeqList& last, hipStream_t s);
