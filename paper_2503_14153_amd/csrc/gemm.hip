@@ -75,13 +75,16 @@ template <int MT>
 __global__ __launch_bounds__(512, 4) void k_gemm_sk(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                     const bf16x8* __restrict__ zfrag, float* __restrict__ out,
                                                     int KB, int NB, int ldo, size_t slot_stride, int rows, int upw, int rem,
-                                                    uint32_t kb_magic, const int32_t* __restrict__ slot0_tab) {
+                                                    uint32_t kb_magic, const int32_t* __restrict__ slot0_tab, OperandTouch touch) {
     __shared__ bf16x8 xs[SK_LDS_UNITS];
     SkGemm<MT> gm;
     gm.setup(Xp, Wp, zfrag, out, KB, NB, ldo, slot_stride, rows, upw, rem, kb_magic, slot0_tab, blockIdx.x, gridDim.x);
+    uint32_t t = 0;
+    if (touch.shares) t = touch_operand(Xp + (size_t)gm.cur.kb * SkGemm<MT>::PER_KB, upw * SkGemm<MT>::PER_KB * 16, touch);
     gm.issue_x();                                      // the short L2 loads first: a wave's loads return in order
     gm.issue_ring();
     gm.template run<false>(xs, SkRowScale{nullptr, 0, 0.f, 0.f}, nullptr);
+    touched(t);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -369,7 +372,9 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
     pv.cnt = p.uniform ? nullptr : p.cnt_dev;         // NULL: nmax slots everywhere, the consumer need not look it up
     pv.nmax = p.slots;
     const uint32_t kb_magic = (uint32_t)((0x100000000ull + (uint64_t)p.KB - 1) / (uint64_t)p.KB);
-#define SK_ARGS (const bf16x8*)Xp, (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.upw, p.rem, kb_magic, p.slot0_dev
+    // (aligned splits: one segment of one column group per workgroup)
+    const OperandTouch touch = !p.CG && p.rem == 0 && p.KB % p.upw == 0 ? operand_touch(p.G, p.KB / p.upw) : OperandTouch{0, 0};
+#define SK_ARGS (const bf16x8*)Xp, (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.upw, p.rem, kb_magic, p.slot0_dev, touch
 #define SK_LAUNCH(KERNEL_, THREADS_, ...)                                                                  \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \

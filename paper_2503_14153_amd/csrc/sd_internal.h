@@ -115,6 +115,26 @@ struct PartView {
 static __device__ inline int part_count(const PartView& p, int col) { return p.cnt ? p.cnt[col >> 8] : p.nmax; }
 #endif
 
+// The launch before a GEMM has just written its activations: the first workgroup of an XCD that asks for a line of them waits for
+// memory, and since the workgroups of a segment walk in step, each does so at every step. So the workgroups that share an
+// XCD (they are dealt round-robin) and a segment fetch the segment's lines together at the start, one line per thread, while
+// the first weights are on their way; the loads of the walk then find them in L2. (Another mapping only costs time.)
+// k_gemm_sk only: steps of four layers at 64 rows 724.5 -> 719 us, five 12-node trees 770 -> 761, 16 k rows 907 -> 899. Level or
+// slower for k_gemm_kw (16 rows 553 -> 554) and k_gemm_rows (256 rows 1286 -> 1310: four times the lines).
+struct OperandTouch { uint32_t magic; int shares; };   // ceil(2^32 / period), workgroups of an XCD and a segment
+static inline OperandTouch operand_touch(int G, int S) {
+    int period = 8;
+    while (period % S) period += 8;                    // (workgroup g: XCD g % 8, segment g % S)
+    return OperandTouch{(uint32_t)((0x100000000ull + period - 1) / period), (G + period - 1) / period};
+}
+#ifdef __HIPCC__
+static __device__ __forceinline__ uint32_t touch_operand(const void* slice, int bytes, OperandTouch t) {
+    const int lines = bytes >> 7, l = (int)__umulhi(blockIdx.x, t.magic) + t.shares * (int)threadIdx.x;
+    return *(const uint32_t*)((const char*)slice + ((size_t)min(l, lines - 1) << 7));
+}
+static __device__ __forceinline__ void touched(uint32_t v) { asm volatile("" ::"v"(v)); }     // (keeps the load)
+#endif
+
 // Rows whose RMSNorm scale is applied AFTER the contraction (the operand holds x * gain, see row_ops.h):
 // ssq [ceil(n_parts / 4)][Mp][4] partial sums of squares of every row (Mp = the GEMM's padded row count, part p of
 // row m at ((p / 4) * Mp + m) * 4 + p % 4; parts beyond n_parts are zero); every output of row m is multiplied by
