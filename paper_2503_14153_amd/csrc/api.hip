@@ -941,13 +941,14 @@ static bool fused_eligible(const sd_model* m, int M) {
 }
 // The geometry that the pass over B sequences of Tp rows will launch: worked out once per pass, launched, and part of the
 // key under which the pass is captured. (float32 attention has no parts: none of its launches depends on n_hi.)
-struct PassGeom : AttnGeom { AttnSplit split; };
+struct PassGeom : AttnGeom { AttnSplit split; bool whole; };
 static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int Tp, int n_hi) {
     PassGeom g = {};
     if (m->f32) return g;
     // (a batch is cut sequence by sequence once its longest one has 256 rows)
     static_cast<AttnGeom&>(g) = attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
                                                       B > 1 && n_hi >= 256);
+    g.whole = !fused_eligible(m, B * Tp) && attn_whole_pays(m->cfg.n_heads, B, Tp, n_hi);
     if (g.per == 0) {
         int len[SD_MAX_BATCH];
         for (int i = 0; i < B; ++i) len[i] = kv->len_hi[seq ? seq[i] : i];
@@ -1002,13 +1003,18 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         // 11.8 us launch gone, step -0.8 %); so it is with the parts of a batch that is cut sequence by sequence, the last of
         // which takes the tree.
         const AttnSplit* split = ag.split.n ? &ag.split : nullptr;
-        const bool fr = Tp <= 64 && (ag.tree_sep || ag.ncparts == 1 || split);
+        const bool fr = Tp <= 64 && (ag.whole || ag.tree_sep || ag.ncparts == 1 || split);
         if (!fr) launch_rope_kv(pq, m->rt, rr, m->q, kt, vt, B, Tp, nh, hd, s);
         // algorithmic bytes: one read of K and V of the committed rows (upper bound n_hi) + tree rows
         const int pa = prof_claim(m, PROF_ATTN, (double)B * (n_hi + Tp) * 2.0 * d * 2.0);
-        launch_tree_attn(m->q, kv->kc + l * kv->layer_stride, kv->vc + l * kv->layer_stride, kt, vt, kv->kv_len,
-                         m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s,
-                         prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr, split);
+        const uint16_t *kc = kv->kc + l * kv->layer_stride, *vc = kv->vc + l * kv->layer_stride;
+        if (ag.whole)
+            launch_attn_whole(m->q, kc, vc, kt, vt, kv->kv_len, m->rt.anc, m->attn_x, rr, B, nh, hd, Tp, kv->cap_blocks, MB, s,
+                              prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
+        else
+            launch_tree_attn(m->q, kc, vc, kt, vt, kv->kv_len, m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks,
+                             ag.ncparts, ag.per, ag.tree_sep, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr,
+                             fr ? &m->rt : nullptr, split);
         if (few) {
             FewLinear a = few_linear(nullptr, 0, lw.wo, m->KBd, m->NBo, M, d / 16, m->x, d);
             a.Xp = (const bf16x8*)m->attn_x;
@@ -1029,7 +1035,7 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
             few_launch(m, d, m->KBf, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
             continue;                                  // (prev stays empty: the residual stream is complete)
         }
-        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
+        if (!ag.whole) launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
         PartView po = run_projection(m, plan(KW_O), m->attn_x, lw.wo, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
@@ -1595,7 +1601,8 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     if (m->use_graphs && !m->prof.on && !ty) {
         // everything the launch sequence depends on besides device-resident state
         std::vector<uint64_t> key = {kv->uid, tree_uid, (uint64_t)(uintptr_t)parent, (uint64_t)T, (uint64_t)Tp,
-                                     (uint64_t)ag.ncparts, (uint64_t)ag.per, (uint64_t)ag.tree_sep, (uint64_t)(uintptr_t)stop_mask,
+                                     (uint64_t)ag.ncparts, (uint64_t)ag.per, (uint64_t)ag.tree_sep, (uint64_t)ag.whole,
+                                     (uint64_t)(uintptr_t)stop_mask,
                                      (uint64_t)(uintptr_t)n_accept, (uint64_t)(uintptr_t)tokens,
                                      (uint64_t)(uintptr_t)slots, (uint64_t)(uintptr_t)io->n_accept_raw,
                                      (uint64_t)(uintptr_t)io->logits, (uint64_t)(uintptr_t)io->argmax,

@@ -104,3 +104,11 @@ static inline AttnSplit attn_split(int n_heads, int B, const int* len) {
     }
     return s;
 }
+
+// One workgroup per (sequence, head, row block) instead of parts (attn_whole.hip, which has the figures behind this line): two
+// row blocks or more, at least 64 such workgroups, and no more blocks per workgroup than 18 where there are 64 of them, 36 where
+// there are 128, and so on.
+static inline bool attn_whole_pays(int n_heads, int B, int Tp, int n_hi) {
+    const int groups = B * n_heads * (Tp / 32), blocks = (n_hi + 31) / 32 + Tp / 32;
+    return Tp >= 64 && groups >= 64 && blocks * 64 <= 18 * groups;
+}

@@ -178,12 +178,10 @@ static __device__ __forceinline__ void norm_tile(float* __restrict__ x, const Pa
 // q_unit0: subtracted from the 16-byte unit index of the query fragments (a caller that keeps one head's queries in a
 // buffer of its own, e.g. in LDS, passes that head's offset). k_copy / v_copy: if not NULL, this head's key / value
 // blocks are written there as well (block layouts, offsets within the head); k_copy2 / v_copy2 the same, as row t2.
-template <bool BATCH, int NS = 0>
-static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const RowTable& rt, bf16x8* __restrict__ qp,
-                                                    uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp, int nh,
-                                                    int hd, int which, int h, int a, int t, int b, int m, size_t q_unit0 = 0,
-                                                    uint16_t* k_copy = nullptr, uint16_t* v_copy = nullptr,
-                                                    uint16_t* k_copy2 = nullptr, uint16_t* v_copy2 = nullptr, int t2 = 0) {
+// The values of an item: lo = dims 8a .. 8a + 7, hi = their partners, rotated if q or k.
+template <bool BATCH, int NS>
+static __device__ __forceinline__ void rope_kv_values(const PartView& pv, const RowTable& rt, int nh, int hd, int which, int h, int a,
+                                                      int m, float (&r1)[8], float (&r2)[8]) {
     const int d = nh * hd, half = hd / 2;
     const int col0 = which * d + h * hd + a * 8;
     const float* p0 = pv.base + (size_t)m * pv.ld + col0;
@@ -218,12 +216,33 @@ static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const Ro
             hi[4] += x3.x; hi[5] += x3.y; hi[6] += x3.z; hi[7] += x3.w;
         }
     }
+    if (which == 2) {                                   // (values: not rotated)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { r1[i] = lo[i]; r2[i] = hi[i]; }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float2 cs = rt.cs[(size_t)m * half + a * 8 + i];
+        r1[i] = lo[i] * cs.x - hi[i] * cs.y;
+        r2[i] = hi[i] * cs.x + lo[i] * cs.y;
+    }
+}
+template <bool BATCH, int NS = 0>
+static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const RowTable& rt, bf16x8* __restrict__ qp,
+                                                    uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp, int nh,
+                                                    int hd, int which, int h, int a, int t, int b, int m, size_t q_unit0 = 0,
+                                                    uint16_t* k_copy = nullptr, uint16_t* v_copy = nullptr,
+                                                    uint16_t* k_copy2 = nullptr, uint16_t* v_copy2 = nullptr, int t2 = 0) {
+    const int half = hd / 2;
+    float r1[8], r2[8];
+    rope_kv_values<BATCH, NS>(pv, rt, nh, hd, which, h, a, m, r1, r2);
     const int TB = Tp / 32;
     const size_t head_off = ((size_t)b * nh + h) * TB * (32 * hd);
     if (which == 2) {                                   // values: not rotated, scattered bf16
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            __bf16 w1 = (__bf16)lo[i], w2 = (__bf16)hi[i];
+            __bf16 w1 = (__bf16)r1[i], w2 = (__bf16)r2[i];
             vt[head_off + vblk_index(t, a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w1);
             vt[head_off + vblk_index(t, half + a * 8 + i, hd)] = __builtin_bit_cast(uint16_t, w2);
             if (v_copy) {
@@ -236,13 +255,6 @@ static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const Ro
             }
         }
         return;
-    }
-    float r1[8], r2[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float2 cs = rt.cs[(size_t)m * half + a * 8 + i];
-        r1[i] = lo[i] * cs.x - hi[i] * cs.y;
-        r2[i] = hi[i] * cs.x + lo[i] * cs.y;
     }
     if (which == 0) {                                   // queries: two-term expansion
         bf16x8 h1, l1, h2, l2;

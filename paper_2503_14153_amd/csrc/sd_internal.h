@@ -336,6 +336,11 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
                       RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int ncparts, int per, int tree_sep,
                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const PartView* qkv = nullptr,
                       const RowTable* rt = nullptr, const struct AttnSplit* split = nullptr);
+// one workgroup per (sequence, head, 32 rows): the merged result, as a packed operand of MB row blocks. qkv, rt as above (Tp = 64)
+void launch_attn_whole(const void* q_packed, const void* kc, const void* vc, void* kt, void* vt, const int32_t* kv_len,
+                       const uint32_t* anc, void* x_packed, RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int MB,
+                       hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const PartView* qkv = nullptr,
+                       const RowTable* rt = nullptr);
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s, const AttnSplit* split = nullptr);
 // the same, as few.hip's ready-made operand
