@@ -222,6 +222,129 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
 }
 
 // ------------------------------------------------------------------------------------------
+// Prompt passes whose tiles are 256 rows x six column blocks: the same work for four waves. A wave has two row blocks, so every
+// weight fragment that it reads from LDS feeds four products instead of two (half the LDS bytes), and a barrier comes once per
+// two contraction blocks. These launches run into the card's power limit, so bytes moved are time even where no unit is full:
+// alone on its SIMD a wave hides less (256 rows: 3-10 % slower than the eight), but over a long contraction 1024 rows take
+// 197 us for 207 (QKV) and 350 for 376 (gate/up); a prompt of 1500 tokens, four layers, 5470 -> 5390 us. Not for groups of four and
+// eight blocks (level).
+// Per iteration (two contraction blocks): the next iteration's weight fragments go to the other LDS buffer; products of the first
+// block, the loads of later iterations among them; barrier; the next first block's fragments are read; products of the second
+// block; the next second block's fragments are read.
+template <int CG>
+__global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
+                                                      const bf16x8* __restrict__ zfrag, float* __restrict__ out, int KB, int NB,
+                                                      int ldo, size_t slot_stride, int rows, int S, int MB, int RT, int n_combo) {
+    static_assert(CG % 2 == 0, "two blocks' fragments are dealt to four waves");
+    constexpr int LW = CG / 2;                          // weight fragments that a wave loads per iteration
+    constexpr int D = 2;                                // iterations in flight
+    __shared__ bf16x8 ws[2][2 * CG * 64];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int q = blockIdx.x >> 3, tile = q % RT, combo = (q / RT) * 8 + (blockIdx.x & 7);      // as in k_gemm_rows
+    if (combo >= n_combo) return;
+    const int rb = tile * 8 + wave * 2;                 // this wave's row blocks: rb and rb + 1
+    const int ng = combo / S, seg = combo - ng * S;
+    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2;
+    const bf16x8* wp[LW];                               // fragment f of an iteration: contraction block f / CG, column block f % CG
+    int wk[LW];
+#pragma unroll
+    for (int l = 0; l < LW; ++l) {
+        const int f = wave + 4 * l;
+        wk[l] = f / CG;
+        wp[l] = Wp + ((size_t)(kb0 + wk[l]) * NB + min(ng * CG + f % CG, NB - 1)) * 64 + lane;
+    }
+    const size_t wstep = (size_t)NB * 128, xstep = (size_t)MB * 128;
+    const bf16x8* xp[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) xp[t] = Xp + ((size_t)kb0 * MB + min(rb + t, MB - 1)) * 128 + lane;
+    const bf16x8* zl = zfrag + lane;                    // blocks past n read zeros
+    f32x16 acc[2][CG];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < CG; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
+    bf16x8 w[D][LW], x[D][2][2][2], b0[CG], b1[CG];     // x: [contraction block][row block][hi, lo]
+    auto wload = [&](int slot, int it) {
+#pragma unroll
+        for (int l = 0; l < LW; ++l) w[slot][l] = __builtin_nontemporal_load(2 * it + wk[l] < n ? wp[l] + (size_t)it * wstep : zl);
+    };
+    auto xload = [&](int slot, int it, int k) {
+        const bool ok = 2 * it + k < n;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const bf16x8* p = ok ? xp[t] + (size_t)(2 * it + k) * xstep : zl;
+            x[slot][k][t][0] = p[0];
+            x[slot][k][t][1] = p[ok ? 64 : 0];
+        }
+    };
+    auto wstore = [&](int slot, int buf) {
+#pragma unroll
+        for (int l = 0; l < LW; ++l) ws[buf][(wave + 4 * l) * 64 + lane] = w[slot][l];
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) { wload(i, i); xload(i, i, 0); xload(i, i, 1); }
+    wstore(0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < CG; ++j) { b0[j] = ws[0][j * 64 + lane]; b1[j] = ws[0][(CG + j) * 64 + lane]; }
+    wload(0, D);
+    for (int i0 = 0; i0 < NI; i0 += 2 * D) {
+#pragma unroll
+        for (int ii = 0; ii < 2 * D; ++ii) {
+            const int it = i0 + ii, sl = ii % D, nx = (ii + 1) % D, buf = (ii + 1) & 1;
+            wstore(nx, buf);                            // (the buffer's readers passed the previous barrier)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int j = 0; j < CG; ++j)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][0][t][p], b0[j], acc[t][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (p == 0) wload(nx, it + 1 + D);
+                else xload(sl, it + D, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < CG; ++j) b0[j] = ws[buf][j * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                for (int j = 0; j < CG; ++j)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][1][t][p], b1[j], acc[t][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            xload(sl, it + D, 1);
+#pragma unroll
+            for (int j = 0; j < CG; ++j) b1[j] = ws[buf][(CG + j) * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
+    asm volatile("" : "+v"(gq), "+s"(ldo_here));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(rb + t) * 32, rows, ldo_here);
+#pragma unroll
+        for (int j = 0; j < CG; ++j) {
+            const int nb = ng * CG + j;
+            if (nb < NB) {
+                const int col = nb * 32 + (lane & 31);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ts.put(acc[t][j][v], ((8 * (v >> 2) + 4 * gq + (v & 3)) * ldo_here + col) * 4);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Sums the slots of selected rows only: output row (i, b), i < H, b < B, is row i*M + sel[b] of a
 // row-chunked GEMM sequence; this launch covers the chunk holding rows [row0, row0 + rows) and
 // writes dst row i*B + b when that row lies in it.
@@ -386,16 +509,17 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
         const int combos = (p.NB + p.CG - 1) / p.CG * p.S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
         pv.cnt = nullptr;
         pv.nmax = p.S;
-#define ROWS_LAUNCH(MT_, CG_, TILED_)                                                                      \
+#define ROWS_GO(KERNEL_, THREADS_)                                                                         \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
-            hipExtLaunchKernelGGL((k_gemm_rows<MT_, CG_, TILED_>), dim3(G), dim3(512), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
+            hipExtLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, ev0, ev1, 0, (const bf16x8*)Xp,  \
                                   (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, \
                                   p.MB, p.RT, combos);                                                     \
         else                                                                                               \
-            hipLaunchKernelGGL((k_gemm_rows<MT_, CG_, TILED_>), dim3(G), dim3(512), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
+            hipLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
                                (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos); \
     } while (0)
+#define ROWS_LAUNCH(MT_, CG_, TILED_) ROWS_GO((k_gemm_rows<MT_, CG_, TILED_>), 512)
         const int key = (p.RT ? 100 + p.MT * 10 : p.MB * 10) + p.CG;
         if (key == 88) ROWS_LAUNCH(8, 8, false);
         else if (key == 86) ROWS_LAUNCH(8, 6, false);
@@ -403,12 +527,13 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
         else if (key == 48) ROWS_LAUNCH(4, 8, false);
         else if (key == 44) ROWS_LAUNCH(4, 4, false);
         else if (key == 188) ROWS_LAUNCH(8, 8, true);
-        else if (key == 186) ROWS_LAUNCH(8, 6, true);
+        else if (key == 186) ROWS_GO((k_gemm_tile<6>), 256);
         else if (key == 184) ROWS_LAUNCH(8, 4, true);
         else if (key == 148) ROWS_LAUNCH(4, 8, true);
         else if (key == 144) ROWS_LAUNCH(4, 4, true);
         else pv.nmax = 0;                              // the planners make no other: nothing launched, nothing to read
 #undef ROWS_LAUNCH
+#undef ROWS_GO
         return pv;
     }
     switch (p.MB) {                                    // one or two row blocks
