@@ -942,13 +942,15 @@ static bool fused_eligible(const sd_model* m, int M) {
 // The geometry that the pass over B sequences of Tp rows will launch: worked out once per pass, launched, and part of the
 // key under which the pass is captured. (float32 attention has no parts: none of its launches depends on n_hi.)
 struct PassGeom : AttnGeom { AttnSplit split; bool whole; };
-static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int Tp, int n_hi) {
+// M: the pass's rows (a short prompt has fewer than its padded B * Tp).
+static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int M, int Tp, int n_hi) {
     PassGeom g = {};
     if (m->f32) return g;
     // (a batch is cut sequence by sequence once its longest one has 256 rows)
     static_cast<AttnGeom&>(g) = attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
                                                       B > 1 && n_hi >= 256);
-    g.whole = !fused_eligible(m, B * Tp) && attn_whole_pays(m->cfg.n_heads, B, Tp, n_hi);
+    // (a handful of rows take the merged parts as an operand of another layout)
+    g.whole = !fused_eligible(m, B * Tp) && !few_layers(m, M) && attn_whole_pays(m->cfg.n_heads, B, Tp, n_hi);
     if (g.per == 0) {
         int len[SD_MAX_BATCH];
         for (int i = 0; i < B; ++i) len[i] = kv->len_hi[seq ? seq[i] : i];
@@ -1402,7 +1404,7 @@ static void run_prompt_pass(sd_model* m, sd_kv* kv, const int32_t* tokens, const
     const int n_fin = ending_rows(p.chunks, rm, &last, &fin);
     launch_build_rows_chain(m->rt, tokens, ca, rm, m->rm_dev, kv->kv_len, A, Tp, c.head_dim, m->rope_freq, m->embed, m->f32 ? 1 : 0,
                             c.d_model, c.vocab, m->x, s);
-    const PassGeom ag = pass_geometry(m, kv, rm.seq, A, Tp, n_hi);
+    const PassGeom ag = pass_geometry(m, kv, rm.seq, A, M, Tp, n_hi);
     PartView prev = run_forward(m, kv, rm, A, M, 0, Tp, n_hi, ag, false, false, s);
     launch_prefill_commit_setup(ca, rm, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);
     m->scratch = scratch_of_pass(kv, rm, A, M, Tp, ca.len, 0);
@@ -1553,7 +1555,7 @@ static int step_common(sd_model* m, sd_kv* kv, uint64_t tree_uid, const int32_t*
     int32_t* slots = io->src_slots ? io->src_slots : kv->i_slots;
     const int32_t* cand = io->forced_cand ? io->forced_cand : kv->cand;
 
-    const PassGeom ag = pass_geometry(m, kv, nullptr, B, Tp, n_hi);
+    const PassGeom ag = pass_geometry(m, kv, nullptr, B, M, Tp, n_hi);
     const ScratchRows scratch = scratch_of_pass(kv, rm, B, M, Tp, nullptr, T);
     auto enqueue = [&](hipStream_t s) {
     launch_build_rows_tree(m->rt, parent, depth, rank, kv->root_tok, cand, kv->kv_len, B, T, Tp, R, H, c.topk, c.head_dim,

@@ -35,6 +35,13 @@ def test_a_ragged_batch_in_one_pass(sd):
            [300, 5, 64, 31, 40, 1, 33, 90], [20, 32, 1, 7, 25, 31, 3, 12])
 
 
+# one to eight rows in a pass whose row blocks are those of the widest (padded) pass: alone, behind committed rows, and the
+# remainder of a prompt of whole passes
+@pytest.mark.parametrize("old,new", [([0], [5]), ([100], [8]), ([40], [1]), ([0], [1024 + 3]), ([7, 70], [2, 6])])
+def test_prompts_that_end_in_a_handful_of_rows(sd, old, new):
+    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=32, head_dim=64, d_model=2048, d_ffn=256), old, new)
+
+
 def _check(sd, shape, old, new):
     weights = wl.make_weights(shape, medusa_bias_std=0.1)
     w64 = lockstep.weights_to_f64(weights)
