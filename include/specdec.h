@@ -116,7 +116,8 @@ int sd_kv_destroy(sd_kv* kv);
 int sd_kv_len(sd_kv* kv, int32_t* out_len, void* stream);
 /* Set the committed length per sequence from host len[batch] (roll back after a step, or
  * declare rows written by sd_kv_write_rows as committed). Rows beyond len are ignored. `len` is
- * read during the call; the lengths take effect in the order of `stream`.                   */
+ * read during the call; the lengths take effect in the order of `stream`, which must not be
+ * under capture (SD_ERR_STATE).                                                             */
 int sd_kv_set_len(sd_kv* kv, const int32_t* len, void* stream);
 /* Copy `nrows` rows starting at cache row `row0` of sequence `seq`, layer `layer`, between
  * the cache and natural-layout device arrays k_rows / v_rows: [nrows][n_heads][head_dim] of the

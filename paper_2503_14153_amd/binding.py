@@ -240,6 +240,8 @@ class KVCache:
         return k, v
 
     def set_draft(self, root_tok, cand):
+        if torch.cuda.is_current_stream_capturing():   # (a replay would read temporaries that are gone)
+            raise RuntimeError("set_draft: the stream is being captured")
         root_tok = torch.as_tensor(root_tok, dtype=torch.int32).reshape(self.batch).cuda().contiguous()
         s = self.model.shape
         cand = torch.as_tensor(cand, dtype=torch.int32).reshape(self.batch, s.n_medusa, s.topk).cuda().contiguous()

@@ -736,6 +736,10 @@ extern "C" int sd_kv_set_len(sd_kv* kv, const int32_t* len, void* stream) {
     if (!kv || !len) return fail(SD_ERR_NULL, "sd_kv_set_len: NULL argument");
     for (int b = 0; b < kv->B; ++b)
         if (len[b] < 0 || len[b] > kv->cap) return fail(SD_ERR_SHAPE, "sd_kv_set_len: length %d out of range", len[b]);
+    // a replay would set the device's lengths behind the host's bounds on them
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing((hipStream_t)stream, &cap));
+    if (cap != hipStreamCaptureStatusNone) return fail(SD_ERR_STATE, "sd_kv_set_len: the stream is being captured");
     launch_set_i32(len, kv->kv_len, kv->B, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     for (int b = 0; b < kv->B; ++b) kv->len_hi[b] = len[b];

@@ -42,3 +42,27 @@ def test_inputs_may_go_away_at_once(dtype):
             assert kv.len() == [1, 2, 3]
         assert all(torch.equal(a.cpu(), b) for a, b in zip(got, want))
         del junk
+
+
+def test_refused_under_capture():
+    """A replay would set what the host has other bounds on, or read temporaries that are gone; the capture itself goes on."""
+    import paper_2503_14153_amd as sd
+    shape = wl.preset("tiny").model
+    model = sd.Model(shape, {k: v.cuda() for k, v in wl.make_weights(shape).items()}, 64)
+    kv = sd.KVCache(model, 1, 100)
+    kv.set_len([7])
+    root = torch.zeros(1, dtype=torch.int32, device="cuda")
+    cand = torch.zeros(1, shape.n_medusa, shape.topk, dtype=torch.int32, device="cuda")
+    x, graph = torch.zeros(4, device="cuda"), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        x += 1
+        with pytest.raises(Exception, match="captured"):
+            kv.set_len([9])
+        with pytest.raises(RuntimeError, match="captured"):
+            kv.set_draft(root, cand)
+    for n in (1, 2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert x.tolist() == [float(n)] * 4
+    assert kv.len() == [7]
