@@ -98,7 +98,7 @@ struct sd_model {
     float2* best; void* ranked;                 // ranking scratch: arg-max per row and chunk, top-k per head row and chunk
     float4* row_stats;                     // [Mp]: per tree row, statistics for typical acceptance
     uint32_t* zero_stop;
-    const void* zfrag;                       // 1 KiB of zeros
+    const void* zfrag;                       // 2 KiB of zeros
     size_t part_floats;
     int max_parts;
     // HIP-graph mode: one captured graph per distinct launch sequence of a step
@@ -456,7 +456,7 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
     size_t w_rk = wtake((size_t)std::min(H * SD_MAX_BATCH, 256) * rank_chunks(V) * cfg->topk * 8);
     size_t w_rs = wtake((size_t)Mp * 16), w_rm = wtake(sizeof(PassMap)), w_freq = wtake((size_t)(hd / 2) * 8);
     size_t w_xh = wtake(align_up((size_t)H * Mp, 256) * d * 4);
-    size_t w_zs = wtake((size_t)ceil_div(V, 32) * 4), w_zf = wtake(1024);
+    size_t w_zs = wtake((size_t)ceil_div(V, 32) * 4), w_zf = wtake(2048);
     size_t w_ssqa = wtake((size_t)align_up(d / 16, 4) * Mp * 4), w_ssqf = wtake((size_t)align_up(d / 16, 4) * Mp * 4);
     size_t w_xn2 = wtake((size_t)Mp * d * 4);
     // the persistent layer kernel: partial sums of each of its four GEMMs in a buffer of their own, a second

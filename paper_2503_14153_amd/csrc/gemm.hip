@@ -16,7 +16,7 @@
 // cores idle most of the time in an HBM-bound kernel, each activation enters as a two-term
 // bf16 expansion x = hi + lo (two MFMAs per weight fragment), which keeps ~16 mantissa bits
 // of x and makes the product exact up to fp32 accumulation.
-#include <string.h>
+#include <type_traits>
 
 #include "sd_internal.h"
 #include "sk_gemm.h"
@@ -119,7 +119,7 @@ template <int MT, int CG, bool TILED>
 __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                       const bf16x8* __restrict__ zfrag, float* __restrict__ out,
                                                       int KB, int NB, int ldo, size_t slot_stride, int rows, int S, int MB_,
-                                                      int RT, int n_combo) {
+                                                      int RT, int n_combo, int chain) {
     static_assert((MT == 4 || MT == 8) && (CG * MT) % 16 == 0 && CG <= 8, "row blocks / column group");
     constexpr int R = 4;                                // ring depth in steps; even (the LDS buffer of step i is i & 1)
     constexpr int CPW = CG * MT / 8;                    // column blocks per wave: 8 waves cover MT rows x CG columns
@@ -150,6 +150,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
     for (int j = 0; j < CPW; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    constexpr bool FOLDS = TILED && CPW <= 4;           // (gemm_tile_folds; not TILED: chain is 0)
+    f32x16 sum[FOLDS ? CPW : 1];                        // of the chains folded so far
+    int fold_at = chain;
+    if constexpr (FOLDS)
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) sum[j] = acc[j];
     bf16x8 w[R], xh[R], xl[R], b[CPW];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -203,7 +209,20 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
         }
         wp += R * wstep;
         xp += R * xstep;
+        if constexpr (FOLDS)
+            if (s0 + R == fold_at && s0 + R < n) {
+                fold_at += chain;
+#pragma unroll
+                for (int j = 0; j < CPW; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) { sum[j][v] += acc[j][v]; acc[j][v] = 0.f; }
+            }
     }
+    if constexpr (FOLDS)
+#pragma unroll
+        for (int j = 0; j < CPW; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][v] += sum[j][v];
     int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
     asm volatile("" : "+v"(gq), "+s"(ldo_here));
     const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(rb) * 32, rows, ldo_here);
@@ -231,52 +250,64 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
 // Per iteration (two contraction blocks): the next iteration's weight fragments go to the other LDS buffer; products of the first
 // block, the loads of later iterations among them; barrier; the next first block's fragments are read; products of the second
 // block; the next second block's fragments are read.
+//
+// chain: every so many contraction blocks (a multiple of eight, the loop's grain) the products are added to a second set and
+// begin again at zero: see gemm_plan_prompt. Of its twelve blocks eight are in LDS and four in registers, all there is room
+// for; the loads in flight stay so (an edition that drained and refilled the pipeline at every fold took 7 us a fold, this
+// one 3; LDS atomics instead of read, add and write 35). 1024 rows at the 7B shape: QKV 173 us in one chain, 183 in four;
+// gate/up 336 and 346 in two.
 template <int CG>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                       const bf16x8* __restrict__ zfrag, float* __restrict__ out, int KB, int NB,
-                                                      int ldo, size_t slot_stride, int rows, int S, int MB, int RT, int n_combo) {
+                                                      int ldo, size_t slot_stride, int rows, int S, int MB, int RT, int n_combo,
+                                                      int chain) {
     static_assert(CG % 2 == 0, "two blocks' fragments are dealt to four waves");
     constexpr int LW = CG / 2;                          // weight fragments that a wave loads per iteration
     constexpr int D = 2;                                // iterations in flight
+    constexpr int NF = 2 * CG, NL = NF - 4;             // product blocks of a wave; the second set of NL of them is in LDS
     __shared__ bf16x8 ws[2][2 * CG * 64];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    __shared__ f32x4 far[NL * 4][256];                  // (every thread its own)
+    // (wave in a scalar register: a load's address is a scalar plus the lane's 16 bytes, no vector registers hold addresses)
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int q = blockIdx.x >> 3, tile = q % RT, combo = (q / RT) * 8 + (blockIdx.x & 7);      // as in k_gemm_rows
     if (combo >= n_combo) return;
     const int rb = tile * 8 + wave * 2;                 // this wave's row blocks: rb and rb + 1
     const int ng = combo / S, seg = combo - ng * S;
-    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2;
+    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2, len = chain ? chain : n + 2 * D * 2;
     const bf16x8* wp[LW];                               // fragment f of an iteration: contraction block f / CG, column block f % CG
     int wk[LW];
 #pragma unroll
     for (int l = 0; l < LW; ++l) {
         const int f = wave + 4 * l;
         wk[l] = f / CG;
-        wp[l] = Wp + ((size_t)(kb0 + wk[l]) * NB + min(ng * CG + f % CG, NB - 1)) * 64 + lane;
+        wp[l] = Wp + ((size_t)kb0 * NB + min(ng * CG + f % CG, NB - 1)) * 64;
     }
-    const size_t wstep = (size_t)NB * 128, xstep = (size_t)MB * 128;
+    const size_t wstep = (size_t)NB * 64, xstep = (size_t)MB * 128;      // of a contraction block
     const bf16x8* xp[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) xp[t] = Xp + ((size_t)kb0 * MB + min(rb + t, MB - 1)) * 128 + lane;
-    const bf16x8* zl = zfrag + lane;                    // blocks past n read zeros
+    for (int t = 0; t < 2; ++t) xp[t] = Xp + ((size_t)kb0 * MB + min(rb + t, MB - 1)) * 128;
+    const uint32_t lane16 = lane * 16;
+    auto at = [&](const bf16x8* p) { return (const bf16x8*)((const char*)p + lane16); };
+    f32x16 near[NF - NL];                               // the second set, sums of the chains folded so far: here and in far
+#pragma unroll
+    for (int f = 0; f < NF - NL; ++f) near[f] = f32x16{0.f};
     f32x16 acc[2][CG];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int j = 0; j < CG; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
+        for (int j = 0; j < CG; ++j) acc[t][j] = f32x16{0.f};
     bf16x8 w[D][LW], x[D][2][2][2], b0[CG], b1[CG];     // x: [contraction block][row block][hi, lo]
     auto wload = [&](int slot, int it) {
 #pragma unroll
-        for (int l = 0; l < LW; ++l) w[slot][l] = __builtin_nontemporal_load(2 * it + wk[l] < n ? wp[l] + (size_t)it * wstep : zl);
+        for (int l = 0; l < LW; ++l) w[slot][l] = __builtin_nontemporal_load(at(wp[l] + (size_t)min(2 * it + wk[l], n - 1) * wstep));
     };
     auto xload = [&](int slot, int it, int k) {
-        const bool ok = 2 * it + k < n;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const bf16x8* p = ok ? xp[t] + (size_t)(2 * it + k) * xstep : zl;
-            x[slot][k][t][0] = p[0];
-            x[slot][k][t][1] = p[ok ? 64 : 0];
+            // past the end zeros (on the last weights again); a select, no branch in the middle of the products
+            const bf16x8* p = __builtin_unpredictable(2 * it + k < n) ? xp[t] + (size_t)(2 * it + k) * xstep : zfrag;
+            x[slot][k][t][0] = *at(p);
+            x[slot][k][t][1] = *at(p + 64);
         }
     };
     auto wstore = [&](int slot, int buf) {
@@ -285,63 +316,111 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
     };
 #pragma unroll
     for (int i = 0; i < D; ++i) { wload(i, i); xload(i, i, 0); xload(i, i, 1); }
+    if (chain)                                          // (workgroup-uniform)
+#pragma unroll
+        for (int i = 0; i < NL * 4; ++i) far[i][tid] = f32x4{0.f, 0.f, 0.f, 0.f};
     wstore(0, 0);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < CG; ++j) { b0[j] = ws[0][j * 64 + lane]; b1[j] = ws[0][(CG + j) * 64 + lane]; }
     wload(0, D);
-    for (int i0 = 0; i0 < NI; i0 += 2 * D) {
+    constexpr int AHEAD = 6;                            // pieces of four sums read before they are added to
+    f32x4 o[AHEAD];
+    auto fetch = [&](int i) {
+        if (i < NL * 4) o[i % AHEAD] = far[i < NL * 4 ? i : 0][tid];
+    };
+    for (int i0 = 0;;) {                                // a chain: iterations [i0, i1)
+        const int i1 = min(i0 + len / 2, NI);
+        for (; i0 < i1; i0 += 2 * D) {
 #pragma unroll
-        for (int ii = 0; ii < 2 * D; ++ii) {
-            const int it = i0 + ii, sl = ii % D, nx = (ii + 1) % D, buf = (ii + 1) & 1;
-            wstore(nx, buf);                            // (the buffer's readers passed the previous barrier)
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-#pragma unroll
-                for (int j = 0; j < CG; ++j)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][0][t][p], b0[j], acc[t][j], 0, 0, 0);
+            for (int ii = 0; ii < 2 * D; ++ii) {
+                const int it = i0 + ii, sl = ii % D, nx = (ii + 1) % D, buf = (ii + 1) & 1;
+                wstore(nx, buf);                            // (the buffer's readers passed the previous barrier)
                 __builtin_amdgcn_sched_barrier(0);
-                if (p == 0) wload(nx, it + 1 + D);
-                else xload(sl, it + D, 0);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                    for (int j = 0; j < CG; ++j)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][0][t][p], b0[j], acc[t][j], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (p == 0) wload(nx, it + 1 + D);
+                    else xload(sl, it + D, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < CG; ++j) b0[j] = ws[buf][j * 64 + lane];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+#pragma unroll
+                    for (int j = 0; j < CG; ++j)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][1][t][p], b1[j], acc[t][j], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                xload(sl, it + D, 1);
+#pragma unroll
+                for (int j = 0; j < CG; ++j) b1[j] = ws[buf][(CG + j) * 64 + lane];
                 __builtin_amdgcn_sched_barrier(0);
             }
-            __syncthreads();
+        }
+        if (i1 >= NI) break;
 #pragma unroll
-            for (int j = 0; j < CG; ++j) b0[j] = ws[buf][j * 64 + lane];
-            __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < AHEAD; ++i) fetch(i);
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
+        for (int f = 0; f < NF; ++f) {
+            f32x16 a = acc[f / CG][f % CG];
+            asm volatile("" : "+a"(a));                 // (not read before its turn)
+            if (f < NL) {
 #pragma unroll
-                for (int j = 0; j < CG; ++j)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][1][t][p], b1[j], acc[t][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < 4; ++q) {
+                    const int i = f * 4 + q;
+                    far[f < NL ? i : 0][tid] = o[i % AHEAD] + f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+                    fetch(i + AHEAD);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                near[f < NL ? 0 : f - NL] += a;
             }
-            xload(sl, it + D, 1);
-#pragma unroll
-            for (int j = 0; j < CG; ++j) b1[j] = ws[buf][(CG + j) * 64 + lane];
+            acc[f / CG][f % CG] = f32x16{0.f};
             __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int j = 0; j < CG; ++j) { b0[j] = ws[0][j * 64 + lane]; b1[j] = ws[0][(CG + j) * 64 + lane]; }     // (again)
     }
     int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
     asm volatile("" : "+v"(gq), "+s"(ldo_here));
+    auto finish = [&](auto folded) {                    // block by block: few registers
+        constexpr bool FOLDED = decltype(folded)::value;
+        if constexpr (FOLDED)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(rb + t) * 32, rows, ldo_here);
+            for (int i = 0; i < AHEAD; ++i) fetch(i);
 #pragma unroll
-        for (int j = 0; j < CG; ++j) {
-            const int nb = ng * CG + j;
-            if (nb < NB) {
-                const int col = nb * 32 + (lane & 31);
+        for (int f = 0; f < NF; ++f) {
+            f32x16 a = acc[f / CG][f % CG];
+            asm volatile("" : "+a"(a));                 // (not read before its turn)
+            if constexpr (FOLDED)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) ts.put(acc[t][j][v], ((8 * (v >> 2) + 4 * gq + (v & 3)) * ldo_here + col) * 4);
-            }
+                for (int q = 0; q < 4; ++q) {
+                    const int i = f * 4 + q;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) a[4 * q + v] += f < NL ? o[i % AHEAD][v] : near[f < NL ? 0 : f - NL][4 * q + v];
+                    if (f < NL) fetch(i + AHEAD);
+                }
+            const TileStore ts(out + (size_t)seg * slot_stride, (rb + f / CG) * 32, rows, ldo_here);
+            const int nb = ng * CG + f % CG, col = nb * 32 + (lane & 31);
+            if (nb < NB)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ts.put(a[v], ((8 * (v >> 2) + 4 * gq + (v & 3)) * ldo_here + col) * 4);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    if (chain) finish(std::true_type{});                // (then there has been a fold)
+    else finish(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------
@@ -371,67 +450,9 @@ void launch_reduce_selected(PartView pv, float* dst, const int32_t* sel, int B, 
 }
 
 // ------------------------------------------------------------------------------------------
-#define SK_MAX_WG 256       // one workgroup of 8 waves per CU (at 94 registers k_gemm_sk leaves room for two: not tried as a plan)
 #ifndef SK_SMALL_U
 #define SK_SMALL_U (16 * SK_MAX_WG * 2)   // (column groups x contraction blocks) up to which half the workgroups are used
 #endif
-
-// Four and eight row blocks (k_gemm_rows): the width of a column group, CG blocks, and the number of segments S the
-// contraction is split into, S a divisor of KB, at most 16. Cost of a candidate in shader cycles, from the kernel's
-// measured pace: a step costs its MFMAs (two waves per SIMD, 2 x CPW MFMAs of 32 cycles each) plus about 300 cycles
-// of hand-over; a workgroup runs KB / S steps (rounded up to the ring), the grid ceil(groups x S / 256) rounds; the S
-// partial tiles are written at the end of the kernel and read by the consumer at about 2500 bytes per cycle each
-// way. Narrow groups buy workgroups and few slots for the matrices with few columns (O and down projection at the
-// 7B shape, 256 rows: 4 blocks x 8 segments instead of 8 x 16: 22 us against 26, 41 against 43, and the consumer
-// reads half as much); six-block groups fill the chip where eight-block ones leave a quarter of it idle (QKV: 64
-// groups x 4 = 256 workgroups, 45 us against 55 with 48 x 4; gate/up 115 x 2 = 230 against 86 x 2 = 172: 76 against 89).
-static void gemm_plan_rows(GemmPlan* p) {
-    const int MT = p->MB;
-    static const int widths8[] = {8, 6, 4}, widths4[] = {8, 4};
-    const int* widths = MT == 8 ? widths8 : widths4;
-    const int n_widths = MT == 8 ? 3 : 2;
-    double best = 0;
-    for (int wi = 0; wi < n_widths; ++wi) {
-        const int CG = widths[wi], groups = (p->NB + CG - 1) / CG;
-        for (int S = 1; S <= 16 && S <= p->KB; ++S) {
-            if (p->KB % S) continue;
-            const int G = groups * S, rounds = (G + SK_MAX_WG - 1) / SK_MAX_WG;
-            const int steps = (p->KB / S + 3) / 4 * 4;
-            const double step_cycles = 16.0 * CG * MT + 300.0;
-            const double tile_bytes = (double)S * MT * 32 * p->NB * 32 * 4;
-            const double cost = rounds * steps * step_cycles + 2.0 * tile_bytes / 2500.0;
-            if (p->CG == 0 || cost < best) { best = cost; p->CG = CG; p->S = S; }
-        }
-    }
-    if (p->S > p->slots_max) p->slots_max = p->S;
-}
-
-// Prompt passes of more than 256 rows: tiles of eight or four row blocks, the cost of gemm_plan_rows over all of them, and
-// 6000 cycles (launch, first loads, stores) per round of workgroups. With this many rows there is one segment or two, where
-// 256 rows need four to eight to fill the chip, so the partial tiles all but disappear; the weights are read once per pass.
-// 7B shape, a prompt of 1500 tokens through four layers: 6641 us in six passes of up to 256 rows, 5649 in passes of 1024 and
-// 476. The launches themselves run at what the card's power allows for dense data, 0.97-1.05 PFLOP/s of two-term work at
-// 256 and at 1024 rows alike (1.26-1.36 with operands of zeros): what is saved lies between them.
-void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles) {
-    memset(p, 0, sizeof(*p));
-    p->MB = MB; p->KB = KB; p->NB = NB;
-    static const int widths8[] = {8, 6, 4}, widths4[] = {8, 4};
-    double best = 0;
-    for (int MT = 8; MT >= 4; MT /= 2)
-        for (int wi = 0; wi < (MT == 8 ? 3 : 2); ++wi) {
-            const int CG = MT == 8 ? widths8[wi] : widths4[wi], groups = (NB + CG - 1) / CG, RT = (MB + MT - 1) / MT;
-            for (int S = 1; S <= 4 && S <= KB; ++S) {
-                if (KB % S) continue;
-                const int rounds = (groups * S * RT + SK_MAX_WG - 1) / SK_MAX_WG, steps = (KB / S + 3) / 4 * 4;
-                const double tile_bytes = (double)S * MB * 32 * NB * 32 * 4;
-                const double cost = rounds * (steps * (16.0 * CG * MT + 300.0) + 6000.0) + 2.0 * tile_bytes / 2500.0;
-                if (p->CG == 0 || cost < best) { best = cost; p->CG = CG; p->S = S; p->MT = MT; p->RT = RT; }
-            }
-        }
-    p->slots = p->slots_max = p->S;
-    p->uniform = 1;
-    *cycles = best;
-}
 
 void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int32_t* slot0_host) {
     p->MB = MB; p->KB = KB; p->NB = NB;
@@ -481,7 +502,7 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     for (int ng = 0; ng < p->NG; ++ng) p->uniform &= (cnt_host[ng] == slots);
     p->CG = 0;
     p->S = 0;
-    p->RT = p->MT = 0;
+    p->RT = p->MT = p->chain = 0;
     p->slots_max = slots;
     if (MB >= 4) gemm_plan_rows(p);
 }
@@ -514,10 +535,10 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
         if (ev0 || ev1)                                                                                    \
             hipExtLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, ev0, ev1, 0, (const bf16x8*)Xp,  \
                                   (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, \
-                                  p.MB, p.RT, combos);                                                     \
+                                  p.MB, p.RT, combos, p.chain);                                                     \
         else                                                                                               \
             hipLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos); \
+                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos, p.chain); \
     } while (0)
 #define ROWS_LAUNCH(MT_, CG_, TILED_) ROWS_GO((k_gemm_rows<MT_, CG_, TILED_>), 512)
         const int key = (p.RT ? 100 + p.MT * 10 : p.MB * 10) + p.CG;

@@ -26,10 +26,12 @@
 #include <stddef.h>
 
 #include "../../include/specdec.h"
+#include "gemm_plan.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 #ifdef __HIPCC__
 // two-term bf16 expansion of eight floats: hi = bf16(f), lo = bf16(f - hi)
@@ -145,24 +147,6 @@ struct SkRowScale {
     float inv_d, eps;
 };
 
-// How one GEMM shape is launched (made once per shape at model creation).
-struct GemmPlan {
-    int MB, KB, NB;
-    int G, NG;               // workgroups, 256-column groups
-    int upw, rem;            // units per workgroup; the first `rem` workgroups take one more
-    int slots;               // slots the output buffer must hold
-    int uniform;             // 1: every column group has exactly `slots` contributors
-    int CG, S;               // four / eight row blocks as launched by launch_gemm: column groups of CG blocks, each
-                             // split into S segments of the contraction (workgroup = group * S + segment, slot =
-                             // segment); 0 for one and two row blocks. The fields above then describe the balanced
-                             // split that the persistent layer kernel walks at eight row blocks.
-    int RT, MT;              // prompt passes of more than 256 rows: RT tiles of MT row blocks each (MB = all of them), one
-                             // workgroup per tile, column group and segment; 0 otherwise
-    int slots_max;           // slots the output buffer must hold for either
-    int32_t* cnt_dev;        // [NG] contributors per column group (device)
-    int32_t* slot0_dev;      // [G] slot of every workgroup's first segment (device)
-};
-
 // ---- the persistent layer kernel (fused.hip) -----------------------------------------------
 // One weight-streaming GEMM as a phase: its plan, operands and the buffer of its partial sums.
 struct FusedGemm {
@@ -238,9 +222,7 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int nb_offset,
 // fills every field of the plan except cnt_dev; cnt_host receives the per-group counts
 // cnt_host [>= ceil(NB/8)] and slot0_host [>= 256] receive the tables the device copies hold
 void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int32_t* slot0_host);
-// the plan of a prompt pass of MB > 8 row blocks (no tables); cycles: its modelled cost
-void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles);
-// out must hold plan.slots * (MB*32) * (NB*32) floats; zfrag: 1 KiB of zeros (device);
+// out must hold plan.slots * (MB*32) * (NB*32) floats; zfrag: 2 KiB of zeros (device);
 // returns the view consumers read
 // ev0 / ev1 (both or neither): events that receive the kernel's own start and end time stamps,
 // for per-kernel timing without launch gaps
