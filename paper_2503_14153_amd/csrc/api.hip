@@ -92,7 +92,7 @@ struct sd_model {
     int prompt_rows = 0;                     // rows of the largest prompt pass; above 256 its plans and buffers exist:
     KwPlan kw[2][3];                         // 16, 32 rows; QKV, O, down projection
     std::vector<GemmPlan> prompt_plans;      // of 9 .. prompt_rows / 32 row blocks
-    std::vector<double> prompt_cost;         // [row blocks]: modelled cycles of a layer of a pass of that many (0: none)
+    std::vector<double> prompt_us;           // [row blocks]: modelled time of a layer of a pass of that many
     void *ktp = nullptr, *vtp = nullptr;     // one layer's keys and values of such a pass, [chunk][head][blocks]
     int32_t *g_parent, *g_depth, *g_rank, *fin_rows;
     float2* best; void* ranked;                 // ranking scratch: arg-max per row and chunk, top-k per head row and chunk
@@ -416,25 +416,24 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
             pf = std::max(pf, (size_t)m->kw[r][i].S * rows * (size_t)NB * 32);
         }
     }
-    // Prompts: passes of up to 1024 rows (a model of max_rows > 128 has the room for prompt passes of 256). One layer's
-    // cost of a pass in modelled cycles decides how a prompt is cut (prompt_passes); up to 256 rows it is that of the
-    // passes above.
+    // Prompts: passes of up to 1024 rows (a model of max_rows > 128 has the room for prompt passes of 256). The time of a layer
+    // of a pass decides how a prompt is cut (prompt_runs).
     size_t pf_prompt = pf;
     m->prompt_rows = m->MBmax == 8 ? PROMPT_ROWS : max_rows;
     if (m->MBmax == 8) {
         const int shapes[4][2] = {{m->KBd, m->NBqkv}, {m->KBd, m->NBo}, {m->KBd, m->NBgu}, {m->KBf, m->NBo}};
-        m->prompt_cost.assign(PROMPT_ROWS / 32 + 1, 0.0);
-        for (int mb = 1; mb <= PROMPT_ROWS / 32; ++mb)
+        m->prompt_us.assign(PROMPT_ROWS / 32 + 1, 0.0);
+        for (int mb = 1; mb <= PROMPT_ROWS / 32; ++mb) {
+            m->prompt_us[mb] = prompt_pass_us(shapes, mb * 32);
+            if (mb <= 8) continue;
             for (const int* sh : shapes) {
                 GemmPlan pl;
                 double cycles = 0;
                 gemm_plan_prompt(&pl, mb, sh[0], sh[1], &cycles);
-                // (a pass of one or two row blocks streams the weights: 2.2 KB a cycle and 10000 cycles a launch)
-                m->prompt_cost[mb] += mb <= 2 ? (double)sh[0] * sh[1] * 1024 / 2200 + 10000 : cycles;
-                if (mb <= 8) continue;
                 m->prompt_plans.push_back(pl);
                 pf_prompt = std::max(pf_prompt, (size_t)pl.S * mb * 32 * (size_t)sh[1] * 32);
             }
+        }
     }
     // rows of the buffers that a pass fills: packed rows, and rows padded to whole chunks (attention's side)
     const int Mr = std::max(m->MBmax * 32, m->MBmax == 8 ? PROMPT_ROWS : 0), Mc = std::max(m->MBmax * 32, m->MBmax == 8 ? PROMPT_PADDED : 0);
@@ -1347,22 +1346,21 @@ static std::vector<PromptChunk> joined_chunks(const PromptPass* passes, int n, b
     return v;
 }
 
-// How many passes from passes[i] on run as one: as many as its buffers hold, the last of them only if the model of the GEMMs'
-// cost (and 60000 cycles for a layer's other launches) says that a pass of its own is not cheaper (a short remainder).
-static size_t passes_together(const sd_model* m, const std::vector<PromptPass>& passes, size_t i) {
-    if (m->prompt_rows <= 256 || fused_eligible(m, 256)) return 1;
-    auto cost = [&](int rows) { return m->prompt_cost[prompt_blocks(rows)] + 60000.0; };
-    size_t k = 0;
-    int M = 0;
-    while (i + k < passes.size() && M + passes[i + k].M <= m->prompt_rows) {
-        int Tp;
-        const std::vector<PromptChunk> v = joined_chunks(&passes[i], (int)k + 1, i + k + 1 == passes.size(), &Tp);
-        if (k > 0 && (v.size() > SD_MAX_BATCH || (int)v.size() * Tp > PROMPT_PADDED)) break;
-        M += passes[i + k].M;
-        ++k;
-    }
-    if (k > 1 && cost(M) > cost(M - passes[i + k - 1].M) + cost(passes[i + k - 1].M)) --k;
-    return std::max<size_t>(k, 1);
+// Which passes run as one: as many as its buffers hold, where that is the sooner done.
+static std::vector<int> join_passes(const sd_model* m, const std::vector<PromptPass>& passes) {
+    const int n = (int)passes.size();
+    if (m->prompt_rows <= 256 || fused_eligible(m, 256)) return std::vector<int>(n, 1);
+    return prompt_runs(
+        n,
+        [&](int i, int k) {
+            int M = 0, Tp;
+            for (int j = i; j < i + k; ++j) M += passes[j].M;
+            if (k == 1) return M;
+            if (M > m->prompt_rows) return 0;
+            const std::vector<PromptChunk> v = joined_chunks(&passes[i], k, i + k == n, &Tp);
+            return v.size() > SD_MAX_BATCH || (int)v.size() * Tp > PROMPT_PADDED ? 0 : M;
+        },
+        [&](int rows) { return m->prompt_us[prompt_blocks(rows)]; });
 }
 
 // The sequences whose prompts end with these chunks: their last rows (of the pass), and themselves.
@@ -1515,9 +1513,9 @@ extern "C" int sd_prefill(sd_model* m, sd_kv* kv, const int32_t* tokens, const i
         if (pow2_blocks(rows) <= m->MBmax && !have_plans(m, rows, B, true, false))
             return fail(SD_ERR_STATE, "sd_prefill: no launch plan for %d rows (internal inconsistency)", rows);
     const std::vector<PromptPass> passes = cut_prompts(m, lens, B);
-    for (size_t i = 0; i < passes.size();) {
-        const size_t k = passes_together(m, passes, i);
-        if (k > 1) run_prompt_passes(m, kv, tokens, &passes[i], (int)k, i + k == passes.size(), s);
+    size_t i = 0;
+    for (int k : join_passes(m, passes)) {
+        if (k > 1) run_prompt_passes(m, kv, tokens, &passes[i], k, i + k == passes.size(), s);
         else run_prompt_pass(m, kv, tokens, passes[i], s);
         i += k;
     }

@@ -3,6 +3,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <vector>
+
 #define SK_MAX_WG 256       // one workgroup of 8 waves per CU (at 94 registers k_gemm_sk leaves room for two: not tried as a plan)
 
 // How one GEMM shape is launched (made once per shape at model creation).
@@ -106,4 +108,46 @@ static inline void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double*
     p->slots = p->slots_max = p->S;
     p->uniform = 1;
     *cycles = best;
+}
+
+// Time of a layer of a prompt pass, us, from its rows and its four projections (sh: contraction and column blocks of each). Up to
+// 64 rows the weights' bytes; up to 256 the cost above at 1950 cycles per us, with 60000 cycles for the layer's other launches;
+// joined passes at 1700 (less of what they lose is in the model). Measured, us a layer, 7B / 13B shape: up to 32 rows 98-111 /
+// 137-155, 64 rows 132 / 170, 128 rows 173 / 225, 256 rows 253 / 352; joined 320 rows 440 / 636, 512 463 / 740, 640 735 / 975,
+// 768 757 / 1004, 1024 878 / 1420. (Its predecessor took a handful of rows for 165 us, and a prompt of 257 tokens went as one
+// pass of 257 rows: 405 / 611 us where 256 rows and one row take 347 / 503.)
+static inline double prompt_pass_us(const int (*sh)[2], int rows) {
+    double bytes = 0, cycles = 60000;
+    const int mb = (rows + 31) / 32;
+    for (int i = 0; i < 4; ++i) {
+        bytes += (double)sh[i][0] * sh[i][1] * 1024;
+        GemmPlan p;
+        double c = 0;
+        if (mb > 8) {
+            gemm_plan_prompt(&p, mb, sh[i][0], sh[i][1], &c);
+        } else {
+            memset(&p, 0, sizeof(p));
+            p.MB = mb > 4 ? 8 : 4; p.KB = sh[i][0]; p.NB = sh[i][1];
+            c = gemm_plan_rows(&p);
+        }
+        cycles += c;
+    }
+    return mb <= 1 ? bytes / 4.6e6 + 15 : mb == 2 ? bytes / 5.2e6 + 54 : mb <= 8 ? cycles / 1950 : cycles / 1700;
+}
+
+// Which of n passes run as one: the partition into runs of neighbours with the smallest sum of times. rows(i, k): the rows of
+// passes [i, i + k) as one, 0 where they cannot be (and where no longer run can); us(rows): the time. -> the runs' lengths.
+template <class Rows, class Us>
+static inline std::vector<int> prompt_runs(int n, Rows&& rows, Us&& us) {
+    std::vector<double> best(n + 1, 0.0);               // of the passes from i on
+    std::vector<int> take(n, 1), runs;
+    for (int i = n - 1; i >= 0; --i)
+        for (int k = 1; i + k <= n; ++k) {
+            const int r = rows(i, k);
+            if (r == 0) break;
+            const double t = us(r) + best[i + k];
+            if (k == 1 || t < best[i]) { best[i] = t; take[i] = k; }
+        }
+    for (int i = 0; i < n; i += take[i]) runs.push_back(take[i]);
+    return runs;
 }

@@ -18,6 +18,17 @@ extern "C" void plan(int MB, int KB, int NB, int* out) {
     const int f[] = {p.MT, p.CG, p.S, p.RT, p.chain, p.slots_max};
     for (int i = 0; i < 6; ++i) out[i] = f[i];
 }
+extern "C" double us(const int* sh, int rows) { return prompt_pass_us((const int(*)[2])sh, rows); }
+extern "C" int runs(const int* sh, int n, const int* rows, int* out) {     // one sequence: passes of 256 rows, then what is left
+    const auto total = [&](int i, int k) {
+        int M = 0;
+        for (int j = i; j < i + k; ++j) M += rows[j];
+        return k > 1 && M > 1024 ? 0 : M;
+    };
+    const std::vector<int> r = prompt_runs(n, total, [&](int m) { return prompt_pass_us((const int(*)[2])sh, m); });
+    for (size_t i = 0; i < r.size(); ++i) out[i] = r[i];
+    return (int)r.size();
+}
 """
 
 
@@ -59,3 +70,44 @@ def test_chains_are_no_longer_than_in_a_256_row_pass(lib):
                 assert chain % 8 == 0 and chain < n            # (the kernels' grain; there is something to fold)
                 assert p["MT"] * p["CG"] <= 32 or (p["MT"], p["CG"]) == (8, 6)
     assert folds > 100
+
+
+def projections(d, F):
+    return [d // 16, 3 * d // 32, d // 16, d // 32, d // 16, 2 * -(-F // 32), -(-F // 16), d // 32]
+
+
+def cut(lib, d, F, tokens):
+    """Rows of the passes that a prompt of so many tokens becomes."""
+    rows = [256] * (tokens // 256) + [tokens % 256] * (tokens % 256 > 0)
+    out = (C.c_int * len(rows))()
+    n = lib.runs((C.c_int * 8)(*projections(d, F)), len(rows), (C.c_int * len(rows))(*rows), out)
+    ends = [sum(out[:i]) for i in range(n + 1)]
+    assert ends[-1] == len(rows)
+    return [sum(rows[a:b]) for a, b in zip(ends, ends[1:])]
+
+
+# a pass of its own costs a short remainder its weights; joined, it costs all rows a coarser tile (both sides measured: gemm_plan.h)
+@pytest.mark.parametrize("d,F,tokens,passes", [
+    (4096, 11008, 257, [256, 1]), (4096, 11008, 300, [256, 44]), (4096, 11008, 320, [256, 64]), (4096, 11008, 512, [512]),
+    (4096, 11008, 640, [512, 128]), (4096, 11008, 1024, [1024]), (4096, 11008, 1500, [1024, 476]),
+    (5120, 13824, 257, [256, 1]), (5120, 13824, 300, [256, 44]), (5120, 13824, 512, [256, 256]), (5120, 13824, 560, [256, 256, 48]),
+    (5120, 13824, 768, [768]),
+    # the small shapes on which joined passes are compared with the oracle
+    (256, 688, 300, [300]), (256, 688, 351, [351]), (256, 688, 1024, [1024])])
+def test_how_a_prompt_is_cut(lib, d, F, tokens, passes):
+    assert cut(lib, d, F, tokens) == passes
+
+
+def test_every_partition_is_worth_it(lib):
+    """No run of passes is joined that the times say is slower than its passes alone."""
+    lib.us.restype = C.c_double
+    rng = random.Random(3)
+    for _ in range(200):
+        d, F = rng.choice([(4096, 11008), (5120, 13824), (2048, 5504), (256, 688)])
+        sh = (C.c_int * 8)(*projections(d, F))
+        us = lambda rows: lib.us(sh, rows)
+        tokens = rng.randint(1, 5000)
+        got = cut(lib, d, F, tokens)
+        assert sum(got) == tokens and all(r <= 1024 for r in got)
+        alone = [256] * (tokens // 256) + [tokens % 256] * (tokens % 256 > 0)
+        assert sum(map(us, got)) <= sum(map(us, alone)) + 1e-6
