@@ -107,8 +107,14 @@ static inline AttnSplit attn_split(int n_heads, int B, const int* len) {
 
 // One workgroup per (sequence, head, row block) instead of parts (attn_whole.hip, which has the figures behind this line): two
 // row blocks or more, at least 64 such workgroups, and no more blocks per workgroup than 18 where there are 64 of them, 36 where
-// there are 128, and so on.
+// there are 128, and up to 72. One fits a compute unit: beyond 256 of them a second round halves that (13B shape, two 128-node
+// trees, 320 workgroups: 36 blocks level, 67 blocks 2.3 % of the step slower), and with two row blocks per sequence, where the
+// parts' launch makes its queries and tree keys itself in one round, it never pays (four 64-node trees over 100 / 1000 / 2500
+// rows 0.6 / 2.9 / 5.8 % slower).
+// Tp counts what a prompt's layout has room for, not the rows that exist. Counted by those, the last 9 to 32 rows of a prompt
+// would go to the parts' launch, and they are 4-7 % faster here over up to 1000 rows (7B and 13B shape; 33 to 100 rows level).
 static inline bool attn_whole_pays(int n_heads, int B, int Tp, int n_hi) {
-    const int groups = B * n_heads * (Tp / 32), blocks = (n_hi + 31) / 32 + Tp / 32;
-    return Tp >= 64 && groups >= 64 && blocks * 64 <= 18 * groups;
+    const int groups = B * n_heads * (Tp / 32), rounds = (groups + 255) / 256, blocks = (n_hi + 31) / 32 + Tp / 32;
+    if (Tp < 64 || groups < 64 || (rounds > 1 && Tp == 64)) return false;
+    return blocks * rounds * 64 <= 18 * (groups < 256 ? groups : 256);
 }
