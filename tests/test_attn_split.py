@@ -55,3 +55,15 @@ def test_every_sequence_is_covered_once(split, heads):
                 each = max(1, (blocks + own - 1) // own)
                 assert each * own >= blocks
         assert at == len(entries) and most == max(e[2] for e in entries)
+
+
+def test_the_lengths_of_the_gpu_tests_split(split):
+    """The parts that the tests on the GPU say their lengths have."""
+    from tests import test_gpu_appended_prompts, test_gpu_long_prompts as prompts, test_gpu_ragged_attention as steps
+
+    def parts(heads, lens):
+        return [own for _, part, own in split(heads, lens)[0] if part == 0]
+    assert [max(parts(heads, old)) for heads, old in prompts.RAGGED] == [1, 6, 15]
+    assert [max(parts(32, lens)) for lens in steps.LENGTHS] == [3, 1, 3]
+    assert [parts(4, lens) for lens in steps.MANY_PARTS] == [[15, 1], [15, 10, 1]]
+    assert set(parts(32, test_gpu_appended_prompts.OLD)) == {1}

@@ -21,15 +21,18 @@ def sd():
     return sd
 
 
+OLD = [300, 5, 64, 31, 40, 1, 33, 90]
+
+
 def test_prompts_appended_to_a_ragged_batch(sd):
     """Eight sequences of 32 heads (one workgroup per (sequence, head)) whose caches hold 1 to 300 rows get 1 to 45 more
-    tokens each: rows packed without padding, attention in two even parts per sequence; the longest prompt needs a
+    tokens each: rows packed without padding, attention in one part per sequence; the longest prompt needs a
     pass of its own. Committed rows, root and candidates of every sequence against its own oracle run."""
     shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=32, head_dim=64, d_model=2048, d_ffn=256)
     weights = wl.make_weights(shape, medusa_bias_std=0.1)
     w64 = lockstep.weights_to_f64(weights)
     model = sd.Model(shape, {k: v.cuda() for k, v in weights.items()}, 256)
-    old, new, cap = [300, 5, 64, 31, 40, 1, 33, 90], [20, 32, 1, 7, 45, 31, 3, 12], 340
+    old, new, cap = OLD, [20, 32, 1, 7, 45, 31, 3, 12], 340
     kv = sd.KVCache(model, 8, cap)
     states = [orc.DecodeState(orc.KVCache.empty(shape, cap)) for _ in old]
     _fill_synthetic(kv, states, shape, old)

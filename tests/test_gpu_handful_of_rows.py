@@ -26,6 +26,15 @@ def test_a_handful_of_rows_against_the_oracle(sd, B, T):
     print(f"\n[tiny B={B} T={T}] {rep}")
 
 
+# the widest model whose O projection merges the attention parts in LDS (8 bytes an input, 65.5 KiB with the sums'), and the next
+@pytest.mark.parametrize("heads", [96, 97])
+@pytest.mark.parametrize("B", [1, 2])
+def test_one_and_two_rows_at_the_widest(sd, B, heads):
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_layers=1, n_heads=heads, head_dim=64, d_model=64 * heads, d_ffn=256)
+    rep = _run_batch_steps(sd, shape, B, 1, [100, 33][:B], 120, n_steps=2, weights_device="cuda")
+    print(f"\n[{heads} heads B={B}] {rep}")
+
+
 @pytest.mark.parametrize("B", [1, 3, 8])
 def test_with_and_without_draft_heads(sd, B):
     """The base logits of plain decoding do not depend on whether the head rows share their pass of the LM head (bit for bit

@@ -29,10 +29,26 @@ def test_long_prompts_against_the_oracle(sd, old, new):
     _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16"), old, new)
 
 
-def test_a_ragged_batch_in_one_pass(sd):
-    """Eight sequences of 32 heads, one pass of at most 32 rows each: attention in two even parts per sequence."""
-    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=32, head_dim=64, d_model=2048, d_ffn=256),
-           [300, 5, 64, 31, 40, 1, 33, 90], [20, 32, 1, 7, 25, 31, 3, 12])
+# committed rows: one part each, one sequence of six parts, one of fifteen (test_attn_split.py has the numbers)
+RAGGED = [(32, [300, 5, 64, 31, 40, 1, 33, 90]), (32, [1300, 5, 64, 31, 40, 1, 33, 90]), (4, [5000, 5, 700, 31, 40, 1, 33, 90])]
+
+
+@pytest.mark.parametrize("heads,old", RAGGED)
+def test_a_ragged_batch_in_one_pass(sd, heads, old):
+    """Eight sequences, one pass of at most 32 rows each: attention with as many parts as each sequence's rows ask for."""
+    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=heads, head_dim=64, d_model=64 * heads, d_ffn=256),
+           old, [20, 32, 1, 7, 25, 31, 3, 12])
+
+
+# a projection in k_gemm_tile whose segments have an odd number of contraction blocks (the kernel takes them in pairs): 23 in one
+# chain, 25 in chains of 16 and 9, 35 in 16, 16 and 3 with a last column group of four blocks (test_prompt_plans.py has the numbers)
+ODD_SEGMENTS = [(1472, 2768, 400), (1600, 2768, 300), (2240, 400, 1010)]
+
+
+@pytest.mark.parametrize("d,d_ffn,rows", ODD_SEGMENTS)
+def test_segments_of_an_odd_number_of_blocks(sd, d, d_ffn, rows):
+    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=d // 64, head_dim=64, d_model=d, d_ffn=d_ffn),
+           [0], [rows])
 
 
 # one to eight rows in a pass whose row blocks are those of the widest (padded) pass: alone, behind committed rows, and the

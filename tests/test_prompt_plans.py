@@ -111,3 +111,18 @@ def test_every_partition_is_worth_it(lib):
         assert sum(got) == tokens and all(r <= 1024 for r in got)
         alone = [256] * (tokens // 256) + [tokens % 256] * (tokens % 256 > 0)
         assert sum(map(us, got)) <= sum(map(us, alone)) + 1e-6
+
+
+def test_the_shapes_of_the_gpu_test_have_odd_segments(lib):
+    """The prompts of test_gpu_long_prompts.py run as one pass, and a projection of it in the tile of eight row blocks and six
+    columns with so many blocks per segment and chain."""
+    from tests.test_gpu_long_prompts import ODD_SEGMENTS
+    want = [(23, 0), (25, 16), (35, 16)]
+    for (d, F, rows), w in zip(ODD_SEGMENTS, want):
+        assert cut(lib, d, F, rows) == [rows]
+        pr, found = projections(d, F), []
+        for KB, NB in zip(pr[::2], pr[1::2]):
+            p = plan(lib, -(-rows // 32), KB, NB)
+            if (p["MT"], p["CG"]) == (8, 6):
+                found.append((KB // p["S"], p["chain"]))
+        assert w in found, (d, F, rows, found)
