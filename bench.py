@@ -328,7 +328,7 @@ def main():
         "step_hbm_frac": step_bytes / (ms_per_step * 1e-3) / (HBM_PEAK_GBS * 1e9),
         "diverged_resets": state["diverged"], "sampling_replay_mismatches": replay_mismatches, "hip_graphs": args.graph,
         "sync_every": SYNC,
-        "roofline": {"kernel": "k_gemm_sk (weight-streaming MFMA GEMM, all projections)", "bound": "hbm",
+        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_rows)", "bound": "hbm",
                      "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_gbs / HBM_PEAK_GBS,
                      "traffic": counted_traffic("k_gemm_sk_7b_pmc_traffic.txt", "k_gemm_sk_traffic_bytes_per_launch")
                      if (args.workload == "7b" and args.layers is None and not args.fused) else None,
@@ -409,7 +409,7 @@ def bench_batch(args, torch, wl, sd, W):
                                f"{W.kv_cap}, 20% stop ids",
                    "draft_schedule": args.draft_schedule, "decoding": "greedy", "draft_mode": "own heads"},
         "prefill_tokens_per_s": sum(lens) / prefill_s, "hip_graphs": args.graph,
-        "roofline": {"kernel": "k_gemm_sk (weight-streaming MFMA GEMM, all projections)", "bound": "hbm",
+        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_rows)", "bound": "hbm",
                      "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_gbs / HBM_PEAK_GBS,
                      "traffic": None, "avg_launch_us": g["ms"] / max(g["launches"], 1) * 1e3,
                      "launches_per_step": g["launches"] / args.profile_steps,
@@ -461,7 +461,7 @@ def bench_kv_commit(args, torch, wl, sd):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         total_ms, launches = 0.0, 0
         for it in range(args.warmup + args.steps):
-            kv.set_len(lens)                              # synchronises; outside the timed launches
+            kv.set_len(lens)                              # before the timed launches, in the order of the stream
             e0.record()
             for _ in range(per_window):
                 sd.kv_commit_rows(model, kv, slots, n_rows)

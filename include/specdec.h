@@ -94,7 +94,8 @@ typedef struct sd_tree sd_tree;
  * caller's weight buffers are read on `stream` during this call only; the call synchronises
  * the stream before returning, after which the caller may free them. `max_rows` is the
  * largest batch * round_up(tree_nodes, 32) any later call will use (workspace is sized for
- * it). Blocking; allocates device memory. */
+ * it; above 128 also for bfloat16 prompt passes of up to 1024 rows: 180 MB more at the 7B,
+ * 280 MB at the 13B shape). Blocking; allocates device memory. */
 int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_t max_rows, void* stream,
                     sd_model** out);
 int sd_model_destroy(sd_model* m);
@@ -129,7 +130,9 @@ int sd_kv_read_rows(sd_kv* kv, int32_t layer, int32_t seq, int32_t row0, int32_t
                     void* k_rows, void* v_rows, void* stream);
 /* Overwrite the carried draft state of every sequence: the base model's token for the next
  * position (dev root_tok[batch]) and the heads' candidates (dev cand[batch][n_medusa][topk]).
- * Used with synthetic caches, and to resynchronise a lock-step comparison.                 */
+ * Used with synthetic caches, and to resynchronise a lock-step comparison. Both arrays are
+ * borrowed until `stream` has reached the copy: neither may be freed or written from elsewhere
+ * before that. A stream under capture records the copy, and every replay reads the arrays then. */
 int sd_kv_set_draft(sd_kv* kv, const int32_t* root_tok, const int32_t* cand, void* stream);
 /* Read the carried draft state back (same shapes, dev pointers).                           */
 int sd_kv_get_draft(sd_kv* kv, int32_t* root_tok, int32_t* cand, void* stream);

@@ -224,6 +224,7 @@ class KVCache:
         return list(out)
 
     def set_len(self, lens):
+        """Committed lengths, from the current stream on (the call does not wait; `lens` is read at once)."""
         _check(lib().sd_kv_set_len(self.handle, _i32_array(lens), _stream()))
 
     def write_rows(self, layer, seq, row0, k_rows, v_rows):
@@ -240,6 +241,9 @@ class KVCache:
         return k, v
 
     def set_draft(self, root_tok, cand):
+        """Root token and candidates of every sequence, from the current stream on; the call does not wait. int32 tensors on the
+        device are read where they are, in the order of that stream: they may be deleted at once, but must not be written on
+        another stream before it has got there."""
         if torch.cuda.is_current_stream_capturing():   # (a replay would read temporaries that are gone)
             raise RuntimeError("set_draft: the stream is being captured")
         root_tok = torch.as_tensor(root_tok, dtype=torch.int32).reshape(self.batch).cuda().contiguous()

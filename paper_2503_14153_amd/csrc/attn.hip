@@ -69,7 +69,7 @@ template <int N> static __device__ __forceinline__ void wait_vm() { asm volatile
 // as blocks. One query group only (Tp = 32 * TBW). NS: the projection's slot count if the same everywhere, else 0.
 // MAP: the pass's row map is in device memory (prompt passes: rr.map); else every sequence has rr.R rows, one after the
 // other, and nothing is looked up before the first addresses are known.
-// EVEN: every sequence's blocks are split evenly over its ncparts parts (ragged batches, see attn_geometry); else part p
+// EVEN: every sequence's blocks are split evenly over the parts that it has (batches, see attn_split); else part p
 // starts at block p * per and its first blocks are requested before the length is known.
 struct NoSplit {};
 template <int HD, int TBW, int AW, int FR, int NS, bool MAP, bool EVEN>
@@ -507,8 +507,7 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 #define ATT_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (const bf16x8*)kt, (const bf16x8*)vt, \
                  kv_len, anc, opart, mlpart, nh, Tp, cap_blocks, ncparts, per, tree_sep, scale_log2, xcd_stride, B, pv_arg, rt_arg, rr
 #define ATT_E(HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_)                                                             \
-    do {                                                                                                         \
-                                                                                                        \
+    do {                                                                                                        \
         if (ev0 || ev1)                                                                                         \
             hipExtLaunchKernelGGL((k_tree_attn<HD_, TBW_, AW_, FR_, NS_, MAP_, EVEN_>), grid, dim3(256), 0, s, ev0, ev1, 0, ATT_ARGS, \
                                   att_split<EVEN_>(split)); \

@@ -2,8 +2,8 @@
 #pragma once
 #include <stdint.h>
 
-// How the attention of a pass is cut into workgroups (one resident per compute unit: the kernel
-// takes the whole LDS). A group is one (sequence, head, query-block group); it gets `ncparts` cache
+// How the attention of a pass is cut into workgroups (one resident per compute unit where a group has two query blocks: such a
+// one takes the whole LDS; with one block two fit, which attn_split uses). A group is one (sequence, head, query-block group); it gets `ncparts` cache
 // parts of `per` 32-row blocks each, sized from the host's bound on the sequence lengths, and the
 // tree blocks go to a part of their own while the chip has room for it (short contexts) or to the
 // last cache part (long contexts).

@@ -2,7 +2,7 @@
 // column block of its own and shares the activations through LDS: few activation bytes, but every workgroup leaves a whole
 // 256-column tile of partial sums, and filling the chip takes 4 to 16 of those per column. Here a workgroup has C blocks of 16
 // columns, its eight waves take the steps of the contraction (32 inputs) in turn, each with its own operands straight from
-// memory, and their sums meet in LDS: S partial tiles per column instead, S = 1 to 4.
+// memory, and their sums meet in LDS: S partial tiles per column instead, at most eight (7B shape 1 to 4, 13B 1 to 5, more at small widths).
 // Bound by what the L2s deliver (10.6 TB/s): a workgroup reads 32 C bytes of weights and 4 M of activations per input. At 32 rows
 // that is below the weight stream's own time; at 64 rows the activations are most of the bytes and k_gemm_sk is as fast or
 // faster. 7B shape, launches on their own, k_gemm_sk -> here, us (slots): 32 rows QKV 22.1 -> 18.7 (4 -> 2), O 10.1 -> 8.4

@@ -175,9 +175,6 @@ static __device__ __forceinline__ void norm_tile(float* __restrict__ x, const Pa
 // m = the packed row that is read; a padding row (t past the sequence's rows) is given the last real one, so that what is
 // written for it is finite: attention multiplies padding values by probabilities that are exactly 0.
 // NS > 0: every column group of the QKV projection has NS slots (its plan says so): all loads in a straight line.
-// q_unit0: subtracted from the 16-byte unit index of the query fragments (a caller that keeps one head's queries in a
-// buffer of its own, e.g. in LDS, passes that head's offset). k_copy / v_copy: if not NULL, this head's key / value
-// blocks are written there as well (block layouts, offsets within the head); k_copy2 / v_copy2 the same, as row t2.
 // The values of an item: lo = dims 8a .. 8a + 7, hi = their partners, rotated if q or k.
 template <bool BATCH, int NS>
 static __device__ __forceinline__ void rope_kv_values(const PartView& pv, const RowTable& rt, int nh, int hd, int which, int h, int a,
@@ -228,6 +225,9 @@ static __device__ __forceinline__ void rope_kv_values(const PartView& pv, const 
         r2[i] = hi[i] * cs.x + lo[i] * cs.y;
     }
 }
+// The item itself. q_unit0: subtracted from the 16-byte unit index of the query fragments (a caller that keeps one head's queries
+// in a buffer of its own, e.g. in LDS, passes that head's offset). k_copy / v_copy: if not NULL, this head's key / value
+// blocks are written there as well (block layouts, offsets within the head); k_copy2 / v_copy2 the same, as row t2.
 template <bool BATCH, int NS = 0>
 static __device__ __forceinline__ void rope_kv_item(const PartView& pv, const RowTable& rt, bf16x8* __restrict__ qp,
                                                     uint16_t* __restrict__ kt, uint16_t* __restrict__ vt, int Tp, int nh,

@@ -253,6 +253,7 @@ struct FewLinear {
 #define FEW_ROWS 16
 #define FEW_LAYER_ROWS 8         // layers (add, swiglu): one product takes both terms
 #define FEW_MERGE_ROWS 2         // (every workgroup merges all of the rows, 8 bytes of LDS per input)
+// d: 48 KiB of operand beside 17.5 KiB of sums at most, of the 160 KiB that a workgroup may ask for (tested to 6144)
 static inline bool few_merges(int M, int d) { return M <= FEW_MERGE_ROWS && d <= 6144; }
 // 16-byte unit of (row m, inputs 8 k8 ..) in the ready-made operand: hi terms; the lo terms lie 8 units further
 static __host__ __device__ inline int few_unit(int m, int k8) { return (k8 >> 2) * 64 + (k8 & 3) * 16 + m; }
