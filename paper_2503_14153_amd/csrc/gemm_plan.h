@@ -61,9 +61,10 @@ static inline double gemm_plan_rows(GemmPlan* p) {      // -> the cost
 // 6000 cycles (launch, first loads, stores) per round of workgroups. With this many rows a projection needs fewer segments to
 // fill the chip (7B shape, 1024 rows: QKV and gate/up one, O and down two, where 256 rows have two to eight), so fewer partial
 // tiles are written and read; the weights are read once per pass.
-// 7B shape, a prompt of 1500 tokens through four layers: 6560 us in six passes of up to 256 rows, 5620 in passes of 1024 and
-// 476 (5430 with chains of any length). The launches themselves run at what the card's power allows for dense data, 0.97-1.05 PFLOP/s of two-term work at
-// 256 and at 1024 rows alike (1.26-1.36 with operands of zeros): what is saved lies between them.
+// 7B shape, a prompt of 1500 tokens through four layers: 6560 us in six passes of up to 256 rows, 5560 in passes of 1024 and
+// 476 (5400 with chains of any length, see below). The launches themselves run at what the card's power allows for dense data,
+// 0.97-1.05 PFLOP/s of two-term work at 256 and at 1024 rows alike (1.26-1.36 with operands of zeros): what is saved lies
+// between them.
 //
 // Fewer segments are longer sums, and a sum that is rounded at every contraction block strays with its length: with one
 // segment for 256 blocks the QKV sums were 4.5 % further from 64 bits than with the four of a 256-row pass. So no chain of
