@@ -426,12 +426,12 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
         for (int mb = 1; mb <= PROMPT_ROWS / 32; ++mb) {
             m->prompt_us[mb] = prompt_pass_us(shapes, mb * 32);
             if (mb <= 8) continue;
-            for (const int* sh : shapes) {
+            for (const auto& sh : shapes) {
                 GemmPlan pl;
                 double cycles = 0;
-                gemm_plan_prompt(&pl, mb, sh[0], sh[1], &cycles);
+                gemm_plan_prompt(&pl, mb, sh[0], sh[1], &cycles, sh == shapes[2]);
                 m->prompt_plans.push_back(pl);
-                pf_prompt = std::max(pf_prompt, (size_t)pl.S * mb * 32 * (size_t)sh[1] * 32);
+                pf_prompt = std::max(pf_prompt, (size_t)(pl.S / pl.join) * mb * 32 * (size_t)sh[1] * 32);
             }
         }
     }
@@ -864,14 +864,14 @@ static SkRowScale row_scale(const sd_model* m, const float* ssq) {
 static const SkRowScale NO_SCALE = {nullptr, 0, 0.f, 0.f};
 
 static PartView run_gemm(sd_model* m, const void* Xp, const void* Wp, float* out, int rows, int MB, int KB, int NB, int n_real,
-                         hipStream_t s) {
+                         hipStream_t s, void* swiglu = nullptr) {
     const GemmPlan* p = m->find_plan(MB, KB, NB);
     if (!p) {                                          // unreachable after have_plans(); never launch with another shape's plan
         m->plan_missing = true;
         return PartView{out, 0, NB * 32, nullptr, 0};  // no slots: the consumer adds nothing
     }
     const int pi = prof_claim(m, PROF_GEMM, (double)n_real * KB * 16 * 2);
-    return launch_gemm(*p, Xp, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1));
+    return launch_gemm(*p, Xp, Wp, m->zfrag, out, rows, s, prof_ev(m, pi, 0), prof_ev(m, pi, 1), swiglu, m->KBf);
 }
 
 // ---- a handful of rows (few.hip): no packed operands, no partial sums
@@ -1474,8 +1474,10 @@ static void run_prompt_passes(sd_model* m, sd_kv* kv, const int32_t* tokens, con
         launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, V, nh, hd, Tp, ag.nparts, MB, s);
         PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
-        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);
-        launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
+        const GemmPlan* gu = m->find_plan(MB, m->KBd, m->NBgu);
+        const bool whole = gu && gemm_plan_swiglu(*gu);    // the projection sees whole sums: it leaves the next operand itself
+        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s, whole ? m->act : nullptr);
+        if (!whole) launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
         prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
     }
     launch_prefill_commit_setup(sum, seqs, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);

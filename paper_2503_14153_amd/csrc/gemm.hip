@@ -150,7 +150,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
     for (int j = 0; j < CPW; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-    constexpr bool FOLDS = TILED && CPW <= 4;           // (gemm_tile_folds; not TILED: chain is 0)
+    constexpr bool FOLDS = TILED && CPW <= 4;           // (not TILED: chain is 0)
     f32x16 sum[FOLDS ? CPW : 1];                        // of the chains folded so far
     int fold_at = chain;
     if constexpr (FOLDS)
@@ -241,185 +241,276 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__
 }
 
 // ------------------------------------------------------------------------------------------
-// Prompt passes whose tiles are 256 rows x six column blocks: the same work for four waves. A wave has two row blocks, so every
-// weight fragment that it reads from LDS feeds four products instead of two (half the LDS bytes), and a barrier comes once per
-// two contraction blocks. These launches run into the card's power limit, so bytes moved are time even where no unit is full:
-// alone on its SIMD a wave hides less (256 rows: 3-10 % slower than the eight), but over a long contraction 1024 rows take
-// 197 us for 207 (QKV) and 350 for 376 (gate/up); a prompt of 1500 tokens, four layers, 5470 -> 5390 us. Not for groups of four and
-// eight blocks (level).
-// Per iteration (two contraction blocks): the next iteration's weight fragments go to the other LDS buffer; products of the first
-// block, the loads of later iterations among them; barrier; the next first block's fragments are read; products of the second
-// block; the next second block's fragments are read.
+// Prompt passes whose tiles are 256 rows x six or eight column blocks: the same work for four waves. A wave has two row blocks, so
+// every weight fragment that it reads from LDS feeds four products instead of two (half the LDS bytes), and a barrier comes once
+// per two contraction blocks. A wave alone on its SIMD issues everything itself, so loads, LDS reads and writes go one by one
+// between the products, evenly: 1890 cycles per two contraction blocks of six columns, of which the products are 1536.
+// What bounds it is the card's power: at that pace the clock is 1.63 GHz on dense data and 2.29 on zeros (QKV of 1024 rows, the
+// loop alone, 148 and 106 us), products alone run at 1.83. Bytes moved are therefore time even where no unit is full: without
+// the activations' loads 127 us, without the weights' 129, without LDS 119, without any of them 106.
+// 7B shape, four layers, a prompt of 1500 tokens, us: loads in groups of three and four, a launch for SwiGLU, the down projection
+// in tiles of eight by four 5504, this 5126 (QKV of 1024 rows 175 -> 167, gate/up and SwiGLU 346 -> 289, down 200 -> 180).
 //
-// chain: every so many contraction blocks (a multiple of eight, the loop's grain) the products are added to a second set and
-// begin again at zero: see gemm_plan_prompt. Of its twelve blocks eight are in LDS and four in registers, all there is room
-// for; the loads in flight stay so (an edition that drained and refilled the pipeline at every fold took 7 us a fold, this
-// one 3; LDS atomics instead of read, add and write 35). 1024 rows at the 7B shape: QKV 173 us in one chain, 183 in four;
-// gate/up 336 and 346 in two.
-template <int CG>
+// Per iteration (two contraction blocks), a quarter being the products of one block and one term: the next iteration's weight
+// fragments go to the other LDS buffer, the second block's are read; barrier; the next first block's are read; every quarter
+// asks for what the quarter before it has done with.
+//
+// chain: every so many contraction blocks (a multiple of eight, the loop's grain is four) the products are added to a second set
+// and begin again at zero: see gemm_plan_prompt. Eight of its blocks are in LDS; the other four of the tile of six columns are in
+// registers (3 us a fold at 1024 rows), the other eight of the tile of eight in the output, where the sums end up anyway (registers
+// for half of those spill: down projection 233 us for 180).
+//
+// SWIGLU (gate/up with whole sums, gemm_plan_swiglu): half of a group's columns are gate columns, half the up columns that belong
+// to them; the workgroup writes silu(gate) * up as the next projection's operand. The sums, 90 MB at 1024 rows of the 7B shape,
+// are neither written nor read, and a launch of 23 us is gone.
+template <int CG, bool SWIGLU>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
-                                                      const bf16x8* __restrict__ zfrag, float* __restrict__ out, int KB, int NB,
-                                                      int ldo, size_t slot_stride, int rows, int S, int MB, int RT, int n_combo,
-                                                      int chain) {
-    static_assert(CG % 2 == 0, "two blocks' fragments are dealt to four waves");
-    constexpr int LW = CG / 2;                          // weight fragments that a wave loads per iteration
-    constexpr int D = 2;                                // iterations in flight
-    constexpr int NF = 2 * CG, NL = NF - 4;             // product blocks of a wave; the second set of NL of them is in LDS
+                                                      void* __restrict__ out_, int KB, int NB, int ldo, size_t slot_stride, int rows,
+                                                      int S, int MB, int RT, int n_combo, int chain, int KBf) {
+    constexpr int NF = 2 * CG, LW = CG / 2;            // product blocks of a wave; weight fragments that it loads per iteration
+    // the second set of sums: blocks in LDS, in registers, in the output (beyond what there is room for)
+    constexpr int NL = 8, NN = CG == 6 ? 4 : 0, NM = NF - NL - NN;
+    static_assert(NM >= 0 && !(SWIGLU && NM), "an operand has no room for sums");
     __shared__ bf16x8 ws[2][2 * CG * 64];
-    __shared__ f32x4 far[NL * 4][256];                  // (every thread its own)
-    // (wave in a scalar register: a load's address is a scalar plus the lane's 16 bytes, no vector registers hold addresses)
+    __shared__ f32x4 far[NL * 4][256];                 // (every thread its own)
+    // (wave in a scalar register: what follows from it is the same in all lanes)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int q = blockIdx.x >> 3, tile = q % RT, combo = (q / RT) * 8 + (blockIdx.x & 7);      // as in k_gemm_rows
     if (combo >= n_combo) return;
-    const int rb = tile * 8 + wave * 2;                 // this wave's row blocks: rb and rb + 1
+    const int rb = tile * 8 + wave * 2;                // this wave's row blocks: rb and rb + 1
     const int ng = combo / S, seg = combo - ng * S;
-    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2, len = chain ? chain : n + 2 * D * 2;
-    const bf16x8* wp[LW];                               // fragment f of an iteration: contraction block f / CG, column block f % CG
-    int wk[LW];
+    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2, len = chain ? chain / 2 : NI + 2;
+    // column block j of the group: neighbours, or (SWIGLU) half of them gate blocks and half the up blocks that belong to them
+    const int half = NB >> 1;
+    auto column = [&](int j) {
+        if constexpr (!SWIGLU) return ng * CG + j;
+        else return j < CG / 2 ? ng * (CG / 2) + j : half + ng * (CG / 2) + j - CG / 2;
+    };
+    const uint32_t xstep = (uint32_t)MB * 2048u;       // bytes of a contraction block
+    const uint32_t wstep = (uint32_t)NB * 1024u;
+    uint32_t wv[LW], xv[2];                            // this lane's bytes in an iteration's weights and activations
 #pragma unroll
-    for (int l = 0; l < LW; ++l) {
+    for (int l = 0; l < LW; ++l) {                     // fragment f: contraction block f / CG, column block f % CG
         const int f = wave + 4 * l;
-        wk[l] = f / CG;
-        wp[l] = Wp + ((size_t)kb0 * NB + min(ng * CG + f % CG, NB - 1)) * 64;
+        wv[l] = (uint32_t)(f / CG) * wstep + (uint32_t)min(column(f % CG), NB - 1) * 1024u + lane * 16;
     }
-    const size_t wstep = (size_t)NB * 64, xstep = (size_t)MB * 128;      // of a contraction block
-    const bf16x8* xp[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) xp[t] = Xp + ((size_t)kb0 * MB + min(rb + t, MB - 1)) * 128;
-    const uint32_t lane16 = lane * 16;
-    auto at = [&](const bf16x8* p) { return (const bf16x8*)((const char*)p + lane16); };
-    f32x16 near[NF - NL];                               // the second set, sums of the chains folded so far: here and in far
+    for (int k = 0; k < 2; ++k) xv[k] = (uint32_t)k * xstep + (uint32_t)rb * 2048u + lane * 16;
+    const char *wb = (const char*)(Wp + (size_t)kb0 * NB * 64), *xb = (const char*)(Xp + (size_t)kb0 * MB * 128);
+    // an iteration's bytes up to the end of the segment: what lies past it is read as zeros
+    // (32-bit scalar arithmetic, and words that are scalars to the compiler: it would step through the lanes' resources)
+    const int wmost = 0x7fffffff / (int)wstep, xmost = 0x7fffffff / (int)xstep;
+    auto bytes = [&](const char* base, int it, uint32_t step, int most) {
+        return __builtin_amdgcn_make_buffer_rsrc((void*)TileStore::uniform(base + (size_t)it * 2 * step), 0,
+                                                 __builtin_amdgcn_readfirstlane(max(min(n - 2 * it, most), 0) * (int)step), 0x00020000);
+    };
+    auto wfrag = [&](__amdgpu_buffer_rsrc_t r, int l) {
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, wv[l], 0, /*nontemporal*/ 2));
+    };
+    auto xfrag = [&](__amdgpu_buffer_rsrc_t r, int k, int t, int p) {
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, xv[k] + t * 2048 + p * 1024, 0, 0));
+    };
+    f32x16 near[NN ? NN : 1], acc[2][CG];
 #pragma unroll
-    for (int f = 0; f < NF - NL; ++f) near[f] = f32x16{0.f};
-    f32x16 acc[2][CG];
+    for (int f = 0; f < NN; ++f) near[f] = f32x16{0.f};
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int j = 0; j < CG; ++j) acc[t][j] = f32x16{0.f};
-    bf16x8 w[D][LW], x[D][2][2][2], b0[CG], b1[CG];     // x: [contraction block][row block][hi, lo]
-    auto wload = [&](int slot, int it) {
+    bf16x8 w[2][LW], x[2][2][2][2], b[2][CG];          // x: [iteration][contraction block][row block][hi, lo]
 #pragma unroll
-        for (int l = 0; l < LW; ++l) w[slot][l] = __builtin_nontemporal_load(at(wp[l] + (size_t)min(2 * it + wk[l], n - 1) * wstep));
-    };
-    auto xload = [&](int slot, int it, int k) {
+    for (int i = 0; i < 2; ++i) {
+        const auto wr = bytes(wb, i, wstep, wmost), xr = bytes(xb, i, xstep, xmost);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            // past the end zeros (on the last weights again); a select, no branch in the middle of the products
-            const bf16x8* p = __builtin_unpredictable(2 * it + k < n) ? xp[t] + (size_t)(2 * it + k) * xstep : zfrag;
-            x[slot][k][t][0] = *at(p);
-            x[slot][k][t][1] = *at(p + 64);
-        }
-    };
-    auto wstore = [&](int slot, int buf) {
+        for (int l = 0; l < LW; ++l) w[i][l] = wfrag(wr, l);
 #pragma unroll
-        for (int l = 0; l < LW; ++l) ws[buf][(wave + 4 * l) * 64 + lane] = w[slot][l];
-    };
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-    for (int i = 0; i < D; ++i) { wload(i, i); xload(i, i, 0); xload(i, i, 1); }
-    if (chain)                                          // (workgroup-uniform)
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+                    if (i == 0 || k == 0 || p == 0) x[i][k][t][p] = xfrag(xr, k, t, p);
+    }
+    if (chain)                                         // (workgroup-uniform)
 #pragma unroll
         for (int i = 0; i < NL * 4; ++i) far[i][tid] = f32x4{0.f, 0.f, 0.f, 0.f};
-    wstore(0, 0);
+#pragma unroll
+    for (int l = 0; l < LW; ++l) ws[0][(wave + 4 * l) * 64 + lane] = w[0][l];
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < CG; ++j) { b0[j] = ws[0][j * 64 + lane]; b1[j] = ws[0][(CG + j) * 64 + lane]; }
-    wload(0, D);
-    constexpr int AHEAD = 6;                            // pieces of four sums read before they are added to
+    for (int j = 0; j < CG; ++j) b[0][j] = ws[0][j * 64 + lane];
+    {
+        const auto wr = bytes(wb, 2, wstep, wmost);
+#pragma unroll
+        for (int l = 0; l < LW; ++l) w[0][l] = wfrag(wr, l);
+    }
+    // block f of the wave's sums in the output
+    const int gq = lane >> 5;
+    auto store_at = [&](int f) {
+        return TileStore((float*)out_ + (size_t)seg * slot_stride, (rb + f / CG) * 32, rows, ldo);
+    };
+    auto offset = [&](int f, int v, int g, int ld) {
+        return ((8 * (v >> 2) + 4 * g + (v & 3)) * ld + column(f % CG) * 32 + (lane & 31)) * 4;
+    };
+    constexpr int AHEAD = 6;                           // pieces of four sums read before they are added to
     f32x4 o[AHEAD];
     auto fetch = [&](int i) {
         if (i < NL * 4) o[i % AHEAD] = far[i < NL * 4 ? i : 0][tid];
     };
-    for (int i0 = 0;;) {                                // a chain: iterations [i0, i1)
-        const int i1 = min(i0 + len / 2, NI);
-        for (; i0 < i1; i0 += 2 * D) {
+    auto xr_old = bytes(xb, 1, xstep, xmost);                 // (the last quarter of an iteration's activations is asked for in the next one)
+    for (int i0 = 0;;) {                               // a chain: iterations [i0, i1)
+        const int i1 = min(i0 + len, NI);
+        for (; i0 < i1; i0 += 2) {
 #pragma unroll
-            for (int ii = 0; ii < 2 * D; ++ii) {
-                const int it = i0 + ii, sl = ii % D, nx = (ii + 1) % D, buf = (ii + 1) & 1;
-                wstore(nx, buf);                            // (the buffer's readers passed the previous barrier)
-                __builtin_amdgcn_sched_barrier(0);
+            for (int ii = 0; ii < 2; ++ii) {
+                const int it = i0 + ii, buf = ii ^ 1, nx = ii ^ 1;
+                const auto wr = bytes(wb, it + 3, wstep, wmost), xr = bytes(xb, it + 2, xstep, xmost);
+                // the products of one contraction block and one term, n_ops other things spread evenly among them
+                auto quarter = [&](int k, int p, int n_ops, auto&& op) {
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
+                    for (int i = 0; i < NF; ++i) {
+                        acc[i & 1][i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ii][k][i & 1][p], b[k][i >> 1], acc[i & 1][i >> 1], 0, 0, 0);
 #pragma unroll
-                    for (int j = 0; j < CG; ++j)
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-                            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][0][t][p], b0[j], acc[t][j], 0, 0, 0);
+                        for (int u = 0; u < n_ops; ++u)
+                            if ((2 * u + 1) * NF / (2 * n_ops) == i) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                op(u);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
-                    if (p == 0) wload(nx, it + 1 + D);
-                    else xload(sl, it + D, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                };
+                constexpr int W1 = LW / 3, W2 = (LW - W1) / 2, W3 = LW - W1 - W2;     // weight loads of the last three quarters
+                constexpr int B1 = CG / 2, B2 = CG - B1;
+                quarter(0, 0, LW + 2 + CG, [&](int u) {
+                    if (u < LW) ws[buf][(wave + 4 * u) * 64 + lane] = w[nx][u];       // (its readers passed the previous barrier)
+                    else if (u < LW + 2) x[nx][1][u - LW][1] = xfrag(xr_old, 1, u - LW, 1);
+                    else b[1][u - LW - 2] = ws[ii][(CG + u - LW - 2) * 64 + lane];
+                });
+                quarter(0, 1, 2 + W1, [&](int u) {
+                    if (u < 2) x[ii][0][u][0] = xfrag(xr, 0, u, 0);
+                    else w[nx][u - 2] = wfrag(wr, u - 2);
+                });
                 __syncthreads();
-#pragma unroll
-                for (int j = 0; j < CG; ++j) b0[j] = ws[buf][j * 64 + lane];
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-#pragma unroll
-                    for (int j = 0; j < CG; ++j)
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-                            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[sl][1][t][p], b1[j], acc[t][j], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                xload(sl, it + D, 1);
-#pragma unroll
-                for (int j = 0; j < CG; ++j) b1[j] = ws[buf][(CG + j) * 64 + lane];
-                __builtin_amdgcn_sched_barrier(0);
+                quarter(1, 0, 2 + W2 + B1, [&](int u) {
+                    if (u < 2) x[ii][0][u][1] = xfrag(xr, 0, u, 1);
+                    else if (u < 2 + W2) w[nx][W1 + u - 2] = wfrag(wr, W1 + u - 2);
+                    else b[0][u - 2 - W2] = ws[buf][(u - 2 - W2) * 64 + lane];
+                });
+                quarter(1, 1, 2 + W3 + B2, [&](int u) {
+                    if (u < 2) x[ii][1][u][0] = xfrag(xr, 1, u, 0);
+                    else if (u < 2 + B2) b[0][B1 + u - 2] = ws[buf][(B1 + u - 2) * 64 + lane];
+                    else w[nx][W1 + W2 + u - 2 - B2] = wfrag(wr, W1 + W2 + u - 2 - B2);
+                });
+                xr_old = xr;
             }
         }
         if (i1 >= NI) break;
+        const bool first = i1 == len;                  // (the first fold: nothing in the output yet)
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) fetch(i);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             f32x16 a = acc[f / CG][f % CG];
-            asm volatile("" : "+a"(a));                 // (not read before its turn)
+            asm volatile("" : "+a"(a));                // (not read before its turn)
             if (f < NL) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = f * 4 + q;
-                    far[f < NL ? i : 0][tid] = o[i % AHEAD] + f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+                for (int z = 0; z < 4; ++z) {
+                    const int i = f * 4 + z;
+                    far[f < NL ? i : 0][tid] = o[i % AHEAD] + f32x4{a[4 * z], a[4 * z + 1], a[4 * z + 2], a[4 * z + 3]};
                     fetch(i + AHEAD);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+            } else if (f < NL + NN) {
+                near[f < NL || f >= NL + NN ? 0 : f - NL] += a;
             } else {
-                near[f < NL ? 0 : f - NL] += a;
+                int g = gq, ld = ldo;
+                asm volatile("" : "+v"(g), "+s"(ld));
+                const TileStore ts = store_at(f);
+                if (!first)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) a[v] += ts.get(offset(f, v, g, ld));
+                if (column(f % CG) < NB)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) ts.put(a[v], offset(f, v, g, ld));
             }
             acc[f / CG][f % CG] = f32x16{0.f};
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int j = 0; j < CG; ++j) { b0[j] = ws[0][j * 64 + lane]; b1[j] = ws[0][(CG + j) * 64 + lane]; }     // (again)
     }
-    int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
-    asm volatile("" : "+v"(gq), "+s"(ldo_here));
-    auto finish = [&](auto folded) {                    // block by block: few registers
-        constexpr bool FOLDED = decltype(folded)::value;
-        if constexpr (FOLDED)
+    auto finish = [&](auto folded_) {                  // block by block: few registers
+        constexpr bool FOLDED = decltype(folded_)::value;
+        if constexpr (FOLDED && !SWIGLU)
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) fetch(i);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
+        auto total = [&](int f) {                      // block f of the sums, the chains folded away before included
             f32x16 a = acc[f / CG][f % CG];
-            asm volatile("" : "+a"(a));                 // (not read before its turn)
+            asm volatile("" : "+a"(a));                // (not read before its turn)
             if constexpr (FOLDED)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = f * 4 + q;
+                for (int z = 0; z < 4; ++z) {
+                    const int i = f * 4 + z;
+                    if (SWIGLU && f < NL) o[i % AHEAD] = far[f < NL ? i : 0][tid];       // (not in the order of the blocks)
+                    if (f < NL + NN)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) a[4 * q + v] += f < NL ? o[i % AHEAD][v] : near[f < NL ? 0 : f - NL][4 * q + v];
-                    if (f < NL) fetch(i + AHEAD);
+                        for (int v = 0; v < 4; ++v) a[4 * z + v] += f < NL ? o[i % AHEAD][v] : near[f < NL || f >= NL + NN ? 0 : f - NL][4 * z + v];
+                    if (!SWIGLU && f < NL) fetch(i + AHEAD);
                 }
-            const TileStore ts(out + (size_t)seg * slot_stride, (rb + f / CG) * 32, rows, ldo_here);
-            const int nb = ng * CG + f % CG, col = nb * 32 + (lane & 31);
-            if (nb < NB)
+            return a;
+        };
+        if constexpr (!SWIGLU) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) ts.put(a[v], ((8 * (v >> 2) + 4 * gq + (v & 3)) * ldo_here + col) * 4);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int f = 0; f < NF; ++f) {
+                f32x16 a = total(f);
+                int g = gq, ld = ldo;                  // opaque, as in k_gemm_sk: no hoisted row offsets
+                asm volatile("" : "+v"(g), "+s"(ld));
+                const TileStore ts = store_at(f);
+                if (f >= NL + NN && FOLDED)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) a[v] += ts.get(offset(f, v, g, ld));
+                if (column(f % CG) < NB)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) ts.put(a[v], offset(f, v, g, ld));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            // silu(gate) * up, block by block through LDS (a wave's own 4 KiB) into the fragments of the next projection's
+            // operand: two contraction blocks x (hi, lo), written whole
+            __syncthreads();                           // everybody is done with the weights
+            __bf16* turn = (__bf16*)ws + wave * 2048;
+            const bf16x8* turned = (const bf16x8*)turn;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int j = 0; j < CG / 2; ++j) {
+                    const f32x16 gt = total(t * CG + j), up = total(t * CG + j + CG / 2);
+                    const int c = lane & 31;           // column: contraction block c / 16 of the two, lane group c / 8 % 2, element c % 8
+                    int at0 = (c >> 4) * 1024 + 32 * ((c >> 3) & 1) * 8 + (c & 7) + 4 * gq * 8;
+                    asm volatile("" : "+v"(at0));
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float y = gt[v] / (1.f + __expf(-gt[v])) * up[v];
+                        const int at = at0 + (8 * (v >> 2) + (v & 3)) * 8;
+                        const __bf16 hi = (__bf16)y;
+                        turn[at] = hi;
+                        turn[at + 512] = (__bf16)(y - (float)hi);
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const int kb = column(j) * 2;
+                    bf16x8* dst = (bf16x8*)out_ + ((size_t)kb * MB + rb + t) * 128 + lane;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (rb + t < MB && column(j) < half && kb + k < KBf) {
+                            dst[(size_t)k * MB * 128] = turned[k * 128 + lane];
+                            dst[(size_t)k * MB * 128 + 64] = turned[k * 128 + 64 + lane];
+                        }
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
         }
     };
-    if (chain) finish(std::true_type{});                // (then there has been a fold)
+    if (chain && chain < n) finish(std::true_type{});
     else finish(std::false_type{});
 }
 
@@ -502,13 +593,14 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     for (int ng = 0; ng < p->NG; ++ng) p->uniform &= (cnt_host[ng] == slots);
     p->CG = 0;
     p->S = 0;
-    p->RT = p->MT = p->chain = 0;
+    p->RT = p->MT = p->chain = p->fold = 0;
+    p->join = 1;
     p->slots_max = slots;
     if (MB >= 4) gemm_plan_rows(p);
 }
 
 PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
-                     hipEvent_t ev0, hipEvent_t ev1) {
+                     hipEvent_t ev0, hipEvent_t ev1, void* swiglu, int swiglu_KB) {
     PartView pv;
     pv.base = out;
     pv.ld = p.NB * 32;
@@ -527,9 +619,9 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
             hipLaunchKernelGGL(KERNEL_, dim3(p.G), dim3(THREADS_), 0, s, SK_ARGS, ##__VA_ARGS__);          \
     } while (0)
     if (p.CG) {                                        // four / eight row blocks: the aligned split of k_gemm_rows
-        const int combos = (p.NB + p.CG - 1) / p.CG * p.S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
+        const int S = p.RT ? p.S / p.join : p.S, combos = (p.NB + p.CG - 1) / p.CG * S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
         pv.cnt = nullptr;
-        pv.nmax = p.S;
+        pv.nmax = S;
 #define ROWS_GO(KERNEL_, THREADS_)                                                                         \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
@@ -540,21 +632,37 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
             hipLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
                                (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos, p.chain); \
     } while (0)
+#define TILE_GO(CG_, SWIGLU_, OUT_)                                                                        \
+    do {                                                                                                   \
+        if (ev0 || ev1)                                                                                    \
+            hipExtLaunchKernelGGL((k_gemm_tile<CG_, SWIGLU_>), dim3(G), dim3(256), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
+                                  (const bf16x8*)Wp, (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT, combos, \
+                                  p.chain + p.fold, swiglu_KB);                                                     \
+        else                                                                                               \
+            hipLaunchKernelGGL((k_gemm_tile<CG_, SWIGLU_>), dim3(G), dim3(256), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
+                               (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT, combos, p.chain + p.fold, swiglu_KB); \
+    } while (0)
 #define ROWS_LAUNCH(MT_, CG_, TILED_) ROWS_GO((k_gemm_rows<MT_, CG_, TILED_>), 512)
+        if (swiglu) {                                  // (gemm_tile_swiglu)
+            TILE_GO(6, true, swiglu);
+            pv.nmax = 0;
+            return pv;
+        }
         const int key = (p.RT ? 100 + p.MT * 10 : p.MB * 10) + p.CG;
         if (key == 88) ROWS_LAUNCH(8, 8, false);
         else if (key == 86) ROWS_LAUNCH(8, 6, false);
         else if (key == 84) ROWS_LAUNCH(8, 4, false);
         else if (key == 48) ROWS_LAUNCH(4, 8, false);
         else if (key == 44) ROWS_LAUNCH(4, 4, false);
-        else if (key == 188) ROWS_LAUNCH(8, 8, true);
-        else if (key == 186) ROWS_GO((k_gemm_tile<6>), 256);
+        else if (key == 188) TILE_GO(8, false, out);
+        else if (key == 186) TILE_GO(6, false, out);
         else if (key == 184) ROWS_LAUNCH(8, 4, true);
         else if (key == 148) ROWS_LAUNCH(4, 8, true);
         else if (key == 144) ROWS_LAUNCH(4, 4, true);
         else pv.nmax = 0;                              // the planners make no other: nothing launched, nothing to read
 #undef ROWS_LAUNCH
 #undef ROWS_GO
+#undef TILE_GO
         return pv;
     }
     switch (p.MB) {                                    // one or two row blocks

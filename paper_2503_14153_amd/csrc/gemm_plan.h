@@ -21,6 +21,8 @@ struct GemmPlan {
     int RT, MT;              // prompt passes of more than 256 rows: RT tiles of MT row blocks each (MB = all of them), one
                              // workgroup per tile, column group and segment; 0 otherwise
     int chain;               // ... whose sums of products are folded away every `chain` contraction blocks (0: they are not)
+    int join, fold;          // prompt passes, eight by eight blocks: a workgroup takes `join` neighbouring segments (S / join
+                             // partial tiles), its sums folded away every `fold` contraction blocks; else 1 and 0
     int slots_max;           // slots the output buffer must hold for either
     int32_t* cnt_dev;        // [NG] contributors per column group (device)
     int32_t* slot0_dev;      // [G] slot of every workgroup's first segment (device)
@@ -69,10 +71,10 @@ static inline double gemm_plan_rows(GemmPlan* p) {      // -> the cost
 // Fewer segments are longer sums, and a sum that is rounded at every contraction block strays with its length: with one
 // segment for 256 blocks the QKV sums were 4.5 % further from 64 bits than with the four of a 256-row pass. So no chain of
 // products is longer than in a 256-row pass of the same matrix: a workgroup adds its sums to a second set ("folds") that often.
-// The tiles with room for a second set can (registers, and LDS for the tile of eight row blocks and six columns); the tile
-// of eight by eight has none and is taken only with segments that are short enough as they are (7B shape, 1024 rows: the down
-// projection in eight by eight, four segments of 172 blocks, 170 us; in eight by four, two segments of five chains, 193).
-static inline bool gemm_tile_folds(int MT, int CG) { return CG * MT <= 32 || (MT == 8 && CG == 6); }
+// The tile of eight by eight blocks has room for half of a second set and puts the rest into its output: dear, but with few
+// folds the tile that moves the fewest bytes per product is still the fastest. Its segments are as short as they have to be,
+// and a workgroup takes `join` of them (7B shape, 1024 rows, down projection: eight by four, two segments of five chains 200 us;
+// eight by eight, eight segments joined by two 180).
 // Longest chain of a 256-row pass, in contraction blocks.
 static inline int gemm_chain_limit(int KB, int NB) {
     GemmPlan q;
@@ -81,11 +83,14 @@ static inline int gemm_chain_limit(int KB, int NB) {
     gemm_plan_rows(&q);
     return KB / q.S;
 }
-static inline void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles) {
+// gate_up: the matrix is the gate/up projection (gemm_plan_swiglu below: half the bytes written, none read again).
+static inline void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double* cycles, bool gate_up = false) {
     memset(p, 0, sizeof(*p));
     p->MB = MB; p->KB = KB; p->NB = NB;
     static const int widths8[] = {8, 6, 4}, widths4[] = {8, 4};
     const int limit = gemm_chain_limit(KB, NB);
+    const int most = limit < 8 ? 8 : limit / 8 * 8;        // even chains, in the kernels' grain of eight blocks
+    auto even = [&](int n) { const int chains = (n + most - 1) / most; return chains > 1 ? ((n + chains - 1) / chains + 7) / 8 * 8 : 0; };
     double best = 0;
     for (int MT = 8; MT >= 4; MT /= 2)
         for (int wi = 0; wi < (MT == 8 ? 3 : 2); ++wi) {
@@ -93,23 +98,32 @@ static inline void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double*
             for (int S = 1; S <= 4 && S <= KB; ++S) {
                 if (KB % S) continue;
                 const int n = KB / S;
-                int chain = 0;
-                if (n > limit) {                       // even chains, in the kernels' grain of eight blocks
-                    if (!gemm_tile_folds(MT, CG)) continue;
-                    const int most = limit < 8 ? 8 : limit / 8 * 8, chains = (n + most - 1) / most;
-                    if (chains > 1) chain = ((n + chains - 1) / chains + 7) / 8 * 8;
+                int chain = 0, join = 1;
+                if (n > limit && MT * CG == 64) {
+                    while (join <= n && (n % join || n / join > limit)) ++join;
+                    if (join > n) continue;
+                    chain = even(n);
+                } else if (n > limit) {
+                    chain = even(n);
                 }
                 const int rounds = ((groups * S + 7) / 8 * RT + 31) / 32, steps = (n + 3) / 4 * 4;      // (an XCD's)
-                const double tile_bytes = (double)S * MB * 32 * NB * 32 * 4;
-                const double folds = chain ? (n - 1) / chain * 50.0 * CG * MT : 0.0;
+                const double tile_bytes = (double)S * MB * 32 * NB * 32 * 4 * (gate_up && MT == 8 && CG == 6 && S == 1 ? 0.25 : 1.0);
+                const double folds = chain ? (n - 1) / chain * (MT * CG == 64 ? 160.0 : 50.0) * CG * MT : 0.0;
                 const double cost = rounds * (steps * (16.0 * CG * MT + 300.0) + folds + 6000.0) + 2.0 * tile_bytes / 2500.0;
-                if (p->CG == 0 || cost < best) { best = cost; p->CG = CG; p->S = S; p->MT = MT; p->RT = RT; p->chain = chain; }
+                if (p->CG == 0 || cost < best) {
+                    best = cost; p->CG = CG; p->S = S * join; p->MT = MT; p->RT = RT; p->join = join;
+                    p->chain = MT * CG == 64 ? 0 : chain;
+                    p->fold = MT * CG == 64 ? chain : 0;
+                }
             }
         }
     p->slots = p->slots_max = p->S;
     p->uniform = 1;
     *cycles = best;
 }
+// The gate/up projection of a prompt pass whose workgroups see whole sums of 96 gate columns and the up columns that belong to
+// them: it writes silu(gate) * up, as the next projection's operand, instead of the sums (k_gemm_tile).
+static inline bool gemm_plan_swiglu(const GemmPlan& p) { return p.RT && p.MT == 8 && p.CG == 6 && p.S == 1; }
 
 // Time of a layer of a prompt pass, us, from its rows and its four projections (sh: contraction and column blocks of each). Up to
 // 64 rows the weights' bytes; up to 256 the cost above at 1950 cycles per us, with 60000 cycles for the layer's other launches;
@@ -125,7 +139,7 @@ static inline double prompt_pass_us(const int (*sh)[2], int rows) {
         GemmPlan p;
         double c = 0;
         if (mb > 8) {
-            gemm_plan_prompt(&p, mb, sh[i][0], sh[i][1], &c);
+            gemm_plan_prompt(&p, mb, sh[i][0], sh[i][1], &c, i == 2);
         } else {
             memset(&p, 0, sizeof(p));
             p.MB = mb > 4 ? 8 : 4; p.KB = sh[i][0]; p.NB = sh[i][1];

@@ -229,7 +229,7 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
 // sc: deferred RMS scale of the rows (ssq NULL: none; not available at four row blocks)
 // rows: rows that exist; the partial tiles' other rows are not written
 PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const void* zfrag, float* out, int rows, hipStream_t s,
-                     hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                     hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, void* swiglu = nullptr, int swiglu_KB = 0);
 // A handful of rows (few.hip): float32 rows in, every column finished by one workgroup, no partial sums.
 struct FewLinear {
     const float* X; int ldx;                                          // rows [M][ldx] (row m: gather[m] if given)

@@ -17,10 +17,14 @@ struct TileStore {
     __device__ __forceinline__ TileStore(float* tile, int row0, int rows, int ldo)
         : rsrc(__builtin_amdgcn_make_buffer_rsrc(uniform(tile + (size_t)row0 * ldo), 0,
                                                  __builtin_amdgcn_readfirstlane(min(max(rows - row0, 0), 32) * ldo * 4), 0x00020000)) {}
-    static __device__ __forceinline__ float* uniform(float* p) {
+    template <class T>
+    static __device__ __forceinline__ T* uniform(T* p) {
         const uint64_t a = (uint64_t)p;
-        return (float*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
+        return (T*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32);
+    }
+    __device__ __forceinline__ float get(int byte_offset) const {           // (what this thread has put there)
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, byte_offset, 0, /*sc1*/ 16));
     }
     __device__ __forceinline__ void put(float v, int byte_offset) const {
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rsrc, byte_offset, 0, /*sc1*/ 16);

@@ -1,0 +1,93 @@
+"""Prompt passes in k_gemm_tile: the gate/up projection that leaves silu(gate) * up as the next operand, and the tile of eight by
+eight blocks whose workgroups take several segments one after the other."""
+import ctypes as C
+import dataclasses
+import os
+import subprocess
+
+import pytest
+import torch
+
+import workload as wl
+from tests.test_gpu_long_prompts import _check, sd  # noqa: F401  (sd: the fixture)
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CODE = """
+#include "gemm_plan.h"
+extern "C" void plan(int MB, int KB, int NB, int gate_up, int* out) {
+    GemmPlan p;
+    double cycles;
+    gemm_plan_prompt(&p, MB, KB, NB, &cycles, gate_up);
+    int v[] = {gemm_plan_swiglu(p), p.chain, p.MT, p.CG, p.S, p.join, p.fold, gemm_chain_limit(KB, NB)};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
+}
+"""
+
+# (d_model, d_ffn, rows): sums in chains of 8 and 4 blocks, d_ffn half a column block over, a last group of two pairs; 25 row blocks
+# (the last tile has one) and 15 pairs of column blocks; 16 row blocks, a last group of two pairs
+SWIGLU = [(192, 1616, 1000), (64, 720, 800), (64, 944, 512)]
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tiles")
+    (d / "p.cpp").write_text(CODE)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2503_14153_amd", "csrc"),
+                    str(d / "p.cpp"), "-o", str(d / "p.so")], check=True)
+    lib = C.CDLL(str(d / "p.so"))
+
+    def call(rows, KB, NB, gate_up):
+        out = (C.c_int * 8)()
+        lib.plan(-(-rows // 32), KB, NB, gate_up, out)
+        return dict(zip(["swiglu", "chain", "MT", "CG", "S", "join", "fold", "limit"], out))
+    return call
+
+
+def test_the_shapes_below_take_those_paths(plan):
+    got = [plan(rows, d // 16, 2 * -(-F // 32), 1) for d, F, rows in SWIGLU]
+    assert all(p["swiglu"] for p in got) and [p["chain"] for p in got] == [8, 0, 0]
+    assert plan(1024, 256, 688, 1)["swiglu"] and plan(1024, 256, 688, 1)["chain"] == 128
+    p = plan(1024, 688, 128, 0)
+    assert (p["MT"], p["CG"], p["S"], p["join"], p["fold"]) == (8, 8, 8, 2, 64)
+
+
+def test_joined_segments_are_no_longer_than_in_a_256_row_pass(plan):
+    seen = 0
+    for KB, NB in [(688, 128), (320, 480), (320, 864), (864, 160), (1000, 128), (512, 512), (2048, 256)]:
+        for rows in range(288, 1025, 32):
+            p = plan(rows, KB, NB, 0)
+            if p["join"] == 1:
+                assert p["fold"] == 0
+                continue
+            seen += 1
+            assert (p["MT"], p["CG"]) == (8, 8) and p["S"] % p["join"] == 0 and KB % p["S"] == 0 and p["chain"] == 0
+            assert KB // p["S"] <= p["limit"] and p["fold"] % 8 == 0 and 0 < p["fold"] <= max(p["limit"], 8)
+            assert p["fold"] < KB * p["join"] // p["S"]
+    assert seen > 20
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,d_ffn,rows", SWIGLU)
+def test_gate_up_that_leaves_the_next_operand(sd, d, d_ffn, rows):  # noqa: F811
+    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=d // 64, head_dim=64, d_model=d, d_ffn=d_ffn),
+           [0], [rows])
+
+
+@pytest.mark.gpu
+def test_joined_segments_sum_like_single_passes(sd):  # noqa: F811
+    """The second layer's keys and values at the 7B width come through the first layer's gate/up (chains of 128) and down
+    projection (three chains of 64 in one workgroup). In passes of 256 rows the same sums are taken in other orders, so the two
+    float32 results differ by rounding, about 1e-6 of them, and some 1e-3 of the stored values round to a neighbour, 2^-8 away
+    at most: sqrt(1e-3) * 2^-8 = 1.2e-4 of the rows' norm. A block of sums lost or added twice would be of the order of 1."""
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_layers=2, d_model=4096, n_heads=32, head_dim=128, d_ffn=11008)
+    model = sd.Model(shape, wl.make_weights(shape, device="cuda"), 256)
+    tokens = torch.from_numpy(wl.zipf_prompt(shape.vocab, 1024, seed=11)).cuda()
+    got = []
+    for step in (1024, 256):
+        kv = sd.KVCache(model, 1, 1032)
+        for at in range(0, 1024, step):
+            sd.prefill(model, kv, tokens[at:at + step].contiguous(), [step])
+        got.append([t.double() for t in kv.read_rows(1, 0, 0, 1024)])
+    for joined, single in zip(*got):
+        assert (joined - single).norm() <= 5e-4 * single.norm()
+        assert (joined - single).norm(dim=(1, 2)).max() <= 5e-3 * single.norm(dim=(1, 2)).min()      # (no row by itself either)
