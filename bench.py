@@ -328,7 +328,7 @@ def main():
         "step_hbm_frac": step_bytes / (ms_per_step * 1e-3) / (HBM_PEAK_GBS * 1e9),
         "diverged_resets": state["diverged"], "sampling_replay_mismatches": replay_mismatches, "hip_graphs": args.graph,
         "sync_every": SYNC,
-        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_rows)", "bound": "hbm",
+        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_tile)", "bound": "hbm",
                      "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_gbs / HBM_PEAK_GBS,
                      "traffic": counted_traffic("k_gemm_sk_7b_pmc_traffic.txt", "k_gemm_sk_traffic_bytes_per_launch")
                      if (args.workload == "7b" and args.layers is None and not args.fused) else None,
@@ -409,7 +409,7 @@ def bench_batch(args, torch, wl, sd, W):
                                f"{W.kv_cap}, 20% stop ids",
                    "draft_schedule": args.draft_schedule, "decoding": "greedy", "draft_mode": "own heads"},
         "prefill_tokens_per_s": sum(lens) / prefill_s, "hip_graphs": args.graph,
-        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_rows)", "bound": "hbm",
+        "roofline": {"kernel": "projections (weight-streaming MFMA GEMMs: k_gemm_sk; a few rows k_few, k_gemm_kw, many k_gemm_tile)", "bound": "hbm",
                      "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gemm_gbs / HBM_PEAK_GBS,
                      "traffic": None, "avg_launch_us": g["ms"] / max(g["launches"], 1) * 1e3,
                      "launches_per_step": g["launches"] / args.profile_steps,

@@ -50,7 +50,7 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int nb_offset,
 
 // ------------------------------------------------------------------------------------------
 // Balanced streaming ("stream-K") over MT = 1 or 2 row blocks of 32 rows (this kernel; also the GEMM body of the
-// persistent layer kernel, there with eight row blocks as well) or four and eight (the kernel after it).
+// persistent layer kernel, there with eight row blocks as well) or more (the kernel after it).
 //
 // The work of one GEMM is the list of units (column group of 256 outputs, contraction block),
 // contraction block fastest; workgroup g of G takes the contiguous range [g*U/G, (g+1)*U/G),
@@ -88,198 +88,62 @@ __global__ __launch_bounds__(512, 4) void k_gemm_sk(const bf16x8* __restrict__ X
 }
 
 // ------------------------------------------------------------------------------------------
-// Eight (or four) row blocks with the operand roles swapped: the WEIGHT fragments of a step go through LDS and the
-// activations stay in registers. With many row blocks the kernel above reads every activation fragment from LDS
-// once per column block (16 one-KiB reads and 16 MFMAs per wave and step at eight row blocks: the LDS port and
-// the matrix cores are both needed all the time, and neither gets it). Here wave w owns ROW block w % MT and
-// CPW = CG * MT / 8 column blocks of a column group of CG blocks: its two activation fragments of a step (hi, lo)
-// come straight from L2 into registers (nobody else needs them), the first CG waves stream one weight fragment per
-// step through their rings and drop it into LDS, and each weight fragment read from LDS feeds two MFMAs.
+// Four row blocks and more, with the operand roles swapped: the WEIGHT fragments of a step go through LDS and the activations
+// stay in registers. With many row blocks the kernel above reads every activation fragment from LDS once per column block, and
+// the LDS port and the matrix cores are both needed all the time. Here a tile is MT row blocks x CG column blocks for four waves;
+// a wave has two row blocks and all of the columns (MT = 8) or half of them (MT = 4): its activations come straight from L2 into
+// registers, and every weight fragment that it reads from LDS feeds four products.
 //
-// At these row counts the matrix cores, not the weight stream, set the pace, and what a step costs beyond its
-// MFMAs is the hand-over through LDS. So the split is always the aligned one (workgroup g = column group g / S,
-// segment g % S of the contraction: one partial tile per workgroup, slot = segment), the width of a column group is
-// chosen with the split (gemm_plan_rows: narrower groups mean more workgroups and fewer slots), and a step is
-// software-pipelined around its one barrier:
-//   write the NEXT step's fragment to the other LDS buffer (its last readers passed the previous barrier);
-//   MFMAs of the first half of the column blocks (fragments already in registers), the ring's weight load among them;
-//   barrier; read the next step's first-half fragments;
-//   MFMAs of the second half, the two activation loads among them; read the next step's second-half fragments.
-// A wave that arrives at the barrier has its MFMAs queued and the reads it needs next already in flight; the
-// global loads are spread over the step because a wave cannot issue past a vector-memory instruction the address
-// unit has not taken yet (24 loads of 1 KiB per step at once held every wave's next MFMAs back).
-// Measured per step at 256 rows, column groups of six blocks (768 MFMA cycles): 1230 cycles with write, barrier,
-// read, MFMA in sequence; 1075 with the hand-over pipelined; 1030 with the loads spread as well.
+// Workgroup g = column group g / S, segment g % S of the contraction: one partial tile each, slot = segment. The width of a
+// group is chosen with the split (gemm_plan_rows, gemm_plan_prompt). In a prompt pass there are RT tiles of rows: workgroups
+// go to the XCDs round-robin, so the RT tiles of a (column group, segment) are dealt to one XCD, next to one another, and the
+// weights come from memory once. A last tile may reach past the operand's MB row blocks; those products are not stored.
 //
-// TILED (prompt passes of more than 256 rows): the pass is RT tiles of MT row blocks, a workgroup takes one tile of one
-// column group and segment. Workgroups go to the XCDs round-robin, so the RT tiles of a (column group, segment) are dealt to
-// one XCD, next to one another: the weights come from memory once and the other tiles find them in that XCD's L2. A last
-// tile that reaches past the operand's MB row blocks repeats its last one; those products are not stored.
-template <int MT, int CG, bool TILED>
-__global__ __launch_bounds__(512, 2) void k_gemm_rows(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
-                                                      const bf16x8* __restrict__ zfrag, float* __restrict__ out,
-                                                      int KB, int NB, int ldo, size_t slot_stride, int rows, int S, int MB_,
-                                                      int RT, int n_combo, int chain) {
-    static_assert((MT == 4 || MT == 8) && (CG * MT) % 16 == 0 && CG <= 8, "row blocks / column group");
-    constexpr int R = 4;                                // ring depth in steps; even (the LDS buffer of step i is i & 1)
-    constexpr int CPW = CG * MT / 8;                    // column blocks per wave: 8 waves cover MT rows x CG columns
-    constexpr int H = CPW / 2;                          // first half
-    __shared__ bf16x8 ws[2][CG * 64];                   // the weight fragments of two consecutive steps
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int r = wave % MT, ch = wave / MT;
-    int combo = blockIdx.x, tile = 0;                   // combo: column group and segment
-    if constexpr (TILED) {
-        const int q = blockIdx.x >> 3;                  // (of this XCD's workgroups)
-        tile = q % RT;
-        combo = (q / RT) * 8 + (blockIdx.x & 7);
-        if (combo >= n_combo) return;                   // (workgroup-uniform, before any barrier)
-    }
-    const int MB = TILED ? MB_ : MT, rb = tile * MT + r;   // this wave's row block
-    const int ng = combo / S, seg = combo - ng * S;
-    const int n = KB / S, kb0 = seg * n;                // this workgroup's steps: contraction blocks [kb0, kb0 + n)
-    const bool loader = wave < CG;
-    int nbw = ng * CG + wave;
-    if (nbw >= NB) nbw = NB - 1;                        // (a ragged last group: a duplicate fragment, never stored)
-    const size_t wstep = (size_t)NB * 64, xstep = (size_t)MB * 2 * 64;
-    const bf16x8* wp = Wp + ((size_t)kb0 * NB + nbw) * 64 + lane;
-    const bf16x8* xp = Xp + ((size_t)kb0 * MB + (TILED ? min(rb, MB - 1) : rb)) * 2 * 64 + lane;
-    const bf16x8* zl = zfrag + lane;                    // steps past n read zeros (no weight bytes, idle MFMA work)
-
-    f32x16 acc[CPW];
-#pragma unroll
-    for (int j = 0; j < CPW; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-    constexpr bool FOLDS = TILED && CPW <= 4;           // (not TILED: chain is 0)
-    f32x16 sum[FOLDS ? CPW : 1];                        // of the chains folded so far
-    int fold_at = chain;
-    if constexpr (FOLDS)
-#pragma unroll
-        for (int j = 0; j < CPW; ++j) sum[j] = acc[j];
-    bf16x8 w[R], xh[R], xl[R], b[CPW];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const bool ok = i < n;
-        if (loader) w[i] = __builtin_nontemporal_load(ok ? wp + (size_t)i * wstep : zl);
-        xh[i] = *(ok ? xp + (size_t)i * xstep : zl);
-        xl[i] = *(ok ? xp + (size_t)i * xstep + 64 : zl);
-    }
-    wp += R * wstep;
-    xp += R * xstep;
-    // step 0's fragments; its ring slot takes step R
-    if (loader) ws[0][wave * 64 + lane] = w[0];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < CPW; ++j) b[j] = ws[0][(ch * CPW + j) * 64 + lane];
-    if (loader) w[0] = __builtin_nontemporal_load(R < n ? wp : zl);
-    for (int s0 = 0; s0 < n; s0 += R) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            // entering step s0 + i: b holds its fragments (read from buffer i & 1), buffer (i + 1) & 1 is free
-            const bf16x8* wn = (s0 + R + i + 1 < n) ? wp + (size_t)(i + 1) * wstep : zl;   // step s0 + i + 1 + R
-            const bool xok = s0 + R + i < n;                                               // step s0 + i + R
-            const bf16x8* xhn = xok ? xp + (size_t)i * xstep : zl;
-            const bf16x8* xln = xok ? xp + (size_t)i * xstep + 64 : zl;
-            if (loader) ws[(i + 1) & 1][wave * 64 + lane] = w[(i + 1) % R];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < H; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[i], b[j], acc[j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (loader) w[(i + 1) % R] = __builtin_nontemporal_load(wn);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = 0; j < H; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[i], b[j], acc[j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < H; ++j) b[j] = ws[(i + 1) & 1][(ch * CPW + j) * 64 + lane];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = H; j < CPW; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh[i], b[j], acc[j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            xh[i] = *xhn;
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = H; j < CPW; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[i], b[j], acc[j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            xl[i] = *xln;
-#pragma unroll
-            for (int j = H; j < CPW; ++j) b[j] = ws[(i + 1) & 1][(ch * CPW + j) * 64 + lane];
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        wp += R * wstep;
-        xp += R * xstep;
-        if constexpr (FOLDS)
-            if (s0 + R == fold_at && s0 + R < n) {
-                fold_at += chain;
-#pragma unroll
-                for (int j = 0; j < CPW; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) { sum[j][v] += acc[j][v]; acc[j][v] = 0.f; }
-            }
-    }
-    if constexpr (FOLDS)
-#pragma unroll
-        for (int j = 0; j < CPW; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][v] += sum[j][v];
-    int gq = lane >> 5, ldo_here = ldo;                // opaque, as in k_gemm_sk: no hoisted row offsets
-    asm volatile("" : "+v"(gq), "+s"(ldo_here));
-    const TileStore ts(out + (size_t)seg * slot_stride, __builtin_amdgcn_readfirstlane(rb) * 32, rows, ldo_here);
-#pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-        const int nb = ng * CG + ch * CPW + j;
-        if (nb < NB) {
-            const int col = nb * 32 + (lane & 31);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = 8 * (v >> 2) + 4 * gq + (v & 3);
-                ts.put(acc[j][v], (m * ldo_here + col) * 4);
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// Prompt passes whose tiles are 256 rows x six or eight column blocks: the same work for four waves. A wave has two row blocks, so
-// every weight fragment that it reads from LDS feeds four products instead of two (half the LDS bytes), and a barrier comes once
-// per two contraction blocks. A wave alone on its SIMD issues everything itself, so loads, LDS reads and writes go one by one
-// between the products, evenly: 1890 cycles per two contraction blocks of six columns, of which the products are 1536.
+// A wave alone on its SIMD issues everything itself, so loads, LDS reads and writes go one by one between the products, evenly
+// (a wave cannot issue past a load that the address unit has not taken yet). Per iteration (two contraction blocks), a quarter
+// being the products of one block and one term: the next iteration's weight fragments go to the other LDS buffer, the second
+// block's are read; barrier; the next first block's are read; every quarter asks for what the quarter before it has done with.
+// 1890 cycles per iteration of eight row and six column blocks, 1536 of them products; 1490 of 1024 at four by eight.
 // What bounds it is the card's power: at that pace the clock is 1.63 GHz on dense data and 2.29 on zeros (QKV of 1024 rows, the
 // loop alone, 148 and 106 us), products alone run at 1.83. Bytes moved are therefore time even where no unit is full: without
 // the activations' loads 127 us, without the weights' 129, without LDS 119, without any of them 106.
-// 7B shape, four layers, a prompt of 1500 tokens, us: loads in groups of three and four, a launch for SwiGLU, the down projection
-// in tiles of eight by four 5504, this 5126 (QKV of 1024 rows 175 -> 167, gate/up and SwiGLU 346 -> 289, down 200 -> 180).
+// It replaced one of eight waves with a row block each (two products per fragment, a barrier per contraction block): 7B shape,
+// eight 32-node trees 1481 -> 1411 us, ten heads and 256 nodes 1275 -> 1212; 13B shape, 128 nodes 1255 -> 1209; a 256-row launch of
+// gate/up 84.0 -> 81.4, of down 43.8 -> 42.3, a 128-row launch of the 13B shape's gate/up 76.1 -> 72.1. Prompts, four layers, 1500
+// tokens: 5483 -> 5017, of which a part is the next two paragraphs' (gate/up and SwiGLU of 1024 rows 346 -> 289, down 200 -> 180).
+// Not kept: gate/up of 256 rows with whole sums, in tiles of eight by four (88 us; 77 and 11 for SwiGLU).
 //
-// Per iteration (two contraction blocks), a quarter being the products of one block and one term: the next iteration's weight
-// fragments go to the other LDS buffer, the second block's are read; barrier; the next first block's are read; every quarter
-// asks for what the quarter before it has done with.
+// chain (TILE_PROMPT, TILE_SWIGLU): every so many contraction blocks (a multiple of eight, the loop's grain is four) the products
+// are added to a second set and begin again at zero: see gemm_plan_prompt. Eight of its blocks are in LDS; the other four of the
+// tile of six columns are in registers (3 us a fold at 1024 rows), the other eight of the tile of eight in the output, where the
+// sums end up anyway (registers for half of those spill: down projection 233 us for 180).
 //
-// chain: every so many contraction blocks (a multiple of eight, the loop's grain is four) the products are added to a second set
-// and begin again at zero: see gemm_plan_prompt. Eight of its blocks are in LDS; the other four of the tile of six columns are in
-// registers (3 us a fold at 1024 rows), the other eight of the tile of eight in the output, where the sums end up anyway (registers
-// for half of those spill: down projection 233 us for 180).
-//
-// SWIGLU (gate/up with whole sums, gemm_plan_swiglu): half of a group's columns are gate columns, half the up columns that belong
-// to them; the workgroup writes silu(gate) * up as the next projection's operand. The sums, 90 MB at 1024 rows of the 7B shape,
-// are neither written nor read, and a launch of 23 us is gone.
-template <int CG, bool SWIGLU>
+// TILE_SWIGLU (gate/up with whole sums, gemm_plan_swiglu): half of a group's columns are gate columns, half the up columns that
+// belong to them; the workgroup writes silu(gate) * up as the next projection's operand. The sums, 90 MB at 1024 rows of the 7B
+// shape, are neither written nor read, and a launch of 23 us is gone.
+enum { TILE_STEP, TILE_PROMPT, TILE_SWIGLU };
+template <int MT, int CG, int KIND>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__ Xp, const bf16x8* __restrict__ Wp,
                                                       void* __restrict__ out_, int KB, int NB, int ldo, size_t slot_stride, int rows,
                                                       int S, int MB, int RT, int n_combo, int chain, int KBf) {
-    constexpr int NF = 2 * CG, LW = CG / 2;            // product blocks of a wave; weight fragments that it loads per iteration
+    constexpr bool SWIGLU = KIND == TILE_SWIGLU, CHAINS = KIND != TILE_STEP;
+    constexpr int DW = 2;                              // iterations whose weights are in flight (four: steps 0.6-1.2 % slower)
+    static_assert(MT == 8 || (MT == 4 && !SWIGLU), "four waves of two row blocks each, or two beside two");
+    constexpr int RW = MT / 2, CPW = CG * MT / 8;      // waves one above the other; column blocks of a wave
+    constexpr int NF = 2 * CPW, LW = CG / 2;           // product blocks of a wave; weight fragments that it loads per iteration
     // the second set of sums: blocks in LDS, in registers, in the output (beyond what there is room for)
-    constexpr int NL = 8, NN = CG == 6 ? 4 : 0, NM = NF - NL - NN;
+    constexpr int NL = !CHAINS ? 0 : NF < 8 ? NF : 8, NN = CHAINS && NF == 12 ? 4 : 0, NM = CHAINS ? NF - NL - NN : 0;
     static_assert(NM >= 0 && !(SWIGLU && NM), "an operand has no room for sums");
     __shared__ bf16x8 ws[2][2 * CG * 64];
-    __shared__ f32x4 far[NL * 4][256];                 // (every thread its own)
+    __shared__ f32x4 far[NL ? NL * 4 : 1][NL ? 256 : 1];               // (every thread its own)
     // (wave in a scalar register: what follows from it is the same in all lanes)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int q = blockIdx.x >> 3, tile = q % RT, combo = (q / RT) * 8 + (blockIdx.x & 7);      // as in k_gemm_rows
+    const int q = blockIdx.x >> 3, tile = q % RT, combo = (q / RT) * 8 + (blockIdx.x & 7);
     if (combo >= n_combo) return;
-    const int rb = tile * 8 + wave * 2;                // this wave's row blocks: rb and rb + 1
+    const int rb = tile * MT + wave % RW * 2;          // this wave's row blocks: rb and rb + 1
+    const int c0 = wave / RW * CPW;                    // ... and its first column block of the group's
     const int ng = combo / S, seg = combo - ng * S;
-    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2, len = chain ? chain / 2 : NI + 2;
+    const int n = KB / S, kb0 = seg * n, NI = (n + 1) / 2, len = CHAINS && chain ? chain / 2 : NI + DW;
     // column block j of the group: neighbours, or (SWIGLU) half of them gate blocks and half the up blocks that belong to them
     const int half = NB >> 1;
     auto column = [&](int j) {
@@ -310,47 +174,48 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
     auto xfrag = [&](__amdgpu_buffer_rsrc_t r, int k, int t, int p) {
         return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, xv[k] + t * 2048 + p * 1024, 0, 0));
     };
-    f32x16 near[NN ? NN : 1], acc[2][CG];
+    f32x16 near[NN ? NN : 1], acc[2][CPW];
 #pragma unroll
     for (int f = 0; f < NN; ++f) near[f] = f32x16{0.f};
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int j = 0; j < CG; ++j) acc[t][j] = f32x16{0.f};
-    bf16x8 w[2][LW], x[2][2][2][2], b[2][CG];          // x: [iteration][contraction block][row block][hi, lo]
+        for (int j = 0; j < CPW; ++j) acc[t][j] = f32x16{0.f};
+    bf16x8 w[DW][LW], x[2][2][2][2], b[2][CPW];         // x: [iteration][contraction block][row block][hi, lo]
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < DW; ++i) {
         const auto wr = bytes(wb, i, wstep, wmost), xr = bytes(xb, i, xstep, xmost);
 #pragma unroll
         for (int l = 0; l < LW; ++l) w[i][l] = wfrag(wr, l);
+        if (i < 2)
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
-                    if (i == 0 || k == 0 || p == 0) x[i][k][t][p] = xfrag(xr, k, t, p);
+                    if (i == 0 || k == 0 || p == 0) x[i & 1][k][t][p] = xfrag(xr, k, t, p);
     }
-    if (chain)                                         // (workgroup-uniform)
+    if (CHAINS && chain)                               // (workgroup-uniform)
 #pragma unroll
         for (int i = 0; i < NL * 4; ++i) far[i][tid] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int l = 0; l < LW; ++l) ws[0][(wave + 4 * l) * 64 + lane] = w[0][l];
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < CG; ++j) b[0][j] = ws[0][j * 64 + lane];
+    for (int j = 0; j < CPW; ++j) b[0][j] = ws[0][(c0 + j) * 64 + lane];
     {
-        const auto wr = bytes(wb, 2, wstep, wmost);
+        const auto wr = bytes(wb, DW, wstep, wmost);
 #pragma unroll
         for (int l = 0; l < LW; ++l) w[0][l] = wfrag(wr, l);
     }
     // block f of the wave's sums in the output
     const int gq = lane >> 5;
     auto store_at = [&](int f) {
-        return TileStore((float*)out_ + (size_t)seg * slot_stride, (rb + f / CG) * 32, rows, ldo);
+        return TileStore((float*)out_ + (size_t)seg * slot_stride, (rb + f / CPW) * 32, rows, ldo);
     };
     auto offset = [&](int f, int v, int g, int ld) {
-        return ((8 * (v >> 2) + 4 * g + (v & 3)) * ld + column(f % CG) * 32 + (lane & 31)) * 4;
+        return ((8 * (v >> 2) + 4 * g + (v & 3)) * ld + column(c0 + f % CPW) * 32 + (lane & 31)) * 4;
     };
     constexpr int AHEAD = 6;                           // pieces of four sums read before they are added to
     f32x4 o[AHEAD];
@@ -360,11 +225,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
     auto xr_old = bytes(xb, 1, xstep, xmost);                 // (the last quarter of an iteration's activations is asked for in the next one)
     for (int i0 = 0;;) {                               // a chain: iterations [i0, i1)
         const int i1 = min(i0 + len, NI);
-        for (; i0 < i1; i0 += 2) {
+        for (; i0 < i1; i0 += DW) {
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int it = i0 + ii, buf = ii ^ 1, nx = ii ^ 1;
-                const auto wr = bytes(wb, it + 3, wstep, wmost), xr = bytes(xb, it + 2, xstep, xmost);
+            for (int iu = 0; iu < DW; ++iu) {
+                const int it = i0 + iu, ii = iu & 1, buf = ii ^ 1, nx = ii ^ 1, nw = (iu + 1) % DW;      // (LDS buffers, ring slots)
+                const auto wr = bytes(wb, it + 1 + DW, wstep, wmost), xr = bytes(xb, it + 2, xstep, xmost);
                 // the products of one contraction block and one term, n_ops other things spread evenly among them
                 auto quarter = [&](int k, int p, int n_ops, auto&& op) {
 #pragma unroll
@@ -381,38 +246,38 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 constexpr int W1 = LW / 3, W2 = (LW - W1) / 2, W3 = LW - W1 - W2;     // weight loads of the last three quarters
-                constexpr int B1 = CG / 2, B2 = CG - B1;
-                quarter(0, 0, LW + 2 + CG, [&](int u) {
-                    if (u < LW) ws[buf][(wave + 4 * u) * 64 + lane] = w[nx][u];       // (its readers passed the previous barrier)
+                constexpr int B1 = CPW / 2, B2 = CPW - B1;
+                quarter(0, 0, LW + 2 + CPW, [&](int u) {
+                    if (u < LW) ws[buf][(wave + 4 * u) * 64 + lane] = w[nw][u];       // (its readers passed the previous barrier)
                     else if (u < LW + 2) x[nx][1][u - LW][1] = xfrag(xr_old, 1, u - LW, 1);
-                    else b[1][u - LW - 2] = ws[ii][(CG + u - LW - 2) * 64 + lane];
+                    else b[1][u - LW - 2] = ws[ii][(CG + c0 + u - LW - 2) * 64 + lane];
                 });
                 quarter(0, 1, 2 + W1, [&](int u) {
                     if (u < 2) x[ii][0][u][0] = xfrag(xr, 0, u, 0);
-                    else w[nx][u - 2] = wfrag(wr, u - 2);
+                    else w[nw][u - 2] = wfrag(wr, u - 2);
                 });
                 __syncthreads();
                 __builtin_amdgcn_sched_barrier(0);
                 quarter(1, 0, 2 + W2 + B1, [&](int u) {
                     if (u < 2) x[ii][0][u][1] = xfrag(xr, 0, u, 1);
-                    else if (u < 2 + W2) w[nx][W1 + u - 2] = wfrag(wr, W1 + u - 2);
-                    else b[0][u - 2 - W2] = ws[buf][(u - 2 - W2) * 64 + lane];
+                    else if (u < 2 + W2) w[nw][W1 + u - 2] = wfrag(wr, W1 + u - 2);
+                    else b[0][u - 2 - W2] = ws[buf][(c0 + u - 2 - W2) * 64 + lane];
                 });
                 quarter(1, 1, 2 + W3 + B2, [&](int u) {
                     if (u < 2) x[ii][1][u][0] = xfrag(xr, 1, u, 0);
-                    else if (u < 2 + B2) b[0][B1 + u - 2] = ws[buf][(B1 + u - 2) * 64 + lane];
-                    else w[nx][W1 + W2 + u - 2 - B2] = wfrag(wr, W1 + W2 + u - 2 - B2);
+                    else if (u < 2 + B2) b[0][B1 + u - 2] = ws[buf][(c0 + B1 + u - 2) * 64 + lane];
+                    else w[nw][W1 + W2 + u - 2 - B2] = wfrag(wr, W1 + W2 + u - 2 - B2);
                 });
                 xr_old = xr;
             }
         }
-        if (i1 >= NI) break;
+        if (!CHAINS || i1 >= NI) break;
         const bool first = i1 == len;                  // (the first fold: nothing in the output yet)
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) fetch(i);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            f32x16 a = acc[f / CG][f % CG];
+            f32x16 a = acc[f / CPW][f % CPW];
             asm volatile("" : "+a"(a));                // (not read before its turn)
             if (f < NL) {
 #pragma unroll
@@ -431,11 +296,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
                 if (!first)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) a[v] += ts.get(offset(f, v, g, ld));
-                if (column(f % CG) < NB)
+                if (column(c0 + f % CPW) < NB)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) ts.put(a[v], offset(f, v, g, ld));
             }
-            acc[f / CG][f % CG] = f32x16{0.f};
+            acc[f / CPW][f % CPW] = f32x16{0.f};
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -445,7 +310,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) fetch(i);
         auto total = [&](int f) {                      // block f of the sums, the chains folded away before included
-            f32x16 a = acc[f / CG][f % CG];
+            f32x16 a = acc[f / CPW][f % CPW];
             asm volatile("" : "+a"(a));                // (not read before its turn)
             if constexpr (FOLDED)
 #pragma unroll
@@ -469,7 +334,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
                 if (f >= NL + NN && FOLDED)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) a[v] += ts.get(offset(f, v, g, ld));
-                if (column(f % CG) < NB)
+                if (column(c0 + f % CPW) < NB)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) ts.put(a[v], offset(f, v, g, ld));
                 __builtin_amdgcn_sched_barrier(0);
@@ -510,7 +375,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16x8* __restrict__
                 }
         }
     };
-    if (chain && chain < n) finish(std::true_type{});
+    if (CHAINS && chain && chain < n) finish(std::integral_constant<bool, CHAINS>{});
     else finish(std::false_type{});
 }
 
@@ -618,50 +483,37 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
         else                                                                                               \
             hipLaunchKernelGGL(KERNEL_, dim3(p.G), dim3(THREADS_), 0, s, SK_ARGS, ##__VA_ARGS__);          \
     } while (0)
-    if (p.CG) {                                        // four / eight row blocks: the aligned split of k_gemm_rows
+    if (p.CG) {                                        // four row blocks and more: the aligned split of k_gemm_tile
         const int S = p.RT ? p.S / p.join : p.S, combos = (p.NB + p.CG - 1) / p.CG * S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
         pv.cnt = nullptr;
         pv.nmax = S;
-#define ROWS_GO(KERNEL_, THREADS_)                                                                         \
+#define TILE_GO(MT_, CG_, KIND_, OUT_)                                                                        \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
-            hipExtLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, ev0, ev1, 0, (const bf16x8*)Xp,  \
-                                  (const bf16x8*)Wp, (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, \
-                                  p.MB, p.RT, combos, p.chain);                                                     \
-        else                                                                                               \
-            hipLaunchKernelGGL(KERNEL_, dim3(G), dim3(THREADS_), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (const bf16x8*)zfrag, out, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT, combos, p.chain); \
-    } while (0)
-#define TILE_GO(CG_, SWIGLU_, OUT_)                                                                        \
-    do {                                                                                                   \
-        if (ev0 || ev1)                                                                                    \
-            hipExtLaunchKernelGGL((k_gemm_tile<CG_, SWIGLU_>), dim3(G), dim3(256), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
-                                  (const bf16x8*)Wp, (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT, combos, \
+            hipExtLaunchKernelGGL((k_gemm_tile<MT_, CG_, KIND_>), dim3(G), dim3(256), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
+                                  (const bf16x8*)Wp, (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT ? p.RT : 1, combos, \
                                   p.chain + p.fold, swiglu_KB);                                                     \
         else                                                                                               \
-            hipLaunchKernelGGL((k_gemm_tile<CG_, SWIGLU_>), dim3(G), dim3(256), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT, combos, p.chain + p.fold, swiglu_KB); \
+            hipLaunchKernelGGL((k_gemm_tile<MT_, CG_, KIND_>), dim3(G), dim3(256), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
+                               (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT ? p.RT : 1, combos, p.chain + p.fold, swiglu_KB); \
     } while (0)
-#define ROWS_LAUNCH(MT_, CG_, TILED_) ROWS_GO((k_gemm_rows<MT_, CG_, TILED_>), 512)
         if (swiglu) {                                  // (gemm_tile_swiglu)
-            TILE_GO(6, true, swiglu);
+            TILE_GO(8, 6, TILE_SWIGLU, swiglu);
             pv.nmax = 0;
             return pv;
         }
         const int key = (p.RT ? 100 + p.MT * 10 : p.MB * 10) + p.CG;
-        if (key == 88) ROWS_LAUNCH(8, 8, false);
-        else if (key == 86) ROWS_LAUNCH(8, 6, false);
-        else if (key == 84) ROWS_LAUNCH(8, 4, false);
-        else if (key == 48) ROWS_LAUNCH(4, 8, false);
-        else if (key == 44) ROWS_LAUNCH(4, 4, false);
-        else if (key == 188) TILE_GO(8, false, out);
-        else if (key == 186) TILE_GO(6, false, out);
-        else if (key == 184) ROWS_LAUNCH(8, 4, true);
-        else if (key == 148) ROWS_LAUNCH(4, 8, true);
-        else if (key == 144) ROWS_LAUNCH(4, 4, true);
+        if (key == 88) TILE_GO(8, 8, TILE_STEP, out);
+        else if (key == 86) TILE_GO(8, 6, TILE_STEP, out);
+        else if (key == 84) TILE_GO(8, 4, TILE_STEP, out);
+        else if (key == 48) TILE_GO(4, 8, TILE_STEP, out);
+        else if (key == 44) TILE_GO(4, 4, TILE_STEP, out);
+        else if (key == 188) TILE_GO(8, 8, TILE_PROMPT, out);
+        else if (key == 186) TILE_GO(8, 6, TILE_PROMPT, out);
+        else if (key == 184) TILE_GO(8, 4, TILE_PROMPT, out);
+        else if (key == 148) TILE_GO(4, 8, TILE_PROMPT, out);
+        else if (key == 144) TILE_GO(4, 4, TILE_PROMPT, out);
         else pv.nmax = 0;                              // the planners make no other: nothing launched, nothing to read
-#undef ROWS_LAUNCH
-#undef ROWS_GO
 #undef TILE_GO
         return pv;
     }

@@ -28,7 +28,7 @@ struct GemmPlan {
     int32_t* slot0_dev;      // [G] slot of every workgroup's first segment (device)
 };
 
-// Four and eight row blocks (k_gemm_rows): the width of a column group, CG blocks, and the number of segments S the
+// Four and eight row blocks (k_gemm_tile): the width of a column group, CG blocks, and the number of segments S the
 // contraction is split into, S a divisor of KB, at most 16. Cost of a candidate in shader cycles, from the kernel's
 // measured pace: a step costs its MFMAs (two waves per SIMD, 2 x CPW MFMAs of 32 cycles each) plus about 300 cycles
 // of hand-over; a workgroup runs KB / S steps (rounded up to the ring), the grid ceil(groups x S / 256) rounds; the S

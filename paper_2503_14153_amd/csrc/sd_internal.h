@@ -122,7 +122,7 @@ static __device__ inline int part_count(const PartView& p, int col) { return p.c
 // XCD (they are dealt round-robin) and a segment fetch the segment's lines together at the start, one line per thread, while
 // the first weights are on their way; the loads of the walk then find them in L2. (Another mapping only costs time.)
 // k_gemm_sk only: steps of four layers at 64 rows 724.5 -> 719 us, five 12-node trees 770 -> 761, 16 k rows 907 -> 899. Level or
-// slower for k_gemm_kw (16 rows 553 -> 554) and k_gemm_rows (256 rows 1286 -> 1310: four times the lines).
+// slower for k_gemm_kw (16 rows 553 -> 554) and for the 256-row kernel (1286 -> 1310: four times the lines).
 struct OperandTouch { uint32_t magic; int shares; };   // ceil(2^32 / period), workgroups of an XCD and a segment
 static inline OperandTouch operand_touch(int G, int S) {
     int period = 8;

@@ -77,7 +77,7 @@ static __device__ inline SkIter sk_walk_next(SkWalk& w, int KB) {
 // A workgroup (or a whole launch) without units: has_work() is false, the other calls do nothing.
 template <int MT>
 struct SkGemm {
-    static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_rows only");
+    static_assert(MT == 1 || MT == 2 || MT == 8, "four row blocks: k_gemm_tile only");
     // Ring depth R, and XK contraction blocks per activation chunk (a barrier each). A shallow ring: what a wave holds in
     // flight when its stream ends is still to be multiplied then, and a workgroup's steps are padded to a multiple of R.
     // Depth 16 (chunks of 8 / MT) keeps more bytes in flight and is slower: down projection of the 7B shape (43 steps a
