@@ -944,7 +944,7 @@ static bool fused_eligible(const sd_model* m, int M) {
 }
 // The geometry that the pass over B sequences of Tp rows will launch: worked out once per pass, launched, and part of the
 // key under which the pass is captured. (float32 attention has no parts: none of its launches depends on n_hi.)
-struct PassGeom : AttnGeom { AttnSplit split; bool whole; };
+struct PassGeom : AttnGeom { AttnSplit split; int whole; };     // whole: 0, or the parts of attn_whole.hip (1: none)
 // M: the pass's rows (a short prompt has fewer than its padded B * Tp).
 static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t* seq, int B, int M, int Tp, int n_hi) {
     PassGeom g = {};
@@ -953,7 +953,8 @@ static PassGeom pass_geometry(const sd_model* m, const sd_kv* kv, const int32_t*
     static_cast<AttnGeom&>(g) = attn_geometry_of_pass(fused_eligible(m, B * Tp), m->cfg.n_heads, m->max_parts, B, Tp, n_hi,
                                                       B > 1 && n_hi >= 256);
     // (a handful of rows take the merged parts as an operand of another layout)
-    g.whole = !fused_eligible(m, B * Tp) && !few_layers(m, M) && attn_whole_pays(m->cfg.n_heads, B, Tp, n_hi);
+    g.whole = !fused_eligible(m, B * Tp) && !few_layers(m, M) ? attn_whole_parts(m->cfg.n_heads, B, Tp, n_hi) : 0;
+    if (g.whole > 1) g.nparts = g.whole;
     if (g.per == 0) {
         int len[SD_MAX_BATCH];
         for (int i = 0; i < B; ++i) len[i] = kv->len_hi[seq ? seq[i] : i];
@@ -1015,7 +1016,7 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
         const uint16_t *kc = kv->kc + l * kv->layer_stride, *vc = kv->vc + l * kv->layer_stride;
         if (ag.whole)
             launch_attn_whole(m->q, kc, vc, kt, vt, kv->kv_len, m->rt.anc, m->attn_x, rr, B, nh, hd, Tp, kv->cap_blocks, MB, s,
-                              prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr);
+                              prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr, fr ? &m->rt : nullptr, ag.whole, m->opart, m->mlpart);
         else
             launch_tree_attn(m->q, kc, vc, kt, vt, kv->kv_len, m->rt.anc, m->opart, m->mlpart, rr, B, nh, hd, Tp, kv->cap_blocks,
                              ag.ncparts, ag.per, ag.tree_sep, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1), fr ? &pq : nullptr,
@@ -1040,7 +1041,7 @@ static PartView run_layers(sd_model* m, sd_kv* kv, RowRef rr, const RowMap& rm, 
             few_launch(m, d, m->KBf, [&](hipEvent_t e0, hipEvent_t e1) { launch_few_add(a, s, e0, e1); });
             continue;                                  // (prev stays empty: the residual stream is complete)
         }
-        if (!ag.whole) launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
+        if (ag.whole != 1) launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, B, nh, hd, Tp, ag.nparts, MB, s, split);
         PartView po = run_projection(m, plan(KW_O), m->attn_x, lw.wo, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s);

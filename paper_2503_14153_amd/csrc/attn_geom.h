@@ -118,3 +118,17 @@ static inline bool attn_whole_pays(int n_heads, int B, int Tp, int n_hi) {
     if (Tp < 64 || groups < 64 || (rounds > 1 && Tp == 64)) return false;
     return blocks * rounds * 64 <= 18 * (groups < 256 ? groups : 256);
 }
+// Parts of a (sequence, head, row block) in attn_whole.hip: 1 where one workgroup takes all of it (above), 0 where attn.hip's
+// parts are faster, or, for one sequence of two row blocks, as many as fill the chip with workgroups of one row block each:
+// three or four, of up to 33 blocks. Two query blocks share a wave in attn.hip, which halves its reads of a long cache; over a
+// short one its four waves have a block or two each, one after the other, and these have eight. Steps of four layers, 7B shape, 64
+// nodes, us, attn.hip / here: 700 rows 702 / 694 (32 layers: 4652 / 4645), 1100 696.5 / 688, 2200 712 / 701, 3000 729 / 725, 4200 732 / 725, 6000 761 / 763,
+// 16384 873 / 895; 13B shape, two layers: 1200 rows 537 / 524, 2000 541 / 533, 4096 561 / 569. Two parts (two sequences, 128
+// nodes) are level.
+static inline int attn_whole_parts(int n_heads, int B, int Tp, int n_hi) {
+    if (attn_whole_pays(n_heads, B, Tp, n_hi)) return 1;
+    const int groups = B * n_heads * (Tp / 32), blocks = (n_hi + 31) / 32 + Tp / 32;
+    if (Tp != 64 || groups < 64 || groups * 3 > 256) return 0;
+    const int P = 256 / groups;
+    return blocks <= 33 * P ? P : 0;
+}

@@ -2,11 +2,14 @@
 // in LDS and write the merged, normalised result as the next projection's operand. No parts, no partials in memory, no merge
 // launch, and rows past the first block no longer ride with 64 others. attn.hip cuts a head's blocks over several workgroups
 // instead, which a long sequence needs: a workgroup takes about 0.16 us per block and 32 rows (32 MFMAs on two-term queries and
-// probabilities, the softmax and 16 KiB of queries from LDS each), so this one is for few blocks (attn_whole_pays).
+// probabilities, the softmax and 16 KiB of queries from LDS each), so this one is for few blocks (attn_whole_parts).
 // 7B shape, steps of four layers, us, parts and merge -> here: 64 nodes over 300 rows 700 -> 680, over 700 716 -> 711, over 1800 735
 // -> 750; 128 nodes over 1000 942 -> 926; 256 over 512 1302 -> 1264; two sequences of 500 and 900, 64 nodes 939 -> 914; 13B
 // shape, 128 over 4096 1267 -> 1287; one row block never (plain decoding over 1000 rows 441 -> 471). Holding two blocks of
 // keys instead of one changes nothing.
+//
+// PARTS: a workgroup takes one of P equal shares of the blocks (the last one the tree's too) and leaves partial results as attn.hip
+// does, for the same merge: attn_whole_parts has where and what it gives.
 //
 // Arithmetic, layouts and masks as in attn.hip (S^T = K Q^T, values permuted so that exp(S) is the next operand, two-term queries
 // and probabilities, lazily raised maximum). A wave holds one block of keys and values and asks for the next as soon as the
@@ -21,12 +24,13 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 #define NEG_INF (-__builtin_inff())
 #define LAZY_MAX 8.0f                  // the running maximum is raised only past 2^8 of itself (see attn.hip)
 
-template <int HD, int AW, int FR, int NS, bool MAP>
+template <int HD, int AW, int FR, int NS, bool MAP, bool PARTS>
 __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict__ Qp, const bf16x8* Kc, const bf16x8* Vc, bf16x8* Kt,
                                                        bf16x8* Vt, const int32_t* __restrict__ kv_len,
                                                        const uint32_t* __restrict__ anc, bf16x8* __restrict__ xp, int nh, int Tp,
                                                        int cap_blocks, float scale_log2, int stride, int nseq, int MB, PartView pv,
-                                                       RowTable rt, RowRef rr) {
+                                                       RowTable rt, RowRef rr, int P, float* __restrict__ opart,
+                                                       float2* __restrict__ mlpart) {
     constexpr int KK = HD / 16, EB = HD / 32, NV = 2 * EB, BLK = HD * 4, NW = 8;
     constexpr int QU = KK * 2 * 64;    // 16-byte units of the queries
     constexpr int OU = EB * 4 * 64;    // of a wave's O in the merge area
@@ -37,13 +41,15 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, tl = lane & 31;
     // The query blocks of a (sequence, head) lie `stride` workgroups apart, a multiple of eight: on one XCD, whose L2 then serves
     // the blocks that they all read.
-    const int tg = blockIdx.x / stride, combo = blockIdx.x - tg * stride;
+    const int group = blockIdx.x / stride, combo = blockIdx.x - group * stride;
+    const int part = PARTS ? group % P : 0, tg = PARTS ? group / P : group;
     if (combo >= nh * nseq) return;
     const int h = combo % nh, b = combo / nh, TB = Tp / 32;
     if (MAP && tg * 32 >= rr.map->len[b]) return;
     const int row0 = MAP ? rr.map->off[b] : b * rr.R, row_last = (MAP ? rr.map->len[b] : rr.R) - 1;
     const int sq = MAP ? rr.map->seq[b] : b;
-    const int ntree = tg + 1;          // blocks of the tree up to the rows' own (later ones hold no ancestors)
+    // blocks of the tree up to the rows' own (later ones hold no ancestors); the last part has them
+    const int ntree = !PARTS || part == P - 1 ? tg + 1 : 0;
     uint4 ancq[AW / 4];
 #pragma unroll
     for (int q = 0; q < AW / 4; ++q) ancq[q] = *(const uint4*)(anc + ((size_t)b * Tp + tg * 32 + tl) * SD_ANC_WORDS + 4 * q);
@@ -51,6 +57,40 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
     const bf16x8* kcb = Kc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const bf16x8* vcb = Vc + ((size_t)sq * nh + h) * cap_blocks * BLK + lane;
     const size_t thead = ((size_t)b * nh + h) * TB * BLK;
+
+    // Items: the cache's blocks, then the tree's. The waves take equal runs of them. With FR the tree's are in LDS: a wave that
+    // has some comes to them after its cache blocks, when its registers are free.
+    // PARTS: this part's share [b0, nblk) of the sequence's blocks, the tree's counted in.
+    int nblk = (n + 31) >> 5, b0 = 0;
+    if constexpr (PARTS) {
+        const int each = (nblk + tg + 1 + P - 1) / P;
+        b0 = min(part * each, nblk);
+        nblk = part == P - 1 ? nblk : min(b0 + each, nblk);
+    }
+    const int total = nblk - b0 + ntree, base = total / NW, more = total - base * NW;
+    const int j0 = __builtin_amdgcn_readfirstlane(b0 + wave * base + min(wave, more));
+    const int j1 = j0 + base + (wave < more ? 1 : 0);
+    const int je = FR ? max(j0, min(j1, nblk)) : j1;   // items [j0, je) come from memory
+    auto kaddr = [&](int j) -> const bf16x8* {
+        return FR || j < nblk ? kcb + (size_t)min(j, cap_blocks - 1) * BLK : Kt + thead + (size_t)(j - nblk) * BLK + lane;
+    };
+    auto vaddr = [&](int j) -> const bf16x8* {
+        return FR || j < nblk ? vcb + (size_t)min(j, cap_blocks - 1) * BLK : Vt + thead + (size_t)(j - nblk) * BLK + lane;
+    };
+    bf16x8 kr[KK], vr[NV];
+    auto request_k = [&](int j) {
+        const bf16x8* p = kaddr(j);
+#pragma unroll
+        for (int i = 0; i < KK; ++i) kr[i] = __builtin_nontemporal_load(p + i * 64);
+    };
+    auto request_v = [&](int j) {
+        const bf16x8* p = vaddr(j);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) vr[i] = __builtin_nontemporal_load(p + i * 64);
+    };
+    const int jf = min(j0, max(je - 1, 0));            // (a wave without such items: a block in bounds, unused)
+    request_k(jf);
+    request_v(jf);
 
     if constexpr (FR) {
         constexpr int NA = HD / 16;                    // pieces of 8 dims + their rotary partners per row
@@ -99,33 +139,6 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
             if (QU % (NW * 64) == 0 || u < QU) qs[u] = qsrc[u];
         }
     }
-
-    // Items: the cache's blocks, then the tree's. The waves take equal runs of them. With FR the tree's are in LDS: a wave that
-    // has some comes to them after its cache blocks, when its registers are free.
-    const int nblk = (n + 31) >> 5, total = nblk + ntree, base = total / NW, more = total - base * NW;
-    const int j0 = __builtin_amdgcn_readfirstlane(wave * base + min(wave, more));
-    const int j1 = j0 + base + (wave < more ? 1 : 0);
-    const int je = FR ? max(j0, min(j1, nblk)) : j1;   // items [j0, je) come from memory
-    auto kaddr = [&](int j) -> const bf16x8* {
-        return FR || j < nblk ? kcb + (size_t)min(j, cap_blocks - 1) * BLK : Kt + thead + (size_t)(j - nblk) * BLK + lane;
-    };
-    auto vaddr = [&](int j) -> const bf16x8* {
-        return FR || j < nblk ? vcb + (size_t)min(j, cap_blocks - 1) * BLK : Vt + thead + (size_t)(j - nblk) * BLK + lane;
-    };
-    bf16x8 kr[KK], vr[NV];
-    auto request_k = [&](int j) {
-        const bf16x8* p = kaddr(j);
-#pragma unroll
-        for (int i = 0; i < KK; ++i) kr[i] = __builtin_nontemporal_load(p + i * 64);
-    };
-    auto request_v = [&](int j) {
-        const bf16x8* p = vaddr(j);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) vr[i] = __builtin_nontemporal_load(p + i * 64);
-    };
-    const int jf = min(j0, max(je - 1, 0));            // (a wave without such items: a block in bounds, unused)
-    request_k(jf);
-    request_v(jf);
 
     f32x16 O[EB], S;
     float mrun = NEG_INF, lrun = 0.f;
@@ -255,6 +268,8 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
     L += __shfl_xor(L, 32);
     const float inv = L > 0.f ? 1.f / L : 0.f;
     const int t = tg * 32 + tl;
+    const size_t prow = (((size_t)b * nh + h) * P + part) * Tp + t;      // (PARTS)
+    if (PARTS && wave == 0 && g == 0 && t <= row_last) mlpart[prow] = make_float2(M, L);
 #pragma unroll
     for (int q = 0; q < EB * 4 / NW; ++q) {
         const int piece = wave * (EB * 4 / NW) + q;    // dims 8 piece + 4 g ..
@@ -265,6 +280,10 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
             f[0] += sc[w] * x.x; f[1] += sc[w] * x.y; f[2] += sc[w] * x.z; f[3] += sc[w] * x.w;
         }
         if (t > row_last) continue;
+        if constexpr (PARTS) {
+            *(float4*)(opart + prow * HD + piece * 8 + 4 * g) = make_float4(f[0], f[1], f[2], f[3]);
+            continue;
+        }
         bf16x4 hi, lo;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -281,20 +300,22 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
 
 void launch_attn_whole(const void* q_packed, const void* kc, const void* vc, void* kt, void* vt, const int32_t* kv_len,
                        const uint32_t* anc, void* x_packed, RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int MB,
-                       hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, const PartView* qkv, const RowTable* rt) {
+                       hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, const PartView* qkv, const RowTable* rt, int P, float* opart,
+                       float2* mlpart) {
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
     const int stride = (nh * B + 7) / 8 * 8, TG = Tp / 32;
     const PartView pv = qkv ? *qkv : PartView{nullptr, 0, 0, nullptr, 0};
     const RowTable rta = rt ? *rt : RowTable{nullptr, nullptr, nullptr, nullptr};
 #define AW_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (bf16x8*)kt, (bf16x8*)vt, kv_len, anc, (bf16x8*)x_packed, \
-                nh, Tp, cap_blocks, scale_log2, stride, B, MB, pv, rta, rr
-#define AW_GO(HD_, AW_, FR_, NS_, MAP_)                                                                                          \
+                nh, Tp, cap_blocks, scale_log2, stride, B, MB, pv, rta, rr, P, opart, mlpart
+#define AW_GOP(HD_, AW_, FR_, NS_, MAP_, PARTS_)                                                                                          \
     do {                                                                                                                         \
         if (ev0 || ev1)                                                                                                          \
-            hipExtLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_>), dim3(stride * TG), dim3(512), 0, s, ev0, ev1, 0, AW_ARGS); \
+            hipExtLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), dim3(stride * TG * P), dim3(512), 0, s, ev0, ev1, 0, AW_ARGS); \
         else                                                                                                                     \
-            hipLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_>), dim3(stride * TG), dim3(512), 0, s, AW_ARGS);            \
+            hipLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), dim3(stride * TG * P), dim3(512), 0, s, AW_ARGS);            \
     } while (0)
+#define AW_GO(HD_, AW_, FR_, NS_, MAP_) do { if (P > 1) AW_GOP(HD_, AW_, FR_, NS_, MAP_, true); else AW_GOP(HD_, AW_, FR_, NS_, MAP_, false); } while (0)
 #define AW_MAP(HD_, AW_, FR_, NS_) do { if (rr.map) AW_GO(HD_, AW_, FR_, NS_, true); else AW_GO(HD_, AW_, FR_, NS_, false); } while (0)
 #define AW_HD(HD_)                                                                                                               \
     do {                                                                                                                         \
@@ -307,5 +328,6 @@ void launch_attn_whole(const void* q_packed, const void* kc, const void* vc, voi
 #undef AW_HD
 #undef AW_MAP
 #undef AW_GO
+#undef AW_GOP
 #undef AW_ARGS
 }

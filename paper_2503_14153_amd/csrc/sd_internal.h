@@ -323,7 +323,8 @@ void launch_tree_attn(const void* q_packed, const void* kc, const void* vc, cons
 void launch_attn_whole(const void* q_packed, const void* kc, const void* vc, void* kt, void* vt, const int32_t* kv_len,
                        const uint32_t* anc, void* x_packed, RowRef rr, int B, int nh, int hd, int Tp, int cap_blocks, int MB,
                        hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const PartView* qkv = nullptr,
-                       const RowTable* rt = nullptr);
+                       const RowTable* rt = nullptr, int P = 1,
+                       float* opart = nullptr, float2* mlpart = nullptr);
 void launch_attn_merge(const float* opart, const float2* mlpart, void* x_packed, RowRef rr, int longest, int B, int nh, int hd,
                        int Tp, int nparts, int MB, hipStream_t s, const AttnSplit* split = nullptr);
 // the same, as few.hip's ready-made operand
