@@ -1459,6 +1459,7 @@ static void run_prompt_passes(sd_model* m, sd_kv* kv, const int32_t* tokens, con
     const RowRef rr = {m->rm_dev, 0};
     // (parts: what the partials' buffer holds)
     const AttnGeom ag = attn_geometry(nh, std::min(m->max_parts, m->MBmax * 32 * m->max_parts / (V * Tp)), V, Tp, n_hi, false);
+    const bool whole = attn_whole_pays_prompt(Tp, n_hi);
     const int keep_A = V - keep, keep_TB = keep_Tp / 32;
     const size_t keep_stride = (size_t)keep_A * nh * keep_TB * 32 * hd;
     PartView prev = {nullptr, 0, d, nullptr, 0};
@@ -1470,15 +1471,19 @@ static void run_prompt_passes(sd_model* m, sd_kv* kv, const int32_t* tokens, con
                                (uint16_t*)m->kt + l * keep_stride, (uint16_t*)m->vt + l * keep_stride, keep, keep_TB};
         launch_rope_kv(pq, m->rt, rr, m->q, m->ktp, m->vtp, V, Tp, nh, hd, s, &sinks);
         const int pa = prof_claim(m, PROF_ATTN, (double)V * (n_hi + Tp) * 2.0 * d * 2.0);
-        launch_tree_attn(m->q, sinks.kc, sinks.vc, m->ktp, m->vtp, kv->kv_len, m->rt.anc, m->opart, m->mlpart, rr, V, nh, hd, Tp,
-                         kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1));
-        launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, V, nh, hd, Tp, ag.nparts, MB, s);
+        if (whole)
+            launch_attn_whole(m->q, sinks.kc, sinks.vc, m->ktp, m->vtp, kv->kv_len, m->rt.anc, m->attn_x, rr, V, nh, hd, Tp,
+                              kv->cap_blocks, MB, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1));
+        else
+            launch_tree_attn(m->q, sinks.kc, sinks.vc, m->ktp, m->vtp, kv->kv_len, m->rt.anc, m->opart, m->mlpart, rr, V, nh, hd, Tp,
+                             kv->cap_blocks, ag.ncparts, ag.per, ag.tree_sep, s, prof_ev(m, pa, 0), prof_ev(m, pa, 1));
+        if (!whole) launch_attn_merge(m->opart, m->mlpart, m->attn_x, rr, longest, V, nh, hd, Tp, ag.nparts, MB, s);
         PartView po = run_gemm(m, m->attn_x, lw.wo, m->part, M, MB, m->KBd, m->NBo, d, s);
         launch_norm_pack(m->x, po, lw.ffn_norm, c.rms_eps, m->xn, nullptr, M, d, MB, nullptr, s);
         const GemmPlan* gu = m->find_plan(MB, m->KBd, m->NBgu);
-        const bool whole = gu && gemm_plan_swiglu(*gu);    // the projection sees whole sums: it leaves the next operand itself
-        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s, whole ? m->act : nullptr);
-        if (!whole) launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
+        const bool swiglu = gu && gemm_plan_swiglu(*gu);   // the projection sees whole sums: it leaves the next operand itself
+        PartView pg = run_gemm(m, m->xn, lw.wgu, m->part, M, MB, m->KBd, m->NBgu, 2 * c.d_ffn, s, swiglu ? m->act : nullptr);
+        if (!swiglu) launch_swiglu_pack(pg, c.d_ffn, m->Fpad, m->act, M, MB, s);
         prev = run_gemm(m, m->act, lw.wdown, m->part, M, MB, m->KBf, m->NBo, d, s);
     }
     launch_prefill_commit_setup(sum, seqs, A, Tp, kv->i_slots, kv->i_nacc, kv->n_old, kv->kv_len, m->fin_rows, n_fin, last, s);

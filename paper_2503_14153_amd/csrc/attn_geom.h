@@ -132,3 +132,8 @@ static inline int attn_whole_parts(int n_heads, int B, int Tp, int n_hi) {
     const int P = 256 / groups;
     return blocks <= 33 * P ? P : 0;
 }
+// The same for joined prompt passes, whose workgroups come in several rounds: chunks of Tp rows over at most n_hi others. No more
+// than 32 blocks, which is 1024 rows of one prompt. Two layers, us, attn.hip and merge / here: 7B shape, 512 tokens 894 / 882, 800
+// 1645 / 1609, 1024 1697 / 1689, four prompts of 100 - 375 1673 / 1642; 13B shape, 400 tokens 1324 / 1294, 1024 2616 / 2593; beyond, 2048
+// tokens of the 7B shape 3348 / 3388, 4096 6831 / 7263.
+static inline bool attn_whole_pays_prompt(int Tp, int n_hi) { return (n_hi + 31) / 32 + Tp / 32 <= 32; }
