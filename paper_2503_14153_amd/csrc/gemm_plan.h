@@ -30,8 +30,8 @@ struct GemmPlan {
 
 // Four and eight row blocks (k_gemm_tile): the width of a column group, CG blocks, and the number of segments S the
 // contraction is split into, S a divisor of KB, at most 16. Cost of a candidate in shader cycles, from the kernel's
-// measured pace: a step costs its MFMAs (two waves per SIMD, 2 x CPW MFMAs of 32 cycles each) plus about 300 cycles
-// of hand-over; a workgroup runs KB / S steps (rounded up to the ring), the grid ceil(groups x S / 256) rounds; the S
+// measured pace: a step costs its MFMAs (CG x MT / 2 of 32 cycles each per SIMD) plus 160 to 300 cycles of everything
+// else; a workgroup runs KB / S steps (rounded up to the ring), the grid ceil(groups x S / 256) rounds; the S
 // partial tiles are written at the end of the kernel and read by the consumer at about 2500 bytes per cycle each
 // way. Narrow groups buy workgroups and few slots for the matrices with few columns (O and down projection at the
 // 7B shape, 256 rows: 4 blocks x 8 segments instead of 8 x 16: 22 us against 26, 41 against 43, and the consumer
