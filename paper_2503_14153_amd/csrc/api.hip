@@ -426,12 +426,12 @@ extern "C" int sd_model_create(const sd_config* cfg, const sd_weights* w, int32_
         for (int mb = 1; mb <= PROMPT_ROWS / 32; ++mb) {
             m->prompt_us[mb] = prompt_pass_us(shapes, mb * 32);
             if (mb <= 8) continue;
-            for (const auto& sh : shapes) {
+            for (int i = 0; i < 4; ++i) {
                 GemmPlan pl;
                 double cycles = 0;
-                gemm_plan_prompt(&pl, mb, sh[0], sh[1], &cycles, sh == shapes[2]);
+                gemm_plan_prompt(&pl, mb, shapes[i][0], shapes[i][1], &cycles, i == 2);
                 m->prompt_plans.push_back(pl);
-                pf_prompt = std::max(pf_prompt, (size_t)(pl.S / pl.join) * mb * 32 * (size_t)sh[1] * 32);
+                pf_prompt = std::max(pf_prompt, (size_t)pl.slots_max * mb * 32 * (size_t)shapes[i][1] * 32);
             }
         }
     }

@@ -458,8 +458,7 @@ void gemm_plan_make(GemmPlan* p, int MB, int KB, int NB, int32_t* cnt_host, int3
     for (int ng = 0; ng < p->NG; ++ng) p->uniform &= (cnt_host[ng] == slots);
     p->CG = 0;
     p->S = 0;
-    p->RT = p->MT = p->chain = p->fold = 0;
-    p->join = 1;
+    p->RT = p->MT = p->chain = 0;
     p->slots_max = slots;
     if (MB >= 4) gemm_plan_rows(p);
 }
@@ -484,18 +483,18 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
             hipLaunchKernelGGL(KERNEL_, dim3(p.G), dim3(THREADS_), 0, s, SK_ARGS, ##__VA_ARGS__);          \
     } while (0)
     if (p.CG) {                                        // four row blocks and more: the aligned split of k_gemm_tile
-        const int S = p.RT ? p.S / p.join : p.S, combos = (p.NB + p.CG - 1) / p.CG * S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
+        const int combos = (p.NB + p.CG - 1) / p.CG * p.S, G = p.RT ? (combos + 7) / 8 * 8 * p.RT : combos;
         pv.cnt = nullptr;
-        pv.nmax = S;
+        pv.nmax = p.S;
 #define TILE_GO(MT_, CG_, KIND_, OUT_)                                                                        \
     do {                                                                                                   \
         if (ev0 || ev1)                                                                                    \
             hipExtLaunchKernelGGL((k_gemm_tile<MT_, CG_, KIND_>), dim3(G), dim3(256), 0, s, ev0, ev1, 0, (const bf16x8*)Xp, \
-                                  (const bf16x8*)Wp, (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT ? p.RT : 1, combos, \
-                                  p.chain + p.fold, swiglu_KB);                                                     \
+                                  (const bf16x8*)Wp, (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT ? p.RT : 1, combos, \
+                                  p.chain, swiglu_KB);                                                     \
         else                                                                                               \
             hipLaunchKernelGGL((k_gemm_tile<MT_, CG_, KIND_>), dim3(G), dim3(256), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
-                               (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, S, p.MB, p.RT ? p.RT : 1, combos, p.chain + p.fold, swiglu_KB); \
+                               (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT ? p.RT : 1, combos, p.chain, swiglu_KB); \
     } while (0)
         if (swiglu) {                                  // (gemm_tile_swiglu)
             TILE_GO(8, 6, TILE_SWIGLU, swiglu);

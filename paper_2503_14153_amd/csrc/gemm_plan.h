@@ -21,8 +21,6 @@ struct GemmPlan {
     int RT, MT;              // prompt passes of more than 256 rows: RT tiles of MT row blocks each (MB = all of them), one
                              // workgroup per tile, column group and segment; 0 otherwise
     int chain;               // ... whose sums of products are folded away every `chain` contraction blocks (0: they are not)
-    int join, fold;          // prompt passes, eight by eight blocks: a workgroup takes `join` neighbouring segments (S / join
-                             // partial tiles), its sums folded away every `fold` contraction blocks; else 1 and 0
     int slots_max;           // slots the output buffer must hold for either
     int32_t* cnt_dev;        // [NG] contributors per column group (device)
     int32_t* slot0_dev;      // [G] slot of every workgroup's first segment (device)
@@ -72,9 +70,8 @@ static inline double gemm_plan_rows(GemmPlan* p) {      // -> the cost
 // segment for 256 blocks the QKV sums were 4.5 % further from 64 bits than with the four of a 256-row pass. So no chain of
 // products is longer than in a 256-row pass of the same matrix: a workgroup adds its sums to a second set ("folds") that often.
 // The tile of eight by eight blocks has room for half of a second set and puts the rest into its output: dear, but with few
-// folds the tile that moves the fewest bytes per product is still the fastest. Its segments are as short as they have to be,
-// and a workgroup takes `join` of them (7B shape, 1024 rows, down projection: eight by four, two segments of five chains 200 us;
-// eight by eight, eight segments joined by two 180).
+// folds the tile that moves the fewest bytes per product is still the fastest (7B shape, 1024 rows, down projection: eight by
+// four, two segments of five chains each 200 us; eight by eight, four segments of three chains 180).
 // Longest chain of a 256-row pass, in contraction blocks.
 static inline int gemm_chain_limit(int KB, int NB) {
     GemmPlan q;
@@ -98,23 +95,12 @@ static inline void gemm_plan_prompt(GemmPlan* p, int MB, int KB, int NB, double*
             for (int S = 1; S <= 4 && S <= KB; ++S) {
                 if (KB % S) continue;
                 const int n = KB / S;
-                int chain = 0, join = 1;
-                if (n > limit && MT * CG == 64) {
-                    while (join <= n && (n % join || n / join > limit)) ++join;
-                    if (join > n) continue;
-                    chain = even(n);
-                } else if (n > limit) {
-                    chain = even(n);
-                }
+                const int chain = n > limit ? even(n) : 0;
                 const int rounds = ((groups * S + 7) / 8 * RT + 31) / 32, steps = (n + 3) / 4 * 4;      // (an XCD's)
                 const double tile_bytes = (double)S * MB * 32 * NB * 32 * 4 * (gate_up && MT == 8 && CG == 6 && S == 1 ? 0.25 : 1.0);
                 const double folds = chain ? (n - 1) / chain * (MT * CG == 64 ? 160.0 : 50.0) * CG * MT : 0.0;
                 const double cost = rounds * (steps * (16.0 * CG * MT + 300.0) + folds + 6000.0) + 2.0 * tile_bytes / 2500.0;
-                if (p->CG == 0 || cost < best) {
-                    best = cost; p->CG = CG; p->S = S * join; p->MT = MT; p->RT = RT; p->join = join;
-                    p->chain = MT * CG == 64 ? 0 : chain;
-                    p->fold = MT * CG == 64 ? chain : 0;
-                }
+                if (p->CG == 0 || cost < best) { best = cost; p->CG = CG; p->S = S; p->MT = MT; p->RT = RT; p->chain = chain; }
             }
         }
     p->slots = p->slots_max = p->S;

@@ -11,10 +11,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CODE = """
 #include "gemm_plan.h"
 extern "C" int limit(int KB, int NB) { return gemm_chain_limit(KB, NB); }
-extern "C" void plan(int MB, int KB, int NB, int* out) {
+extern "C" void plan(int MB, int KB, int NB, int gate_up, int* out) {
     GemmPlan p;
     double cycles;
-    gemm_plan_prompt(&p, MB, KB, NB, &cycles);
+    gemm_plan_prompt(&p, MB, KB, NB, &cycles, gate_up);
     const int f[] = {p.MT, p.CG, p.S, p.RT, p.chain, p.slots_max};
     for (int i = 0; i < 6; ++i) out[i] = f[i];
 }
@@ -42,34 +42,43 @@ def lib(tmp_path_factory):
     return C.CDLL(str(d / "plans.so"))
 
 
-def plan(lib, MB, KB, NB):
+def plan(lib, MB, KB, NB, gate_up=False):
     out = (C.c_int * 6)()
-    lib.plan(MB, KB, NB, out)
+    lib.plan(MB, KB, NB, gate_up, out)
     return dict(zip(["MT", "CG", "S", "RT", "chain", "slots"], out))
 
 
 def shapes():
-    """(d_model, d_ffn) -> the four projections in blocks of 16 inputs and 32 outputs."""
+    """(d_model, d_ffn) -> the four projections in blocks of 16 inputs and 32 outputs, and whether it is gate/up."""
     rng = random.Random(5)
     for d, F in [(4096, 11008), (5120, 13824), (256, 688), (64, 16)] + [(32 * rng.randint(1, 256), 16 * rng.randint(1, 1800)) for _ in range(60)]:
         gu = 2 * (-(-F // 32))
-        yield from [(d // 16, 3 * d // 32), (d // 16, d // 32), (d // 16, gu), (F // 16, d // 32)]
+        yield from [(d // 16, 3 * d // 32, 0), (d // 16, d // 32, 0), (d // 16, gu, 1), (F // 16, d // 32, 0)]
 
 
 def test_chains_are_no_longer_than_in_a_256_row_pass(lib):
-    folds = 0
-    for KB, NB in shapes():
+    """As launched: S segments of n contraction blocks, S partial tiles, the sums folded away every `chain` blocks."""
+    folds = {}
+    for KB, NB, gate_up in shapes():
         limit = lib.limit(KB, NB)
         for MB in range(9, 33):
-            p = plan(lib, MB, KB, NB)
+            p = plan(lib, MB, KB, NB, gate_up)
             n, chain = KB // p["S"], p["chain"]
-            assert KB % p["S"] == 0 and p["slots"] == p["S"] and p["MT"] * p["RT"] >= MB
+            assert KB % p["S"] == 0 and p["S"] <= 4 and p["slots"] == p["S"] and p["MT"] * p["RT"] >= MB
             assert min(n, chain or n) <= max(limit, 8), (KB, NB, MB, p, limit)
             if chain:
-                folds += 1
+                tile = (p["MT"], p["CG"])
+                folds[tile] = folds.get(tile, 0) + 1
                 assert chain % 8 == 0 and chain < n            # (the kernels' grain; there is something to fold)
-                assert p["MT"] * p["CG"] <= 32 or (p["MT"], p["CG"]) == (8, 6)
-    assert folds > 100
+    assert sum(folds.values()) > 100 and folds[8, 8] > 20 and folds[8, 6] > 20, folds
+
+
+def test_the_plan_of_a_tile_that_folds_says_what_is_launched(lib):
+    """1024 rows of the 7B shape, down projection: tiles of eight by eight blocks, four segments of 172 contraction blocks, each
+    in chains of 64, 64 and 44 (a 256-row pass has chains of 86)."""
+    p = plan(lib, 32, 688, 128)
+    assert lib.limit(688, 128) == 86
+    assert p == {"MT": 8, "CG": 8, "S": 4, "RT": 4, "chain": 64, "slots": 4}
 
 
 def projections(d, F):
