@@ -119,21 +119,26 @@ static inline bool attn_whole_pays(int n_heads, int B, int Tp, int n_hi) {
     return blocks * rounds * 64 <= 18 * (groups < 256 ? groups : 256);
 }
 // Parts of a (sequence, head, row block) in attn_whole.hip: 1 where one workgroup takes all of it (above), 0 where attn.hip's
-// parts are faster, or, for one sequence of two row blocks, as many as fill the chip with workgroups of one row block each:
+// parts are faster, or, for sequences of two row blocks each, as many as fill the chip with workgroups of one row block:
 // three or four, of up to 33 blocks. Two query blocks share a wave in attn.hip, which halves its reads of a long cache; over a
 // short one its four waves have a block or two each, one after the other, and these have eight. Steps of four layers, 7B shape, 64
 // nodes, us, attn.hip / here: 700 rows 702 / 694 (32 layers: 4652 / 4645), 1100 696.5 / 688, 2200 712 / 701, 3000 729 / 725, 4200 732 / 725, 6000 761 / 763,
-// 16384 873 / 895; 13B shape, two layers: 1200 rows 537 / 524, 2000 541 / 533, 4096 561 / 569. Two parts (two sequences, 128
-// nodes) are level.
+// 16384 873 / 895; 13B shape, two layers: 1200 rows 537 / 524, 2000 541 / 533, 4096 561 / 569. Two sequences of 16 to 20 heads and three
+// of 11 to 13 over 700 to 4000 rows, ragged ones too: up to 4 % of the step faster; four of 8 to 10 heads of 64 dims 0 to 6 % faster, of 128 dims
+// from 2 % faster (700 rows) to 2 % slower (nine heads, 2900 rows). Two parts are level.
+// All parts and row blocks of a (sequence, head) run on one XCD and those are dealt to the eight in turn, so the chip is full when
+// the XCD with the most of them is: 41 and 42 (sequence, head) pairs, six on two of the XCDs, are 36 workgroups for 32 compute units
+// there (one sequence of 42 heads over 700 / 2000 / 2900 rows 890 / 913 / 924 in attn.hip, 903 / 941 / 961 here; two of 21 heads, three of 14 the same).
 static inline int attn_whole_parts(int n_heads, int B, int Tp, int n_hi) {
     if (attn_whole_pays(n_heads, B, Tp, n_hi)) return 1;
-    const int groups = B * n_heads * (Tp / 32), blocks = (n_hi + 31) / 32 + Tp / 32;
-    if (Tp != 64 || groups < 64 || groups * 3 > 256) return 0;
-    const int P = 256 / groups;
-    return blocks <= 33 * P ? P : 0;
+    const int pairs = B * n_heads, blocks = (n_hi + 31) / 32 + Tp / 32;
+    if (Tp != 64 || pairs < 32) return 0;
+    const int P = 32 / ((pairs + 7) / 8 * 2);          // 32 compute units of an XCD
+    return P >= 3 && blocks <= 33 * P ? P : 0;
 }
 // The same for joined prompt passes, whose workgroups come in several rounds: chunks of Tp rows over at most n_hi others. No more
 // than 32 blocks, which is 1024 rows of one prompt. Two layers, us, attn.hip and merge / here: 7B shape, 512 tokens 894 / 882, 800
 // 1645 / 1609, 1024 1697 / 1689, four prompts of 100 - 375 1673 / 1642; 13B shape, 400 tokens 1324 / 1294, 1024 2616 / 2593; beyond, 2048
-// tokens of the 7B shape 3348 / 3388, 4096 6831 / 7263.
+// tokens of the 7B shape 3348 / 3388, 4096 6831 / 7263. Few heads ask for no line of their own: 4, 8 and 16 heads, prompts of 300 to 1000 tokens
+// and batches of two to eight in chunks of 32 to 256 rows take 0.92 to 0.99 of the time; eight prompts of 33 tokens, chunks of 32 rows, 0.96 to 1.005.
 static inline bool attn_whole_pays_prompt(int Tp, int n_hi) { return (n_hi + 31) / 32 + Tp / 32 <= 32; }
