@@ -10,6 +10,7 @@ import torch
 
 import workload as wl
 from tests.test_gpu_long_prompts import _check, sd  # noqa: F401  (sd: the fixture)
+from tests.test_prompt_plans import cut, lib as all_plans  # noqa: F401  (all_plans: the fixture)
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CODE = """
@@ -27,9 +28,17 @@ extern "C" void plan(int MB, int KB, int NB, int gate_up, int* out) {
 # (the last tile has one) and 15 pairs of column blocks; 16 row blocks, a last group of two pairs
 SWIGLU = [(192, 1616, 1000), (64, 720, 800), (64, 944, 512)]
 
+# (d_model, d_ffn, rows), eight by eight blocks in chains of 16, 16 and 4: a last tile of two row blocks, the second of 13 rows, and a
+# last group of two columns
+FOLDED = (576, 7712, 557)
+
+# (d_model, head_dim, d_ffn, rows), the down projection in eight by eight blocks, four segments: chains of 64, 64 and 44; 32, 32 and 31, a
+# last tile of three row blocks and a last group of two columns
+SEGMENTS = [(4096, 128, 11008, 1024), (3904, 64, 6080, 589)]
+
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def plan(tmp_path_factory, all_plans):
     d = tmp_path_factory.mktemp("tiles")
     (d / "p.cpp").write_text(CODE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2503_14153_amd", "csrc"),
@@ -40,6 +49,7 @@ def plan(tmp_path_factory):
         out = (C.c_int * 6)()
         lib.plan(-(-rows // 32), KB, NB, gate_up, out)
         return dict(zip(["swiglu", "chain", "MT", "CG", "S", "limit"], out))
+    call.cut = lambda d, F, tokens: cut(all_plans, d, F, tokens)
     return call
 
 
@@ -47,8 +57,15 @@ def test_the_shapes_below_take_those_paths(plan):
     got = [plan(rows, d // 16, 2 * -(-F // 32), 1) for d, F, rows in SWIGLU]
     assert all(p["swiglu"] for p in got) and [p["chain"] for p in got] == [8, 0, 0]
     assert plan(1024, 256, 688, 1)["swiglu"] and plan(1024, 256, 688, 1)["chain"] == 128
-    p = plan(1024, 688, 128, 0)
-    assert (p["MT"], p["CG"], p["S"], p["chain"]) == (8, 8, 4, 64)
+    d, F, rows = FOLDED
+    p = plan(rows, d // 16, 2 * -(-F // 32), 1)
+    assert (p["MT"], p["CG"], p["S"], p["chain"]) == (8, 8, 1, 16) and d // 16 == 36 and 2 * -(-F // 32) % 8 == 2
+    for (d, _, F, rows), (n, chain) in zip(SEGMENTS, [(172, 64), (95, 32)]):
+        p = plan(rows, F // 16, d // 32, 0)
+        assert (p["MT"], p["CG"], p["S"], p["chain"]) == (8, 8, 4, chain) and F // 16 == 4 * n
+    # (and each prompt is one pass)
+    for d, F, rows in [FOLDED] + [(d, F, rows) for d, _, F, rows in SEGMENTS]:
+        assert plan.cut(d, F, rows) == [rows]
 
 
 def test_chains_in_tiles_of_eight_by_eight_are_no_longer_than_in_a_256_row_pass(plan):
@@ -73,20 +90,28 @@ def test_gate_up_that_leaves_the_next_operand(sd, d, d_ffn, rows):  # noqa: F811
 
 
 @pytest.mark.gpu
-def test_chains_sum_like_single_passes(sd):  # noqa: F811
-    """The second layer's keys and values at the 7B width come through the first layer's gate/up (chains of 128) and down
-    projection (chains of 64, 64 and 44). In passes of 256 rows the same sums are taken in other orders, so the two
+def test_folded_sums_in_ragged_tiles(sd):  # noqa: F811
+    d, d_ffn, rows = FOLDED
+    _check(sd, dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_heads=d // 64, head_dim=64, d_model=d, d_ffn=d_ffn),
+           [0], [rows])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,hd,d_ffn,rows", SEGMENTS)
+def test_joined_segments_sum_like_single_passes(sd, d, hd, d_ffn, rows):  # noqa: F811
+    """The second layer's keys and values come through the first layer's gate/up (at the 7B width, chains of 128) and down
+    projection (its segments in three chains). In passes of 256 rows the same sums are taken in other orders, so the two
     float32 results differ by rounding, about 1e-6 of them, and some 1e-3 of the stored values round to a neighbour, 2^-8 away
     at most: sqrt(1e-3) * 2^-8 = 1.2e-4 of the rows' norm. A block of sums lost or added twice would be of the order of 1."""
-    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_layers=2, d_model=4096, n_heads=32, head_dim=128, d_ffn=11008)
+    shape = dataclasses.replace(wl.preset("tiny").model, dtype="bf16", n_layers=2, d_model=d, n_heads=d // hd, head_dim=hd, d_ffn=d_ffn)
     model = sd.Model(shape, wl.make_weights(shape, device="cuda"), 256)
-    tokens = torch.from_numpy(wl.zipf_prompt(shape.vocab, 1024, seed=11)).cuda()
+    tokens = torch.from_numpy(wl.zipf_prompt(shape.vocab, rows, seed=11)).cuda()
     got = []
-    for step in (1024, 256):
-        kv = sd.KVCache(model, 1, 1032)
-        for at in range(0, 1024, step):
-            sd.prefill(model, kv, tokens[at:at + step].contiguous(), [step])
-        got.append([t.double() for t in kv.read_rows(1, 0, 0, 1024)])
+    for step in (rows, 256):
+        kv = sd.KVCache(model, 1, rows + 8)
+        for at in range(0, rows, step):
+            sd.prefill(model, kv, tokens[at:at + step].contiguous(), [min(step, rows - at)])
+        got.append([t.double() for t in kv.read_rows(1, 0, 0, rows)])
     for joined, single in zip(*got):
         assert (joined - single).norm() <= 5e-4 * single.norm()
         assert (joined - single).norm(dim=(1, 2)).max() <= 5e-3 * single.norm(dim=(1, 2)).min()      # (no row by itself either)
