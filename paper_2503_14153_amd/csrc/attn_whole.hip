@@ -31,6 +31,7 @@ __global__ __launch_bounds__(512, 2) void k_attn_whole(const bf16x8* __restrict_
                                                        int cap_blocks, float scale_log2, int stride, int nseq, int MB, PartView pv,
                                                        RowTable rt, RowRef rr, int P, float* __restrict__ opart,
                                                        float2* __restrict__ mlpart) {
+    static_assert(!PARTS || FR, "parts: the last one builds the tree's keys");
     constexpr int KK = HD / 16, EB = HD / 32, NV = 2 * EB, BLK = HD * 4, NW = 8;
     constexpr int QU = KK * 2 * 64;    // 16-byte units of the queries
     constexpr int OU = EB * 4 * 64;    // of a wave's O in the merge area
@@ -308,14 +309,20 @@ void launch_attn_whole(const void* q_packed, const void* kc, const void* vc, voi
     const RowTable rta = rt ? *rt : RowTable{nullptr, nullptr, nullptr, nullptr};
 #define AW_ARGS (const bf16x8*)q_packed, (const bf16x8*)kc, (const bf16x8*)vc, (bf16x8*)kt, (bf16x8*)vt, kv_len, anc, (bf16x8*)x_packed, \
                 nh, Tp, cap_blocks, scale_log2, stride, B, MB, pv, rta, rr, P, opart, mlpart
-#define AW_GOP(HD_, AW_, FR_, NS_, MAP_, PARTS_)                                                                                          \
+#define AW_GOP(HD_, AW_, FR_, NS_, MAP_, PARTS_)                                                                                 \
     do {                                                                                                                         \
+        const dim3 grid(stride * TG * (PARTS_ ? P : 1));                                                                         \
         if (ev0 || ev1)                                                                                                          \
-            hipExtLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), dim3(stride * TG * P), dim3(512), 0, s, ev0, ev1, 0, AW_ARGS); \
+            hipExtLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), grid, dim3(512), 0, s, ev0, ev1, 0, AW_ARGS); \
         else                                                                                                                     \
-            hipLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), dim3(stride * TG * P), dim3(512), 0, s, AW_ARGS);            \
+            hipLaunchKernelGGL((k_attn_whole<HD_, AW_, FR_, NS_, MAP_, PARTS_>), grid, dim3(512), 0, s, AW_ARGS);                 \
     } while (0)
-#define AW_GO(HD_, AW_, FR_, NS_, MAP_) do { if (P > 1) AW_GOP(HD_, AW_, FR_, NS_, MAP_, true); else AW_GOP(HD_, AW_, FR_, NS_, MAP_, false); } while (0)
+    // (parts: two row blocks per sequence, whose queries and tree keys this launch always makes itself: FR)
+#define AW_GO(HD_, AW_, FR_, NS_, MAP_)                                                                                          \
+    do {                                                                                                                         \
+        if (FR_ && P > 1) AW_GOP(HD_, AW_, FR_, NS_, MAP_, FR_ != 0);                                                            \
+        else AW_GOP(HD_, AW_, FR_, NS_, MAP_, false);                                                                            \
+    } while (0)
 #define AW_MAP(HD_, AW_, FR_, NS_) do { if (rr.map) AW_GO(HD_, AW_, FR_, NS_, true); else AW_GO(HD_, AW_, FR_, NS_, false); } while (0)
 #define AW_HD(HD_)                                                                                                               \
     do {                                                                                                                         \
