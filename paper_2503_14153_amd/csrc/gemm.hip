@@ -496,7 +496,7 @@ PartView launch_gemm(const GemmPlan& p, const void* Xp, const void* Wp, const vo
             hipLaunchKernelGGL((k_gemm_tile<MT_, CG_, KIND_>), dim3(G), dim3(256), 0, s, (const bf16x8*)Xp, (const bf16x8*)Wp, \
                                (void*)OUT_, p.KB, p.NB, pv.ld, pv.slot_stride, rows, p.S, p.MB, p.RT ? p.RT : 1, combos, p.chain, swiglu_KB); \
     } while (0)
-        if (swiglu) {                                  // (gemm_tile_swiglu)
+        if (swiglu && gemm_plan_swiglu(p)) {           // (the caller has asked the same of the same plan)
             TILE_GO(8, 6, TILE_SWIGLU, swiglu);
             pv.nmax = 0;
             return pv;

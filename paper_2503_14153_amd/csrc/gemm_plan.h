@@ -27,14 +27,15 @@ struct GemmPlan {
 };
 
 // Four and eight row blocks (k_gemm_tile): the width of a column group, CG blocks, and the number of segments S the
-// contraction is split into, S a divisor of KB, at most 16. Cost of a candidate in shader cycles, from the kernel's
-// measured pace: a step costs its MFMAs (CG x MT / 2 of 32 cycles each per SIMD) plus 160 to 300 cycles of everything
-// else; a workgroup runs KB / S steps (rounded up to the ring), the grid ceil(groups x S / 256) rounds; the S
+// contraction is split into, S a divisor of KB, at most 16. Cost of a candidate in shader cycles: a step costs its MFMAs
+// (CG x MT / 2 of 32 cycles each per SIMD) plus 300 cycles of everything else, the pace of the kernel before this one, which
+// needs 177 at eight by six and 233 at four by eight; a workgroup runs KB / S steps (rounded up to four), the grid
+// ceil(groups x S / 256) rounds; the S
 // partial tiles are written at the end of the kernel and read by the consumer at about 2500 bytes per cycle each
 // way. Narrow groups buy workgroups and few slots for the matrices with few columns (O and down projection at the
-// 7B shape, 256 rows: 4 blocks x 8 segments instead of 8 x 16: 22 us against 26, 41 against 43, and the consumer
+// 7B shape, 256 rows: 4 blocks x 8 segments instead of 8 x 16: 22 us against 27, 43 against 45, and the consumer
 // reads half as much); six-block groups fill the chip where eight-block ones leave a quarter of it idle (QKV: 64
-// groups x 4 = 256 workgroups, 45 us against 55 with 48 x 4; gate/up 115 x 2 = 230 against 86 x 2 = 172: 76 against 89).
+// groups x 4 = 256 workgroups, 48 us against 54 with 48 x 4; gate/up 115 x 2 = 230 against 86 x 2 = 172: 83 against 94).
 static inline double gemm_plan_rows(GemmPlan* p) {      // -> the cost
     const int MT = p->MB;
     static const int widths8[] = {8, 6, 4}, widths4[] = {8, 4};
@@ -61,10 +62,8 @@ static inline double gemm_plan_rows(GemmPlan* p) {      // -> the cost
 // 6000 cycles (launch, first loads, stores) per round of workgroups. With this many rows a projection needs fewer segments to
 // fill the chip (7B shape, 1024 rows: QKV and gate/up one, O and down two, where 256 rows have two to eight), so fewer partial
 // tiles are written and read; the weights are read once per pass.
-// 7B shape, a prompt of 1500 tokens through four layers: 6560 us in six passes of up to 256 rows, 5560 in passes of 1024 and
-// 476 (5400 with chains of any length, see below). The launches themselves run at what the card's power allows for dense data,
-// 0.97-1.05 PFLOP/s of two-term work at 256 and at 1024 rows alike (1.26-1.36 with operands of zeros): what is saved lies
-// between them.
+// 7B shape, a prompt of 1500 tokens through four layers: 6130 us in six passes of up to 256 rows, 5076 in passes of 1024 and
+// 476 (4708 with chains of any length, see below).
 //
 // Fewer segments are longer sums, and a sum that is rounded at every contraction block strays with its length: with one
 // segment for 256 blocks the QKV sums were 4.5 % further from 64 bits than with the four of a 256-row pass. So no chain of
@@ -113,10 +112,13 @@ static inline bool gemm_plan_swiglu(const GemmPlan& p) { return p.RT && p.MT == 
 
 // Time of a layer of a prompt pass, us, from its rows and its four projections (sh: contraction and column blocks of each). Up to
 // 64 rows the weights' bytes; up to 256 the cost above at 1950 cycles per us, with 60000 cycles for the layer's other launches;
-// joined passes at 1700 (less of what they lose is in the model). Measured, us a layer, 7B / 13B shape: up to 32 rows 98-111 /
-// 137-155, 64 rows 132 / 170, 128 rows 173 / 225, 256 rows 253 / 352; joined 320 rows 440 / 636, 512 463 / 740, 640 735 / 975,
-// 768 757 / 1004, 1024 878 / 1420. (Its predecessor took a handful of rows for 165 us, and a prompt of 257 tokens went as one
-// pass of 257 rows: 405 / 611 us where 256 rows and one row take 347 / 503.)
+// joined passes at 1700 (less of what they lose is in the model). Measured, us a layer, 7B / 13B shape (in brackets what this says):
+// 8 rows 90 / 145 (103 / 153), 32 rows 106 / 152, 64 rows 132 / 171 (132 / 176), 128 rows 164 / 221 (178 / 222), 256 rows 237 / 336
+// (253 / 352); joined 288 rows 384 / 510 (443 / 623), 320 387 / 517 (447 / 631), 512 407 / 631 (470 / 711), 640 614 / 883 (705 / 983), 768
+// 707 / 905 (790 / 995), 1024 812 / 1253 (834 / 1291). It was fitted to the kernel before: the times are up to a fifth too
+// long, most for the shorter joined passes, so that some prompts are cut where one pass would be sooner done (13B shape, 512
+// tokens: two passes of 256 rows 672, one 631). A remainder of a few rows is right to run alone (257 tokens: 257 rows as one pass
+// take about 384 / 510, 256 rows and one 330 / 480).
 static inline double prompt_pass_us(const int (*sh)[2], int rows) {
     double bytes = 0, cycles = 60000;
     const int mb = (rows + 31) / 32;
